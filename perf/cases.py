@@ -260,6 +260,104 @@ def run(state):
 
 
 # ------------------------------------------------------------------------------------------------
+# The same results in binary64, from the same draws, in plain torch.  Steps and codes of the inputs are decided in
+# binary32, as Eq. 1 defines them; everything after that is binary64, without the 16-bit storage between the kernels.
+def _codes(x, s, bits=4):
+    q = 2 ** (bits - 1)
+    return torch.round(torch.clamp(x / s, -q, q - 1))
+
+
+def _exact_weights(W, bits):
+    """W as the quantized linear sees it."""
+    if bits == 16:
+        return W.half().double()
+    top = W.abs().amax(dim=1, keepdim=True)
+    s = torch.where(top > 0, top / (7.0 if bits == 4 else 127.0), torch.ones_like(top))
+    return _codes(W, s, bits).double() * s.double()
+
+
+def _f32(v):
+    return torch.tensor(v, dtype=torch.float32, device="cuda")
+
+
+def _exact_linear(c, g):
+    M, K, N = c["M"], c["K"], c["N"]
+    if c["kind"] == "stream":
+        b = torch.randint(0, 256, (N, K // 2), generator=g, device="cuda", dtype=torch.uint8).int()
+        w = torch.stack(((b & 15) ^ 8, (b >> 4) ^ 8), dim=2).reshape(N, K).sub_(8).float()
+        s_w = torch.rand(N, generator=g, device="cuda") * 0.01 + 0.001
+    else:
+        w, s_w = _exact_weights(_randn(g, N, K, std=0.02), 4), None
+    b = _randn(g, N, std=0.01)
+    x = _activations(g, M, K)
+    x = _codes(x.half().float() if c.get("a") == "f16" else x, _f32(STEP))
+    if s_w is not None:
+        # products of codes summed by binary32 are exact in parts of 2^18 codes and fewer
+        y = (x @ w.t()).double() * s_w.double()
+    else:
+        y = x.double() @ w.t()
+    y = y * _f32(STEP).double() + b.double()
+    if c.get("epi") == "residual":
+        y += _randn(g, M, N).half().double()
+    return None if c["out"] == "i4" else y
+
+
+def _exact_attention(qkv, lens, heads):
+    ctx = torch.empty_like(qkv[:, :qkv.shape[1] // 3])
+    at = 0
+    for n in lens:
+        q, k, v = (t.reshape(n, heads, -1).transpose(0, 1).contiguous() for t in qkv[at:at + n].chunk(3, dim=1))
+        p = torch.softmax(q @ k.transpose(1, 2).contiguous() / math.sqrt(q.shape[2]), dim=2)
+        ctx[at:at + n] = (p @ v).transpose(0, 1).reshape(n, -1)
+        at += n
+    return ctx
+
+
+def _exact_encoder(c, g, seed):
+    H, F, heads, M = c["hidden"], c["ffn"], c["heads"], _tokens(c)
+    lens = [int(n) for n in wl.ragged_lengths(M, c["batch"], c["seq"], seed)] if c["tokens"] else [c["seq"]] * c["batch"]
+    h = _randn(g, M, H).half().double()
+    norm = torch.nn.functional.layer_norm
+    for nb in _layer_bits(c):
+        ln = [_randn(g, H, std=0.1, mean=m).double() for m in (1.0, 0.0, 1.0, 0.0)]
+        step = {"qkv": STEP, "ao": 0.05, "up": STEP, "down": 0.05}
+        lin = {}
+        for nm, (_, K, N) in zip(LINEAR_NAMES, wl.layer_gemm_shapes(H, F)):
+            W, b = _exact_weights(_randn(g, N, K, std=0.02), nb), _randn(g, N, std=0.01).double()
+            s = _f32(step[nm] * (1.0 if nb == 4 else 7.0 / 127.0)).double()
+
+            def linear(x, W=W, b=b, s=s):
+                return (x if nb == 16 else _codes(x, s, nb) * s) @ W.t() + b
+
+            lin[nm] = linear
+        u = lin["ao"](_exact_attention(lin["qkv"](h), lens, heads)) + h
+        h1 = norm(u, (H,), ln[0], ln[1], 1e-12)
+        d = lin["down"](torch.nn.functional.gelu(lin["up"](h1))) + h1
+        h = norm(d, (H,), ln[2], ln[3], 1e-12)
+    return h
+
+
+def _exact_calibrate(c, g):
+    x = _activations(g, c["M"], c["K"])
+    x = (x.half().float() if c["x"] == "f16" else x).reshape(-1)
+    k = max(1, x.numel() * c["ppm"] // 1000000)
+    kth = torch.topk(x.abs(), k, sorted=True).values[-1]
+    r = _codes(x, _f32(STEP)).double()
+    xd, s = x.double(), _f32(STEP).double()
+    grads = torch.stack(((r - xd / s).sum(), 2.0 * ((r * s - xd) * r).sum()))
+    return [(x.abs().max().double() / 7.0).reshape(1), (kth.double() / 7.0).reshape(1), grads]
+
+
+def exact(case, seed):
+    g = _gen(seed)
+    if case["kind"] == "encoder":
+        return _exact_encoder(case, g, seed)
+    if case["kind"] == "calibrate":
+        return _exact_calibrate(case, g)
+    return _exact_linear(case, g)
+
+
+# ------------------------------------------------------------------------------------------------
 def work(case):
     c = case
     if c["kind"] == "calibrate":
