@@ -53,6 +53,7 @@ __device__ __forceinline__ int w_row_perm(int i)
 // Compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>).
 // Used where an index selects accumulator registers, which must never become a
 // run-time index (the array would be demoted to scratch memory).
+constexpr int min_i(int a, int b) { return a < b ? a : b; }
 template <int I>
 struct IntC { static constexpr int value = I; };
 template <int N, class F>

@@ -1,25 +1,25 @@
-// Binary16 GEMM  y = a W^T + b  (binary32 accumulate) with the same epilogue options
-// as the quantized linear: the 16-bit float baseline that the W4A4 layer is timed
-// against.  Same skeleton as the int4 kernel: persistent workgroups, a ring of LDS
-// stages filled by direct global->LDS copies, XOR-swizzled 16-byte chunks,
-// v_mfma_f32_32x32x16_f16 with W as the "A" operand (rows read in permuted order so
-// that a lane owns runs of 8 consecutive output channels of one token), fragments
-// of the next k step fetched from LDS while the current one is in the matrix core.
-#include "gemm_common.h"
+// Binary16 linear  y = a W^T + b  (binary32 accumulate) with the same epilogue options as the quantized
+// linear: the 16-bit float baseline that the W4A4 layer is timed against.  It runs the tile kernel of the
+// quantized linears (gemm_tile.h) with binary16 operands, v_mfma_f32_32x32x16_f16 and stages of one 128-byte
+// line (64 values of k) per operand row; the smallest launches have a kernel of their own.
+#include "gemm_tile.h"
 
 namespace mkq {
 
-struct GemmF16Params {
-    const uint8_t *A;  // [M, K] binary16
-    const uint8_t *W;  // [N, K] binary16
-    int M, N, K;
-    const float *bias;        // [N] or null
-    const uint16_t *residual; // [M, N] binary16 or null
-    int act;
-    void *out;
-    int out_dtype;  // MKQ_F32 or MKQ_F16
-};
+template <class Cfg, int KSPLIT = 1>
+static int launch_f16_by_epilogue(const GemmI4Params &p, hipStream_t st)
+{
+    const bool gelu = p.act == MKQ_ACT_GELU;
+    if ((p.N % 8) == 0 && !(p.residual && gelu)) {
+        if (p.out_dtype == MKQ_F16 && p.residual) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 16, KSPLIT>(p, st);
+        if (p.out_dtype == MKQ_F16 && gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, true>, 16, KSPLIT>(p, st);
+        if (p.out_dtype == MKQ_F16) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, 16, KSPLIT>(p, st);
+    }
+    return launch_gemm_i4_dma<Cfg, EpiGeneric, 16, KSPLIT>(p, st);
+}
 
+// ---------------------------------------------------------------------------------
+// The split kernel of the smallest launches: 64-wide k stages, and the k loop shared by two wave groups.
 template <int BM_, int BN_, int WGM_, int WGN_, int S_>
 struct GemmF16Cfg {
     static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, S = S_;
@@ -41,7 +41,7 @@ struct GemmF16Cfg {
 // epilogue (for launches with few tiles, whose lone wave per SIMD is bound by its own
 // instruction stream).
 template <class Cfg, int KSPLIT>
-__global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const GemmF16Params p)
+__global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const GemmI4Params p)
 {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, RB = Cfg::RB, CH = Cfg::CH;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, S = Cfg::S, LPW = Cfg::LPW, KSTEPS = Cfg::KSTEPS;
@@ -171,7 +171,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
 #pragma unroll
                     for (int e = 0; e < 8; ++e) y[e] = acc[j][t][8 * G + e] + bi[e];
                     if (p.residual) {
-                        const uint16_t *r = p.residual + o;
+                        const uint16_t *r = (const uint16_t *)p.residual + o;
                         if (vec_ok) {
                             const uint4 rr = *reinterpret_cast<const uint4 *>(r);
                             const uint32_t rwd[4] = {rr.x, rr.y, rr.z, rr.w};
@@ -269,7 +269,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
 }
 
 template <class Cfg, int KSPLIT = 1>
-static int launch_gemm_f16(const GemmF16Params &p, hipStream_t st, bool setup_only = false)
+static int launch_gemm_f16(const GemmI4Params &p, hipStream_t st)
 {
     const int64_t tiles = ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN);
     if (tiles > 0x7FFFFFFF) return MKQ_ERR_UNSUPPORTED;
@@ -278,31 +278,67 @@ static int launch_gemm_f16(const GemmF16Params &p, hipStream_t st, bool setup_on
     static PerDeviceOnce once;  // per instantiation
     int64_t resident = 0;
     const int rc = resident_workgroups(once, gemm_f16_kernel<Cfg, KSPLIT>, Cfg::THREADS * KSPLIT, lds, 1 << 20, &resident);
-    if (rc != MKQ_OK || setup_only) return rc;
+    if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
     gemm_f16_kernel<Cfg, KSPLIT><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(p);
     return launch_status();
 }
 
-int run_gemm_f16(const GemmF16Params &p, hipStream_t st)
+// K split between two wave groups applies, and there is at most one 64x64 tile per CU
+static bool few_tiles(const GemmI4Params &p)
+{
+    return ceil_div(p.M, 64) * ceil_div(p.N, 64) <= 256 && (p.K % 128) == 0 && p.K >= 256;
+}
+
+// Tile choice, from sweeps over M = 32 .. 16384 at the BERT-base / BERT-large shapes (before: 128x128 tiles, one
+// workgroup per CU, from 192 tiles on, and 64x64 below; us, old -> new):
+//   4096 tokens, K = 768: N = 2304 31.9 -> 24.3, N = 768 14.3 -> 11.8, N = 3072 with GELU 39.8 -> 31.8;
+//   K = 3072, N = 768 33.5 -> 28.8; 2298 tokens 22.0 -> 14.1, 9.4 -> 8.7, 26.8 -> 20.2, 28.8 -> 23.3;
+//   16384 tokens, K = 1024, N = 4096 230 -> 153
+enum { F16_SPLIT = 0, F16_64, F16_128_DEEP, F16_256x128, F16_128, F16_256, F16_CONFIGS };
+static int choose_f16(const GemmI4Params &p)
 {
     const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
-    const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
-    if (t128 >= 192) return launch_gemm_f16<GemmF16Cfg<128, 128, 2, 2, 4>>(p, st);
-    // few tiles: 64x64; while there is at most one workgroup per CU the k loop is split between two
-    // wave groups (four-stage rings), beyond that a three-stage ring lets three workgroups share a CU
-    if (t64 <= 256 && (p.K % 128) == 0 && p.K >= 256) return launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 4>, 2>(p, st);
-    return launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 3>>(p, st);
+    // at most one 64x64 tile per CU: two wave groups share the k loop (a lone wave per SIMD waits for its own loads)
+    if (few_tiles(p)) return F16_SPLIT;
+    if (t128 <= 128) return F16_64;
+    // about one 128x128 tile per CU: a deep ring, since nothing else covers the trip to memory
+    if (t128 <= 256) return F16_128_DEEP;
+    // one 256x128 tile of eight waves per CU in a single round
+    if (ceil_div(p.M, 256) * ceil_div(p.N, 128) <= 256) return F16_256x128;
+    // at least one 256x256 tile per CU: the least traffic per product; in between two 128x128 workgroups per CU
+    // overlap one's epilogue with the other's k loop
+    return ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 256 ? F16_256 : F16_128;
 }
+
+static int run_config(const GemmI4Params &p, int cfg, hipStream_t st)
+{
+    switch (cfg) {
+    case F16_SPLIT: return launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 4>, 2>(p, st);
+    case F16_64: return launch_f16_by_epilogue<GemmI4DmaCfg<64, 64, 2, 2, 128, 3>>(p, st);
+    case F16_128_DEEP: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 128, 4>>(p, st);
+    case F16_256x128: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 128, 4, 2, 128, 3>>(p, st);
+    case F16_128: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 128, 2>>(p, st);
+    default: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 256, 2, 4, 128, 2>>(p, st);
+    }
+}
+
+int run_gemm_f16(const GemmI4Params &p, hipStream_t st) { return run_config(p, choose_f16(p), st); }
 
 // once-per-device setup of every instantiation (nothing is launched)
 int setup_gemm_f16()
 {
-    GemmF16Params p = {};
-    p.M = p.N = p.K = 256;
-    int rc = launch_gemm_f16<GemmF16Cfg<128, 128, 2, 2, 4>>(p, nullptr, true);
-    if (rc == MKQ_OK) rc = launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 4>, 2>(p, nullptr, true);
-    if (rc == MKQ_OK) rc = launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 3>>(p, nullptr, true);
+    int rc = MKQ_OK;
+    for (int cfg = 0; cfg < F16_CONFIGS; ++cfg)
+        for (int e = 0; e < 4 && rc == MKQ_OK; ++e) {
+            GemmI4Params p = {};
+            p.M = p.N = p.K = 256;
+            p.setup_only = true;
+            p.out_dtype = e == 3 ? MKQ_F32 : MKQ_F16;
+            p.act = e == 2 ? MKQ_ACT_GELU : MKQ_ACT_NONE;
+            if (e == 1) p.residual = &p;
+            rc = run_config(p, cfg, nullptr);
+        }
     return rc;
 }
 
@@ -324,10 +360,10 @@ extern "C" int mkq_linear_fp16(const void *a, const void *W, const float *bias, 
         return MKQ_ERR_ALIGN;
     if (M > 0x7FFFFFFF || N > 0x7FFFFFFF || M * K * 2 > 0xFFFFFFFFLL || N * K * 2 > 0xFFFFFFFFLL)
         return MKQ_ERR_UNSUPPORTED;
-    GemmF16Params p;
+    GemmI4Params p = {};
     p.A = (const uint8_t *)a; p.W = (const uint8_t *)W;
     p.M = (int)M; p.N = (int)N; p.K = (int)K;
-    p.bias = bias; p.residual = (const uint16_t *)residual; p.act = act;
+    p.bias = bias; p.residual = residual; p.residual_dtype = MKQ_F16; p.act = act;
     p.out = out; p.out_dtype = out_dtype;
     return run_gemm_f16(p, as_stream(stream));
 }

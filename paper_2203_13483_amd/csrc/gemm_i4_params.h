@@ -4,6 +4,8 @@
 
 #include "gemm_common.h"
 
+#include <type_traits>
+
 namespace mkq {
 
 struct GemmI4Params {
@@ -98,8 +100,10 @@ struct EpiGeneric {
 // wave's position in the workgroup; fr = lane % 32, fh = lane / 32).
 // Register v of a lane holds channel 16*(v/8) + 8*fh + v%8 of its 32-channel tile,
 // token fr of its 32-token tile.
-template <class Cfg, class Epi>
-__device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&acc)[Cfg::TM][Cfg::TN],
+// SCALED: the accumulators are sums of codes; otherwise binary32 sums of a float product, to which only the
+// bias is added.
+template <class Cfg, class Epi, bool SCALED = true, class AccV>
+__device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, AccV (&acc)[Cfg::TM][Cfg::TN],
                                                  int m0, int n0, int wm, int wn, int fr, int fh)
 {
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
@@ -108,7 +112,7 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&a
     const bool res_f32 = Epi::generic ? (p.residual_dtype == MKQ_F32) : false;
     const bool gelu = Epi::generic ? (p.act == MKQ_ACT_GELU) : Epi::gelu;
     const bool vec_ok = Epi::generic ? ((p.N % 8) == 0) : true;
-    int32_t *const acc_out = Epi::generic ? p.acc_out : nullptr;
+    int32_t *const acc_out = Epi::generic && SCALED ? p.acc_out : nullptr;
     uint8_t *const q_extra = Epi::generic ? p.q_out : nullptr;
     const bool need_y = (out_dtype >= 0) || q_extra;
     static_for<TN>([&](auto tc) {
@@ -122,10 +126,12 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&a
             const int nvalid = (p.N - nb) < 8 ? (p.N - nb) : 8;
             float sc[8], bi[8];
             if (vec_ok) {
-                const float4 s0 = *reinterpret_cast<const float4 *>(p.s_w + nb);
-                const float4 s1 = *reinterpret_cast<const float4 *>(p.s_w + nb + 4);
-                sc[0] = s0.x; sc[1] = s0.y; sc[2] = s0.z; sc[3] = s0.w;
-                sc[4] = s1.x; sc[5] = s1.y; sc[6] = s1.z; sc[7] = s1.w;
+                if constexpr (SCALED) {
+                    const float4 s0 = *reinterpret_cast<const float4 *>(p.s_w + nb);
+                    const float4 s1 = *reinterpret_cast<const float4 *>(p.s_w + nb + 4);
+                    sc[0] = s0.x; sc[1] = s0.y; sc[2] = s0.z; sc[3] = s0.w;
+                    sc[4] = s1.x; sc[5] = s1.y; sc[6] = s1.z; sc[7] = s1.w;
+                }
                 if (p.bias) {
                     const float4 b0 = *reinterpret_cast<const float4 *>(p.bias + nb);
                     const float4 b1 = *reinterpret_cast<const float4 *>(p.bias + nb + 4);
@@ -139,12 +145,14 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&a
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
                     const int n = (e < nvalid) ? nb + e : nb;
-                    sc[e] = p.s_w[n];
+                    if constexpr (SCALED) sc[e] = p.s_w[n];
                     bi[e] = p.bias ? p.bias[n] : 0.0f;
                 }
             }
+            if constexpr (SCALED) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sc[e] = (p.s_x * sc[e]) * p.acc_unit;  // power of two: exact
+                for (int e = 0; e < 8; ++e) sc[e] = (p.s_x * sc[e]) * p.acc_unit;  // power of two: exact
+            }
             static_for<TM>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
                 __builtin_amdgcn_sched_barrier(0);
@@ -152,11 +160,11 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&a
                 if (m >= p.M) return;
                 const int64_t o = (int64_t)m * p.N + nb;
                 const int64_t oq = p.q_pitch ? (int64_t)m * p.q_pitch + nb : o;  // in the code outputs
-                int a[8];
+                typename std::conditional<SCALED, int, float>::type a[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) a[e] = acc[j][t][8 * G + e];
 
-                if (acc_out) {
+                if constexpr (SCALED) if (acc_out) {
                     if (vec_ok) {
                         *reinterpret_cast<int4 *>(acc_out + o) = make_int4(a[0] >> p.acc_shift, a[1] >> p.acc_shift, a[2] >> p.acc_shift, a[3] >> p.acc_shift);
                         *reinterpret_cast<int4 *>(acc_out + o + 4) = make_int4(a[4] >> p.acc_shift, a[5] >> p.acc_shift, a[6] >> p.acc_shift, a[7] >> p.acc_shift);
@@ -169,7 +177,7 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, v16i (&a
                 float y[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    y[e] = __fmaf_rn((float)a[e], sc[e], bi[e]);
+                    y[e] = SCALED ? __fmaf_rn((float)a[e], sc[e], bi[e]) : (float)a[e] + bi[e];
                     // keep the binary32 rounding: without this the compiler folds the fma and a
                     // later narrowing into one v_fma_mixlo_f16, which rounds only once
                     asm volatile("" : "+v"(y[e]));
@@ -283,12 +291,18 @@ struct EpiShuffle {
     static constexpr int BIAS_AT = NSL * 64;                       // in floats
     static constexpr int SCALE_BYTES = 2 * BIAS_AT * 4;
     static constexpr int EXTRA_LDS = Cfg::WAVES * SCALE_BYTES;
-    static constexpr bool usable = REGION >= 4096 && Cfg::RB == 64 &&
+    static constexpr bool usable = REGION >= 4096 && Cfg::RB >= 64 &&
                                    (Cfg::LDS_BYTES + EXTRA_LDS) * Cfg::WGS_PER_CU <= 160 * 1024;
 };
 
-template <class Cfg, class Epi>
-__device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, v16i (&acc)[Cfg::TM][Cfg::TN],
+__device__ __forceinline__ int4 acc_bits(int a, int b, int c, int d) { return make_int4(a, b, c, d); }
+__device__ __forceinline__ int4 acc_bits(float a, float b, float c, float d)
+{
+    return make_int4(__float_as_int(a), __float_as_int(b), __float_as_int(c), __float_as_int(d));
+}
+
+template <class Cfg, class Epi, bool SCALED = true, class AccV>
+__device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, AccV (&acc)[Cfg::TM][Cfg::TN],
                                                       int m0, int n0, int wm, int wn, int lane, uint8_t *scr,
                                                       float *sc_lds)
 {
@@ -303,7 +317,7 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, v16
     // power-of-two unit (exact) into the scales once; no bias -> zeros.
 #pragma unroll
     for (int c = lane; c < WTN; c += 64) {
-        sc_lds[c] = (p.s_x * sc_lds[c]) * p.acc_unit;
+        if constexpr (SCALED) sc_lds[c] = (p.s_x * sc_lds[c]) * p.acc_unit;
         if (!p.bias) sc_lds[Sh::BIAS_AT + c] = 0.0f;
     }
     QuantStep qs4 = {}, qs8 = {};
@@ -345,8 +359,11 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, v16
         constexpr int t = decltype(tc)::value;
         const int c0 = t * 32 + 8 * pc;  // first of the reader lane's channels, wave-relative
         const int n = nw + c0;
-        const float4 s0 = *reinterpret_cast<const float4 *>(sc_lds + c0);
-        const float4 s1 = *reinterpret_cast<const float4 *>(sc_lds + c0 + 4);
+        float4 s0 = {}, s1 = {};
+        if constexpr (SCALED) {
+            s0 = *reinterpret_cast<const float4 *>(sc_lds + c0);
+            s1 = *reinterpret_cast<const float4 *>(sc_lds + c0 + 4);
+        }
         const float4 b0 = *reinterpret_cast<const float4 *>(sc_lds + Sh::BIAS_AT + c0);
         const float4 b1 = *reinterpret_cast<const float4 *>(sc_lds + Sh::BIAS_AT + c0 + 4);
         const float sc[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
@@ -360,8 +377,8 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, v16
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
                     *reinterpret_cast<int4 *>(scr + wr_base + (((4 * G + 2 * fh + h) ^ wr_key) * 16)) =
-                        make_int4(acc[j][t][8 * G + 4 * h], acc[j][t][8 * G + 4 * h + 1],
-                                  acc[j][t][8 * G + 4 * h + 2], acc[j][t][8 * G + 4 * h + 3]);
+                        acc_bits(acc[j][t][8 * G + 4 * h], acc[j][t][8 * G + 4 * h + 1],
+                                 acc[j][t][8 * G + 4 * h + 2], acc[j][t][8 * G + 4 * h + 3]);
             // read it back row-wise
             int4 raw[2][2];
 #pragma unroll
@@ -383,7 +400,7 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, v16
                 float y[8];
 #pragma unroll
                 for (int e = 0; e < 8; ++e) {
-                    y[e] = __fmaf_rn((float)a[e], sc[e], bi[e]);
+                    y[e] = SCALED ? __fmaf_rn((float)a[e], sc[e], bi[e]) : __int_as_float(a[e]) + bi[e];
                     asm volatile("" : "+v"(y[e]));  // keep the binary32 rounding (no fused narrowing)
                 }
                 if (Epi::res16) {
@@ -449,7 +466,7 @@ struct EpiLines16 {
                                    (Epi::out == MKQ_F16 || Epi::out == MKQ_BF16);
 };
 
-template <class Cfg, class Epi, bool CACHE_SCALES = true, class AccV>
+template <class Cfg, class Epi, bool CACHE_SCALES = true, bool SCALED = true, class AccV>
 __device__ __forceinline__ void gemm_epilogue_lines16(const GemmI4Params &p, AccV (&acc)[Cfg::TM][Cfg::TN],
                                                       int m0, int n0, int wm, int wn, int lane, uint8_t *scr,
                                                       float *sc_lds)
@@ -458,7 +475,7 @@ __device__ __forceinline__ void gemm_epilogue_lines16(const GemmI4Params &p, Acc
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
     static_assert(EpiLines16<Cfg, Epi>::usable, "64 channels per wave, plain 16-bit outputs");
     const int fr = lane & 31, fh = lane >> 5;
-    sc_lds[lane] = (p.s_x * sc_lds[lane]) * p.acc_unit;
+    if constexpr (SCALED) sc_lds[lane] = (p.s_x * sc_lds[lane]) * p.acc_unit;
     if (!p.bias) sc_lds[Sh::BIAS_AT + lane] = 0.0f;
 
     // the lane's 32 channels: register 8h + e of tile t is channel 32t + 16h + 8fh + e.  Their scales and
@@ -467,7 +484,8 @@ __device__ __forceinline__ void gemm_epilogue_lines16(const GemmI4Params &p, Acc
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
             const int c = 32 * t + 16 * h + 8 * fh + 4 * q;
-            const float4 s4 = *reinterpret_cast<const float4 *>(sc_lds + c);
+            float4 s4 = {};
+            if constexpr (SCALED) s4 = *reinterpret_cast<const float4 *>(sc_lds + c);
             const float4 b4 = *reinterpret_cast<const float4 *>(sc_lds + Sh::BIAS_AT + c);
             s8[4 * q] = s4.x; s8[4 * q + 1] = s4.y; s8[4 * q + 2] = s4.z; s8[4 * q + 3] = s4.w;
             b8[4 * q] = b4.x; b8[4 * q + 1] = b4.y; b8[4 * q + 2] = b4.z; b8[4 * q + 3] = b4.w;
@@ -499,8 +517,9 @@ __device__ __forceinline__ void gemm_epilogue_lines16(const GemmI4Params &p, Acc
                 const float(&b8)[8] = bi[u * (2 * t + h)];
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    float y0 = __fmaf_rn((float)acc[j][t][8 * h + 2 * e], s8[2 * e], b8[2 * e]);
-                    float y1 = __fmaf_rn((float)acc[j][t][8 * h + 2 * e + 1], s8[2 * e + 1], b8[2 * e + 1]);
+                    const float a0 = (float)acc[j][t][8 * h + 2 * e], a1 = (float)acc[j][t][8 * h + 2 * e + 1];
+                    float y0 = SCALED ? __fmaf_rn(a0, s8[2 * e], b8[2 * e]) : a0 + b8[2 * e];
+                    float y1 = SCALED ? __fmaf_rn(a1, s8[2 * e + 1], b8[2 * e + 1]) : a1 + b8[2 * e + 1];
                     asm volatile("" : "+v"(y0), "+v"(y1));  // keep the binary32 rounding (no fused narrowing)
                     hw[e] = (Epi::out == MKQ_F16) ? pack2_f16(y0, y1) : pack2_bf16(y0, y1);
                 }

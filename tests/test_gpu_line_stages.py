@@ -1,0 +1,88 @@
+"""The tile kernels with stages of 128-byte rows against the oracle: 4- and 8-bit configurations by number, at one stage
+per tile, ragged edges, more tiles than resident workgroups, and every kind of epilogue; the binary16 linear at sizes
+on every side of its tile choice.  Everything is exact: integer sums, correctly rounded binary32 epilogues, and for
+binary16 small integer operands, whose sums binary32 holds exactly in any order."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import RTOL, assert_float_close, to_dev, to_np
+
+pytestmark = pytest.mark.gpu
+GROUPS4 = {46: 2, 47: 2, 48: 2}  # wave groups that share the k loop
+GROUPS8 = {47: 2}
+
+
+@pytest.fixture(scope="module")
+def mkq():
+    import torch
+    assert torch.cuda.is_available()
+    import paper_2203_13483_amd as m
+    m.load()
+    return m
+
+
+def _case(M, N, K, bits, seed):
+    rng = np.random.default_rng(seed)
+    q = 1 << (bits - 1)
+    A = rng.integers(-q, q, (M, K), dtype=np.int8)
+    Wc = rng.integers(-q, q, (N, K), dtype=np.int8)
+    s_w = rng.uniform(0.001, 0.05, N).astype(np.float32) / (1 if bits == 4 else 256)
+    res = rng.normal(0, 1, (M, N)).astype(np.float16)
+    return A, Wc, s_w, np.float32(0.02), rng.normal(0, 0.5, N).astype(np.float32), res
+
+
+# one stage per tile; several stages and ragged edges; more tiles than any configuration keeps resident
+@pytest.mark.parametrize("M,N,stages", [(300, 520, 1), (257, 136, 5), (1500, 1104, 2), (8200, 2312, 1)])
+@pytest.mark.parametrize("bits,cfg", [(4, c) for c in range(43, 50)] + [(8, c) for c in (43, 44, 46, 47)])
+def test_configurations(mkq, bits, cfg, M, N, stages):
+    K = stages * (1024 // bits) * (GROUPS4 if bits == 4 else GROUPS8).get(cfg, 1)
+    A, Wc, s_w, s_x, bias, res = _case(M, N, K, bits, cfg + M + K)
+    clamp = dict(qmin=-128, qmax=127) if bits == 8 else {}
+
+    def run(out_dtype, **kw):
+        if bits == 8:
+            return mkq.mkq_linear_int8(to_dev(A), float(s_x), to_dev(Wc), to_dev(s_w), to_dev(bias), out_dtype, config=cfg, **kw)
+        return mkq.mkq_linear_int4(mkq.mkq_pack_codes_int4(to_dev(A)), float(s_x), mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1),
+                                   to_dev(s_w), to_dev(bias), N, K, out_dtype, config=cfg, **kw)
+
+    ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, out_dtype=oracle.BF16, s_next=0.9, **clamp)
+    assert np.array_equal(to_np(run(mkq.MKQ_BF16)["out"]).astype(np.float32), ref["y"])
+    codes = to_np(run(mkq.MKQ_I4 if bits == 4 else mkq.MKQ_I8, s_next=0.9)["out"])
+    assert np.array_equal(codes, oracle.pack_nibbles(ref["q"]) if bits == 4 else ref["q"])
+    ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, residual=res.astype(np.float32), out_dtype=oracle.F16, **clamp)
+    assert np.array_equal(to_np(run(mkq.MKQ_F16, residual=to_dev(res))["out"]).astype(np.float32), ref["y"])
+    if M < 1000:
+        r = run(mkq.MKQ_F32, want_acc=True)
+        ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, **clamp)
+        assert np.array_equal(to_np(r["acc"]), ref["acc"]) and np.array_equal(to_np(r["out"]), ref["y"])
+        r = run(mkq.MKQ_F16)
+        assert np.array_equal(to_np(r["out"]).astype(np.float32), oracle.round_storage(ref["y"], oracle.F16))
+
+
+def test_configurations_need_whole_stages(mkq):
+    A, Wc, s_w, s_x, bias, _ = _case(64, 64, 384, 4, 0)
+    a, w = mkq.mkq_pack_codes_int4(to_dev(A)), mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1)
+    for cfg in range(43, 50):
+        with pytest.raises(mkq.MkqError):
+            mkq.mkq_linear_int4(a, float(s_x), w, to_dev(s_w), to_dev(bias), 64, 384, mkq.MKQ_F16, config=cfg)
+
+
+# one shape per tile choice, in its order, with one and with several stages; a ragged N takes the general epilogue
+@pytest.mark.parametrize("M,N,K", [(100, 72, 256), (1, 8, 64), (70, 136, 192), (33, 77, 128), (1500, 1544, 64), (1500, 1540, 320),
+                                   (2100, 2056, 128), (2100, 2056, 64), (4100, 2312, 192), (8200, 2312, 64), (8200, 2312, 192)])
+def test_linear_fp16_tile_choices(mkq, M, N, K):
+    import torch
+    rng = np.random.default_rng(M + K)
+    a, W = (rng.integers(-8, 8, s).astype(np.float16) for s in ((M, K), (N, K)))
+    b, res = (rng.integers(-64, 64, s).astype(np.float32) for s in ((N,), (M, N)))
+    ref = a.astype(np.float32) @ W.astype(np.float32).T + b
+    args = [to_dev(a), to_dev(W), to_dev(b)]
+    assert np.array_equal(to_np(mkq.mkq_linear_fp16(*args, mkq.MKQ_F32)), ref)
+    assert np.array_equal(to_np(mkq.mkq_linear_fp16(*args, mkq.MKQ_F16)), ref.astype(np.float16))
+    got = mkq.mkq_linear_fp16(*args, mkq.MKQ_F16, mkq.MKQ_ACT_NONE, to_dev(res.astype(np.float16)))
+    assert np.array_equal(to_np(got), (ref + res).astype(np.float16))
+    small = [to_dev(a * np.float16(2.0 ** -6)), args[1], to_dev(b * np.float32(2.0 ** -6))]
+    got = to_np(mkq.mkq_linear_fp16(*small, mkq.MKQ_F16, mkq.MKQ_ACT_GELU))
+    want = torch.nn.functional.gelu(torch.from_numpy(ref.astype(np.float64) * 2.0 ** -6)).numpy()
+    assert_float_close(got, want, RTOL[1], "GELU")
