@@ -12,38 +12,97 @@ __device__ __forceinline__ double wave_sum_f64(double v)
     return v;
 }
 
+constexpr int CAL_THREADS = 1024;
+
 __global__ void zero_words_kernel(uint32_t *p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
 }
 
+// Address of group w (8 elements) of an [M, K] tensor with rows of ldx elements.  CONTIG: ldx == K, no split into
+// row and column (a 64-bit division for every eight elements: a third of the vector operations of these kernels).
+template <typename T, bool CONTIG>
+__device__ __forceinline__ const T *group_at(const T *x, int64_t w, int64_t groups_per_row, int64_t ldx)
+{
+    if (CONTIG) return x + w * 8;
+    const int64_t m = w / groups_per_row;
+    return x + m * ldx + (w - m * groups_per_row) * 8;
+}
+
+// Calls f with the eight values of every group that this thread owns.  AHEAD groups are fetched before the first of
+// them is used: with one load in flight per wave the trip to memory bounds the kernel (4.7 TB/s, four: 6).
+template <typename T, bool CONTIG, int AHEAD, class F>
+__device__ __forceinline__ void for_each_group(const T *__restrict__ x, int64_t total, int64_t groups_per_row, int64_t ldx,
+                                               int64_t every, F &&f)
+{
+    const int64_t stride = (int64_t)gridDim.x * every * blockDim.x;
+    for (int64_t w = (int64_t)blockIdx.x * every * blockDim.x + threadIdx.x; w < total; w += AHEAD * stride) {
+        float v[AHEAD][8];
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a) {
+            const int64_t wa = w + a * stride;
+            load8<T>(group_at<T, CONTIG>(x, wa < total ? wa : w, groups_per_row, ldx), v[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a)
+            if (w + a * stride < total) f(v[a]);
+    }
+}
+
+// The codes of Eq. 1 for eight values, as floats, without a division per value (QuantStep): one branch to the
+// division if any of the eight lies within the margin of a rounding boundary or is NaN or infinite.
+template <int BITS>
+__device__ __forceinline__ void codes8(const float (&x)[8], const QuantStep &q, float (&c)[8])
+{
+    constexpr float lo = (BITS == 4) ? (float)QMIN : -128.0f, hi = (BITS == 4) ? (float)QMAX : 127.0f;
+    bool divide = false;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float v = x[e] * q.rs, r = __builtin_rintf(v);
+        // beyond the clamp range the product's error may exceed the margin, and either quotient clamps alike
+        divide |= !(fabsf(v - r) <= q.thr);
+        c[e] = __builtin_amdgcn_fmed3f(r, lo, hi);
+    }
+    if (__builtin_expect(divide, 0)) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) c[e] = (float)((BITS == 4) ? quantize_code(x[e], q.s) : quantize_code8(x[e], q.s));
+    }
+}
+
 // g[0] += sum_i ( round(x_i/s) - x_i/s ),  g[1] += 2 sum_i ( Q[x_i] - x_i ) round(x_i/s)
 // with round() = the code of Eq. 1 (clamp included), decided in binary32 like the quantizer;
 // the terms and sums are binary64.
-template <typename T, int BITS>
-__global__ __launch_bounds__(256) void scale_gradients_kernel(const T *__restrict__ x, int64_t M, int64_t K,
+// A binary64 atomic addition is a compare-and-swap loop, and workgroups that meet in it are served one after the
+// other: with 2048 workgroups that was most of the kernel's time.  Few, large workgroups therefore (at most one per
+// CU).
+template <typename T, int BITS, bool CONTIG>
+__global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *__restrict__ x, int64_t M, int64_t K,
                                                               int64_t ldx, float s, double *__restrict__ g)
 {
-    __shared__ double part[2][4];
+    __shared__ double part[2][CAL_THREADS / 64];
     const double sd = (double)s, inv = 1.0 / sd;
+    const QuantStep qs = quant_step<BITS>(s);
     const int64_t groups_per_row = K / 8;
     const int64_t total = M * groups_per_row;
-    double ste = 0.0, mse = 0.0;
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
-         w += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t m = w / groups_per_row;
-        const int64_t kg = w - m * groups_per_row;
-        float v[8];
-        load8<T>(x + m * ldx + kg * 8, v);
+    // sum(c - x/s) = sum c - (sum x)/s and sum((s c - x) c) = s sum c^2 - sum(x c): the sums of c and c^2 of eight
+    // values are whole numbers that binary32 holds exactly, so binary64 is left with two sums per element, not three
+    double sc = 0.0, scc = 0.0, sx = 0.0, sxc = 0.0;
+    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, 1, [&](const float(&v)[8]) {
+        float c[8], c1 = 0.0f, c2 = 0.0f;
+        codes8<BITS>(v, qs, c);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const int c = (BITS == 4) ? quantize_code(v[e], s) : quantize_code8(v[e], s);
-            const double cd = (double)c, xd = (double)v[e];
-            ste += __builtin_fma(-xd, inv, cd);
-            mse = __builtin_fma(__builtin_fma(sd, cd, -xd), cd, mse);
+            c1 += c[e];
+            c2 = __builtin_fmaf(c[e], c[e], c2);
+            const double xd = (double)v[e];
+            sx += xd;
+            sxc = __builtin_fma(xd, (double)c[e], sxc);
         }
-    }
+        sc += (double)c1;
+        scc += (double)c2;
+    });
+    double ste = __builtin_fma(-sx, inv, sc), mse = __builtin_fma(sd, scc, -sxc);
     ste = wave_sum_f64(ste);
     mse = wave_sum_f64(mse);
     if ((threadIdx.x & 63) == 0) {
@@ -51,87 +110,65 @@ __global__ __launch_bounds__(256) void scale_gradients_kernel(const T *__restric
         part[1][threadIdx.x >> 6] = mse;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        atomicAdd(g, (part[0][0] + part[0][1]) + (part[0][2] + part[0][3]));
-        atomicAdd(g + 1, 2.0 * ((part[1][0] + part[1][1]) + (part[1][2] + part[1][3])));
+    if (threadIdx.x < 2) {  // one lane per sum: the two loops run side by side
+        double sum = 0.0;
+        for (int i = 0; i < CAL_THREADS / 64; ++i) sum += part[threadIdx.x][i];
+        atomicAdd(g + threadIdx.x, threadIdx.x ? 2.0 * sum : sum);
     }
 }
 
 // ---- percentile calibration: exact k-th largest of |x| by radix selection -------------
 // |x| >= 0, so its binary32 bit pattern (31 bits) orders like an unsigned integer.  Three
 // passes count, among the elements whose higher bits equal the prefix chosen so far, the
-// next 11, 10 and 10 bits; after each a single workgroup walks the counts from the top
-// and fixes the digit in which the k-th largest falls.
+// next 11, 10 and 10 bits; after each the last workgroup to finish walks the counts from the
+// top and fixes the digit in which the k-th largest falls.
+// The first pass would count every element, and the LDS atomics of that are what it is bound by (40 us for 16384 x
+// 4096 binary16 values, a plain read takes 22).  A sample of the tensor goes first: the k-th largest of a part is
+// no larger than the k-th largest of the whole, so elements in bins below the sample's are left out of the count.
 constexpr int PCT_BINS = 2048;
+constexpr int PCT_SAMPLE = 64;  // one group of 256 * 8 elements in this many
+enum { PCT_FLOOR = 3 };         // the pass over the sample
 struct PctWorkspace {
     uint32_t hist[3][PCT_BINS];
     uint32_t prefix;  // bits fixed so far
     uint32_t k;       // rank still to find inside the prefix
-    uint32_t pad[2];
+    uint32_t done;    // workgroups of the running pass that have added their counts
+    uint32_t floor;   // lowest bin of pass 0 that can hold the k-th largest
 };
 
-// Four copies of the counts, chosen by lane % 4: activations pile up in a few dozen bins
-// (one binade is 8 bins of pass 0), and lanes of one LDS atomic that hit the same counter
-// are served one after the other.
-template <typename T, int PASS>
-__global__ __launch_bounds__(256) void percentile_hist_kernel(const T *__restrict__ x, int64_t M, int64_t K,
-                                                              int64_t ldx, PctWorkspace *__restrict__ ws)
+__device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
 {
-    constexpr int COPIES = 4;  // interleaved, so the copies of one bin sit in different banks
-    __shared__ uint32_t h[PCT_BINS * COPIES];
-    for (int i = threadIdx.x; i < COPIES * PCT_BINS; i += 256) h[i] = 0u;
-    __syncthreads();
-    uint32_t *const mine = h + (threadIdx.x & (COPIES - 1));
-    const uint32_t prefix = PASS ? ws->prefix : 0u;
-    const int64_t groups_per_row = K / 8;
-    const int64_t total = M * groups_per_row;
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
-         w += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t m = w / groups_per_row;
-        const int64_t kg = w - m * groups_per_row;
-        float v[8];
-        load8<T>(x + m * ldx + kg * 8, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const uint32_t bits = (v[e] != v[e]) ? 0u : (__float_as_uint(v[e]) & 0x7FFFFFFFu);
-            if (PASS == 0) {
-                atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
-            } else if (PASS == 1) {
-                if ((bits >> 20) == prefix) atomicAdd(&mine[((bits >> 10) & 1023u) * COPIES], 1u);
-            } else {
-                if ((bits >> 10) == prefix) atomicAdd(&mine[(bits & 1023u) * COPIES], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < PCT_BINS; i += 256) {
-        const uint32_t c = (h[4 * i] + h[4 * i + 1]) + (h[4 * i + 2] + h[4 * i + 3]);
-        if (c) atomicAdd(&ws->hist[PASS][i], c);
-    }
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One workgroup.  PASS 0 starts from rank k0; the later passes from the rank left over.
+// One workgroup, of which 256 threads own bins.  PASS 0 (and the sample's) starts from rank k0; the later passes from the rank left over.
 // Thread t owns PER consecutive bins; the thread whose bins hold the k-th largest (fewer
 // than k elements in the bins above its own, at least k from its lowest bin up) fixes
 // the digit.  After PASS 2 the prefix is the whole bit pattern of T and the step
-// T / qmax is written.
+// T / qmax is written.  scratch: 272 words of LDS.
 template <int PASS>
-__global__ __launch_bounds__(256) void percentile_select_kernel(PctWorkspace *__restrict__ ws, uint32_t k0,
-                                                                float qmax, float *__restrict__ s_out)
+__device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws, uint32_t k0, float qmax,
+                                                  float *__restrict__ s_out, uint32_t *scratch)
 {
-    constexpr int NB = PASS == 0 ? 2048 : 1024;
+    constexpr int NB = (PASS == 0 || PASS == PCT_FLOOR) ? 2048 : 1024;
     constexpr int PER = NB / 256;
-    __shared__ uint32_t chunk[256], group[16];
+    constexpr int H = PASS == PCT_FLOOR ? 2 : PASS;  // the sample's counts borrow the last pass's
+    uint32_t *const chunk = scratch, *const group = scratch + 256;
     const int t = threadIdx.x;
+    const bool owner = t < 256;
     uint32_t mine[PER], sum = 0;
+    if (owner) {
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-        mine[i] = ws->hist[PASS][t * PER + i];
-        sum += mine[i];
+        for (int i = 0; i < PER; ++i) {
+            mine[i] = load_agent(&ws->hist[H][t * PER + i]);
+            if (PASS == PCT_FLOOR) ws->hist[H][t * PER + i] = 0u;
+            sum += mine[i];
+        }
+        chunk[t] = sum;
     }
-    chunk[t] = sum;
-    const uint32_t k = PASS ? ws->k : k0;
-    const uint32_t old_prefix = PASS ? ws->prefix : 0u;
+    const bool first = PASS == 0 || PASS == PCT_FLOOR;
+    const uint32_t k = first ? k0 : ws->k;
+    const uint32_t old_prefix = first ? 0u : ws->prefix;
     __syncthreads();
     if (t < 16) {
         uint32_t gs = 0;
@@ -140,6 +177,7 @@ __global__ __launch_bounds__(256) void percentile_select_kernel(PctWorkspace *__
         group[t] = gs;
     }
     __syncthreads();
+    if (!owner) return;
     // elements in the bins above this thread's: later threads of its group of 16, later groups
     uint32_t above = 0;
 #pragma unroll
@@ -161,19 +199,73 @@ __global__ __launch_bounds__(256) void percentile_select_kernel(PctWorkspace *__
                 }
             }
         }
-        const uint32_t prefix = PASS == 0 ? (uint32_t)(t * PER + b) : ((old_prefix << 10) | (uint32_t)(t * PER + b));
-        ws->prefix = prefix;
-        ws->k = k - cum;
-        if (PASS == 2) {
-            const float tv = __uint_as_float(prefix);
-            s_out[0] = (tv > 0.0f) ? tv / qmax : 1.0f;
+        if (PASS == PCT_FLOOR) {
+            ws->floor = (uint32_t)(t * PER + b);
+        } else {
+            const uint32_t prefix = PASS == 0 ? (uint32_t)(t * PER + b) : ((old_prefix << 10) | (uint32_t)(t * PER + b));
+            ws->prefix = prefix;
+            ws->k = k - cum;
+            if (PASS == 2) {
+                const float tv = __uint_as_float(prefix);
+                s_out[0] = (tv > 0.0f) ? tv / qmax : 1.0f;
+            }
         }
     }
 }
 
-static inline int stream_grid(int64_t items, int max_blocks = 256 * 8)
+// Four copies of the counts, chosen by lane % 4: activations pile up in a few dozen bins
+// (one binade is 8 bins of pass 0), and lanes of one LDS atomic that hit the same counter
+// are served one after the other.
+// (workgroups of 1024 threads: a quarter of the atomic additions on the few bins that all of them hit)
+template <typename T, int PASS, bool CONTIG>
+__global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *__restrict__ x, int64_t M, int64_t K,
+                                                              int64_t ldx, PctWorkspace *__restrict__ ws, uint32_t k0,
+                                                              float qmax, float *__restrict__ s_out)
 {
-    int64_t b = ceil_div(items, 256);
+    constexpr int COPIES = 4;  // interleaved, so the copies of one bin sit in different banks
+    __shared__ uint32_t h[PCT_BINS * COPIES];
+    for (int i = threadIdx.x; i < COPIES * PCT_BINS; i += CAL_THREADS) h[i] = 0u;
+    __syncthreads();
+    uint32_t *const mine = h + (threadIdx.x & (COPIES - 1));
+    const uint32_t prefix = (PASS == 1 || PASS == 2) ? ws->prefix : PASS == 0 ? ws->floor : 0u;
+    const int64_t groups_per_row = K / 8;
+    const int64_t total = M * groups_per_row;
+    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, PASS == PCT_FLOOR ? PCT_SAMPLE : 1, [&](const float(&v)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t bits = (v[e] != v[e]) ? 0u : (__float_as_uint(v[e]) & 0x7FFFFFFFu);
+            if (PASS == PCT_FLOOR) {
+                atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
+            } else if (PASS == 0) {
+                if ((bits >> 20) >= prefix) atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
+            } else if (PASS == 1) {
+                if ((bits >> 20) == prefix) atomicAdd(&mine[((bits >> 10) & 1023u) * COPIES], 1u);
+            } else {
+                if ((bits >> 10) == prefix) atomicAdd(&mine[(bits & 1023u) * COPIES], 1u);
+            }
+        }
+    });
+    __syncthreads();
+    for (int i = threadIdx.x; i < PCT_BINS; i += CAL_THREADS) {
+        const uint32_t c = (h[4 * i] + h[4 * i + 1]) + (h[4 * i + 2] + h[4 * i + 3]);
+        if (c) atomicAdd(&ws->hist[PASS == PCT_FLOOR ? 2 : PASS][i], c);
+    }
+    // the last workgroup to get here selects the digit: its ticket is drawn after every wave's counts have
+    // reached memory (the counts and the ticket are agent-scope atomics), nobody waits for anybody
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        const uint32_t old = __hip_atomic_fetch_add(&ws->done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        h[0] = old == gridDim.x - 1;
+        if (old == gridDim.x - 1) __hip_atomic_store(&ws->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (h[0] != 0u) percentile_select<PASS>(ws, k0, qmax, s_out, h + 64);
+}
+
+static inline int stream_grid(int64_t items, int max_blocks)
+{
+    int64_t b = ceil_div(items, CAL_THREADS);
     if (b < 1) b = 1;
     if (b > max_blocks) b = max_blocks;
     return (int)b;
@@ -203,12 +295,14 @@ extern "C" int mkq_scale_gradients(const void *x, int x_dtype, int64_t M, int64_
     if (reinterpret_cast<uintptr_t>(g_out) & 7u) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     zero_words_kernel<<<1, 64, 0, st>>>((uint32_t *)g_out, 4);
-    const int grid = stream_grid(M * (K / 8));
-#define MKQ_SG(T, B) scale_gradients_kernel<T, B><<<grid, 256, 0, st>>>((const T *)x, M, K, ldx, s, g_out)
+    const int grid = stream_grid(M * (K / 8), 256);
+#define MKQ_SG(T, B)                                                                                             \
+    if (ldx == K) scale_gradients_kernel<T, B, true><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, s, g_out); \
+    else scale_gradients_kernel<T, B, false><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, s, g_out)
     if (x_dtype == MKQ_F32) {
-        if (bits == 4) MKQ_SG(float, 4); else MKQ_SG(float, 8);
+        if (bits == 4) { MKQ_SG(float, 4); } else { MKQ_SG(float, 8); }
     } else {
-        if (bits == 4) MKQ_SG(__half, 4); else MKQ_SG(__half, 8);
+        if (bits == 4) { MKQ_SG(__half, 4); } else { MKQ_SG(__half, 8); }
     }
 #undef MKQ_SG
     return launch_status();
@@ -235,14 +329,26 @@ extern "C" int mkq_percentile_scale(const void *x, int x_dtype, int64_t M, int64
     hipStream_t st = as_stream(stream);
     constexpr int words = (int)(sizeof(PctWorkspace) / 4);
     zero_words_kernel<<<(words + 255) / 256, 256, 0, st>>>((uint32_t *)ws, words);
-    const int grid = stream_grid(M * (K / 8), 256 * 4);  // 32 KiB of LDS each: all resident at once
-#define MKQ_PASS(P)                                                                                     \
-    if (x_dtype == MKQ_F32) percentile_hist_kernel<float, P><<<grid, 256, 0, st>>>((const float *)x, M, K, ldx, ws); \
-    else percentile_hist_kernel<__half, P><<<grid, 256, 0, st>>>((const __half *)x, M, K, ldx, ws);     \
-    percentile_select_kernel<P><<<1, 256, 0, st>>>(ws, (uint32_t)k, qmax, s_out)
+    const int grid = stream_grid(M * (K / 8), 256 * 2);  // all resident at once
+#define MKQ_HIST(T, P, C, G) percentile_hist_kernel<T, P, C><<<G, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, ws, (uint32_t)k, qmax, s_out)
+#define MKQ_PASS_ON(P, G)                                                                    \
+    if (x_dtype == MKQ_F32) {                                                                \
+        if (ldx == K) { MKQ_HIST(float, P, true, G); } else { MKQ_HIST(float, P, false, G); }   \
+    } else {                                                                                 \
+        if (ldx == K) { MKQ_HIST(__half, P, true, G); } else { MKQ_HIST(__half, P, false, G); } \
+    }
+#define MKQ_PASS(P) MKQ_PASS_ON(P, grid)
+    // a sample that holds four times the elements above the step leaves most of the tensor out of the first count;
+    // below 4 M elements its launch costs more than the atomics
+    if (n >= ((int64_t)1 << 22) && 4 * PCT_SAMPLE * k <= n) {
+        const int sgrid = stream_grid(ceil_div(M * (K / 8), PCT_SAMPLE), 64);
+        MKQ_PASS_ON(PCT_FLOOR, sgrid);
+    }
     MKQ_PASS(0);
     MKQ_PASS(1);
     MKQ_PASS(2);
 #undef MKQ_PASS
+#undef MKQ_PASS_ON
+#undef MKQ_HIST
     return launch_status();
 }

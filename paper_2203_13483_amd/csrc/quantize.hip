@@ -72,7 +72,8 @@ __global__ __launch_bounds__(256) void quantize_contig_kernel(const T *__restric
 
 // max |x| over a block's share, combined with an atomic max on the bit pattern
 // (non-negative floats order like unsigned integers).  *acc_bits must be 0 on entry.
-template <typename T>
+// CONTIG: ldx == K, no split into row and column (a 64-bit division for every eight elements).
+template <typename T, bool CONTIG>
 __global__ __launch_bounds__(256) void absmax_tensor_kernel(const T *__restrict__ x, int64_t M,
                                                             int64_t K, int64_t ldx,
                                                             uint32_t *__restrict__ acc_bits)
@@ -81,14 +82,24 @@ __global__ __launch_bounds__(256) void absmax_tensor_kernel(const T *__restrict_
     const int64_t groups_per_row = K / 8;
     const int64_t total = M * groups_per_row;
     float mx = 0.0f;
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
-         w += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t m = w / groups_per_row;
-        const int64_t kw = w - m * groups_per_row;
-        float v[8];
-        load8<T>(x + m * ldx + kw * 8, v);
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    // four groups in flight per thread: with one the trip to memory bounds the kernel
+    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total; w += 4 * stride) {
+        float v[4][8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(v[i]));  // fmaxf drops NaN
+        for (int a = 0; a < 4; ++a) {
+            const int64_t wa = w + a * stride < total ? w + a * stride : w;  // (a group twice does not change the maximum)
+            const T *src = x + wa * 8;
+            if constexpr (!CONTIG) {
+                const int64_t m = wa / groups_per_row;
+                src = x + m * ldx + (wa - m * groups_per_row) * 8;
+            }
+            load8<T>(src, v[a]);
+        }
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) mx = fmaxf(mx, fabsf(v[a][i]));  // fmaxf drops NaN
     }
     mx = wave_max(mx);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = mx;
@@ -464,10 +475,13 @@ extern "C" int mkq_absmax_scale(const void *x, int x_dtype, int64_t M, int64_t K
     }
     fill_zero_kernel<<<1, 64, 0, st>>>((uint32_t *)s_out, 1);
     const int grid = grid_for(M * (K / 8), 256, 1024);
-    if (x_dtype == MKQ_F32)
-        absmax_tensor_kernel<float><<<grid, 256, 0, st>>>((const float *)x, M, K, ldx, (uint32_t *)s_out);
-    else
-        absmax_tensor_kernel<__half><<<grid, 256, 0, st>>>((const __half *)x, M, K, ldx, (uint32_t *)s_out);
+#define MKQ_ABSMAX(T, C) absmax_tensor_kernel<T, C><<<grid, 256, 0, st>>>((const T *)x, M, K, ldx, (uint32_t *)s_out)
+    if (x_dtype == MKQ_F32) {
+        if (ldx == K) MKQ_ABSMAX(float, true); else MKQ_ABSMAX(float, false);
+    } else {
+        if (ldx == K) MKQ_ABSMAX(__half, true); else MKQ_ABSMAX(__half, false);
+    }
+#undef MKQ_ABSMAX
     finalize_scale_kernel<<<1, 64, 0, st>>>(s_out, 1);
     return launch_status();
 }

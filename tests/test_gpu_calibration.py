@@ -89,3 +89,46 @@ def test_percentile_step_feeds_the_quantizer(mkq):
     assert np.array_equal(codes, ref)
     clipped = (np.abs(x.astype(np.float32)) >= 7 * s).mean()
     assert 0.015 < clipped < 0.025
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("order", ["random", "sorted", "outliers outside", "constant"])
+def test_percentile_of_a_tensor_large_enough_to_be_sampled(mkq, order, dtype):
+    """4 M elements and more: a sample (64th pieces of 2048 elements) bounds the first count from below.  Any
+    arrangement of the values and any stride of the rows gives the same order statistic."""
+    M, K = 2049, 2056
+    x = _activations(M, K, 17, dtype)
+    if order == "sorted":
+        x = np.sort(x, axis=None).reshape(M, K)
+    elif order == "outliers outside":
+        x.flat[:2048] = 0.0  # the sample's first piece
+        x.flat[2048:2048 + 4096] = 60.0
+    elif order == "constant":
+        x[:] = 1.5
+    wide = np.full((M, K + 24), 1000, dtype)
+    wide[:, 8:8 + K] = x
+    for ppm, bits in ((0, 4), (10, 8), (1000, 4), (3900, 4), (3910, 4)):  # (either side of the sample's limit, 1 / 256)
+        ref, _ = oracle.percentile_scale(x.astype(np.float32), ppm, 7 if bits == 4 else 127)
+        assert float(to_np(mkq.mkq_percentile_scale(to_dev(x), ppm, bits))[0]) == ref, ppm
+        assert float(to_np(mkq.mkq_percentile_scale(to_dev(wide)[:, 8:8 + K], ppm, bits))[0]) == ref, ppm
+    assert float(to_np(mkq.mkq_absmax_scale(to_dev(wide)[:, 8:8 + K]))[0]) == np.float32(np.abs(x.astype(np.float32)).max()) / np.float32(7)
+
+
+@pytest.mark.parametrize("bits,s", [(4, 1.0 / 3), (8, 0.0173), (4, 2.0 ** -120)])
+def test_scale_gradients_next_to_rounding_boundaries(mkq, bits, s):
+    """Values at, and an ulp beside, every boundary k + 1/2 (and far beyond the clamp range), where the product with
+    1/s could round the other way: the codes are the division's, so the sums are the oracle's."""
+    s = np.float32(s)
+    q = 1 << (bits - 1)
+    at = ((np.arange(-q - 2, q + 2, dtype=np.float64) + 0.5) * float(s)).astype(np.float32)
+    x = np.concatenate([at, np.nextafter(at, np.float32(np.inf)), np.nextafter(at, np.float32(-np.inf)), at * np.float32(1e4)])
+    x = np.concatenate([x, np.zeros(-len(x) % 8, np.float32)]).reshape(1, -1)
+    g = to_np(mkq.mkq_scale_gradients(to_dev(x), float(s), bits))
+    ste, mse = oracle.scale_gradients(x, s, -q, q - 1)
+    # either side rounds every one of its n partial sums once, by 2^-53 of at most the sum of the terms' magnitudes; a
+    # code that fell the other way would show as a whole unit (the sums hold 1e4 steps per code at most)
+    c = oracle.quantize(x, s, -q, q - 1).astype(np.float64)
+    xd, sd = x.astype(np.float64), float(s)
+    bound = 2 * x.size * 2.0 ** -53
+    assert abs(g[0] - ste) <= bound * np.abs(c - xd / sd).sum() < 0.5
+    assert abs(g[1] - mse) <= bound * np.abs(2 * (sd * c - xd) * c).sum()
