@@ -173,9 +173,10 @@ int mkq_init(void);
  *     out      = narrow(y)  or  codes(y; s_next) packed     (Eq. 1 again)
  *   a        [M, K]: packed codes (a_dtype == MKQ_I4, rows of K/2 bytes) or float
  *            activations (MKQ_F32 / MKQ_F16), which are first quantized with s_x
- *            into `workspace` by a launch of mkq_quantize's kernel that precedes the
- *            GEMM (two launches: inside one launch the hand-over between the
- *            quantizing and the multiplying workgroups cost more than the second launch)
+ *            into `workspace`: by a launch of mkq_quantize's kernel that precedes the
+ *            GEMM (inside one launch a hand-over between quantizing and multiplying
+ *            workgroups cost more than the second launch), or, for a few sentences
+ *            (K <= 1024, at most one 32x32 tile per CU), by the GEMM's own workgroups
  *   Wq, s_w  from mkq_pack_weights_int4;  bias [N] binary32 or NULL
  *   out      [M, N] of out_dtype (F32, F16, BF16) or [M, N/2] bytes (I4); may be
  *            NULL when epi->q_out or epi->acc_out is the only result wanted

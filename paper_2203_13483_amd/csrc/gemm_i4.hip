@@ -33,6 +33,9 @@ bool gemm_i4_stream_ok(const GemmI4Params &p);
 int run_gemm_i4_stream(const GemmI4Params &p, const SplitKScratch *scr, int forced_ks, hipStream_t st);
 int setup_gemm_i4_stream(const GemmI4Params &p, hipStream_t st);
 int run_gemm_i4_wstream(const GemmI4Params &p, const SplitKScratch *scr, int forced_ks, int variant, hipStream_t st);
+// quantizer and GEMM of a few tokens in one launch (gemm_small.hip)
+bool small_quantizing_ok(const GemmI4Params &p, const void *a, int elem_bytes);
+int run_gemm_i4_small(const GemmI4Params &p, const void *a, int a_dtype, hipStream_t st);
 // tile kernels with 128-byte stage rows (gemm_lines.hip)
 int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int run_gemm_i8_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
@@ -1017,6 +1020,9 @@ static int linear_int4_run(const void *a, int a_dtype, float s_x, const uint8_t 
     p.q_pitch = (int)q_pitch;
     p.acc_shift = 8;
     p.acc_unit = 0.00390625f;
+    // the caller's workspace stays unused on this route
+    if (a_dtype != MKQ_I4 && !stream_layout && forced_cfg < 0 && small_quantizing_ok(p, a, a_dtype == MKQ_F32 ? 4 : 2))
+        return run_gemm_i4_small(p, a, a_dtype, as_stream(stream));
     // the kernel that will run is set up (and a forced configuration that does not apply is refused)
     // before anything is enqueued
     auto run = [&]() {
