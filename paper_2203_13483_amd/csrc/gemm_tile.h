@@ -35,11 +35,16 @@ struct GemmI4DmaCfg : GemmI4Cfg<BM_, BN_, WGM_, WGN_, RB_> {
     static constexpr int WAVES_PER_EU = (WGS_PER_CU * WAVES / 4 < 2 && RB_ == 128) ? 2 : WGS_PER_CU * WAVES / 4;
     static_assert(COPIES % WAVES == 0, "copies must divide evenly over the waves");
     static_assert(BM_ % ROWS_PER_COPY == 0, "a copy must not straddle the A / W boundary");
-    // Stages in flight right after a stage's copies are issued: past a stage's boundary every wave holds the
-    // rest of that stage in registers, so its own slot is refilled there.
-    static constexpr int INFLIGHT = S - 1;
+    // Which slot is refilled behind a stage's boundary.  OWN: the slot of the stage just read, which every wave holds
+    // in registers by then; one more stage in flight from the same ring, what rings of two and three stages need.
+    // Otherwise (64-byte stages, three stages and more) the slot of the stage before it, by copies that directly
+    // follow the boundary: with the own slot these kernels were 0-10 % slower at short k loops (median 2.4 % of 162
+    // shapes with 256x128 tiles, 2.8 % of 154 with 64x64 four-stage tiles of two wave groups).
+    static constexpr bool OWN = RB_ != 64;
+    // stages in flight right after a stage's copies are issued
+    static constexpr int INFLIGHT = OWN ? S - 1 : S - 2;
     static_assert(RB_ == 32 || RB_ == 64 || RB_ == 128, "a stage is one, two or four 32-byte rounds");
-    static_assert(S >= 2 && INFLIGHT * LPW <= 63, "vmcnt immediate is 6 bits");
+    static_assert(S >= (OWN ? 2 : 3) && INFLIGHT * LPW <= 63, "vmcnt immediate is 6 bits");
     static_assert(LDS_BYTES <= 160 * 1024, "LDS is 160 KiB per CU");
 };
 
@@ -99,6 +104,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
     constexpr int S = Cfg::S, LPW = Cfg::LPW;
     constexpr int ROUNDS = Cfg::ROUNDS, INFLIGHT = Cfg::INFLIGHT;
+    constexpr bool OWN = Cfg::OWN && ROUNDS > 1;  // (one-round stages refill their own slot in a loop of their own)
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     const int tid = threadIdx.x;
@@ -186,12 +192,12 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
     uint32_t raw[BUFS][NF][4];
 
     // Steps of a stage, counted from its boundary (POST of them follow it, the others are the first ones of the
-    // next iteration); a wave's copies into the slot just read are spread over SPREAD steps from the boundary on:
+    // next iteration); OWN: a wave's copies into the slot just read are spread over SPREAD steps from the boundary on:
     // issued together, the 16 cycles that the address unit needs for each of them stall the wave and its matrix
     // pipe.  A two-stage ring waits for the copies at the next boundary, so they go out in its first half.
     constexpr int STEPS = BITS == 4 ? 2 * ROUNDS : ROUNDS;
     constexpr int POST = ROUNDS == 1 ? STEPS : BITS == 4 ? 2 : AHEAD;
-    constexpr int SPREAD = ROUNDS == 1 ? 1 : (S >= 3 ? STEPS : (STEPS + 1) / 2);
+    constexpr int SPREAD = !OWN ? 1 : (S >= 3 ? STEPS : (STEPS + 1) / 2);
     constexpr int FIRST = SPREAD <= POST ? LPW : POST * LPW / SPREAD;  // copies of the POST steps
     v4i wid[2][NF];          // widened operands of two k steps
 
@@ -326,7 +332,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
         copy_advance();
     }
     static_for<FIRST>([&](auto qc) { copy_one(INFLIGHT, qc); });
-    if constexpr (ROUNDS == 1) copy_advance();
+    if constexpr (!OWN) copy_advance();
     wait_vmcnt<(INFLIGHT - 1) * LPW + FIRST>();
     lds_barrier();
     static_for<AHEAD>([&](auto rc) {
@@ -406,29 +412,31 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
         if constexpr (ROWS_EPI) {
             if (grp == 0 && ck == scale_stage) stage_scales(ct);
         }
-        // A stage's slot is refilled from its boundary on, except behind a tile's last stage: there it first
+        // OWN: a stage's slot is refilled from its boundary on, except behind a tile's last stage: there it first
         // serves the epilogue as scratch and each wave refills its share after that.
-        const bool last = ROUNDS > 1 && ck + 1 == kt_count;
+        const bool last = OWN && ck + 1 == kt_count;
         if constexpr (BITS != 4) {
             const int nbuf = next_slot(buf);
             const int pbuf = prev_slot(buf);
             static_for<ROUNDS - AHEAD>([&](auto hc) { k_step8(hc, buf * Cfg::STAGE_BYTES, pbuf, true); });
-            copy_advance();
+            if constexpr (OWN) copy_advance();
             stage_boundary();
             static_for<AHEAD>([&](auto hc) {
-                k_step8(IntC<ROUNDS - AHEAD + decltype(hc)::value>{}, nbuf * Cfg::STAGE_BYTES, buf, !last);
+                k_step8(IntC<ROUNDS - AHEAD + decltype(hc)::value>{}, nbuf * Cfg::STAGE_BYTES, OWN ? buf : pbuf, !last);
             });
+            if constexpr (!OWN) copy_advance();
             buf = nbuf;
             ck += 1;
         } else if constexpr (ROUNDS > 1) {
             // one stage of ROUNDS rounds: rounds 1 .. are fetched from the same stage, then the boundary,
-            // then round 0 of the next stage while the slot just read is refilled
+            // then round 0 of the next stage while a slot is refilled
             const int nbuf = next_slot(buf);
             const int pbuf = prev_slot(buf);
             static_for<2 * ROUNDS - 2>([&](auto hc) { k_step(hc, buf * Cfg::STAGE_BYTES, pbuf, true); });
-            copy_advance();
+            if constexpr (OWN) copy_advance();
             stage_boundary();
-            k_step(IntC<2 * ROUNDS - 2>{}, nbuf * Cfg::STAGE_BYTES, buf, !last);
+            k_step(IntC<2 * ROUNDS - 2>{}, nbuf * Cfg::STAGE_BYTES, OWN ? buf : pbuf, !last);
+            if constexpr (!OWN) copy_advance();
             k_step(IntC<2 * ROUNDS - 1>{}, 0, buf, !last);
             buf = nbuf;
             ck += 1;
@@ -551,13 +559,13 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
             }
             if (grp == 0 && finish) {
                 if constexpr (ROWS_EPI) {
-                    // the slot of the stage just finished is idle: each wave shuffles through the share of it
-                    // that it refills itself
+                    // the slot of the stage just finished is idle (!OWN: until every wave has passed the next
+                    // boundary): each wave shuffles through the share of it that it refills itself
                     const int done_slot = (buf == 0) ? S - 1 : buf - 1;
                     // the scale / bias copies have landed: only the stage copies issued after them (those of
-                    // INFLIGHT - 1 boundaries, fewer in a shorter tile) may be in flight
-                    if (kt_count >= INFLIGHT) wait_vmcnt<(INFLIGHT - 1) * LPW>();
-                    else wait_vmcnt<0>();
+                    // INFLIGHT boundaries, one less with OWN, fewer in a shorter tile) may be in flight
+                    if (kt_count >= INFLIGHT) wait_vmcnt<(INFLIGHT - (OWN ? 1 : 0)) * LPW>();
+                    else wait_vmcnt<OWN ? 0 : LPW>();
                     // plain 16-bit outputs of 64-channel waves take the line epilogue, without its register
                     // cache of the scales (with it this kernel spills)
                     if constexpr (EpiLines16<Cfg, Epi>::usable)
@@ -574,9 +582,9 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
             }
             const bool interior = (tile_m + 1) * BM <= p.M && (tile_n + 1) * BN <= p.N;
             // (a group without stores must not count them in its waits)
-            // (behind the stores only the copies of the slot refilled next are waited for with them)
-            stores_pending = (ASYNC_STORES && interior && grp == 0 && finish) ? INFLIGHT - (ROUNDS > 1 ? 1 : 0) : 0;
-            if constexpr (ROUNDS > 1) {
+            // (OWN: the copies of the slot refilled next come behind the stores, one boundary less)
+            stores_pending = (ASYNC_STORES && interior && grp == 0 && finish) ? INFLIGHT - (OWN ? 1 : 0) : 0;
+            if constexpr (OWN) {
                 __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): the wave is done with its scratch
                 const int done = __builtin_amdgcn_readfirstlane(prev_slot(buf));
                 static_for<FIRST>([&](auto qc) { copy_one(done, qc); });
