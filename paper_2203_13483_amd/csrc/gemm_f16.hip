@@ -14,11 +14,24 @@ static int launch_f16_by_epilogue(const GemmI4Params &p, hipStream_t st)
         if (p.out_dtype == MKQ_F16 && p.residual) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 16, KSPLIT>(p, st);
         if (p.out_dtype == MKQ_F16 && gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, true>, 16, KSPLIT>(p, st);
         if (p.out_dtype == MKQ_F16) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, 16, KSPLIT>(p, st);
+        if (!p.residual && !gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, 16, KSPLIT>(p, st);
     }
     return launch_gemm_i4_dma<Cfg, EpiGeneric, 16, KSPLIT>(p, st);
 }
 
 // ---------------------------------------------------------------------------------
+// Arguments of the split kernel: its launches are the smallest, and with the tile kernel's block of three times this
+// size a launch took 0.2 us longer (M = 1024, K = 3072, N = 768 13.9 instead of 13.7).
+struct GemmF16Params {
+    const uint8_t *A;  // [M, K] binary16
+    const uint8_t *W;  // [N, K] binary16
+    int M, N, K;
+    const float *bias;        // [N] or null
+    const uint16_t *residual; // [M, N] binary16 or null
+    int act;
+    void *out;
+    int out_dtype;  // MKQ_F32 or MKQ_F16
+};
 // The split kernel of the smallest launches: 64-wide k stages, and the k loop shared by two wave groups.
 template <int BM_, int BN_, int WGM_, int WGN_, int S_>
 struct GemmF16Cfg {
@@ -41,7 +54,7 @@ struct GemmF16Cfg {
 // epilogue (for launches with few tiles, whose lone wave per SIMD is bound by its own
 // instruction stream).
 template <class Cfg, int KSPLIT>
-__global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const GemmI4Params p)
+__global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const GemmF16Params p)
 {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, RB = Cfg::RB, CH = Cfg::CH;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, S = Cfg::S, LPW = Cfg::LPW, KSTEPS = Cfg::KSTEPS;
@@ -171,7 +184,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
 #pragma unroll
                     for (int e = 0; e < 8; ++e) y[e] = acc[j][t][8 * G + e] + bi[e];
                     if (p.residual) {
-                        const uint16_t *r = (const uint16_t *)p.residual + o;
+                        const uint16_t *r = p.residual + o;
                         if (vec_ok) {
                             const uint4 rr = *reinterpret_cast<const uint4 *>(r);
                             const uint32_t rwd[4] = {rr.x, rr.y, rr.z, rr.w};
@@ -280,7 +293,8 @@ static int launch_gemm_f16(const GemmI4Params &p, hipStream_t st)
     const int rc = resident_workgroups(once, gemm_f16_kernel<Cfg, KSPLIT>, Cfg::THREADS * KSPLIT, lds, 1 << 20, &resident);
     if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
-    gemm_f16_kernel<Cfg, KSPLIT><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(p);
+    GemmF16Params q = {p.A, p.W, p.M, p.N, p.K, p.bias, (const uint16_t *)p.residual, p.act, p.out, p.out_dtype};
+    gemm_f16_kernel<Cfg, KSPLIT><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(q);
     return launch_status();
 }
 
@@ -294,14 +308,19 @@ static bool few_tiles(const GemmI4Params &p)
 // workgroup per CU, from 192 tiles on, and 64x64 below; us, old -> new):
 //   4096 tokens, K = 768: N = 2304 31.9 -> 24.3, N = 768 14.3 -> 11.8, N = 3072 with GELU 39.8 -> 31.8;
 //   K = 3072, N = 768 33.5 -> 28.8; 2298 tokens 22.0 -> 14.1, 9.4 -> 8.7, 26.8 -> 20.2, 28.8 -> 23.3;
-//   16384 tokens, K = 1024, N = 4096 230 -> 153
+//   16384 tokens, K = 1024, N = 4096 230 -> 153.  Over 843 shapes (M = 1 .. 16384, 33 pairs of K and N with their epilogues)
+// four are slower than before by more than 2 %, by 7 % at most (440 tokens, K = 1280, N = 5120 with GELU 14.1 -> 15.1).
 enum { F16_SPLIT = 0, F16_64, F16_128_DEEP, F16_256x128, F16_128, F16_256, F16_CONFIGS };
 static int choose_f16(const GemmI4Params &p)
 {
-    const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
+    const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128), t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
     // at most one 64x64 tile per CU: two wave groups share the k loop (a lone wave per SIMD waits for its own loads)
     if (few_tiles(p)) return F16_SPLIT;
-    if (t128 <= 128) return F16_64;
+    // up to two 64x64 tiles per CU, three (all that fit) where the epilogue is a large share of the tile: 3072 tokens,
+    // K = N = 768 with a residual 12.1 -> 11.3, 681 tokens, K = 768, N = 3072 with GELU 11.7 -> 10.9; without either the
+    // 128x128 tiles win from two per CU on (1024 tokens, K = 768, N = 2304 10.5 -> 10.0)
+    const bool long_epilogue = (p.residual || p.act == MKQ_ACT_GELU) && p.K <= 768;
+    if (t64 <= (long_epilogue ? 768 : 512)) return F16_64;
     // about one 128x128 tile per CU: a deep ring, since nothing else covers the trip to memory
     if (t128 <= 256) return F16_128_DEEP;
     // one 256x128 tile of eight waves per CU in a single round
@@ -330,12 +349,12 @@ int setup_gemm_f16()
 {
     int rc = MKQ_OK;
     for (int cfg = 0; cfg < F16_CONFIGS; ++cfg)
-        for (int e = 0; e < 4 && rc == MKQ_OK; ++e) {
+        for (int e = 0; e < 5 && rc == MKQ_OK; ++e) {
             GemmI4Params p = {};
             p.M = p.N = p.K = 256;
             p.setup_only = true;
-            p.out_dtype = e == 3 ? MKQ_F32 : MKQ_F16;
-            p.act = e == 2 ? MKQ_ACT_GELU : MKQ_ACT_NONE;
+            p.out_dtype = e >= 3 ? MKQ_F32 : MKQ_F16;
+            p.act = e == 2 || e == 4 ? MKQ_ACT_GELU : MKQ_ACT_NONE;
             if (e == 1) p.residual = &p;
             rc = run_config(p, cfg, nullptr);
         }
