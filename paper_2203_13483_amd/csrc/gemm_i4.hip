@@ -449,50 +449,84 @@ using DmaBig8 = GemmI4DmaCfg<256, 256, 2, 4, 64, 5>;   // 2 waves per SIMD, 128x
 using DmaMid = GemmI4DmaCfg<128, 128, 2, 2, 64, 4>;    // 64 KiB LDS: two workgroups per CU
 using DmaSmall = GemmI4DmaCfg<64, 64, 2, 2, 64, 8>;
 
-// Tile choice of the ring kernels, from sweeps over M = 128 .. 65536 at the BERT-base / BERT-large shapes (and
-// 4096^2, 8192^2 weights).  Where whole 256-code stages fit K the 128-byte-row kernels (43 .. 49, gemm_lines.hip)
-// take the call wherever they measured faster than the 64-byte-row ones (us, 64-byte -> 128-byte):
-//   45, at least two 256x256 tiles per CU: M = 65536, K = 1024, N = 4096 272 -> 250; 16384 tokens 77 -> 68; 8192
-//       tokens with GELU 52.5 -> 48; M = 8192, K = N = 4096 112 -> 101
-//   44, 256x128: M = 8192, K = 1024, N = 3072 31.0 -> 28.5; K = 4096, N = 1024 36.6 -> 33.7; M = 2298, K = 768, N = 2304
-//       10.7 -> 9.2, N = 3072 with GELU 15.0 -> 14.2 (a single round of at most one tile per CU, or a long enough
-//       k loop: at K = 768 over two rounds nothing covers the epilogue, 20.7 -> 24.7 with GELU)
-//   49, 128x128 on eight waves: M = 4096, K = 768, N = 2304 15.2 -> 14.0
-//   43, 64x64: M = 4096, K = 768, N = 768 8.6 -> 8.1; M = 440, N = 3072 with GELU 8.1 -> 7.2; M = 1024 9.7 -> 8.8
-//   46, 47, 48, two wave groups share the k loop of a 128x128, 64x64 or 128x64 tile: M = 440, 1024, 2298, K = 3072, N = 768
-//       8.7 -> 7.8, 8.8 -> 8.2, 12.8 -> 10.8; M = 128, K = N = 4096 9.8 -> 8.8
-// Otherwise, 64-byte rows: very large problems 256x128 tiles, two workgroups per CU (18).  Few tiles: 64x64,
+// Tile choice of the kernels with 64-byte stage rows, from sweeps over M = 256 .. 65536 at the BERT-base / BERT-large
+// shapes (and 4096^2, 8192^2 weights).  Very large problems: 256x128 tiles, two workgroups per CU (18).  Few tiles: 64x64,
 // four per CU (27; the launch is latency-bound, parallelism wins).  In between 128x128 with a three-stage ring,
 // three per CU (29), or 128x64, four per CU (28), when 128x128 tiles would leave most of the 768 slots empty and
 // the k loop is short.
-static int choose_tiles(const GemmI4Params &p)
+static int choose_rows64(const GemmI4Params &p)
 {
     const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t128x64 = ceil_div(p.M, 128) * ceil_div(p.N, 64);
-    const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
     const double ops = 2.0 * p.M * p.N * p.K;
-    const bool gelu = p.act == MKQ_ACT_GELU;
-    const bool lines = (p.K % 256) == 0, split = lines && (p.K % 512) == 0;
-    if (t256x128 >= 512 && ops >= 6e10)
-        return lines && ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 512 ? 45 : 18;
-    // a long k loop and at most two 64x64 tiles per CU: the wave groups of a workgroup share it (a lone wave per SIMD
-    // is bound by its own instruction stream)
-    if (split && t128x64 <= 256 && t64 <= 256 && p.K >= 1024) return 47;
-    if (split && t128x64 <= 256 && t64 <= 512 && p.K >= 2048) return 48;
-    if (t128x64 <= 256) return lines && p.K < 1536 ? 43 : 27;
+    if (t256x128 >= 512 && ops >= 6e10) return 18;
+    if (t128x64 <= 256) return 27;
     // GELU (and the code decision behind it) makes the epilogue a large share of a short tile: up to four 64x64
     // workgroups per CU spread it over all SIMDs (FFN-up at M = 1024: 9.2 instead of 10.4 us)
-    if (gelu && p.K < 2048 && t64 <= 1024) return lines ? 43 : 27;
+    if (p.act == MKQ_ACT_GELU && p.K < 2048 && ceil_div(p.M, 64) * ceil_div(p.N, 64) <= 1024) return 27;
     if (t128 >= 400 || p.K >= 2048) {
         // at most one 128x128 workgroup per CU and a long k loop: two wave groups share the tile's K; 6-14 % at
         // N = 768 / 1024, K = 3072 ... 8192, M = 2560 ... 5120
-        if (t128 <= 256 && p.K >= 2048 && (p.K % 256) == 0) return split ? 46 : 35;
-        if (lines && (t256x128 <= 256 || (p.K >= 1024 && !gelu))) return 44;
-        return lines && p.K < 1024 && !gelu ? 49 : 29;
+        if (t128 <= 256 && p.K >= 2048 && (p.K % 256) == 0) return 35;
+        return 29;
     }
-    if (lines) return t128 < 256 ? 43 : 44;
     return 28;
+}
+
+// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49, gemm_lines.hip) in the
+// ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
+// 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
+// rounds of tiles).  (us, 64-byte -> 128-byte rows)
+static int choose_tiles(const GemmI4Params &p)
+{
+    const int rows64 = choose_rows64(p);
+    if ((p.K % 256) != 0) return rows64;
+    const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
+    const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128), t256 = ceil_div(p.M, 256) * ceil_div(p.N, 256);
+    const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32;
+    const bool codes = p.out_dtype == MKQ_I4;
+    const bool split = (p.K % 512) == 0;  // two wave groups with whole stages each
+    // The large tiles only where their epilogue has a compile-time instantiation and writes whole lines: their waves own 64
+    // channels, and 16-bit rows of other lengths than a multiple of 64 start inside a line (M = 4096, K = 768, N = 2008
+    // 11.2 -> 12.3, N = 2306 at M = 2048 24.5 -> 27.8; with N = 2304 12.4 -> 12.3)
+    const bool fixed = classify_epilogue(p) != EPI_GENERIC && ((p.N % 64) == 0 || codes || res);
+    if (rows64 == 18) {
+        // 45, one 256x256 tile per CU and round: for code outputs (M = 8192, K = 1024, N = 4096 with GELU 52.2 -> 49.6) or a
+        // long k loop (K = N = 4096 104.2 -> 99.5); at K <= 1024 a plain epilogue, which nothing covers, eats the gain
+        // (f16, M = 12288 50.6 -> 52.0) until nine rounds (M = 65536 251 -> 247).  A last round that is less than five eighths full
+        // takes as long as a full one, where 18 fills it with one workgroup per CU (M = 10240 with GELU 63.7 -> 68.6);
+        // residuals at short k and binary32 outputs lose everywhere (M = 12288 65.7 -> 72.6).
+        const int64_t last = t256 % 256;
+        const bool many = t256 >= 9 * 256, full = t256 >= 512 && (many || last == 0 || last >= 160);
+        return full && fixed && !f32 && (codes || p.K >= 2048 || (many && !res)) ? 45 : 18;
+    }
+    if (t64 <= 512 && ceil_div(p.M, 128) * ceil_div(p.N, 64) <= 256 && p.K >= 1024) {
+        // few tiles and a long k loop, shared by the wave groups of a workgroup (a lone wave per SIMD is bound by its own
+        // instruction stream): 47, 64x64: M = 440, K = 3072, N = 768 8.3 -> 7.8; 48, 128x64: M = 2298 12.5 -> 10.7
+        if (split) return t64 <= 256 ? 47 : p.K >= 1536 ? 48 : 43;
+        // an odd number of 256-code stages: the 64-byte rows can be shared (K = 1280, N = 312 with a residual 43 would take
+        // 6.4 instead of 5.9; K = 2304, N = 768, M = 440 8.6 instead of 7.3)
+        return p.K >= 2048 || (res && t64 <= 256) ? rows64 : 43;
+    }
+    // 43, 64x64, up to three per CU: M = 4096, K = N = 768 with a residual 8.7 -> 8.1; M = 1024, N = 3072 with GELU 9.2 -> 8.6
+    if (t64 <= 768 && (p.K < 1536 || (p.K < 2048 && (gelu || !split)))) return 43;
+    // about one 128x128 tile per CU: 49, on eight waves (M = 1280, K = 768, N = 3072 with GELU 10.7 -> 9.6; M = 4096,
+    // K = N = 1024 10.0 -> 9.5, where 43 with four 64x64 tiles per CU takes 10.5), or 46, two wave groups share the k loop
+    // (M = 3072, K = 3072, N = 768 15.6 -> 14.4)
+    if (t128 <= 256) {
+        if (f32 && p.K < 1536) return rows64;  // (M = 1280, K = 768, N = 3072 10.2 -> 10.7)
+        if (p.K >= (gelu ? 2048 : 1536)) return split ? 46 : rows64;
+        return fixed ? 49 : rows64;
+    }
+    if (!fixed) return rows64;
+    // one and a half rounds of 43 still beat two of anything larger where the epilogue is long (M = 1536, K = 768, N = 3072 with
+    // GELU 13.0 -> 11.3; M = 6144, K = N = 768 with a residual 11.0 -> 10.2)
+    if (t64 <= 1536 && ((gelu && p.K < 2048) || (res && p.K <= 1024 && t64 > 1024))) return 43;
+    // 44, a single round of 256x128 tiles (M = 2298, K = 768, N = 2304 10.3 -> 9.5; M = 8192, K = 4096, N = 1024 37.3 -> 34.7);
+    // in a second round nothing covers the first one's epilogue (M = 4096, K = 1024, N = 3072 15.4 -> 18.3)
+    if (t256x128 <= (res && p.K <= 1024 ? 192 : 256) && t64 > 1024 && p.K >= (gelu ? 768 : 512) && !f32) return 44;
+    return rows64;
 }
 
 // K split across workgroups of a tile kernel with BM x BN tiles and `groups` wave groups per workgroup: fills
