@@ -635,26 +635,31 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
     }
 }
 
-// Tile choice of the 8-bit linear, from sweeps over M = 440 .. 8192 at the BERT shapes (us, best 64-byte-row kernel ->
-// choice; K = 768 unless said otherwise):
-//   43, 64x64:    M = 440, N = 2304 / 768 6.1 -> 5.4, 5.9 -> 5.2; M = 2298, N = 768 7.3 -> 7.0, K = 3072 17.4 -> 13.8;
-//                 M = 4096, K = 3072, N = 768 25.1 -> 20.3
-//   47, its k loop shared by two wave groups: M = 440, 1024, K = 3072, N = 768 12.1 -> 8.4, 11.9 -> 8.7
-//   44, 256x128:  M = 2298, N = 2304 13.7 -> 9.3, N = 3072 with GELU 17.5 -> 16.5; M = 8192, K = 4096, N = 1024 43.5 -> 38.5
-//   46, 128x128:  M = 4096, N = 2304 17.5 -> 16.1; M = 8192, K = 1024, N = 1024 18.7 -> 17.2
-//   29, 64-byte rows, three workgroups per CU: GELU over several rounds of tiles (46 has two): M = 4096, N = 3072 24.2
-//                 (46: 25.8); M = 8192, K = 1024, N = 4096 58.7 (18, as for 4 bits: 63.2)
+// Tile choice of the 8-bit linear, from sweeps of every configuration at 1300 calls (as for 4 bits, M to 16384; us, best
+// 64-byte-row choice -> here):
+//   47, 64x64, its long k loop shared by two wave groups: M = 440, K = 3072, N = 768 12.1 -> 8.4
+//   43, 64x64, up to three per CU (M = 4096, K = 3072, N = 768 25.1 -> 20.3), and where the epilogue is long up to six (GELU,
+//       M = 1280, K = 1024, N = 4096 17.1 -> 13.9) or four (residual, short k: M = 5120, K = N = 768 10.7 -> 9.3)
+//   46, 128x128, two per CU: M = 1691, K = 768, N = 2304 8.3 -> 7.9; M = 2048, K = N = 2048 20.9 -> 13.0; M = 4096, K = 1024,
+//       N = 3072 19.0 -> 18.5
+//   44, a single round of 256x128: M = 2298, K = 768, N = 2304 13.7 -> 9.3; not for a residual at short k (its rows come late)
+//       nor for binary32 (M = 2560, K = 768, N = 3072 46 16.7, 44 19.6)
+//   29, 64-byte rows, three per CU, where 46 would need a second, nearly empty round (M = 12288, K = N = 768 18.9 instead of
+//       21.1), at short k (M = 12288, K = 256, N = 768 10.5 instead of 11.8) and for GELU over several rounds
 static int choose_tiles_i8(const GemmI4Params &p)
 {
-    const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128), t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
-    const bool gelu = p.act == MKQ_ACT_GELU, lines = (p.K % 128) == 0;
+    if ((p.K % 128) != 0) return choose_rows64(p);
+    const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
+    const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
+    const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr;
     if (!gelu && t256x128 >= 512 && 2.0 * p.M * p.N * p.K >= 6e10) return 18;
-    if (t128 <= 256) {
-        if (!lines) return 27;
-        return (p.K % 256) == 0 && p.K >= 2048 && ceil_div(p.M, 64) * ceil_div(p.N, 64) <= 256 ? 47 : 43;
-    }
-    if (lines && t256x128 <= 256 && (!p.residual || p.K >= 2048)) return 44;
-    return lines && !gelu ? 46 : 29;
+    if (t64 <= 256 && (p.K % 256) == 0 && p.K >= 2048) return 47;
+    if (t64 <= 768 || (gelu && p.K < 1536 && t64 <= 1536) || (res && p.K <= 1024 && t64 <= 1024)) return 43;
+    // (the general epilogue, eight values of one token per lane: M = 1691, K = 768, N = 2306 21.1 -> 25.9 with the large tiles)
+    if (p.K < 2048 && classify_epilogue(p) == EPI_GENERIC) return choose_rows64(p);
+    if (t128 <= 256) return 46;
+    if (t256x128 <= 256 && p.out_dtype != MKQ_F32 && (!res || p.K >= 2048)) return 44;
+    return t128 > 512 && (t128 <= 640 || p.K < 768 || (gelu && p.K < 1536)) ? 29 : 46;
 }
 
 int run_gemm_i8(const GemmI4Params &p, hipStream_t st, int forced_cfg = -1)
