@@ -46,24 +46,26 @@ __global__ __launch_bounds__(SmallCfg::THREADS) void gemm_i4_small_kernel(const 
         if (u < units) fw[i] = *reinterpret_cast<const uint4 *>(wp + u * 32);
     }
 
-    // quantize rows m0 .. m0 + 31 (past the edge: the last row again), eight values per thread and turn
+    // quantize the tile's rows, eight values per thread and turn.  Rows past the edge stay as the LDS happens to hold
+    // them: they are only multiplied into sums that are never stored (with the last row in their place, M = 1, K = N =
+    // 1024 took 6.5 us, two launches 5.5; now 3.9).
     const QuantStep qs = quant_step<4>(p.s_x);
-    const int gpr = p.K / 8, total = 32 * gpr;
+    const int gpr = p.K / 8, rows = p.M - m0 < 32 ? p.M - m0 : 32, total = rows * gpr;
     for (int g0 = tid; g0 < total; g0 += AHEAD * SmallCfg::THREADS) {
         float v[AHEAD][8];
         int at[AHEAD], to[AHEAD];
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
-            int g = g0 + i * SmallCfg::THREADS;
-            g = g < total ? g : g0;  // (written twice with the same codes)
+            const int g = g0 + i * SmallCfg::THREADS;
+            if (g >= total) break;
             const int r = g / gpr, c = g - r * gpr;
-            const int m = m0 + r < p.M ? m0 + r : p.M - 1;
             at[i] = r * pitch + c * 4;
-            to[i] = m * row_bytes + c * 4;
-            load8<T>(x + (size_t)m * p.K + c * 8, v[i]);
+            to[i] = (m0 + r) * row_bytes + c * 4;
+            load8<T>(x + (size_t)(m0 + r) * p.K + c * 8, v[i]);
         }
 #pragma unroll
         for (int i = 0; i < AHEAD; ++i) {
+            if (g0 + i * SmallCfg::THREADS >= total) break;
             const uint32_t codes = quantize8<4>(v[i], qs).x;
             *reinterpret_cast<uint32_t *>(smem + at[i]) = codes;
             if (n0 == 0) *reinterpret_cast<uint32_t *>(codes_out + to[i]) = codes;
@@ -106,8 +108,9 @@ __global__ __launch_bounds__(SmallCfg::THREADS) void gemm_i4_small_kernel(const 
 }
 
 // At most one tile per CU and rows that a thread fetches in one go.  Kernel times inside a graph, us, two launches ->
-// one: K = 768, N = 768, binary32, M = 16 / 64 / 128 / 256 6.3 -> 6.0, 7.2 -> 6.1, 7.1 -> 6.4, 7.2 -> 6.4; binary16 M = 256
-// 7.2 -> 5.9; N = 3072, M = 64 7.3 -> 6.4.  With two tiles per CU (M = 384, N = 768) 7.4 -> 10.1; with K = 3072 9.7 -> 14.0.
+// one: K = 768, N = 768, binary32, M = 1 / 16 / 64 / 128 / 256 5.3 -> 3.7, 6.1 -> 4.6, 7.0 -> 5.9, 7.4 -> 5.8, 7.5 -> 6.0;
+// binary16 M = 256 7.2 -> 5.9; N = 3072, M = 64 7.1 -> 5.9; K = 1024, N = 1024, M = 1 / 8 / 32 5.6 -> 3.9, 6.2 -> 4.4, 6.8 -> 6.6;
+// K = 1024, N = 8192, M = 32, the least favourable, 6.8 -> 6.9.  With two tiles per CU (M = 384, N = 768) 7.4 -> 10.1; with K = 3072 9.7 -> 14.0.
 constexpr int64_t SMALL_MAX_TILES = 256, SMALL_MAX_K = 1024;
 
 // Whether the one-launch route takes a linear with activations a of the given element size.
