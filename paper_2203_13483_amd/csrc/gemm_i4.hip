@@ -1059,7 +1059,7 @@ static int linear_int4_run(const void *a, int a_dtype, float s_x, const uint8_t 
     p.q_pitch = (int)q_pitch;
     p.acc_shift = 8;
     p.acc_unit = 0.00390625f;
-    // the caller's workspace stays unused on this route
+    // a few sentences: quantizer and GEMM in one launch, which leaves the codes in the workspace as the two launches do
     if (a_dtype != MKQ_I4 && !stream_layout && forced_cfg < 0 && small_quantizing_ok(p, a, a_dtype == MKQ_F32 ? 4 : 2))
         return run_gemm_i4_small(p, a, a_dtype, as_stream(stream));
     // the kernel that will run is set up (and a forced configuration that does not apply is refused)

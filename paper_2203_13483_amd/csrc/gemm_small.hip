@@ -119,17 +119,19 @@ bool small_quantizing_ok(const GemmI4Params &p, const void *a, int elem_bytes)
     if ((p.K % 64) != 0 || p.K > SMALL_MAX_K) return false;
     const int64_t tiles = ceil_div(p.M, 32) * ceil_div(p.N, 32);
     if (tiles > SMALL_MAX_TILES) return false;
-    // an output that overlaps the activations would be written while other workgroups still read
-    // them (the quantizer as a launch of its own has read everything before)
-    const uintptr_t a0 = reinterpret_cast<uintptr_t>(a), a1 = a0 + (uintptr_t)p.M * p.K * elem_bytes;
-    auto apart = [&](const void *q, int64_t bytes) {
-        const uintptr_t b0 = reinterpret_cast<uintptr_t>(q);
-        return !q || b0 + (uintptr_t)bytes <= a0 || a1 <= b0;
+    // an output that overlaps the activations would be written while other workgroups still read them, one that
+    // overlaps the workspace while others still leave their codes there (the quantizer as a launch of its own has
+    // read and written everything before)
+    auto apart = [](const void *q, int64_t q_bytes, const void *r, int64_t r_bytes) {
+        const uintptr_t q0 = reinterpret_cast<uintptr_t>(q), r0 = reinterpret_cast<uintptr_t>(r);
+        return !q || q0 + (uintptr_t)q_bytes <= r0 || r0 + (uintptr_t)r_bytes <= q0;
     };
+    const int64_t a_bytes = (int64_t)p.M * p.K * elem_bytes, code_bytes = (int64_t)p.M * p.K / 2;
+    auto untouched = [&](const void *q, int64_t bytes) { return apart(q, bytes, a, a_bytes) && apart(q, bytes, p.A, code_bytes); };
     const int64_t pitch = p.q_pitch ? p.q_pitch : p.N;
     const int64_t out_bytes = p.out_dtype == MKQ_I4 ? p.M * pitch / 2 : (int64_t)p.M * p.N * (p.out_dtype == MKQ_F32 ? 4 : 2);
-    return apart(p.A, (int64_t)p.M * p.K / 2) && apart(p.out, out_bytes) && apart(p.q_out, p.M * pitch / 2) &&
-           apart(p.acc_out, (int64_t)p.M * p.N * 4);
+    return apart(p.A, code_bytes, a, a_bytes) && untouched(p.out, out_bytes) && untouched(p.q_out, p.M * pitch / 2) &&
+           untouched(p.acc_out, (int64_t)p.M * p.N * 4);
 }
 
 int run_gemm_i4_small(const GemmI4Params &p, const void *a, int a_dtype, hipStream_t st)

@@ -63,3 +63,21 @@ def test_output_in_place_of_the_activations(mkq):
     xd = to_dev(x)
     mkq.mkq_linear_int4(xd, 0.3, mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1), to_dev(s_w), None, N, K, mkq.MKQ_F32, out=xd)
     assert np.array_equal(to_np(xd), ref["y"])
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 32, 1024), (64, 64, 832)])
+def test_output_over_the_workspace(mkq, M, N, K):
+    """out over the workspace at sizes that the GEMM's own launch serves with a single workgroup, which reads every code
+    before it writes: such a call keeps its quantizer launch (in one launch, the codes of one 32-row tile would race with
+    the results of the other)."""
+    import torch
+    rng = np.random.default_rng(K)
+    x = rng.standard_normal((M, K)).astype(np.float32)
+    Wc = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    s_w = rng.uniform(0.001, 0.05, N).astype(np.float32)
+    ref = oracle.linear_int4(oracle.quantize(x, np.float32(0.3)), np.float32(0.3), Wc, s_w, None)
+    ws = torch.zeros(mkq.mkq_linear_int4_workspace_bytes(M, N, K, mkq.MKQ_F32), dtype=torch.uint8, device="cuda")
+    out = ws[: M * N * 4].view(torch.float32).reshape(M, N)
+    mkq.mkq_linear_int4(to_dev(x), 0.3, mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1), to_dev(s_w), None, N, K, mkq.MKQ_F32,
+                        out=out, workspace=ws)
+    assert np.array_equal(to_np(out), ref["y"])
