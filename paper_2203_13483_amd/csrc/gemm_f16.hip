@@ -71,8 +71,8 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
 
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     const int total_tiles = tiles_m * tiles_n;
-    const int row_bytes = p.K * 2;
-    const int kt_count = row_bytes / RB / KSPLIT;
+    const uint32_t row_bytes = (uint32_t)p.K * 2;
+    const int kt_count = (int)(row_bytes / (RB * KSPLIT));
     const int k_first = grp * kt_count * RB;
     const int my_tiles = (total_tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int steps = my_tiles * kt_count;
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
                 g = tn * BN + (row - BM);
                 g = g < p.N ? g : p.N - 1;
             }
-            goff[q] = (uint32_t)g * (uint32_t)row_bytes + chunk * 16;
+            goff[q] = (uint32_t)g * row_bytes + chunk * 16;
         }
     };
     int lt = blockIdx.x, lk = 0;

@@ -122,8 +122,8 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
 
     const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
     const int total_tiles = tiles_m * tiles_n * ks;     // (tile, slice) pairs: pair v is slice v % ks of tile v / ks
-    const int row_bytes = p.K * BITS / 8;
-    const int kt_count = row_bytes / RB / KSPLIT / ks;  // stages per pair of this group
+    const uint32_t row_bytes = (uint32_t)p.K / 8 * BITS;  // (below 4 GiB, beyond an int: K % 32 == 0)
+    const int kt_count = (int)(row_bytes / (RB * KSPLIT)) / ks;  // stages per pair of this group
     // Persistent workgroup: pairs blockIdx.x, blockIdx.x + gridDim.x, ... run through ONE
     // software pipeline, so a tile's first stages are in flight during the previous
     // tile's epilogue.
@@ -151,7 +151,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
                 g = tn * BN + (row - BM);
                 g = g < p.N ? g : p.N - 1;
             }
-            goff[q] = (uint32_t)g * (uint32_t)row_bytes + chunk * 16;
+            goff[q] = (uint32_t)g * row_bytes + chunk * 16;
         }
     };
     Acc acc[TM][TN];

@@ -86,3 +86,15 @@ def test_linear_fp16_tile_choices(mkq, M, N, K):
     got = to_np(mkq.mkq_linear_fp16(*small, mkq.MKQ_F16, mkq.MKQ_ACT_GELU))
     want = torch.nn.functional.gelu(torch.from_numpy(ref.astype(np.float64) * 2.0 ** -6)).numpy()
     assert_float_close(got, want, RTOL[1], "GELU")
+
+
+def test_linear_fp16_long_rows(mkq):
+    """Rows of 256 MiB and more, whose bytes times eight pass 2^31: a few whole numbers in rows of zeros, exact."""
+    import torch
+    K = (1 << 27) + 64
+    at = torch.tensor([0, 63, 64, (1 << 26) + 5, (1 << 27) - 1, 1 << 27, K - 1], device="cuda")
+    a, W = (torch.zeros((rows, K), dtype=torch.float16, device="cuda") for rows in (2, 3))
+    a[:, at] = torch.arange(14, device="cuda").reshape(2, 7).half()
+    W[:, at] = torch.arange(-10, 11, device="cuda").reshape(3, 7).half()
+    ref = a[:, at].cpu().float() @ W[:, at].cpu().float().T
+    assert np.array_equal(to_np(mkq.mkq_linear_fp16(a, W, None, mkq.MKQ_F32)), ref.numpy())
