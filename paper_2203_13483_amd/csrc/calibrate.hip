@@ -13,6 +13,10 @@ __device__ __forceinline__ double wave_sum_f64(double v)
 }
 
 constexpr int CAL_THREADS = 1024;
+// Threads per workgroup of the gradient sums: a tensor that 64 small workgroups cover takes small ones, which spread it over
+// more CUs (128 x 768 binary32 7.3 -> 6.7 us); beyond that the sums of many workgroups would queue in their atomic
+// additions (440 x 768: 7.4 us with 42 large ones, 7.9 with 165 small ones).
+static inline int gradient_threads(int64_t groups) { return groups <= 64 * 256 ? 256 : CAL_THREADS; }
 
 __global__ void zero_words_kernel(uint32_t *p, int n)
 {
@@ -31,17 +35,31 @@ __device__ __forceinline__ const T *group_at(const T *x, int64_t w, int64_t grou
 }
 
 // Calls f with the eight values of every group that this thread owns.  AHEAD groups are fetched before the first of
-// them is used: with one load in flight per wave the trip to memory bounds the kernel (4.7 TB/s, four: 6).
+// them is used, so that a thread has as many loads in flight.  A batch that reaches past the end fetches its first group
+// again, which is cheaper than a branch per load (25.7 instead of 27.0 us for a counting pass over 16384 x 4096 binary16
+// values) -- unless rows have gaps: the address of a group is a 64-bit division then, so whole batches go first, without
+// checks, and the last one skips what does not exist (percentile of 128 rows of 768 + 64 binary32 values 21.2 -> 18.3 us).
 template <typename T, bool CONTIG, int AHEAD, class F>
 __device__ __forceinline__ void for_each_group(const T *__restrict__ x, int64_t total, int64_t groups_per_row, int64_t ldx,
-                                               int64_t every, F &&f)
+                                               F &&f)
 {
-    const int64_t stride = (int64_t)gridDim.x * every * blockDim.x;
-    for (int64_t w = (int64_t)blockIdx.x * every * blockDim.x + threadIdx.x; w < total; w += AHEAD * stride) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if constexpr (!CONTIG) {
+        for (; w + (AHEAD - 1) * stride < total; w += AHEAD * stride) {
+            float v[AHEAD][8];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) load8<T>(group_at<T, CONTIG>(x, w + a * stride, groups_per_row, ldx), v[a]);
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) f(v[a]);
+        }
+    }
+    for (; w < total; w += AHEAD * stride) {
         float v[AHEAD][8];
 #pragma unroll
         for (int a = 0; a < AHEAD; ++a) {
             const int64_t wa = w + a * stride;
+            if (!CONTIG && wa >= total) break;
             load8<T>(group_at<T, CONTIG>(x, wa < total ? wa : w, groups_per_row, ldx), v[a]);
         }
 #pragma unroll
@@ -88,7 +106,7 @@ __global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *_
     // sum(c - x/s) = sum c - (sum x)/s and sum((s c - x) c) = s sum c^2 - sum(x c): the sums of c and c^2 of eight
     // values are whole numbers that binary32 holds exactly, so binary64 is left with two sums per element, not three
     double sc = 0.0, scc = 0.0, sx = 0.0, sxc = 0.0;
-    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, 1, [&](const float(&v)[8]) {
+    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, [&](const float(&v)[8]) {
         float c[8], c1 = 0.0f, c2 = 0.0f;
         codes8<BITS>(v, qs, c);
 #pragma unroll
@@ -112,7 +130,7 @@ __global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *_
     __syncthreads();
     if (threadIdx.x < 2) {  // one lane per sum: the two loops run side by side
         double sum = 0.0;
-        for (int i = 0; i < CAL_THREADS / 64; ++i) sum += part[threadIdx.x][i];
+        for (int i = 0; i < (int)blockDim.x / 64; ++i) sum += part[threadIdx.x][i];
         atomicAdd(g + threadIdx.x, threadIdx.x ? 2.0 * sum : sum);
     }
 }
@@ -122,18 +140,16 @@ __global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *_
 // passes count, among the elements whose higher bits equal the prefix chosen so far, the
 // next 11, 10 and 10 bits; after each the last workgroup to finish walks the counts from the
 // top and fixes the digit in which the k-th largest falls.
-// The first pass would count every element, and the LDS atomics of that are what it is bound by (40 us for 16384 x
-// 4096 binary16 values, a plain read takes 22).  A sample of the tensor goes first: the k-th largest of a part is
-// no larger than the k-th largest of the whole, so elements in bins below the sample's are left out of the count.
+// 16384 x 4096 binary16 values: 30.6 + 25.7 + 26.0 us, the later passes at 5.2 TB/s (absmax, which only reads: 27.0); the
+// first adds every element to a counter in LDS.  (A bound from a sample of the tensor spares most of these additions,
+// but its own pass costs more, at every size: 26.8 + 8.8 instead of 30.6.)
 constexpr int PCT_BINS = 2048;
-constexpr int PCT_SAMPLE = 64;  // one group of 256 * 8 elements in this many
-enum { PCT_FLOOR = 3 };         // the pass over the sample
 struct PctWorkspace {
     uint32_t hist[3][PCT_BINS];
     uint32_t prefix;  // bits fixed so far
     uint32_t k;       // rank still to find inside the prefix
     uint32_t done;    // workgroups of the running pass that have added their counts
-    uint32_t floor;   // lowest bin of pass 0 that can hold the k-th largest
+    uint32_t pad;
 };
 
 __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
@@ -141,7 +157,7 @@ __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// One workgroup, of which 256 threads own bins.  PASS 0 (and the sample's) starts from rank k0; the later passes from the rank left over.
+// One workgroup, of which 256 threads own bins.  PASS 0 starts from rank k0; the later passes from the rank left over.
 // Thread t owns PER consecutive bins; the thread whose bins hold the k-th largest (fewer
 // than k elements in the bins above its own, at least k from its lowest bin up) fixes
 // the digit.  After PASS 2 the prefix is the whole bit pattern of T and the step
@@ -150,9 +166,8 @@ template <int PASS>
 __device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws, uint32_t k0, float qmax,
                                                   float *__restrict__ s_out, uint32_t *scratch)
 {
-    constexpr int NB = (PASS == 0 || PASS == PCT_FLOOR) ? 2048 : 1024;
+    constexpr int NB = PASS == 0 ? 2048 : 1024;
     constexpr int PER = NB / 256;
-    constexpr int H = PASS == PCT_FLOOR ? 2 : PASS;  // the sample's counts borrow the last pass's
     uint32_t *const chunk = scratch, *const group = scratch + 256;
     const int t = threadIdx.x;
     const bool owner = t < 256;
@@ -160,15 +175,13 @@ __device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws,
     if (owner) {
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            mine[i] = load_agent(&ws->hist[H][t * PER + i]);
-            if (PASS == PCT_FLOOR) ws->hist[H][t * PER + i] = 0u;
+            mine[i] = load_agent(&ws->hist[PASS][t * PER + i]);
             sum += mine[i];
         }
         chunk[t] = sum;
     }
-    const bool first = PASS == 0 || PASS == PCT_FLOOR;
-    const uint32_t k = first ? k0 : ws->k;
-    const uint32_t old_prefix = first ? 0u : ws->prefix;
+    const uint32_t k = PASS ? ws->k : k0;
+    const uint32_t old_prefix = PASS ? ws->prefix : 0u;
     __syncthreads();
     if (t < 16) {
         uint32_t gs = 0;
@@ -199,16 +212,12 @@ __device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws,
                 }
             }
         }
-        if (PASS == PCT_FLOOR) {
-            ws->floor = (uint32_t)(t * PER + b);
-        } else {
-            const uint32_t prefix = PASS == 0 ? (uint32_t)(t * PER + b) : ((old_prefix << 10) | (uint32_t)(t * PER + b));
-            ws->prefix = prefix;
-            ws->k = k - cum;
-            if (PASS == 2) {
-                const float tv = __uint_as_float(prefix);
-                s_out[0] = (tv > 0.0f) ? tv / qmax : 1.0f;
-            }
+        const uint32_t prefix = PASS == 0 ? (uint32_t)(t * PER + b) : ((old_prefix << 10) | (uint32_t)(t * PER + b));
+        ws->prefix = prefix;
+        ws->k = k - cum;
+        if (PASS == 2) {
+            const float tv = __uint_as_float(prefix);
+            s_out[0] = (tv > 0.0f) ? tv / qmax : 1.0f;
         }
     }
 }
@@ -227,17 +236,15 @@ __global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *_
     for (int i = threadIdx.x; i < COPIES * PCT_BINS; i += CAL_THREADS) h[i] = 0u;
     __syncthreads();
     uint32_t *const mine = h + (threadIdx.x & (COPIES - 1));
-    const uint32_t prefix = (PASS == 1 || PASS == 2) ? ws->prefix : PASS == 0 ? ws->floor : 0u;
+    const uint32_t prefix = PASS ? ws->prefix : 0u;
     const int64_t groups_per_row = K / 8;
     const int64_t total = M * groups_per_row;
-    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, PASS == PCT_FLOOR ? PCT_SAMPLE : 1, [&](const float(&v)[8]) {
+    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, [&](const float(&v)[8]) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
             const uint32_t bits = (v[e] != v[e]) ? 0u : (__float_as_uint(v[e]) & 0x7FFFFFFFu);
-            if (PASS == PCT_FLOOR) {
+            if (PASS == 0) {
                 atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
-            } else if (PASS == 0) {
-                if ((bits >> 20) >= prefix) atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
             } else if (PASS == 1) {
                 if ((bits >> 20) == prefix) atomicAdd(&mine[((bits >> 10) & 1023u) * COPIES], 1u);
             } else {
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *_
     __syncthreads();
     for (int i = threadIdx.x; i < PCT_BINS; i += CAL_THREADS) {
         const uint32_t c = (h[4 * i] + h[4 * i + 1]) + (h[4 * i + 2] + h[4 * i + 3]);
-        if (c) atomicAdd(&ws->hist[PASS == PCT_FLOOR ? 2 : PASS][i], c);
+        if (c) atomicAdd(&ws->hist[PASS][i], c);
     }
     // the last workgroup to get here selects the digit: its ticket is drawn after every wave's counts have
     // reached memory (the counts and the ticket are agent-scope atomics), nobody waits for anybody
@@ -263,9 +270,9 @@ __global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *_
     if (h[0] != 0u) percentile_select<PASS>(ws, k0, qmax, s_out, h + 64);
 }
 
-static inline int stream_grid(int64_t items, int max_blocks)
+static inline int stream_grid(int64_t items, int threads, int max_blocks)
 {
-    int64_t b = ceil_div(items, CAL_THREADS);
+    int64_t b = ceil_div(items, threads);
     if (b < 1) b = 1;
     if (b > max_blocks) b = max_blocks;
     return (int)b;
@@ -295,10 +302,11 @@ extern "C" int mkq_scale_gradients(const void *x, int x_dtype, int64_t M, int64_
     if (reinterpret_cast<uintptr_t>(g_out) & 7u) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     zero_words_kernel<<<1, 64, 0, st>>>((uint32_t *)g_out, 4);
-    const int grid = stream_grid(M * (K / 8), 256);
+    const int threads = gradient_threads(M * (K / 8));
+    const int grid = stream_grid(M * (K / 8), threads, 256);
 #define MKQ_SG(T, B)                                                                                             \
-    if (ldx == K) scale_gradients_kernel<T, B, true><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, s, g_out); \
-    else scale_gradients_kernel<T, B, false><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, s, g_out)
+    if (ldx == K) scale_gradients_kernel<T, B, true><<<grid, threads, 0, st>>>((const T *)x, M, K, ldx, s, g_out); \
+    else scale_gradients_kernel<T, B, false><<<grid, threads, 0, st>>>((const T *)x, M, K, ldx, s, g_out)
     if (x_dtype == MKQ_F32) {
         if (bits == 4) { MKQ_SG(float, 4); } else { MKQ_SG(float, 8); }
     } else {
@@ -329,26 +337,18 @@ extern "C" int mkq_percentile_scale(const void *x, int x_dtype, int64_t M, int64
     hipStream_t st = as_stream(stream);
     constexpr int words = (int)(sizeof(PctWorkspace) / 4);
     zero_words_kernel<<<(words + 255) / 256, 256, 0, st>>>((uint32_t *)ws, words);
-    const int grid = stream_grid(M * (K / 8), 256 * 2);  // all resident at once
-#define MKQ_HIST(T, P, C, G) percentile_hist_kernel<T, P, C><<<G, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, ws, (uint32_t)k, qmax, s_out)
-#define MKQ_PASS_ON(P, G)                                                                    \
-    if (x_dtype == MKQ_F32) {                                                                \
-        if (ldx == K) { MKQ_HIST(float, P, true, G); } else { MKQ_HIST(float, P, false, G); }   \
-    } else {                                                                                 \
-        if (ldx == K) { MKQ_HIST(__half, P, true, G); } else { MKQ_HIST(__half, P, false, G); } \
-    }
-#define MKQ_PASS(P) MKQ_PASS_ON(P, grid)
-    // a sample that holds four times the elements above the step leaves most of the tensor out of the first count;
-    // below 4 M elements its launch costs more than the atomics
-    if (n >= ((int64_t)1 << 22) && 4 * PCT_SAMPLE * k <= n) {
-        const int sgrid = stream_grid(ceil_div(M * (K / 8), PCT_SAMPLE), 64);
-        MKQ_PASS_ON(PCT_FLOOR, sgrid);
+    const int grid = stream_grid(M * (K / 8), CAL_THREADS, 256 * 2);  // all resident at once
+#define MKQ_HIST(T, P, C) percentile_hist_kernel<T, P, C><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, ws, (uint32_t)k, qmax, s_out)
+#define MKQ_PASS(P)                                                                    \
+    if (x_dtype == MKQ_F32) {                                                          \
+        if (ldx == K) { MKQ_HIST(float, P, true); } else { MKQ_HIST(float, P, false); }   \
+    } else {                                                                           \
+        if (ldx == K) { MKQ_HIST(__half, P, true); } else { MKQ_HIST(__half, P, false); } \
     }
     MKQ_PASS(0);
     MKQ_PASS(1);
     MKQ_PASS(2);
 #undef MKQ_PASS
-#undef MKQ_PASS_ON
 #undef MKQ_HIST
     return launch_status();
 }
