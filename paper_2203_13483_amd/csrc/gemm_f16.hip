@@ -6,17 +6,17 @@
 
 namespace mkq {
 
-template <class Cfg, int KSPLIT = 1>
+template <class Cfg>
 static int launch_f16_by_epilogue(const GemmI4Params &p, hipStream_t st)
 {
     const bool gelu = p.act == MKQ_ACT_GELU;
     if ((p.N % 8) == 0 && !(p.residual && gelu)) {
-        if (p.out_dtype == MKQ_F16 && p.residual) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 16, KSPLIT>(p, st);
-        if (p.out_dtype == MKQ_F16 && gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, true>, 16, KSPLIT>(p, st);
-        if (p.out_dtype == MKQ_F16) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, 16, KSPLIT>(p, st);
-        if (!p.residual && !gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, 16, KSPLIT>(p, st);
+        if (p.out_dtype == MKQ_F16 && p.residual) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 16>(p, st);
+        if (p.out_dtype == MKQ_F16 && gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, true>, 16>(p, st);
+        if (p.out_dtype == MKQ_F16) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, 16>(p, st);
+        if (!p.residual && !gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, 16>(p, st);
     }
-    return launch_gemm_i4_dma<Cfg, EpiGeneric, 16, KSPLIT>(p, st);
+    return launch_gemm_i4_dma<Cfg, EpiGeneric, 16>(p, st);
 }
 
 // ---------------------------------------------------------------------------------
@@ -32,47 +32,40 @@ struct GemmF16Params {
     void *out;
     int out_dtype;  // MKQ_F32 or MKQ_F16
 };
-// The split kernel of the smallest launches: 64-wide k stages, and the k loop shared by two wave groups.
-template <int BM_, int BN_, int WGM_, int WGN_, int S_>
-struct GemmF16Cfg {
-    static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_, S = S_;
-    static constexpr int RB = 128;  // bytes per row per stage = 64 elements of k
-    static constexpr int CH = RB / 16;
-    static constexpr int KSTEPS = RB / 32;  // MFMA k steps (16 elements) per stage
-    static constexpr int WAVES = WGM * WGN, THREADS = WAVES * 64;
-    static constexpr int WTM = BM / WGM, WTN = BN / WGN, TM = WTM / 32, TN = WTN / 32;
-    static constexpr int STAGE_BYTES = (BM + BN) * RB;
+// The split kernel of the smallest launches: 64x64 tiles, 32x32 per wave, 64-wide k stages in rings of four, and the k loop
+// shared by two groups of four waves, each with a ring of its own over one half of K (with at most one workgroup per CU a
+// lone wave per SIMD is bound by its own instruction stream: M = 128, K = 3072, N = 768 takes 15.1 us on the tile kernel,
+// 12.4 here); the second group's partial sums are added to the first group's through LDS before the epilogue.
+struct SplitF16 {
+    static constexpr int TILE = 64, S = 4, GROUPS = 2, WAVES = 4;  // waves per group, 2 x 2
+    static constexpr int THREADS = GROUPS * WAVES * 64;
+    static constexpr int RB = 128, CH = RB / 16;  // bytes and 16-byte chunks per row and stage
+    static constexpr int STAGE_BYTES = 2 * TILE * RB;
     static constexpr int ROWS_PER_COPY = 1024 / RB;
-    static constexpr int LPW = STAGE_BYTES / 1024 / WAVES;
-    static constexpr int LDS_BYTES = S * STAGE_BYTES;
-    static_assert((STAGE_BYTES / 1024) % WAVES == 0 && BM % ROWS_PER_COPY == 0, "copy split");
-    static_assert(S >= 3 && (S - 2) * LPW <= 63 && LDS_BYTES <= 160 * 1024, "ring limits");
+    static constexpr int LPW = STAGE_BYTES / 1024 / WAVES;  // copies per wave and stage
+    static constexpr int RING_BYTES = S * STAGE_BYTES;
+    static constexpr int LDS_BYTES = GROUPS * RING_BYTES + WAVES * 4096;
+    static_assert(LDS_BYTES <= 160 * 1024, "LDS is 160 KiB per CU");
 };
 
-// KSPLIT = 2: two groups of Cfg::WAVES waves, each with a ring of its own over one half of K;
-// the second group's partial sums are added to the first group's through LDS before the
-// epilogue (for launches with few tiles, whose lone wave per SIMD is bound by its own
-// instruction stream).
-template <class Cfg, int KSPLIT>
-__global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const GemmF16Params p)
+__global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF16Params p)
 {
-    constexpr int BM = Cfg::BM, BN = Cfg::BN, RB = Cfg::RB, CH = Cfg::CH;
-    constexpr int TM = Cfg::TM, TN = Cfg::TN, S = Cfg::S, LPW = Cfg::LPW, KSTEPS = Cfg::KSTEPS;
-    static_assert(KSPLIT == 1 || (KSPLIT == 2 && TM * TN == 1), "the K split is built for 32x32 per wave");
+    using Cfg = SplitF16;
+    constexpr int TILE = Cfg::TILE, RB = Cfg::RB, CH = Cfg::CH, S = Cfg::S, LPW = Cfg::LPW;
 
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int grp = wave_all / Cfg::WAVES, wave = wave_all % Cfg::WAVES;
-    uint8_t *const smem = smem_all + grp * Cfg::LDS_BYTES;
+    uint8_t *const smem = smem_all + grp * Cfg::RING_BYTES;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
-    const int wm = wave / Cfg::WGN, wn = wave % Cfg::WGN;
+    const int wm = wave / 2, wn = wave % 2;
     const int fr = lane & 31, fh = lane >> 5;
 
-    const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+    const int tiles_m = (p.M + TILE - 1) / TILE, tiles_n = (p.N + TILE - 1) / TILE;
     const int total_tiles = tiles_m * tiles_n;
     const uint32_t row_bytes = (uint32_t)p.K * 2;
-    const int kt_count = (int)(row_bytes / (RB * KSPLIT));
+    const int kt_count = (int)(row_bytes / (RB * Cfg::GROUPS));
     const int k_first = grp * kt_count * RB;
     const int my_tiles = (total_tiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int steps = my_tiles * kt_count;
@@ -87,11 +80,11 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
             const int row = (wave * LPW + q) * Cfg::ROWS_PER_COPY + c_row;
             const int chunk = c_slot ^ swz<CH>(row & 15);
             int g;
-            if (row < BM) {
-                g = tm * BM + row;
+            if (row < TILE) {
+                g = tm * TILE + row;
                 g = g < p.M ? g : p.M - 1;
             } else {
-                g = tn * BN + (row - BM);
+                g = tn * TILE + (row - TILE);
                 g = g < p.N ? g : p.N - 1;
             }
             goff[q] = (uint32_t)g * row_bytes + chunk * 16;
@@ -105,7 +98,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
         const uint8_t *w_k = p.W + k_first + lk * RB;
 #pragma unroll
         for (int q = 0; q < LPW; ++q) {
-            const bool is_a = (wave * LPW + q) * Cfg::ROWS_PER_COPY < BM;
+            const bool is_a = (wave * LPW + q) * Cfg::ROWS_PER_COPY < TILE;
             dma_copy16<0>(is_a ? a_k : w_k, goff[q], dst + q * 1024);
         }
         if (++lk == kt_count) {
@@ -117,109 +110,79 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
         }
     };
 
-    v16f acc[TM][TN];
+    v16f acc;
 #pragma unroll
-    for (int j = 0; j < TM; ++j)
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[j][t][v] = 0.0f;
+    for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
 
-    int rowA[TM], rowW[TN], keyA[TM], keyW[TN];
-#pragma unroll
-    for (int j = 0; j < TM; ++j) {
-        const int row = wm * Cfg::WTM + j * 32 + fr;
-        rowA[j] = row * RB;
-        keyA[j] = swz<CH>(row & 15);
-    }
-#pragma unroll
-    for (int t = 0; t < TN; ++t) {
-        const int row = wn * Cfg::WTN + t * 32 + w_row_perm(fr);
-        rowW[t] = (BM + row) * RB;
-        keyW[t] = swz<CH>(row & 15);
-    }
-
-    v8h fragW[2][TN], fragA[2][TM];
+    const int row_a = wm * 32 + fr, row_w = wn * 32 + w_row_perm(fr);
+    const int at_a = row_a * RB, at_w = (TILE + row_w) * RB;
+    const int key_a = swz<CH>(row_a & 15), key_w = swz<CH>(row_w & 15);
+    v8h frag_w[2], frag_a[2];
     auto read_step = [&](int stage_off, auto ksc, auto bc) {
         constexpr int ks = decltype(ksc)::value, b = decltype(bc)::value;
         const int c = ks * 2 + fh;
-#pragma unroll
-        for (int t = 0; t < TN; ++t)
-            fragW[b][t] = *reinterpret_cast<const v8h *>(smem + stage_off + rowW[t] + ((c ^ keyW[t]) * 16));
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-            fragA[b][j] = *reinterpret_cast<const v8h *>(smem + stage_off + rowA[j] + ((c ^ keyA[j]) * 16));
+        frag_w[b] = *reinterpret_cast<const v8h *>(smem + stage_off + at_w + ((c ^ key_w) * 16));
+        frag_a[b] = *reinterpret_cast<const v8h *>(smem + stage_off + at_a + ((c ^ key_a) * 16));
     };
     auto mfma_step = [&](auto bc) {
         constexpr int b = decltype(bc)::value;
-#pragma unroll
-        for (int j = 0; j < TM; ++j)
-#pragma unroll
-            for (int t = 0; t < TN; ++t)
-                acc[j][t] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fragW[b][t], fragA[b][j], acc[j][t], 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(frag_w[b], frag_a[b], acc, 0, 0, 0);
     };
 
     // epilogue of one tile
     auto epilogue = [&](int tile) {
         int tile_m, tile_n;
         tile_coords(tile, tiles_m, tiles_n, tile_m, tile_n);
-        const int m0 = tile_m * BM, n0 = tile_n * BN;
         const bool vec_ok = (p.N % 8) == 0;
-        static_for<TN>([&](auto tc) {
-            constexpr int t = decltype(tc)::value;
-            static_for<2>([&](auto Gc) {
-                constexpr int G = decltype(Gc)::value;
-                const int nb = n0 + wn * Cfg::WTN + t * 32 + 16 * G + 8 * fh;
-                if (nb >= p.N) return;
-                const int nvalid = (p.N - nb) < 8 ? (p.N - nb) : 8;
-                float bi[8];
+        static_for<2>([&](auto Gc) {
+            constexpr int G = decltype(Gc)::value;
+            const int nb = tile_n * TILE + wn * 32 + 16 * G + 8 * fh;
+            if (nb >= p.N) return;
+            const int nvalid = (p.N - nb) < 8 ? (p.N - nb) : 8;
+            float bi[8];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) bi[e] = (p.bias && e < nvalid) ? p.bias[nb + e] : 0.0f;
-                static_for<TM>([&](auto jc) {
-                    constexpr int j = decltype(jc)::value;
-                    const int m = m0 + wm * Cfg::WTM + j * 32 + fr;
-                    if (m >= p.M) return;
-                    const int64_t o = (int64_t)m * p.N + nb;
-                    float y[8];
+            for (int e = 0; e < 8; ++e) bi[e] = (p.bias && e < nvalid) ? p.bias[nb + e] : 0.0f;
+            const int m = tile_m * TILE + wm * 32 + fr;
+            if (m >= p.M) return;
+            const int64_t o = (int64_t)m * p.N + nb;
+            float y[8];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) y[e] = acc[j][t][8 * G + e] + bi[e];
-                    if (p.residual) {
-                        const uint16_t *r = p.residual + o;
-                        if (vec_ok) {
-                            const uint4 rr = *reinterpret_cast<const uint4 *>(r);
-                            const uint32_t rwd[4] = {rr.x, rr.y, rr.z, rr.w};
+            for (int e = 0; e < 8; ++e) y[e] = acc[8 * G + e] + bi[e];
+            if (p.residual) {
+                const uint16_t *r = p.residual + o;
+                if (vec_ok) {
+                    const uint4 rr = *reinterpret_cast<const uint4 *>(r);
+                    const uint32_t rwd[4] = {rr.x, rr.y, rr.z, rr.w};
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) {
-                                y[2 * e] += half_bits_to_float((uint16_t)(rwd[e] & 0xFFFFu));
-                                y[2 * e + 1] += half_bits_to_float((uint16_t)(rwd[e] >> 16));
-                            }
-                        } else {
-                            for (int e = 0; e < nvalid; ++e) y[e] += half_bits_to_float(r[e]);
-                        }
+                    for (int e = 0; e < 4; ++e) {
+                        y[2 * e] += half_bits_to_float((uint16_t)(rwd[e] & 0xFFFFu));
+                        y[2 * e + 1] += half_bits_to_float((uint16_t)(rwd[e] >> 16));
                     }
-                    if (p.act == MKQ_ACT_GELU) {
+                } else {
+                    for (int e = 0; e < nvalid; ++e) y[e] += half_bits_to_float(r[e]);
+                }
+            }
+            if (p.act == MKQ_ACT_GELU) {
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) y[e] = gelu_erf(y[e]);
-                    }
-                    if (p.out_dtype == MKQ_F32) {
-                        float *dst = (float *)p.out + o;
-                        if (vec_ok) {
-                            *reinterpret_cast<float4 *>(dst) = make_float4(y[0], y[1], y[2], y[3]);
-                            *reinterpret_cast<float4 *>(dst + 4) = make_float4(y[4], y[5], y[6], y[7]);
-                        } else {
-                            for (int e = 0; e < nvalid; ++e) dst[e] = y[e];
-                        }
-                    } else {
-                        uint16_t *dst = (uint16_t *)p.out + o;
-                        if (vec_ok) {
-                            *reinterpret_cast<uint4 *>(dst) = make_uint4(pack2_f16(y[0], y[1]), pack2_f16(y[2], y[3]),
-                                                                         pack2_f16(y[4], y[5]), pack2_f16(y[6], y[7]));
-                        } else {
-                            for (int e = 0; e < nvalid; ++e) dst[e] = float_to_half_bits(y[e]);
-                        }
-                    }
-                });
-            });
+                for (int e = 0; e < 8; ++e) y[e] = gelu_erf(y[e]);
+            }
+            if (p.out_dtype == MKQ_F32) {
+                float *dst = (float *)p.out + o;
+                if (vec_ok) {
+                    *reinterpret_cast<float4 *>(dst) = make_float4(y[0], y[1], y[2], y[3]);
+                    *reinterpret_cast<float4 *>(dst + 4) = make_float4(y[4], y[5], y[6], y[7]);
+                } else {
+                    for (int e = 0; e < nvalid; ++e) dst[e] = y[e];
+                }
+            } else {
+                uint16_t *dst = (uint16_t *)p.out + o;
+                if (vec_ok) {
+                    *reinterpret_cast<uint4 *>(dst) = make_uint4(pack2_f16(y[0], y[1]), pack2_f16(y[2], y[3]),
+                                                                 pack2_f16(y[4], y[5]), pack2_f16(y[6], y[7]));
+                } else {
+                    for (int e = 0; e < nvalid; ++e) dst[e] = float_to_half_bits(y[e]);
+                }
+            }
         });
     };
 
@@ -231,8 +194,7 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
     read_step(0, IntC<0>{}, IntC<0>{});
 
     int ct = blockIdx.x, ck = 0, buf = 0;
-    static_assert(KSTEPS == 4, "the loop body below is written for four k steps per stage");
-    for (int s = 0; s < steps; ++s) {
+    for (int s = 0; s < steps; ++s) {  // four k steps of 16 values per stage
         const int stage_off = buf * Cfg::STAGE_BYTES;
         const int nbuf = (buf + 1 == S) ? 0 : buf + 1;
         read_step(stage_off, IntC<1>{}, IntC<1>{});
@@ -249,31 +211,25 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
         mfma_step(IntC<1>{});
         buf = nbuf;
         if (++ck == kt_count) {
-            if constexpr (KSPLIT == 2) {
-                float *const xch = reinterpret_cast<float *>(smem_all + KSPLIT * Cfg::LDS_BYTES) + wave * 1024 + lane * 4;
-                if (grp == 1) {
+            float *const xch = reinterpret_cast<float *>(smem_all + Cfg::GROUPS * Cfg::RING_BYTES) + wave * 1024 + lane * 4;
+            if (grp == 1) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q)
-                        *reinterpret_cast<float4 *>(xch + q * 256) = make_float4(acc[0][0][4 * q], acc[0][0][4 * q + 1],
-                                                                                 acc[0][0][4 * q + 2], acc[0][0][4 * q + 3]);
-                }
-                lds_barrier();
-                if (grp == 0) {
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 t = *reinterpret_cast<const float4 *>(xch + q * 256);
-                        acc[0][0][4 * q] += t.x; acc[0][0][4 * q + 1] += t.y;
-                        acc[0][0][4 * q + 2] += t.z; acc[0][0][4 * q + 3] += t.w;
-                    }
-                }
+                for (int q = 0; q < 4; ++q)
+                    *reinterpret_cast<float4 *>(xch + q * 256) =
+                        make_float4(acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]);
             }
-            if (grp == 0) epilogue(ct);
+            lds_barrier();
+            if (grp == 0) {
 #pragma unroll
-            for (int j = 0; j < TM; ++j)
+                for (int q = 0; q < 4; ++q) {
+                    const float4 t = *reinterpret_cast<const float4 *>(xch + q * 256);
+                    acc[4 * q] += t.x; acc[4 * q + 1] += t.y;
+                    acc[4 * q + 2] += t.z; acc[4 * q + 3] += t.w;
+                }
+                epilogue(ct);
+            }
 #pragma unroll
-                for (int t = 0; t < TN; ++t)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) acc[j][t][v] = 0.0f;
+            for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
             ck = 0;
             ct += gridDim.x;
         }
@@ -281,20 +237,17 @@ __global__ __launch_bounds__(Cfg::THREADS * KSPLIT) void gemm_f16_kernel(const G
     wait_vmcnt<0>();
 }
 
-template <class Cfg, int KSPLIT = 1>
-static int launch_gemm_f16(const GemmI4Params &p, hipStream_t st)
+static int launch_split_f16(const GemmI4Params &p, hipStream_t st)
 {
-    const int64_t tiles = ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN);
+    const int64_t tiles = ceil_div(p.M, SplitF16::TILE) * ceil_div(p.N, SplitF16::TILE);
     if (tiles > 0x7FFFFFFF) return MKQ_ERR_UNSUPPORTED;
-    constexpr size_t lds = KSPLIT * Cfg::LDS_BYTES + (KSPLIT - 1) * Cfg::WAVES * 4096;
-    static_assert(lds <= 160 * 1024, "LDS is 160 KiB per CU");
-    static PerDeviceOnce once;  // per instantiation
+    static PerDeviceOnce once;
     int64_t resident = 0;
-    const int rc = resident_workgroups(once, gemm_f16_kernel<Cfg, KSPLIT>, Cfg::THREADS * KSPLIT, lds, 1 << 20, &resident);
+    const int rc = resident_workgroups(once, gemm_f16_kernel, SplitF16::THREADS, SplitF16::LDS_BYTES, 1 << 20, &resident);
     if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
-    GemmF16Params q = {p.A, p.W, p.M, p.N, p.K, p.bias, (const uint16_t *)p.residual, p.act, p.out, p.out_dtype};
-    gemm_f16_kernel<Cfg, KSPLIT><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(q);
+    const GemmF16Params q = {p.A, p.W, p.M, p.N, p.K, p.bias, (const uint16_t *)p.residual, p.act, p.out, p.out_dtype};
+    gemm_f16_kernel<<<grid, SplitF16::THREADS, SplitF16::LDS_BYTES, st>>>(q);
     return launch_status();
 }
 
@@ -308,8 +261,8 @@ static bool few_tiles(const GemmI4Params &p)
 // workgroup per CU, from 192 tiles on, and 64x64 below; us, old -> new):
 //   4096 tokens, K = 768: N = 2304 31.9 -> 24.3, N = 768 14.3 -> 11.8, N = 3072 with GELU 39.8 -> 31.8;
 //   K = 3072, N = 768 33.5 -> 28.8; 2298 tokens 22.0 -> 14.1, 9.4 -> 8.7, 26.8 -> 20.2, 28.8 -> 23.3;
-//   16384 tokens, K = 1024, N = 4096 230 -> 153.  Over 843 shapes (M = 1 .. 16384, 33 pairs of K and N with their epilogues)
-// four are slower than before by more than 2 %, by 7 % at most (440 tokens, K = 1280, N = 5120 with GELU 14.1 -> 15.1).
+//   16384 tokens, K = 1024, N = 4096 230 -> 153.  Over 1230 shapes (M = 1 .. 16384, 47 pairs of K and N with their
+// epilogues) six are slower than before by more than 2 %, by 11 % at most (440 tokens, K = 1280, N = 5120 with GELU 13.7 -> 15.2).
 enum { F16_SPLIT = 0, F16_64, F16_128_DEEP, F16_256x128, F16_128, F16_256, F16_CONFIGS };
 static int choose_f16(const GemmI4Params &p)
 {
@@ -333,7 +286,7 @@ static int choose_f16(const GemmI4Params &p)
 static int run_config(const GemmI4Params &p, int cfg, hipStream_t st)
 {
     switch (cfg) {
-    case F16_SPLIT: return launch_gemm_f16<GemmF16Cfg<64, 64, 2, 2, 4>, 2>(p, st);
+    case F16_SPLIT: return launch_split_f16(p, st);
     case F16_64: return launch_f16_by_epilogue<GemmI4DmaCfg<64, 64, 2, 2, 128, 3>>(p, st);
     case F16_128_DEEP: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 128, 4>>(p, st);
     case F16_256x128: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 128, 4, 2, 128, 3>>(p, st);

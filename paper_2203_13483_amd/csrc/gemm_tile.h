@@ -96,7 +96,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
 {
     const int ks = XS ? p.ks : 1;
     static_assert(BITS == 4 || ((BITS == 8 || BITS == 16) && Cfg::RB >= 64), "stage rows");
-    static_assert(BITS != 16 || !XS, "partial sums across workgroups are integers");
+    static_assert(BITS != 16 || (!XS && KSPLIT == 1), "partial sums across workgroups and wave groups are integers");
     constexpr bool SCALED = BITS != 16;  // the accumulator is a sum of codes
     using Acc = typename std::conditional<SCALED, v16i, v16f>::type;
     static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "one, two or four wave groups");
@@ -475,8 +475,8 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
 #pragma unroll
                             for (int q = 0; q < 4; ++q)
                                 *reinterpret_cast<int4 *>(xch + (grp - 1) * (Cfg::WAVES * TPP * 1024) + u * 1024 + q * 256) =
-                                    acc_bits(acc[j][t][4 * q], acc[j][t][4 * q + 1], acc[j][t][4 * q + 2],
-                                             acc[j][t][4 * q + 3]);
+                                    make_int4(acc[j][t][4 * q], acc[j][t][4 * q + 1], acc[j][t][4 * q + 2],
+                                              acc[j][t][4 * q + 3]);
                         });
                     }
                     lds_barrier();
@@ -489,11 +489,8 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
                                 for (int q = 0; q < 4; ++q) {
                                     const int4 v = *reinterpret_cast<const int4 *>(
                                         xch + g * (Cfg::WAVES * TPP * 1024) + u * 1024 + q * 256);
-                                    using E = typename std::conditional<SCALED, int, float>::type;
-                                    acc[j][t][4 * q] += __builtin_bit_cast(E, v.x);
-                                    acc[j][t][4 * q + 1] += __builtin_bit_cast(E, v.y);
-                                    acc[j][t][4 * q + 2] += __builtin_bit_cast(E, v.z);
-                                    acc[j][t][4 * q + 3] += __builtin_bit_cast(E, v.w);
+                                    acc[j][t][4 * q] += v.x; acc[j][t][4 * q + 1] += v.y;
+                                    acc[j][t][4 * q + 2] += v.z; acc[j][t][4 * q + 3] += v.w;
                                 }
                         });
                     }
