@@ -28,7 +28,8 @@ def _activations(M, K, seed, dtype):
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
 @pytest.mark.parametrize("M,K,bits,s", [(1, 8, 4, 0.5), (37, 200, 4, 0.34), (1024, 768, 4, 0.34),
-                                         (1024, 768, 8, 0.02), (4096, 3072, 4, 0.21)])
+                                         (1024, 768, 8, 0.02), (4096, 3072, 4, 0.21),
+                                         (128, 1024, 8, 0.02), (129, 1024, 8, 0.02)])  # small and large workgroups
 def test_scale_gradients(mkq, M, K, bits, s, dtype):
     x = _activations(M, K, M + K + bits, dtype)
     g = to_np(mkq.mkq_scale_gradients(to_dev(x), s, bits))
@@ -92,22 +93,22 @@ def test_percentile_step_feeds_the_quantizer(mkq):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float16])
-@pytest.mark.parametrize("order", ["random", "sorted", "outliers outside", "constant"])
-def test_percentile_of_a_tensor_large_enough_to_be_sampled(mkq, order, dtype):
-    """4 M elements and more: a sample (64th pieces of 2048 elements) bounds the first count from below.  Any
+@pytest.mark.parametrize("order", ["random", "sorted", "outliers first", "constant"])
+def test_percentile_in_any_order(mkq, order, dtype):
+    """A little more than one group of eight per thread of the largest grid, so that most threads fetch past the end.  Any
     arrangement of the values and any stride of the rows gives the same order statistic."""
     M, K = 2049, 2056
     x = _activations(M, K, 17, dtype)
     if order == "sorted":
         x = np.sort(x, axis=None).reshape(M, K)
-    elif order == "outliers outside":
-        x.flat[:2048] = 0.0  # the sample's first piece
-        x.flat[2048:2048 + 4096] = 60.0
+    elif order == "outliers first":
+        x.flat[:8192] = 0.0
+        x.flat[8192:8192 + 4096] = 60.0
     elif order == "constant":
         x[:] = 1.5
     wide = np.full((M, K + 24), 1000, dtype)
     wide[:, 8:8 + K] = x
-    for ppm, bits in ((0, 4), (10, 8), (1000, 4), (3900, 4), (3910, 4)):  # (either side of the sample's limit, 1 / 256)
+    for ppm, bits in ((0, 4), (10, 8), (1000, 4), (3900, 4), (3910, 4)):
         ref, _ = oracle.percentile_scale(x.astype(np.float32), ppm, 7 if bits == 4 else 127)
         assert float(to_np(mkq.mkq_percentile_scale(to_dev(x), ppm, bits))[0]) == ref, ppm
         assert float(to_np(mkq.mkq_percentile_scale(to_dev(wide)[:, 8:8 + K], ppm, bits))[0]) == ref, ppm
@@ -132,3 +133,23 @@ def test_scale_gradients_next_to_rounding_boundaries(mkq, bits, s):
     bound = 2 * x.size * 2.0 ** -53
     assert abs(g[0] - ste) <= bound * np.abs(c - xd / sd).sum() < 0.5
     assert abs(g[1] - mse) <= bound * np.abs(2 * (sd * c - xd) * c).sum()
+
+
+def test_rows_with_gaps_over_several_batches(mkq):
+    """Rows with gaps take whole batches of groups without checks and a last one with them: a tensor of four groups per
+    thread and a little more, for the percentile, the abs-max and the gradient sums."""
+    M, K = 4100, 4104
+    x = _activations(M, K, 23, np.float16)
+    wide = np.full((M, K + 8), 1000, np.float16)
+    wide[:, :K] = x
+    view = to_dev(wide)[:, :K]
+    xf = x.astype(np.float32)
+    for ppm in (10, 200000):
+        assert float(to_np(mkq.mkq_percentile_scale(view, ppm))[0]) == oracle.percentile_scale(xf, ppm, 7)[0]
+    assert float(to_np(mkq.mkq_absmax_scale(view))[0]) == np.abs(xf).max() / np.float32(7)
+    g = to_np(mkq.mkq_scale_gradients(view, 0.34))
+    ste, mse = oracle.scale_gradients(xf, 0.34, -8, 7)
+    c = oracle.quantize(xf, np.float32(0.34)).astype(np.float64)
+    xd, sd = xf.astype(np.float64), float(np.float32(0.34))
+    assert abs(g[0] - ste) <= 1e-10 * np.abs(c - xd / sd).sum()
+    assert abs(g[1] - mse) <= 1e-10 * np.abs(2 * (sd * c - xd) * c).sum()

@@ -1,12 +1,13 @@
 """The tile kernels with stages of 128-byte rows against the oracle: 4- and 8-bit configurations by number, at one stage
 per tile, ragged edges, more tiles than resident workgroups, and every kind of epilogue; the binary16 linear at sizes
 on every side of its tile choice.  Everything is exact: integer sums, correctly rounded binary32 epilogues, and for
-binary16 small integer operands, whose sums binary32 holds exactly in any order."""
+binary16 small integer operands, whose sums binary32 holds exactly in any order; only codes behind a GELU may fall
+either way at a tie."""
 import numpy as np
 import pytest
 
 import oracle
-from helpers import RTOL, assert_float_close, to_dev, to_np
+from helpers import RTOL, assert_codes_match_with_tie_band, assert_float_close, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 GROUPS4 = {46: 2, 47: 2, 48: 2}  # wave groups that share the k loop
@@ -32,8 +33,9 @@ def _case(M, N, K, bits, seed):
     return A, Wc, s_w, np.float32(0.02), rng.normal(0, 0.5, N).astype(np.float32), res
 
 
-# one stage per tile; several stages and ragged edges; more tiles than any configuration keeps resident
-@pytest.mark.parametrize("M,N,stages", [(300, 520, 1), (257, 136, 5), (1500, 1104, 2), (8200, 2312, 1)])
+# one stage per tile; several stages and ragged edges; N % 8 != 0 (the general epilogue); more tiles than any
+# configuration keeps resident
+@pytest.mark.parametrize("M,N,stages", [(300, 520, 1), (257, 136, 5), (330, 522, 3), (1500, 1104, 2), (8200, 2312, 1)])
 @pytest.mark.parametrize("bits,cfg", [(4, c) for c in range(43, 50)] + [(8, c) for c in (43, 44, 46, 47)])
 def test_configurations(mkq, bits, cfg, M, N, stages):
     K = stages * (1024 // bits) * (GROUPS4 if bits == 4 else GROUPS8).get(cfg, 1)
@@ -52,9 +54,15 @@ def test_configurations(mkq, bits, cfg, M, N, stages):
     assert np.array_equal(codes, oracle.pack_nibbles(ref["q"]) if bits == 4 else ref["q"])
     ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, residual=res.astype(np.float32), out_dtype=oracle.F16, **clamp)
     assert np.array_equal(to_np(run(mkq.MKQ_F16, residual=to_dev(res))["out"]).astype(np.float32), ref["y"])
+    ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, **clamp)
+    assert np.array_equal(to_np(run(mkq.MKQ_F32)["out"]), ref["y"])
+    # GELU and codes behind it (the tie bands of the other GELU tests, which derive from the two erf forms)
+    s_next, band = (0.9, {}) if bits == 4 else (0.05, dict(band=2.0 ** -7, max_frac=2e-3))
+    refg = oracle.linear_int4(A, s_x, Wc, s_w, bias, act=oracle.ACT_GELU, s_next=s_next, **clamp)
+    g = to_np(run(mkq.MKQ_I4 if bits == 4 else mkq.MKQ_I8, act=mkq.MKQ_ACT_GELU, s_next=s_next)["out"])
+    assert_codes_match_with_tie_band(oracle.unpack_nibbles(g, N) if bits == 4 else g, refg["q"], refg["y"], s_next, what="GELU", **band)
     if M < 1000:
         r = run(mkq.MKQ_F32, want_acc=True)
-        ref = oracle.linear_int4(A, s_x, Wc, s_w, bias, **clamp)
         assert np.array_equal(to_np(r["acc"]), ref["acc"]) and np.array_equal(to_np(r["out"]), ref["y"])
         r = run(mkq.MKQ_F16)
         assert np.array_equal(to_np(r["out"]).astype(np.float32), oracle.round_storage(ref["y"], oracle.F16))

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import to_dev, to_np
+from helpers import RTOL, assert_codes_match_with_tie_band, assert_float_close, to_dev, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -81,3 +81,32 @@ def test_output_over_the_workspace(mkq, M, N, K):
     mkq.mkq_linear_int4(to_dev(x), 0.3, mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1), to_dev(s_w), None, N, K, mkq.MKQ_F32,
                         out=out, workspace=ws)
     assert np.array_equal(to_np(out), ref["y"])
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float16])
+@pytest.mark.parametrize("M,N,K", [(1, 8, 64), (33, 40, 704), (70, 200, 832), (128, 768, 768)])
+def test_every_output_of_the_general_epilogue(mkq, M, N, K, dtype):
+    """GELU, codes beside a float output, and code rows with a pitch (zero codes behind the last channel), with float
+    activations; only codes behind a GELU may fall either way at a tie."""
+    import torch
+    rng = np.random.default_rng(M * N + K)
+    x = rng.standard_normal((M, K)).astype(dtype)
+    Wc = rng.integers(-8, 8, (N, K), dtype=np.int8)
+    s_w = rng.uniform(0.001, 0.05, N).astype(np.float32)
+    bias = rng.normal(0, 0.5, N).astype(np.float32)
+    s_x = np.float32(0.34)
+    codes = oracle.quantize(x.astype(np.float32), s_x)
+    args = (to_dev(x), float(s_x), mkq.mkq_pack_codes_int4(to_dev(Wc)).reshape(-1), to_dev(s_w), to_dev(bias), N, K)
+    pitch = N + 24
+    pad = np.zeros((M, 24), np.int8)
+    ref = oracle.linear_int4(codes, s_x, Wc, s_w, bias, s_next=0.7)
+    q = torch.full((M, pitch // 2), 255, dtype=torch.uint8, device="cuda")
+    r = mkq.mkq_linear_int4(*args, mkq.MKQ_F32, s_next=0.7, q_out=q, q_pitch=pitch)
+    assert np.array_equal(to_np(r["out"]), ref["y"])
+    assert np.array_equal(oracle.unpack_nibbles(to_np(q), pitch), np.hstack([ref["q"], pad]))
+    r = mkq.mkq_linear_int4(*args, mkq.MKQ_I4, s_next=0.7, q_pitch=pitch)
+    assert np.array_equal(oracle.unpack_nibbles(to_np(r["out"]), pitch), np.hstack([ref["q"], pad]))
+    refg = oracle.linear_int4(codes, s_x, Wc, s_w, bias, act=oracle.ACT_GELU, s_next=0.7)
+    r = mkq.mkq_linear_int4(*args, mkq.MKQ_F32, act=mkq.MKQ_ACT_GELU, s_next=0.7, want_q=True)
+    assert_float_close(to_np(r["out"]), refg["y"], RTOL[0], "GELU")
+    assert_codes_match_with_tie_band(oracle.unpack_nibbles(to_np(r["q"]), N), refg["q"], refg["y"], 0.7, what="GELU codes")

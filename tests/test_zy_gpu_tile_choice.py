@@ -6,10 +6,11 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-CONFIGS = [11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35]
-# (M, K, N): BERT-base layer GEMMs at M = 1024 and 4096, BERT-large at M = 8192, the large-M sweep at M = 16384
-SHAPES = ([(M, K, N) for M in (1024, 4096) for (K, N) in ((768, 2304), (768, 768), (768, 3072), (3072, 768))]
-          + [(8192, 1024, 3072), (8192, 1024, 1024), (8192, 1024, 4096), (8192, 4096, 1024)]
+CONFIGS = [11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49]
+# (M, K, N): BERT-base layer GEMMs at M = 1024 and 4096 and at ragged token counts, BERT-large at M = 4096 and 8192, the
+# large-M sweep at M = 16384
+SHAPES = ([(M, K, N) for M in (440, 1024, 2298, 4096) for (K, N) in ((768, 2304), (768, 768), (768, 3072), (3072, 768))]
+          + [(M, K, N) for M in (4096, 8192) for (K, N) in ((1024, 3072), (1024, 1024), (1024, 4096), (4096, 1024))]
           + [(16384, 1024, 4096), (16384, 4096, 1024), (16384, 768, 3072)])
 
 
@@ -36,7 +37,7 @@ def _time(fn, rep=10, samples=7):
 
 # the layer's own epilogues at the BERT-base shapes: binary16 residual (attention-out, FFN-down), GELU with
 # codes out (FFN-up)
-EPILOGUES = [(M, K, N, kind) for M in (1024, 4096)
+EPILOGUES = [(M, K, N, kind) for M in (440, 1024, 2298, 4096)
              for (K, N, kind) in ((768, 768, "residual"), (768, 3072, "gelu"), (3072, 768, "residual"))]
 
 
