@@ -6,7 +6,9 @@ K = 1024, N = 4096): nibble-packed int4 codes in -> int4 x int4 GEMM (int32 accu
 -> dequantize epilogue with per-channel scales -> bfloat16 out.  Inputs are synthetic and
 resident in HBM before the timed region.  The other workloads (BERT-base layer GEMMs at
 M = 1024 with the activation quantizer, the rest of the large-M sweep, few-token weight
-streaming, the 12-layer encoder, ...) are measured beside it under "extra".  Prints ONE JSON line.
+streaming, the 12-layer encoder, ...) are measured beside it.  Prints ONE JSON line; the side measurements, several
+times its length, go to standard error as {"extra": ...}, so that the line stays whole where only the last kilobytes of
+the output are kept.
 """
 from __future__ import annotations
 
@@ -249,7 +251,7 @@ def main():
             if line.startswith("traffic_bytes_per_launch:"):
                 traffic = int(line.split(":")[1])
     roofline = {
-        "bound": "mfma", "kernel": "gemm_i4_dma_kernel<256x128 tiles, 3-stage ring, bf16 line epilogue>",
+        "bound": "mfma", "kernel": "gemm_i4_dma_kernel<256x256 tiles on eight waves, 2-stage ring of 128-byte rows, bf16 line epilogue>",
         "achieved": achieved, "peak": INT8_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": achieved / INT8_MFMA_PEAK_TOPS,
         "traffic": traffic, "algorithmic_bytes_per_launch": alg_bytes, "us_per_launch": launch_s * 1e6,
         "measured_mfma_ceiling_TOPS": ceil["mfma_i8_TOPS"], "frac_of_measured_mfma_ceiling": achieved / ceil["mfma_i8_TOPS"],
@@ -266,7 +268,7 @@ def main():
         "metric": "int4_linear_TOPS", "value": value, "unit": "TOPS", "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms_per_step, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "int4 (int8 MFMA, int32 accumulate)", "data": "synthetic",
-        "config": {"workload": f"BASELINE configs[4], largest point: int4 GEMM M={M}, K={K}, N={N}; signed int4 "
+        "config": {"workload": f"largest point of the large-M sweep: int4 GEMM M={M}, K={K}, N={N}; signed int4 "
                                "uniform codes in [-8,7] in (nibble-packed, resident in HBM), per-channel fp32 scales "
                                "U(0.001,0.05), bf16 out; one step = one linear (GEMM + dequantize epilogue)",
                    "launch": "eager, back-to-back on one stream",
@@ -280,12 +282,12 @@ def main():
         res["cpu_baseline"] = cpu_baseline(A, Wc, s_w, s_x, rows=16384)
     if not args.no_extra:
         res["summary"] = summary(extra)
-    res["extra"] = extra
+    print(json.dumps({"extra": extra}), file=sys.stderr, flush=True)
     print(json.dumps(res))
 
 
 def summary(extra):
-    """The target-bearing side measurements in short form, ahead of the long `extra` object: fractions of the
+    """The target-bearing side measurements in short form, beside the long `extra` object: fractions of the
     published peaks (int8 matrix 5000 TOP/s, HBM 8000 GB/s) and, second, of the ceilings measured in this run."""
     r3 = lambda v: None if v is None else round(v, 3)
     out = {"large_m_MKN_frac_int8_peak_frac_measured_ceiling_e3m2_route_frac_rotating_buffers_frac": [
