@@ -493,10 +493,11 @@ static int choose_tiles(const GemmI4Params &p)
     const bool fixed = classify_epilogue(p) != EPI_GENERIC && ((p.N % 64) == 0 || codes || res);
     if (rows64 == 18) {
         // 45, one 256x256 tile per CU and round: for code outputs (M = 8192, K = 1024, N = 4096 with GELU 52.2 -> 49.6) or a
-        // long k loop (K = N = 4096 104.2 -> 99.5; K = 4096, N = 1024, M = 16384, a single round, 53.4 -> 49.5); at K <= 1024 a plain epilogue, which nothing covers, eats the gain
-        // (f16, M = 12288 50.6 -> 52.0) until nine rounds (M = 65536 251 -> 247).  A last round that is less than five eighths full
-        // takes as long as a full one, where 18 fills it with one workgroup per CU (M = 10240 with GELU 63.7 -> 68.6);
-        // residuals at short k and binary32 outputs lose everywhere (M = 12288 65.7 -> 72.6).
+        // long k loop (K = N = 4096 104.2 -> 99.5; K = 4096, N = 1024, M = 16384, a single round, 53.4 -> 49.5); at K <= 1024 a
+        // plain epilogue, which nothing covers, eats the gain (f16, M = 12288 50.6 -> 52.0) until nine rounds (M = 65536 251
+        // -> 247).  A last round that is less than five eighths full takes as long as a full one, where 18 fills it with one
+        // workgroup per CU (M = 10240 with GELU 63.7 -> 68.6); residuals at short k and binary32 outputs lose everywhere
+        // (M = 12288 65.7 -> 72.6).
         const int64_t last = t256 % 256;
         const bool many = t256 >= 9 * 256, full = many || last == 0 || last >= 160;
         return full && fixed && !f32 && (codes || p.K >= 2048 || (many && !res)) ? 45 : 18;
