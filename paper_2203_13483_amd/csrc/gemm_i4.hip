@@ -636,15 +636,17 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
     }
 }
 
-// Tile choice of the 8-bit linear, from sweeps of every configuration at 1300 calls (as for 4 bits, M to 16384; us, best
-// 64-byte-row choice -> here):
+// Tile choice of the 8-bit linear, from sweeps of every configuration at 2200 calls (as for 4 bits, with the general epilogue's
+// forms; M to 65536; us, best 64-byte-row choice -> here):
 //   47, 64x64, its long k loop shared by two wave groups: M = 440, K = 3072, N = 768 12.1 -> 8.4
 //   43, 64x64, up to three per CU (M = 4096, K = 3072, N = 768 25.1 -> 20.3), and where the epilogue is long up to six (GELU,
 //       M = 1280, K = 1024, N = 4096 17.1 -> 13.9) or four (residual, short k: M = 5120, K = N = 768 10.7 -> 9.3)
 //   46, 128x128, two per CU: M = 1691, K = 768, N = 2304 8.3 -> 7.9; M = 2048, K = N = 2048 20.9 -> 13.0; M = 4096, K = 1024,
 //       N = 3072 19.0 -> 18.5
 //   44, a single round of 256x128: M = 2298, K = 768, N = 2304 13.7 -> 9.3; not for a residual at short k (its rows come late)
-//       nor for binary32 (M = 2560, K = 768, N = 3072 46 16.7, 44 19.6)
+//       nor for binary32 until K = 1536 (M = 2560, K = 768, N = 3072 46 16.7, 44 19.6; M = 6144, K = 3072, N = 768 25.6, 23.5);
+//       and very large problems, GELU and binary32 apart (K = N = 1536, M = 16384 50.4 -> 41.0; K = 1024, N = 4096, M = 32768
+//       174 -> 161)
 //   29, 64-byte rows, three per CU, where 46 would need a second, nearly empty round (M = 12288, K = N = 768 18.9 instead of
 //       21.1), at short k (M = 12288, K = 256, N = 768 10.5 instead of 11.8) and for GELU over several rounds
 static int choose_tiles_i8(const GemmI4Params &p)
@@ -652,14 +654,24 @@ static int choose_tiles_i8(const GemmI4Params &p)
     if ((p.K % 128) != 0) return choose_rows64(p);
     const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
-    const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr;
-    if (!gelu && t256x128 >= 512 && 2.0 * p.M * p.N * p.K >= 6e10) return 18;
+    const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32, whole = (p.N % 8) == 0;
+    if (!gelu && t256x128 >= 512 && 2.0 * p.M * p.N * p.K >= 6e10) return whole && !f32 ? 44 : 18;
     if (t64 <= 256 && (p.K % 256) == 0 && p.K >= 2048) return 47;
-    if (t64 <= 768 || (gelu && p.K < 1536 && t64 <= 1536) || (res && p.K <= 1024 && t64 <= 1024)) return 43;
-    // (the general epilogue, eight values of one token per lane: M = 1691, K = 768, N = 2306 21.1 -> 25.9 with the large tiles)
-    if (p.K < 2048 && classify_epilogue(p) == EPI_GENERIC) return choose_rows64(p);
+    const bool general = p.K < 2048 && classify_epilogue(p) == EPI_GENERIC;
+    if (t64 <= 768 || (gelu && p.K < 1536 && t64 <= (general && p.K < 768 ? 1024 : 1536)) ||
+        (res && !f32 && p.K <= 1024 && t64 <= 1024))
+        return 43;
+    // The general epilogue, eight values of one token per lane: ragged rows and 32-bit values are stored piece by piece, and
+    // the large tiles cover that badly (M = 1691, K = 768, N = 2306 21.1 -> 25.9); otherwise as below, 43 to a
+    // larger count (codes, K = 768, N = 2304, M = 2048 28 12.8, 43 11.9) and 29 for GELU (M = 16384, N = 3072 18 108, 29 84)
+    if (general) {
+        if (!whole || f32) return choose_rows64(p);
+        if (p.K >= 768 && t64 <= 1536) return 43;
+        if (t256x128 <= 256) return t128 > 400 ? 44 : choose_rows64(p);
+        return gelu ? 29 : choose_rows64(p);
+    }
     if (t128 <= 256) return 46;
-    if (t256x128 <= 256 && p.out_dtype != MKQ_F32 && (!res || p.K >= 2048)) return 44;
+    if (t256x128 <= 256 && (!f32 || p.K >= 1536) && (!res || p.K >= 2048)) return 44;
     return t128 > 512 && (t128 <= 640 || p.K < 768 || (gelu && p.K < 1536)) ? 29 : 46;
 }
 
