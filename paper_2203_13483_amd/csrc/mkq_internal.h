@@ -259,24 +259,28 @@ __device__ __forceinline__ uint32_t pack2_f16(float a, float b)
 }
 
 // GELU, erf form, binary32 (activation functions stay in float32, section 5), without branches.
-// erf comes from the exponential-times-polynomial form of Abramowitz & Stegun 7.1.26,
-// erf(z) = 1 - (a1 t + ... + a5 t^5) exp(-z^2), t = 1 / (1 + p z) for z >= 0 (absolute error of the
-// formula <= 1.5e-7; v_rcp_f32 and v_exp_f32 add about 1e-7).  With z = |x| / sqrt(2) folded into the
-// constants, Phi(x) = 1 - u for x >= 0 and u for x < 0, u = (a1 t + ... + a5 t^5) exp(-x^2 / 2) / 2,
-// so  gelu(x) = x Phi(x) = max(x, 0) - |x| u.
+// gelu(x) = x Phi(x) = max(x, 0) - |x| u with u = Phi(-|x|), and log2(u) is so smooth that one polynomial of degree 8
+// gives it: -1 at 0 exactly, the other coefficients a minimax fit (linear program over Chebyshev nodes, our own) of the
+// error of |x| u on [0, 6.5], 1.3e-8 there; the leading one is negative, so beyond the fit u goes on falling to 0.
+// What bounds the epilogues that use it is vector issue: eleven operations with one quarter-rate exponential, 56 cycles
+// per value and wave.  The form before (Abramowitz & Stegun 7.1.26: reciprocal, five coefficients, exp(-x^2 / 2)) took
+// thirteen with two quarter-rate ones, 76 cycles.  Evaluated in binary32 against binary64: largest error on [-10, 10] 2.5e-7
+// (before 3.3e-7; most of it the rounding of results near 4), root mean square under unit Gaussian inputs 1.4e-8 (3.4e-8).
 __device__ __forceinline__ float gelu_erf(float x)
 {
     const float ax = fabsf(x);
-    const float t = __builtin_amdgcn_rcpf(__builtin_fmaf(0.3275911f * 0.70710678118654752440f, ax, 1.0f));
-    float p = __builtin_fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-    p = __builtin_fmaf(p, t, 0.5f * 1.421413741f);
-    p = __builtin_fmaf(p, t, 0.5f * -0.284496736f);
-    p = __builtin_fmaf(p, t, 0.5f * 0.254829592f);
-    p *= t;
-    const float e = __builtin_amdgcn_exp2f(x * x * (-0.5f * 1.4426950408889634f));
+    float l = __builtin_fmaf(-1.5206792360580395e-06f, ax, 2.3473889547716273e-05f);
+    l = __builtin_fmaf(l, ax, -1.0947861108404527e-04f);
+    l = __builtin_fmaf(l, ax, -3.2621452154775064e-04f);
+    l = __builtin_fmaf(l, ax, 7.318362107740638e-03f);
+    l = __builtin_fmaf(l, ax, -5.268055803436432e-02f);
+    l = __builtin_fmaf(l, ax, -4.591433832864385e-01f);
+    l = __builtin_fmaf(l, ax, -1.1511134697079117f);
+    l = __builtin_fmaf(l, ax, -1.0f);
+    const float u = __builtin_amdgcn_exp2f(l);
     // max(x, 0) as a median of three: one instruction (fmaxf first quiets its operand with a second one); a
     // NaN still reaches the result through the product
-    return __builtin_fmaf(-ax, p * e, __builtin_amdgcn_fmed3f(x, 0.0f, __builtin_inff()));
+    return __builtin_fmaf(-ax, u, __builtin_amdgcn_fmed3f(x, 0.0f, __builtin_inff()));
 }
 
 }  // namespace mkq

@@ -117,6 +117,25 @@ def test_code_outputs_with_a_row_pitch(mkq, M, N, K, pitch):
         _run(mkq, A, Wc, s_w, s_x, bias, mkq.MKQ_I4, s_next=s_next, q_pitch=N - 8)
 
 
+@pytest.mark.parametrize("out", [0, 1])
+def test_gelu_over_its_range(mkq, out):
+    """Zero codes, so that GELU meets the biases as they are: |error| against binary64 within the fit's 1.3e-8, the
+    exponent's roundings (a few 2^-24 of at most 2.7 where |x| u is largest: 6.5e-8) and the result's own."""
+    import torch
+    x = np.concatenate([np.linspace(-12, 12, 4081), [0.0, -0.0, 1e-30, -1e-30, 1e-3, -1e-3, 20.0, -20.0, 1e4, -1e4, 6e4, -6e4,
+                                                     6.5, -6.5, 100.0]]).astype(np.float32)
+    N = x.size
+    dt = [mkq.MKQ_F32, mkq.MKQ_F16][out]
+    r = mkq.mkq_linear_int4(torch.zeros((3, 16), dtype=torch.uint8, device="cuda"), 0.1,
+                            torch.zeros((N, 16), dtype=torch.uint8, device="cuda"), torch.ones(N, device="cuda"),
+                            torch.from_numpy(x).cuda(), N, 32, dt, act=mkq.MKQ_ACT_GELU)
+    xd = torch.from_numpy(x).double()
+    want = (xd * torch.special.ndtr(xd)).numpy()
+    got = to_np(r["out"]).astype(np.float64)
+    ulp = 2.0 ** -23 if out == 0 else 2.0 ** -11
+    assert np.all(np.abs(got - want) <= 8e-8 + ulp * np.abs(want) + (0 if out == 0 else 2.0 ** -25))
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 3072, 768), (130, 202, 96)])
 def test_gelu_then_requant(mkq, M, N, K):
     A, Wc, s_w, s_x, bias = _codes_case(M, N, K, seed=9)
