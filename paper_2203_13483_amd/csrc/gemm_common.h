@@ -67,21 +67,28 @@ __device__ __forceinline__ void static_for(F &&f)
 
 // XCD-aware tile order.  Workgroups are dealt round-robin to the 8 XCDs, each with
 // its own L2; consecutive logical tiles are therefore given to the same XCD, and
-// logical tiles walk GROUP_M token tiles before moving to the next channel tile, so
+// logical tiles walk group_m token tiles before moving to the next channel tile, so
 // the tiles resident on one XCD at a time share a few A and W row panels.
-__device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, int &tm, int &tn)
+// (The host chooses group_m, tile_group: an address computation in front of the first copy is latency.)
+__device__ __forceinline__ void tile_coords(int bid, int tiles_m, int tiles_n, int group_m, int &tm, int &tn)
 {
-    constexpr int XCDS = 8, GROUP_M = 8;
-    const int total = tiles_m * tiles_n;
-    int L = bid;
-    if (total % XCDS == 0) L = (bid % XCDS) * (total / XCDS) + bid / XCDS;
-    const int per_group = GROUP_M * tiles_n;
+    const int L = xcd_index(bid, tiles_m * tiles_n);
+    const int per_group = group_m * tiles_n;
     const int group = L / per_group;
-    const int first_m = group * GROUP_M;
-    const int rows = (tiles_m - first_m) < GROUP_M ? (tiles_m - first_m) : GROUP_M;
+    const int first_m = group * group_m;
+    const int rows = (tiles_m - first_m) < group_m ? (tiles_m - first_m) : group_m;
     const int in_group = L - group * per_group;
     tm = first_m + in_group % rows;
     tn = in_group / rows;
+}
+
+// group_m.  By rows, XCD x has all channels of the x-th eighth of the token tiles, as the kernels around a linear do
+// (xcd_index); else groups of eight token tiles, whose weights the XCDs share out when there are few tiles.
+constexpr int TILE_GROUP = 8;
+inline int tile_group(bool by_rows, int64_t tiles_m)
+{
+    if (!by_rows || tiles_m >= TILE_GROUP * XCDS) return TILE_GROUP;
+    return tiles_m >= 2 * XCDS ? (int)(tiles_m / XCDS) : 1;
 }
 
 // One wave-level global->LDS copy: lane l fetches 16 bytes at base + voff and they

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF
     const int c_row = lane / CH, c_slot = lane % CH;
     auto set_tile = [&](int tile) {
         int tm, tn;
-        tile_coords(tile, tiles_m, tiles_n, tm, tn);
+        tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tm, tn);
 #pragma unroll
         for (int q = 0; q < LPW; ++q) {
             const int row = (wave * LPW + q) * Cfg::ROWS_PER_COPY + c_row;
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF
     // epilogue of one tile
     auto epilogue = [&](int tile) {
         int tile_m, tile_n;
-        tile_coords(tile, tiles_m, tiles_n, tile_m, tile_n);
+        tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tile_m, tile_n);
         const bool vec_ok = (p.N % 8) == 0;
         static_for<2>([&](auto Gc) {
             constexpr int G = decltype(Gc)::value;
@@ -337,5 +337,6 @@ extern "C" int mkq_linear_fp16(const void *a, const void *W, const float *bias, 
     p.M = (int)M; p.N = (int)N; p.K = (int)K;
     p.bias = bias; p.residual = residual; p.residual_dtype = MKQ_F16; p.act = act;
     p.out = out; p.out_dtype = out_dtype;
+    p.by_rows = tiles_by_rows(p, 16);
     return run_gemm_f16(p, as_stream(stream));
 }

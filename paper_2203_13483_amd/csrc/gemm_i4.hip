@@ -87,7 +87,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_kernel(const GemmI4Param
     }
     auto set_tile = [&](int tile) {
         int tm, tn;
-        tile_coords(tile, tiles_m, tiles_n, tm, tn);
+        tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tm, tn);
 #pragma unroll
         for (int i = 0; i < Cfg::A_PER_T; ++i) {
             const int idx = tid + i * THREADS;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_kernel(const GemmI4Param
 
     auto epilogue = [&](int tile) {
         int tile_m, tile_n;
-        tile_coords(tile, tiles_m, tiles_n, tile_m, tile_n);
+        tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tile_m, tile_n);
         gemm_i4_epilogue<Cfg, EpiGeneric>(p, acc, tile_m * BM, tile_n * BN, wm, wn, fr, fh);
     };  // epilogue
 
@@ -753,7 +753,7 @@ void gemm_e3m2_kernel(const GemmI4Params p)
     uint32_t goff[LPW];
     auto set_fetch_tile = [&](int t) {
         int tm, tn;
-        tile_coords(t, tiles_m, tiles_n, tm, tn);
+        tile_coords(t, tiles_m, tiles_n, TILE_GROUP, tm, tn);
         // (recomputed from the lane index at every tile change: kept across the k loop, the per-copy rows and
         // chunks would cost more registers than the wave has to spare)
         int l = lane;
@@ -800,7 +800,7 @@ void gemm_e3m2_kernel(const GemmI4Params p)
     float *const sc_lds = reinterpret_cast<float *>(smem + Cfg::LDS_BYTES + wave * Sh::SCALE_BYTES);
     auto issue_scales = [&](int t) {
         int tm, tn;
-        tile_coords(t, tiles_m, tiles_n, tm, tn);
+        tile_coords(t, tiles_m, tiles_n, TILE_GROUP, tm, tn);
         int n = tn * BN + wn * Cfg::WTN + lane;
         n = n < p.N ? n : p.N - 1;
         const uint32_t dst = lds0 + Cfg::LDS_BYTES + wave * Sh::SCALE_BYTES;
@@ -906,7 +906,7 @@ void gemm_e3m2_kernel(const GemmI4Params p)
 
         const int done_slot = (slot == 0) ? S - 1 : slot - 1;  // idle: read by every wave, not yet refilled
         int tm, tn;
-        tile_coords(tile, tiles_m, tiles_n, tm, tn);
+        tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tm, tn);
         constexpr bool LINES16 = EpiLines16<Cfg, Epi>::usable;
         if constexpr (LINES16) {
             // the scale copies are older than every stage copy issued during the tile; a one-stage tile
@@ -1072,6 +1072,7 @@ static int linear_int4_run(const void *a, int a_dtype, float s_x, const uint8_t 
     p.q_pitch = (int)q_pitch;
     p.acc_shift = 8;
     p.acc_unit = 0.00390625f;
+    p.by_rows = tiles_by_rows(p, 4);
     // a few sentences: quantizer and GEMM in one launch, which leaves the codes in the workspace as the two launches do
     if (a_dtype != MKQ_I4 && !stream_layout && forced_cfg < 0 && small_quantizing_ok(p, a, a_dtype == MKQ_F32 ? 4 : 2))
         return run_gemm_i4_small(p, a, a_dtype, as_stream(stream));
@@ -1316,6 +1317,7 @@ static int linear_int8_run(const int8_t *a, float s_x, const int8_t *Wq, const f
     p.q_pitch = (int)q_pitch;
     p.acc_shift = 0;   // byte operands enter the MFMA as they are
     p.acc_unit = 1.0f;
+    p.by_rows = tiles_by_rows(p, 8);
     return run_gemm_i8(p, as_stream(stream), forced_cfg);
 }
 

@@ -33,9 +33,26 @@ struct GemmI4Params {
     int ks = 1;
     unsigned *sk_counters = nullptr;
     int32_t *sk_partials = nullptr;
+    int group_m = TILE_GROUP;  // tile order: see tile_coords; the launch sets it
+    bool by_rows = false;
     // host side only: do the once-per-device setup of the kernel that would run, launch nothing
     bool setup_only = false;
 };
+
+// Whether the tiles are dealt to the XCDs by rows: every XCD then reads all weights, and what it reads and writes of the
+// tokens stays in its L2 for the kernels around.  Weights come out of memory at about 5 TB/s, lines that another XCD has
+// just written at under 2, so the weights seven more times (7 W / 5) against the tokens' side once (/ 2) is 2.5 W; and
+// the weights leave most of the L2 to the tokens.  bits: of an operand.
+// 4-bit layers in a graph, us, the former order -> this: student (hidden 312) of 1024 / 2048 / 4096 tokens 40.3 -> 35.5,
+// 46.7 -> 38.6, 58.0 -> 49.2; base of 440 / 1024 / 4096 44.3 -> 42.3, 50.5 -> 46.5, 84.0 -> 83.2.  Without the first limit
+// binary16 layers of 768 tokens lost 7 %; with 2 MiB allowed K = 1024, N = 4096 of 1000 ... 3000 tokens 3 %, with 8 MiB 9 %.
+inline bool tiles_by_rows(const GemmI4Params &p, int bits)
+{
+    const double w = (double)p.N * p.K * bits / 8;
+    const double out_bytes = p.out_dtype == MKQ_F32 ? 4 : p.out_dtype == MKQ_I8 ? 1 : p.out_dtype == MKQ_I4 ? 0.5 : 2;
+    const double tokens = (double)p.M * (p.K * bits / 8.0 + p.N * (out_bytes + (p.residual ? 2 : 0)));
+    return 2.5 * w <= tokens && w <= 1.5 * 1024 * 1024;
+}
 
 // Scratch of a K split across workgroups, as the host hands it over: `counters` (SPLITK_MAX_TILES
 // ticket counters, zero between launches) and room for the slices' partial accumulators.

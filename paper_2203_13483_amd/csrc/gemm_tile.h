@@ -137,7 +137,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
     int k_first = 0;  // first byte, in a row, of this group's K range in the pair the copy cursor is in
     auto set_tile = [&](int pair) {
         int tm, tn;
-        tile_coords(pair / ks, tiles_m, tiles_n, tm, tn);
+        tile_coords(pair / ks, tiles_m, tiles_n, p.group_m, tm, tn);
         k_first = ((pair % ks) * KSPLIT + grp) * kt_count * RB;
 #pragma unroll
         for (int q = 0; q < LPW; ++q) {
@@ -388,7 +388,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
     // copies s_w / bias of this wave's channels of tile `tile` to sc_lds
     auto stage_scales = [&](int pair) {
         int tm, tn;
-        tile_coords(pair / ks, tiles_m, tiles_n, tm, tn);
+        tile_coords(pair / ks, tiles_m, tiles_n, p.group_m, tm, tn);
         const uint32_t dst = lds0 + Cfg::LDS_BYTES + wave * EpiShuffle<Cfg>::SCALE_BYTES;
         static_for<EpiShuffle<Cfg>::NSL>([&](auto ic) {
             constexpr int i = decltype(ic)::value;
@@ -460,7 +460,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
 
         if (ck == kt_count) {
             int tile_m, tile_n;
-            tile_coords(ct / ks, tiles_m, tiles_n, tile_m, tile_n);
+            tile_coords(ct / ks, tiles_m, tiles_n, p.group_m, tile_m, tile_n);
             if constexpr (KSPLIT > 1) {
                 // the other groups hand their partial sums over, KSplitXch<Cfg>::TPP 32x32 tiles of a wave
                 // (16 registers per lane, 4 KiB per tile) per pass through the exchange buffer
@@ -616,7 +616,9 @@ static int launch_gemm_i4_dma(const GemmI4Params &p, hipStream_t st)
                                        1 << 20, &resident);
     if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
-    gemm_i4_dma_kernel<Cfg, Epi, BITS, KSPLIT, XS><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(p);
+    GemmI4Params q = p;
+    q.group_m = tile_group(p.by_rows, ceil_div(p.M, Cfg::BM));
+    gemm_i4_dma_kernel<Cfg, Epi, BITS, KSPLIT, XS><<<grid, Cfg::THREADS * KSPLIT, lds, st>>>(q);
     return launch_status();
 }
 

@@ -20,7 +20,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restri
                                                         uint32_t *__restrict__ q, int q_bits, int q_chunks)
 {
     const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int row = xcd_index(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
     if (row >= M) return;
     const int chunks = D / 8;  // 16-byte chunks of 8 elements
     float v[MAXC][8];
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void layernorm_half_kernel(const uint16_t *__r
                                                              uint32_t *__restrict__ q, int q_bits, int q_chunks)
 {
     const int lane = threadIdx.x & 31;
-    const int row = blockIdx.x * 8 + (threadIdx.x >> 5);
+    const int row = xcd_index(blockIdx.x, gridDim.x) * 8 + (threadIdx.x >> 5);
     if (row >= M) return;
     const int chunks = D / 8;
     float v[MAXC][8], gg[MAXC][8], bb[MAXC][8];
@@ -196,7 +196,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const uint16_t *__restri
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 31, fh = lane >> 5;
-    const int b = blockIdx.x / heads, head = blockIdx.x % heads;
+    const int bh = xcd_index(blockIdx.x, gridDim.x), b = bh / heads, head = bh % heads;
     // padding-free batches: sequence b is rows cu_seqlens[b] .. cu_seqlens[b+1] - 1 (at most 32*KT of
     // them, any number); otherwise every sequence has seq_fixed rows
     const int64_t row0 = cu_seqlens ? (int64_t)cu_seqlens[b] : (int64_t)b * seq_fixed;
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256, 3) void attention_blocks_kernel(const uint16_t
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 31, fh = lane >> 5;
-    const int qb = blockIdx.x % q_blocks, bh = blockIdx.x / q_blocks;
+    const int block = xcd_index(blockIdx.x, gridDim.x), qb = block % q_blocks, bh = block / q_blocks;
     const int b = bh / heads, head = bh % heads;
     const int64_t row0 = cu_seqlens ? (int64_t)cu_seqlens[b] : (int64_t)b * seq_fixed;
     const int seq = cu_seqlens ? (cu_seqlens[b + 1] - cu_seqlens[b]) : seq_fixed;

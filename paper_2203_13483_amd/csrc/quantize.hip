@@ -26,7 +26,7 @@ __global__ __launch_bounds__(256) void quantize_kernel(const T *__restrict__ x, 
     const int64_t words_per_row = Kp / 8;
     const int64_t total = M * words_per_row;
     const QuantStep qs = quant_step<4>(s);  // the division's decision without dividing every value
-    for (int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; w < total;
+    for (int64_t w = (int64_t)xcd_index(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; w < total;
          w += (int64_t)gridDim.x * blockDim.x) {
         const int64_t m = w / words_per_row;
         const int64_t kw = w - m * words_per_row;
@@ -50,9 +50,8 @@ template <typename T>
 __global__ __launch_bounds__(256) void quantize_contig_kernel(const T *__restrict__ x, int total_words, float s,
                                                               uint32_t *__restrict__ q)
 {
-    const int stride = (int)(gridDim.x * blockDim.x);
-    const int w0 = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-    const int w1 = w0 + stride;
+    const int w0 = xcd_index(blockIdx.x, gridDim.x) * 512 + (int)threadIdx.x;
+    const int w1 = w0 + 256;
     if (w0 >= total_words) return;
     const bool two = w1 < total_words;
     float v0[8], v1[8];
@@ -247,7 +246,7 @@ __global__ __launch_bounds__(256) void quantize8_kernel(const T *__restrict__ x,
     const int64_t groups_per_row = K / 8;
     const int64_t total = M * groups_per_row;
     const QuantStep qs = quant_step<8>(s);
-    for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total;
+    for (int64_t g = (int64_t)xcd_index(blockIdx.x, gridDim.x) * blockDim.x + threadIdx.x; g < total;
          g += (int64_t)gridDim.x * blockDim.x) {
         const int64_t m = g / groups_per_row;
         const int64_t kg = g - m * groups_per_row;

@@ -117,6 +117,27 @@ def test_code_outputs_with_a_row_pitch(mkq, M, N, K, pitch):
         _run(mkq, A, Wc, s_w, s_x, bias, mkq.MKQ_I4, s_next=s_next, q_pitch=N - 8)
 
 
+# tiles dealt to the XCDs by rows: token tiles fewer than two per XCD, a few, more than eight; tile counts that are and are
+# not multiples of eight; one channel tile; ragged edges
+@pytest.mark.parametrize("bits", [4, 8])
+@pytest.mark.parametrize("M,N,K", [(700, 40, 256), (1100, 200, 256), (2298, 312, 384), (3000, 96, 128), (4097, 264, 128),
+                                   (9000, 136, 64)])
+def test_tiles_dealt_by_rows(mkq, bits, M, N, K):
+    import torch
+    g = torch.Generator().manual_seed(M + bits)
+    q = 2 ** (bits - 1)
+    A = torch.randint(-q, q, (M, K), generator=g, dtype=torch.int8)
+    W = torch.randint(-q, q, (N, K), generator=g, dtype=torch.int8)
+    want = (A.double() @ W.double().t()).numpy()
+    s_w, bias = torch.ones(N, device="cuda"), torch.zeros(N, device="cuda")
+    if bits == 4:
+        a, w = (to_dev(oracle.pack_nibbles(t.numpy())) for t in (A, W))
+        r = mkq.mkq_linear_int4(a, 1.0, w, s_w, bias, N, K, mkq.MKQ_F32)
+    else:
+        r = mkq.mkq_linear_int8(A.cuda(), 1.0, W.cuda(), s_w, bias, mkq.MKQ_F32)
+    assert np.array_equal(to_np(r["out"]), want.astype(np.float32))  # sums below 2^24: exact
+
+
 @pytest.mark.parametrize("out", [0, 1])
 def test_gelu_over_its_range(mkq, out):
     """Zero codes, so that GELU meets the biases as they are: |error| against binary64 within the fit's 1.3e-8, the
