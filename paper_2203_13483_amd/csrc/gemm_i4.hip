@@ -1109,6 +1109,7 @@ static int epilogue_scratch(const mkq_epilogue *epi, SplitKScratch *scr, bool *h
 
 namespace mkq {
 int setup_gemm_f16();  // gemm_f16.hip
+int setup_attention();  // attention.hip
 }
 
 // Scratch of the entry point that allocates nothing (mkq_linear_int4_stream_static): ticket counters, then
@@ -1178,6 +1179,7 @@ extern "C" int mkq_init(void)
         }
     }
     if (rc == MKQ_OK) rc = setup_gemm_f16();
+    if (rc == MKQ_OK) rc = setup_attention();
     void *scratch_ptr = nullptr;
     if (rc == MKQ_OK) rc = static_scratch(&scratch_ptr);
     return rc;

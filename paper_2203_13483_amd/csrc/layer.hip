@@ -2,7 +2,7 @@
 // LayerNorm and the attention core, each with a fused re-quantization of its
 // result for the next W4A4 linear, and the host-side sequencing of one post-LN
 // BERT layer in the int4 and in the binary16 baseline flavour.
-#include "gemm_common.h"
+#include "attention.h"
 
 #include <type_traits>
 
@@ -347,7 +347,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const uint16_t *__restri
 }
 
 // ---------------------------------------------------------------------------------
-// Attention core for any sequence length and any even head size d_k <= DKP (DKP = 32 or 64; the head
+// Attention core (beyond the kernel of attention.hip) for any sequence length and any even head size d_k <= DKP (DKP = 32 or 64; the head
 // dimensions d_k .. DKP-1 are zero in the staged q, k, v and never stored).  One workgroup per (sequence,
 // head, block of 128 queries); the keys go through LDS in blocks of 128, twice:
 //   pass 1  S^T = K Q^T / sqrt(d_k) per key block, running row maximum and denominator of the softmax
@@ -686,6 +686,15 @@ static int attention_run(const void *qkv, int64_t batch, int64_t seq, int64_t hi
     if (!aligned16(qkv) || (ctx && !aligned16(ctx)) || (q_out && !aligned16(q_out))) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     const uint16_t *in = (const uint16_t *)qkv;
+    // Up to 512 keys are held in registers between softmax and product with V; heads of 64 and up to 128 keys keep the kernel
+    // above, which fits more workgroups on a CU (64 x 128 tokens, 12 heads 13.0 us, held 14.6; 64 x 32 4.7, 7.4; with few
+    // workgroups held is ahead by 2 to 8 % of 6 us).  The kernel that goes over the keys twice is left with longer
+    // sequences and heads of 34 to 62 that are no multiple of 8.
+    if ((dk != 64 || seq > 128 || q_pitch != hidden) && seq <= ATTENTION_HELD_KEYS && (dk <= 32 || dk % 8 == 0)) {
+        const AttentionParams p = {in, cu, (int)batch, (int)seq, (int)hidden, (int)heads, (int)dk, (int)q_blocks,
+                                   (uint16_t *)ctx, q_out, s_next, q_bits, (int)q_pitch};
+        return run_attention_held(p, st);
+    }
     if (dk != 64 || seq > 128 || q_pitch != hidden) {
         const unsigned grid = (unsigned)(batch * heads * q_blocks);
 #define MKQ_ATT(DKP, VEC)                                                                                        \

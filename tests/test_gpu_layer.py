@@ -102,6 +102,35 @@ def test_attention_any_head_size_and_length(mkq, B, S, heads, dk):
     assert np.abs(to_np(ctx1).astype(np.float32) - 1.0).max() < 4e-3
 
 
+@pytest.mark.parametrize("S,dk", [(1, 26), (33, 32), (64, 26), (65, 8), (128, 26), (129, 64), (160, 26), (191, 48),
+                                  (193, 32), (256, 64), (257, 64), (320, 26), (448, 32), (449, 64), (512, 64), (512, 26),
+                                  (513, 62), (700, 32), (1000, 64)])
+@pytest.mark.parametrize("scores", ["rising", "falling", "equal", "far apart"])
+def test_attention_at_the_edges_of_its_key_groups(mkq, S, dk, scores):
+    """Scores that put the maximum of a row first, last or nowhere, at the edges of the kernels' groups of keys, against the
+    softmax in binary64.  Every probability is rounded to binary16 once (2^-11 of it, or 2^-25 below the smallest normal
+    number), the sums are binary32 and the result is binary16."""
+    import torch
+    H = 4 * dk
+    g = torch.Generator().manual_seed(S + dk)
+    qkv = torch.randn(S, 3 * H, generator=g) * 0.3
+    t = torch.arange(S) / S
+    lift = {"rising": 40.0 * t, "falling": -40.0 * t, "equal": 0.0 * t,
+            "far apart": 25.0 * (torch.arange(S) % 97 == 5).float() + 60.0 * (torch.arange(S) == S - 1).float()}[scores]
+    for h in range(4):  # q = (c, noise), k = (lift, noise): scores about lift
+        qkv[:, h * dk] = dk ** 0.5
+        qkv[:, H + h * dk] = lift
+    qkv = qkv.half()
+    ctx, _ = mkq.mkq_attention(qkv.cuda(), 1, S, H, 4)
+    q, k, v = (x.double().reshape(S, 4, dk).transpose(0, 1) for x in qkv.chunk(3, dim=1))
+    p = torch.softmax(q @ k.transpose(1, 2).contiguous() / dk ** 0.5, dim=2)
+    want = (p @ v).transpose(0, 1).reshape(S, H).numpy()
+    mass = (p @ v.abs()).transpose(0, 1).reshape(S, H).numpy()
+    got = to_np(ctx).astype(np.float64)
+    small = S * 2.0 ** -25 * float(v.abs().max())
+    assert np.all(np.abs(got - want) <= (2.0 ** -11 + 2.0 ** -14) * mass + small + 2.0 ** -11 * np.abs(want) + 2.0 ** -24)
+
+
 @pytest.mark.parametrize("batch,total,max_seq,heads,dk", [(5, 2300, 512, 4, 64), (5, 700, 300, 12, 26),
                                                           (4, 9, 512, 2, 64), (3, 520, 512, 2, 32)])
 def test_attention_over_long_ragged_sequences(mkq, batch, total, max_seq, heads, dk):
