@@ -34,33 +34,55 @@ __device__ __forceinline__ const T *group_at(const T *x, int64_t w, int64_t grou
     return x + m * ldx + (w - m * groups_per_row) * 8;
 }
 
-// Calls f with the eight values of every group that this thread owns.  AHEAD groups are fetched before the first of
+// Eight values of a tensor as they are fetched
+struct Floats8 {
+    float v[8];
+    template <typename T>
+    __device__ __forceinline__ void load(const T *p) { load8<T>(p, v); }
+};
+
+// Calls f with the eight values (a Group) of every group that this thread owns.  AHEAD groups are fetched before the first of
 // them is used, so that a thread has as many loads in flight.  A batch that reaches past the end fetches its first group
 // again, which is cheaper than a branch per load (25.7 instead of 27.0 us for a counting pass over 16384 x 4096 binary16
 // values) -- unless rows have gaps: the address of a group is a 64-bit division then, so whole batches go first, without
 // checks, and the last one skips what does not exist (percentile of 128 rows of 768 + 64 binary32 values 21.2 -> 18.3 us).
-template <typename T, bool CONTIG, int AHEAD, class F>
+// WINDOW (contiguous tensors): the groups of a batch are neighbours, so that all workgroups together read one window of memory
+// that moves on, instead of AHEAD of them megabytes apart; only batches that the whole grid fills, so that the rest is spread
+// as evenly as before.
+template <class Group, typename T, bool CONTIG, int AHEAD, bool WINDOW = false, class F>
 __device__ __forceinline__ void for_each_group(const T *__restrict__ x, int64_t total, int64_t groups_per_row, int64_t ldx,
                                                F &&f)
 {
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     int64_t w = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if constexpr (WINDOW && CONTIG) {
+        const int64_t span = AHEAD * stride, whole = total < span ? 0 : (int64_t)((uint32_t)total / (uint32_t)span) * span;
+        const T *at = x + ((int64_t)blockIdx.x * blockDim.x * AHEAD + threadIdx.x) * 8;
+        for (int64_t done = 0; done < whole; done += span, at += span * 8) {
+            Group v[AHEAD];
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) v[a].load(at + a * (int64_t)blockDim.x * 8);
+#pragma unroll
+            for (int a = 0; a < AHEAD; ++a) f(v[a]);
+        }
+        w += whole;
+    }
     if constexpr (!CONTIG) {
         for (; w + (AHEAD - 1) * stride < total; w += AHEAD * stride) {
-            float v[AHEAD][8];
+            Group v[AHEAD];
 #pragma unroll
-            for (int a = 0; a < AHEAD; ++a) load8<T>(group_at<T, CONTIG>(x, w + a * stride, groups_per_row, ldx), v[a]);
+            for (int a = 0; a < AHEAD; ++a) v[a].load(group_at<T, CONTIG>(x, w + a * stride, groups_per_row, ldx));
 #pragma unroll
             for (int a = 0; a < AHEAD; ++a) f(v[a]);
         }
     }
     for (; w < total; w += AHEAD * stride) {
-        float v[AHEAD][8];
+        Group v[AHEAD];
 #pragma unroll
         for (int a = 0; a < AHEAD; ++a) {
             const int64_t wa = w + a * stride;
             if (!CONTIG && wa >= total) break;
-            load8<T>(group_at<T, CONTIG>(x, wa < total ? wa : w, groups_per_row, ldx), v[a]);
+            v[a].load(group_at<T, CONTIG>(x, wa < total ? wa : w, groups_per_row, ldx));
         }
 #pragma unroll
         for (int a = 0; a < AHEAD; ++a)
@@ -106,7 +128,8 @@ __global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *_
     // sum(c - x/s) = sum c - (sum x)/s and sum((s c - x) c) = s sum c^2 - sum(x c): the sums of c and c^2 of eight
     // values are whole numbers that binary32 holds exactly, so binary64 is left with two sums per element, not three
     double sc = 0.0, scc = 0.0, sx = 0.0, sxc = 0.0;
-    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, [&](const float(&v)[8]) {
+    for_each_group<Floats8, T, CONTIG, 4>(x, total, groups_per_row, ldx, [&](const Floats8 &g8) {
+        const float(&v)[8] = g8.v;
         float c[8], c1 = 0.0f, c2 = 0.0f;
         codes8<BITS>(v, qs, c);
 #pragma unroll
@@ -136,14 +159,59 @@ __global__ __launch_bounds__(CAL_THREADS) void scale_gradients_kernel(const T *_
 }
 
 // ---- percentile calibration: exact k-th largest of |x| by radix selection -------------
-// |x| >= 0, so its binary32 bit pattern (31 bits) orders like an unsigned integer.  Three
-// passes count, among the elements whose higher bits equal the prefix chosen so far, the
-// next 11, 10 and 10 bits; after each the last workgroup to finish walks the counts from the
-// top and fixes the digit in which the k-th largest falls.
-// 16384 x 4096 binary16 values: 30.6 + 25.7 + 26.0 us, the later passes at 5.2 TB/s (absmax, which only reads: 27.0); the
-// first adds every element to a counter in LDS.  (A bound from a sample of the tensor spares most of these additions,
-// but its own pass costs more, at every size: 26.8 + 8.8 instead of 30.6.)
+// |x| >= 0, so its bit pattern orders like an unsigned integer: the 31 bits of a binary32 value, the 15 of a binary16 one
+// (with six zeros behind them).  Passes over the tensor count, among the elements whose higher bits equal the prefix
+// chosen so far, the next 11, 10 and 10 bits; after each the last workgroup to finish walks the counts from the
+// top and fixes the digit in which the k-th largest falls.  Two passes for binary16, three for binary32.
+// In a graph, us, binary16 as binary32 patterns (three passes, the last of which finds nothing but zeros in its digit)
+// -> this: 64 x 768 17.5 -> 13.6, 4096 x 768 32.6 -> 25.1, 16384 x 4096 84.0 -> 55.7.
+// (A bound from a sample of the tensor spares most of the first pass's additions, but its own pass costs more, at every
+// size.)
 constexpr int PCT_BINS = 2048;
+// What is selected on: the bits of a key, and a group of eight values as fetched, with keys() for NaN as 0
+template <typename T>
+struct PctKey;
+template <>
+struct PctKey<float> {
+    static constexpr int BITS = 31, PASSES = 3;
+    __device__ static float value(uint32_t key) { return __uint_as_float(key); }
+    struct Group {
+        float4 a, b;
+        __device__ __forceinline__ void load(const float *p)
+        {
+            a = *reinterpret_cast<const float4 *>(p);
+            b = *reinterpret_cast<const float4 *>(p + 4);
+        }
+        __device__ __forceinline__ void keys(uint32_t (&k)[8]) const
+        {
+            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) k[e] = (v[e] != v[e]) ? 0u : (__float_as_uint(v[e]) & 0x7FFFFFFFu);
+        }
+    };
+};
+template <>
+struct PctKey<__half> {
+    static constexpr int BITS = 21, PASSES = 2;
+    __device__ static float value(uint32_t key) { return half_bits_to_float((uint16_t)(key >> 6)); }
+    struct Group {
+        uint4 a;
+        __device__ __forceinline__ void load(const __half *p) { a = *reinterpret_cast<const uint4 *>(p); }
+        __device__ __forceinline__ void keys(uint32_t (&k)[8]) const
+        {
+            const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const uint32_t h = (e & 1) ? (w[e >> 1] >> 16) & 0x7FFFu : w[e >> 1] & 0x7FFFu;
+                k[e] = h > 0x7C00u ? 0u : h << 6;
+            }
+        }
+    };
+};
+// bits of a key below the digit of a pass
+template <typename T>
+constexpr int pct_shift(int pass) { return PctKey<T>::BITS - 11 - 10 * pass; }
+
 struct PctWorkspace {
     uint32_t hist[3][PCT_BINS];
     uint32_t prefix;  // bits fixed so far
@@ -160,9 +228,9 @@ __device__ __forceinline__ uint32_t load_agent(const uint32_t *p)
 // One workgroup, of which 256 threads own bins.  PASS 0 starts from rank k0; the later passes from the rank left over.
 // Thread t owns PER consecutive bins; the thread whose bins hold the k-th largest (fewer
 // than k elements in the bins above its own, at least k from its lowest bin up) fixes
-// the digit.  After PASS 2 the prefix is the whole bit pattern of T and the step
+// the digit.  After the last pass the prefix is the whole key of T and the step
 // T / qmax is written.  scratch: 272 words of LDS.
-template <int PASS>
+template <typename KT, int PASS>
 __device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws, uint32_t k0, float qmax,
                                                   float *__restrict__ s_out, uint32_t *scratch)
 {
@@ -215,15 +283,15 @@ __device__ __forceinline__ void percentile_select(PctWorkspace *__restrict__ ws,
         const uint32_t prefix = PASS == 0 ? (uint32_t)(t * PER + b) : ((old_prefix << 10) | (uint32_t)(t * PER + b));
         ws->prefix = prefix;
         ws->k = k - cum;
-        if (PASS == 2) {
-            const float tv = __uint_as_float(prefix);
+        if (PASS == PctKey<KT>::PASSES - 1) {
+            const float tv = PctKey<KT>::value(prefix);
             s_out[0] = (tv > 0.0f) ? tv / qmax : 1.0f;
         }
     }
 }
 
 // Four copies of the counts, chosen by lane % 4: activations pile up in a few dozen bins
-// (one binade is 8 bins of pass 0), and lanes of one LDS atomic that hit the same counter
+// (a binade of binary32 is 8 bins of pass 0), and lanes of one LDS atomic that hit the same counter
 // are served one after the other.
 // (workgroups of 1024 threads: a quarter of the atomic additions on the few bins that all of them hit)
 template <typename T, int PASS, bool CONTIG>
@@ -239,16 +307,17 @@ __global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *_
     const uint32_t prefix = PASS ? ws->prefix : 0u;
     const int64_t groups_per_row = K / 8;
     const int64_t total = M * groups_per_row;
-    for_each_group<T, CONTIG, 4>(x, total, groups_per_row, ldx, [&](const float(&v)[8]) {
+    using Group = typename PctKey<T>::Group;
+    constexpr int SHIFT = pct_shift<T>(PASS);
+    for_each_group<Group, T, CONTIG, sizeof(T) == 2 ? 8 : 4, sizeof(T) == 2>(x, total, groups_per_row, ldx, [&](const Group &g) {
+        uint32_t key[8];
+        g.keys(key);
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const uint32_t bits = (v[e] != v[e]) ? 0u : (__float_as_uint(v[e]) & 0x7FFFFFFFu);
             if (PASS == 0) {
-                atomicAdd(&mine[(bits >> 20) * COPIES], 1u);
-            } else if (PASS == 1) {
-                if ((bits >> 20) == prefix) atomicAdd(&mine[((bits >> 10) & 1023u) * COPIES], 1u);
+                atomicAdd(&mine[(key[e] >> SHIFT) * COPIES], 1u);
             } else {
-                if ((bits >> 10) == prefix) atomicAdd(&mine[(bits & 1023u) * COPIES], 1u);
+                if ((key[e] >> (SHIFT + 10)) == prefix) atomicAdd(&mine[((key[e] >> SHIFT) & 1023u) * COPIES], 1u);
             }
         }
     });
@@ -267,7 +336,7 @@ __global__ __launch_bounds__(CAL_THREADS) void percentile_hist_kernel(const T *_
         if (old == gridDim.x - 1) __hip_atomic_store(&ws->done, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    if (h[0] != 0u) percentile_select<PASS>(ws, k0, qmax, s_out, h + 64);
+    if (h[0] != 0u) percentile_select<T, PASS>(ws, k0, qmax, s_out, h + 64);
 }
 
 static inline int stream_grid(int64_t items, int threads, int max_blocks)
@@ -339,15 +408,16 @@ extern "C" int mkq_percentile_scale(const void *x, int x_dtype, int64_t M, int64
     zero_words_kernel<<<(words + 255) / 256, 256, 0, st>>>((uint32_t *)ws, words);
     const int grid = stream_grid(M * (K / 8), CAL_THREADS, 256 * 2);  // all resident at once
 #define MKQ_HIST(T, P, C) percentile_hist_kernel<T, P, C><<<grid, CAL_THREADS, 0, st>>>((const T *)x, M, K, ldx, ws, (uint32_t)k, qmax, s_out)
-#define MKQ_PASS(P)                                                                    \
-    if (x_dtype == MKQ_F32) {                                                          \
-        if (ldx == K) { MKQ_HIST(float, P, true); } else { MKQ_HIST(float, P, false); }   \
-    } else {                                                                           \
-        if (ldx == K) { MKQ_HIST(__half, P, true); } else { MKQ_HIST(__half, P, false); } \
+#define MKQ_PASS(T, P)                                                    \
+    if (ldx == K) { MKQ_HIST(T, P, true); } else { MKQ_HIST(T, P, false); }
+    if (x_dtype == MKQ_F32) {
+        MKQ_PASS(float, 0);
+        MKQ_PASS(float, 1);
+        MKQ_PASS(float, 2);
+    } else {
+        MKQ_PASS(__half, 0);
+        MKQ_PASS(__half, 1);
     }
-    MKQ_PASS(0);
-    MKQ_PASS(1);
-    MKQ_PASS(2);
 #undef MKQ_PASS
 #undef MKQ_HIST
     return launch_status();
