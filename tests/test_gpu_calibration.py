@@ -153,3 +153,33 @@ def test_rows_with_gaps_over_several_batches(mkq):
     xd, sd = xf.astype(np.float64), float(np.float32(0.34))
     assert abs(g[0] - ste) <= 1e-10 * np.abs(c - xd / sd).sum()
     assert abs(g[1] - mse) <= 1e-10 * np.abs(2 * (sd * c - xd) * c).sum()
+
+
+@pytest.mark.parametrize("M,K", [(1, 131072), (1, 131080), (8, 16392), (2048, 8192), (2049, 8200), (8200, 4104)])
+def test_contiguous_tensors_around_the_batches(mkq, M, K):
+    """One group more or less than what 64 small workgroups, one batch of the whole grid and whole windows of it cover; the
+    largest value in the last and in the first place.  Order statistics and maxima: exact."""
+    import torch
+    for dtype in (torch.float16, torch.float32):
+        g = torch.Generator(device="cuda").manual_seed(M + K)
+        x = torch.randn(M, K, generator=g, device="cuda").to(dtype)
+        for at in (-1, 0):
+            x.view(-1)[at] = -70.0
+            assert float(mkq.mkq_absmax_scale(x)) == np.float32(70.0) / np.float32(7)
+            for ppm in (0, 200):
+                k = max(1, M * K * ppm // 10 ** 6)
+                kth = torch.topk(x.view(-1).abs().float(), k).values[-1]
+                assert float(mkq.mkq_percentile_scale(x, ppm)) == np.float32(float(kth)) / np.float32(7), (dtype, at, ppm)
+            x.view(-1)[at] = 0.5
+
+
+def test_percentile_of_every_binary16_value(mkq):
+    """All 65536 bit patterns, subnormals, infinities and NaN (which rank as 0) among them, at every rank."""
+    import torch
+    x = np.arange(65536, dtype=np.uint16).view(np.float16).reshape(64, 1024)
+    order = np.sort(np.where(np.isnan(x), 0, np.abs(x)).astype(np.float32), axis=None)[::-1]
+    d = to_dev(x)
+    for ppm in (0, 16, 31, 1000, 30000, 31250, 40000, 250000, 499000, 900000, 968000, 999990, 1000000):
+        t = order[max(1, 65536 * ppm // 10 ** 6) - 1]
+        want = np.float32(t) / np.float32(7) if t > 0 else np.float32(1)
+        assert to_np(mkq.mkq_percentile_scale(d, ppm))[0] == want, ppm
