@@ -160,24 +160,40 @@ def _check(status: int, where: str):
         raise MkqError(status, where)
 
 
+# What follows runs in every call, and the smallest linears are bound by their calls: addresses go to ctypes as the integers
+# they are, and torch's Stream object is not built only to read its handle.  From call to call, us, with the block
+# of options passed only where there are any: 128 tokens of binary32 through K = N = 768 10.4 -> 6.1, 16 rows of codes through
+# K = N = 4096 9.6 -> 6.1 (the kernels are 5.8).
+_torch_module = None
+_dtype_codes = {}
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _dtype_codes.update({torch.float32: MKQ_F32, torch.float16: MKQ_F16, torch.bfloat16: MKQ_BF16})
+        _torch_module = torch
+    return _torch_module
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream=None):
+    if stream is not None:
+        return stream.cuda_stream
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return C.c_void_p(s.cuda_stream)
+    if not torch.cuda.is_initialized():
+        return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _dtype_code(t):
-    torch = _torch()
-    return {torch.float32: MKQ_F32, torch.float16: MKQ_F16, torch.bfloat16: MKQ_BF16}[t.dtype]
+    if not _dtype_codes:
+        _torch()
+    return _dtype_codes[t.dtype]
 
 
 def _torch_dtype(code):
@@ -343,44 +359,41 @@ def mkq_linear_int4(a, s_x: float, Wq, s_w, bias, N: int, K: int, out_dtype: int
     torch = _torch()
     if a_is_codes is None:
         a_is_codes = a.dtype == torch.uint8
-    M = a.shape[0]
+    M = a.size(0)
     a_dtype = MKQ_I4 if a_is_codes else _dtype_code(a)
-    dev = a.device
     code_cols = (int(q_pitch) or N) // 2
     if out is None:
-        out = (torch.empty((M, code_cols), dtype=torch.uint8, device=dev) if out_dtype == MKQ_I4
-               else torch.empty((M, N), dtype=_torch_dtype(out_dtype), device=dev))
-    q = q_out if q_out is not None else (torch.empty((M, code_cols), dtype=torch.uint8, device=dev) if want_q else None)
-    acc = torch.empty((M, N), dtype=torch.int32, device=dev) if want_acc else None
-    epi = Epilogue(act=int(act), residual=residual.data_ptr() if residual is not None else None,
-                   residual_dtype=_dtype_code(residual) if residual is not None else MKQ_F32,
-                   s_next=float(s_next), q_out=q.data_ptr() if q is not None else None,
-                   acc_out=acc.data_ptr() if acc is not None else None,
-                   splitk_scratch=splitk_scratch.data_ptr() if splitk_scratch is not None else None,
-                   splitk_scratch_bytes=(splitk_scratch.numel() * splitk_scratch.element_size()
-                                         if splitk_scratch is not None else 0), q_pitch=int(q_pitch))
-    need = mkq_linear_int4_workspace_bytes(M, N, K, a_dtype)
-    if need and workspace is None:
-        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
+        out = (torch.empty((M, code_cols), dtype=torch.uint8, device=a.device) if out_dtype == MKQ_I4
+               else torch.empty((M, N), dtype=_torch_dtype(out_dtype), device=a.device))
+    q = q_out if q_out is not None else (torch.empty((M, code_cols), dtype=torch.uint8, device=a.device) if want_q else None)
+    acc = torch.empty((M, N), dtype=torch.int32, device=a.device) if want_acc else None
+    epi = None  # (what it says when nothing is asked for is what the library takes a null pointer for)
+    if act or residual is not None or s_next or q is not None or want_acc or splitk_scratch is not None or q_pitch:
+        epi = C.byref(Epilogue(
+            act=int(act), residual=_ptr(residual), residual_dtype=_dtype_code(residual) if residual is not None else MKQ_F32,
+            s_next=float(s_next), q_out=_ptr(q), acc_out=_ptr(acc), splitk_scratch=_ptr(splitk_scratch),
+            splitk_scratch_bytes=splitk_scratch.nbytes if splitk_scratch is not None else 0, q_pitch=int(q_pitch)))
+    if workspace is None and not a_is_codes:
+        workspace = torch.empty(mkq_linear_int4_workspace_bytes(M, N, K, a_dtype), dtype=torch.uint8, device=a.device)
+    ws_bytes = workspace.nbytes if workspace is not None else 0
     if w_stream:
         if not prefetch_stages and not k_slices:
             _check(load().mkq_linear_int4_stream(_ptr(a), a_dtype, float(s_x), _ptr(Wq), _ptr(s_w), _ptr(bias),
-                                                 M, N, K, _ptr(out), int(out_dtype), C.byref(epi), _ptr(workspace),
+                                                 M, N, K, _ptr(out), int(out_dtype), epi, _ptr(workspace),
                                                  ws_bytes, _stream(stream)), "mkq_linear_int4_stream")
         else:
             _check(load().mkq_tuning_linear_int4_stream(_ptr(a), a_dtype, float(s_x), _ptr(Wq), _ptr(s_w),
                                                         _ptr(bias), M, N, K, _ptr(out), int(out_dtype),
-                                                        C.byref(epi), _ptr(workspace), ws_bytes, _stream(stream),
+                                                        epi, _ptr(workspace), ws_bytes, _stream(stream),
                                                         int(prefetch_stages), int(k_slices)),
                    "mkq_tuning_linear_int4_stream")
     elif config is None and not k_slices:
         _check(load().mkq_linear_int4(_ptr(a), a_dtype, float(s_x), _ptr(Wq), _ptr(s_w), _ptr(bias),
-                                      M, N, K, _ptr(out), int(out_dtype), C.byref(epi), _ptr(workspace),
+                                      M, N, K, _ptr(out), int(out_dtype), epi, _ptr(workspace),
                                       ws_bytes, _stream(stream)), "mkq_linear_int4")
     else:
         _check(load().mkq_tuning_linear_int4(_ptr(a), a_dtype, float(s_x), _ptr(Wq), _ptr(s_w), _ptr(bias),
-                                             M, N, K, _ptr(out), int(out_dtype), C.byref(epi), _ptr(workspace),
+                                             M, N, K, _ptr(out), int(out_dtype), epi, _ptr(workspace),
                                              ws_bytes, _stream(stream), -1 if config is None else int(config),
                                              int(k_slices)), "mkq_tuning_linear_int4")
     return {"out": out, "q": q, "acc": acc}
