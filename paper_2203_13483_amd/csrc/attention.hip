@@ -179,8 +179,8 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
             if (NG == 8 || (NG < 8 ? g & 1 : (g & 3) == 3)) __builtin_amdgcn_sched_barrier(0);  // (else the fragments of all groups are fetched at once: spills)
         }
         mx = fmaxf(m2[0], m2[1]);
-        mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-        mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = lane_pair<16>(mx, MaxF32());
+        mx = lane_pair<32>(mx, MaxF32());
         const float shift = -mx * c_exp;
         float d2[2] = {0.0f, 0.0f};
 #pragma unroll
@@ -195,8 +195,8 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
                     }
             }
         den = d2[0] + d2[1];
-        den += __shfl_xor(den, 16, 64);
-        den += __shfl_xor(den, 32, 64);
+        den = lane_pair<16>(den, AddF32());
+        den = lane_pair<32>(den, AddF32());
     };
     // byte of this lane's chunk lg of its rows of V^T; chunk 4 g + lg is 4 (g % 4) chunks away under the swizzle, 16 (g / 4) beyond
     int vat[2 * DS];

@@ -12,6 +12,11 @@ namespace mkq {
 // LayerNorm over the last dimension: one wavefront per row, the row lives in
 // registers (binary32), two passes for mean and variance, wave-level reductions.
 // Writes the binary16 result and / or its 4-bit codes (Eq. 1 on the binary32 value).
+// A few rows are bound by one chain: row from memory, two reductions, result.  gamma and beta are fetched beside the row (up
+// to D = 1024; beyond, in the registers the row leaves) and the reductions stay in the vector unit (lane_pair).  us in a graph,
+// gamma and beta after the reductions and these through LDS -> reductions in the vector unit -> this: 440 x 768 with codes
+// 3.55 -> 3.23 -> 3.01, 440 x 4096 7.68 -> 7.43 -> 7.05; the half-wave kernel below 4096 x 768 with codes 5.25 -> 4.96, 8192 x 1024
+// 9.33 -> 9.09.
 template <int MAXC>
 __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restrict__ x, int M, int D,
                                                         const float *__restrict__ gamma,
@@ -23,14 +28,36 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restri
     const int row = xcd_index(blockIdx.x, gridDim.x) * 4 + (threadIdx.x >> 6);
     if (row >= M) return;
     const int chunks = D / 8;  // 16-byte chunks of 8 elements
-    float v[MAXC][8];
+    float v[MAXC][8], gg[MAXC][8], bb[MAXC][8];
+    auto affine = [&](int i) __attribute__((always_inline)) {
+        const int c = lane + i * 64;
+        const bool in = c < chunks;
+        const float4 g0 = (gamma && in) ? *reinterpret_cast<const float4 *>(gamma + c * 8) : make_float4(1, 1, 1, 1);
+        const float4 g1 = (gamma && in) ? *reinterpret_cast<const float4 *>(gamma + c * 8 + 4) : make_float4(1, 1, 1, 1);
+        const float4 b0 = (beta && in) ? *reinterpret_cast<const float4 *>(beta + c * 8) : make_float4(0, 0, 0, 0);
+        const float4 b1 = (beta && in) ? *reinterpret_cast<const float4 *>(beta + c * 8 + 4) : make_float4(0, 0, 0, 0);
+        gg[i][0] = g0.x; gg[i][1] = g0.y; gg[i][2] = g0.z; gg[i][3] = g0.w;
+        gg[i][4] = g1.x; gg[i][5] = g1.y; gg[i][6] = g1.z; gg[i][7] = g1.w;
+        bb[i][0] = b0.x; bb[i][1] = b0.y; bb[i][2] = b0.z; bb[i][3] = b0.w;
+        bb[i][4] = b1.x; bb[i][5] = b1.y; bb[i][6] = b1.z; bb[i][7] = b1.w;
+    };
+    constexpr bool EARLY = MAXC <= 2;  // gamma and beta fetched beside the row, not after its reductions
     float sum = 0.0f;
+    uint4 rows[MAXC];
+#pragma unroll
+    for (int i = 0; i < MAXC; ++i) {
+        const int c = lane + i * 64;
+        if (c < chunks) rows[i] = *reinterpret_cast<const uint4 *>(x + (int64_t)row * D + c * 8);
+    }
+    if constexpr (EARLY) {
+#pragma unroll
+        for (int i = 0; i < MAXC; ++i) affine(i);
+    }
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
         const int c = lane + i * 64;
         if (c < chunks) {
-            const uint4 raw = *reinterpret_cast<const uint4 *>(x + (int64_t)row * D + c * 8);
-            const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+            const uint32_t w[4] = {rows[i].x, rows[i].y, rows[i].z, rows[i].w};
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 v[i][2 * e] = half_bits_to_float((uint16_t)(w[e] & 0xFFFFu));
@@ -58,14 +85,9 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restri
         const int c = lane + i * 64;
         if (c < chunks) {
             float o[8];
-            const float4 g0 = gamma ? *reinterpret_cast<const float4 *>(gamma + c * 8) : make_float4(1, 1, 1, 1);
-            const float4 g1 = gamma ? *reinterpret_cast<const float4 *>(gamma + c * 8 + 4) : make_float4(1, 1, 1, 1);
-            const float4 b0 = beta ? *reinterpret_cast<const float4 *>(beta + c * 8) : make_float4(0, 0, 0, 0);
-            const float4 b1 = beta ? *reinterpret_cast<const float4 *>(beta + c * 8 + 4) : make_float4(0, 0, 0, 0);
-            const float gg[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-            const float bb[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
+            if constexpr (!EARLY) affine(i);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (v[i][e] - mean) * rstd * gg[e] + bb[e];
+            for (int e = 0; e < 8; ++e) o[e] = (v[i][e] - mean) * rstd * gg[i][e] + bb[i][e];
             if (y)
                 *reinterpret_cast<uint4 *>(y + (int64_t)row * D + c * 8) =
                     make_uint4(pack2_f16(o[0], o[1]), pack2_f16(o[2], o[3]), pack2_f16(o[4], o[5]), pack2_f16(o[6], o[7]));
@@ -131,8 +153,7 @@ __global__ __launch_bounds__(256) void layernorm_half_kernel(const uint16_t *__r
 #pragma unroll
         for (int e = 0; e < 8; ++e) sum += v[i][e];
     }
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    sum = lane_reduce<32>(sum, AddF32());
     const float mean = sum / (float)D;
     float sq = 0.0f;
 #pragma unroll
@@ -145,8 +166,7 @@ __global__ __launch_bounds__(256) void layernorm_half_kernel(const uint16_t *__r
             }
         }
     }
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+    sq = lane_reduce<32>(sq, AddF32());
     const float rstd = 1.0f / sqrtf(sq / (float)D + eps);
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
@@ -287,7 +307,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const uint16_t *__restri
             sc[kt][v] = (key < seq) ? sc[kt][v] : -1.0e30f;
             mx = fmaxf(mx, sc[kt][v]);
         }
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = lane_pair<32>(mx, MaxF32());
     const float shift = -mx * c_exp;
     float den = 0.0f;
 #pragma unroll
@@ -297,7 +317,7 @@ __global__ __launch_bounds__(256) void attention_kernel(const uint16_t *__restri
             sc[kt][v] = __builtin_amdgcn_exp2f(__fmaf_rn(sc[kt][v], c_exp, shift));
             den += sc[kt][v];
         }
-    den += __shfl_xor(den, 32, 64);
+    den = lane_pair<32>(den, AddF32());
     const float inv = 1.0f / den;
 
     // O^T = V^T P^T
@@ -496,7 +516,7 @@ __global__ __launch_bounds__(256, 3) void attention_blocks_kernel(const uint16_t
                 float bm = sc[0];
 #pragma unroll
                 for (int v = 1; v < 16; ++v) bm = fmaxf(bm, sc[v]);
-                bm = fmaxf(bm, __shfl_xor(bm, 32, 64));
+                bm = lane_pair<32>(bm, MaxF32());
                 const float m_new = fmaxf(mx, bm);
                 const float shift = -m_new * c_exp;
                 float part = 0.0f;
@@ -515,7 +535,7 @@ __global__ __launch_bounds__(256, 3) void attention_blocks_kernel(const uint16_t
         }
         __syncthreads();
     }
-    den += __shfl_xor(den, 32, 64);
+    den = lane_pair<32>(den, AddF32());
     // p = exp2(x c - max c - log2(denominator)): the division folded into the exponent
     const float shift2 = -mx * c_exp - __log2f(den);
 

@@ -192,19 +192,44 @@ __device__ __forceinline__ uint2 quantize8(const float (&x)[8], const QuantStep 
     return out;
 }
 
-__device__ __forceinline__ float wave_max(float v)
+// f of a lane's value and that of lane ^ OFF, for an f that does not depend on their order.  All 2 OFF lanes have to be
+// active (16 for OFF = 4, where the values also have to agree between lane and lane ^ 8, as they do after a step of 8).
+// Lane permutations of the vector unit: what __shfl_xor gives takes a trip through LDS, about 100 cycles, and the two
+// reductions of a row's LayerNorm are ten of them one after the other.
+template <int OFF, class F>
+__device__ __forceinline__ float lane_pair(float v, F &&f)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    return v;
+    static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "a power of two within a wave");
+    const unsigned u = __float_as_uint(v);
+    if constexpr (OFF >= 16) {
+        const auto r = OFF == 32 ? __builtin_amdgcn_permlane32_swap(u, u, false, false) : __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    } else {
+        constexpr int PERM = OFF == 1 ? 0xB1 : OFF == 2 ? 0x4E : 0x120 + OFF;  // of four lanes: 1 0 3 2, 2 3 0 1; of 16: turned by OFF
+        return f(v, __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)u, PERM, 0xF, 0xF, true)));
+    }
 }
 
-__device__ __forceinline__ float wave_sum(float v)
+// Over LANES neighbouring lanes (32 or 64), from the far ones to the near ones
+template <int LANES, class F>
+__device__ __forceinline__ float lane_reduce(float v, F &&f)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    if constexpr (LANES == 64) v = lane_pair<32>(v, f);
+    v = lane_pair<16>(v, f);
+    v = lane_pair<8>(v, f);
+    v = lane_pair<4>(v, f);
+    v = lane_pair<2>(v, f);
+    return lane_pair<1>(v, f);
 }
+
+struct AddF32 {
+    __device__ __forceinline__ float operator()(float a, float b) const { return a + b; }
+};
+struct MaxF32 {
+    __device__ __forceinline__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+__device__ __forceinline__ float wave_max(float v) { return lane_reduce<64>(v, MaxF32()); }
+__device__ __forceinline__ float wave_sum(float v) { return lane_reduce<64>(v, AddF32()); }
 
 __device__ __forceinline__ float half_bits_to_float(uint16_t h)
 {

@@ -45,6 +45,21 @@ def test_layernorm(mkq, M, D):
     assert_float_close(to_np(y0).astype(np.float32), oracle.layernorm(x.astype(np.float32), eps=1e-5), RTOL[1], "ln plain")
 
 
+@pytest.mark.parametrize("M,D", [(9, 8), (65, 64), (513, 512), (1025, 1024), (1031, 1032), (2047, 312), (2049, 312), (2049, 256),
+                                 (2051, 1024), (4097, 4096)])
+def test_layernorm_counts_every_lane_once(mkq, M, D):
+    """Rows with one value that is not zero, in every place: a lane that a reduction missed or counted twice moves mean and
+    variance of its rows by as much as they are.  Binary32 sums of exact zeros and one value, one binary16 rounding."""
+    import torch
+    x = torch.zeros(M, D, dtype=torch.float16, device="cuda")
+    at = torch.arange(M, device="cuda")
+    x[at, at % D] = 8.0
+    y, _ = mkq.mkq_layernorm(x, None, None, 1e-5)
+    xd = x.double()
+    want = torch.nn.functional.layer_norm(xd, (D,), eps=1e-5)
+    assert bool(((y.double() - want).abs() <= (2.0 ** -11 + 4e-6) * want.abs() + 2.0 ** -24).all())
+
+
 @pytest.mark.parametrize("B,S,heads", [(2, 128, 12), (3, 64, 2), (1, 32, 1), (2, 96, 4)])
 def test_attention(mkq, B, S, heads):
     H = heads * 64
