@@ -45,7 +45,7 @@ def test_layernorm(mkq, M, D):
     assert_float_close(to_np(y0).astype(np.float32), oracle.layernorm(x.astype(np.float32), eps=1e-5), RTOL[1], "ln plain")
 
 
-@pytest.mark.parametrize("M,D", [(9, 8), (65, 64), (513, 512), (1025, 1024), (1031, 1032), (2047, 312), (2049, 312), (2049, 256),
+@pytest.mark.parametrize("M,D", [(9, 8), (65, 64), (513, 512), (1025, 1024), (1031, 1032), (2047, 312), (2049, 312), (2049, 256), (2049, 768), (2050, 520),
                                  (2051, 1024), (4097, 4096)])
 def test_layernorm_counts_every_lane_once(mkq, M, D):
     """Rows with one value that is not zero, in every place: a lane that a reduction missed or counted twice moves mean and
