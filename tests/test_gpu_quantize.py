@@ -56,6 +56,30 @@ def test_quantize_all_half_values(mkq):
         assert np.array_equal(q, ref)
 
 
+@pytest.mark.parametrize("bits", [4, 8])
+def test_one_value_of_eight_takes_the_division(mkq, bits):
+    """Groups of eight in which one value, in every place, is NaN, infinite or next to a rounding boundary, and the others are
+    far from one: codes exact, and the sum of codes less quotients as the codes say."""
+    s, q = np.float32(0.34), 2 ** (bits - 1)
+    ties = (np.arange(-q, q) + 0.5).astype(np.float32) * s
+    odd = np.concatenate([ties, np.nextafter(ties, np.float32(np.inf)), np.nextafter(ties, np.float32(-np.inf)),
+                          np.float32([np.nan, np.inf, -np.inf, 3e38, -3e38])])
+    x = np.tile((np.arange(8) % 3 - 1).astype(np.float32) * s, (odd.size, 8, 1))  # [odd value, place, group of eight]
+    for place in range(8):
+        x[:, place, place] = odd
+    x = x.reshape(-1, 64)
+    ref = oracle.quantize(x, s, qmin=-q, qmax=q - 1)
+    if bits == 4:
+        assert np.array_equal(to_np(mkq.mkq_quantize(to_dev(x), float(s))), oracle.pack_nibbles(ref))
+    else:
+        assert np.array_equal(to_np(mkq.mkq_quantize_int8(to_dev(x), float(s))), ref)
+    x = x[np.abs(x).max(axis=1) < 1e30]  # (false for NaN)
+    c = oracle.quantize(x, s, qmin=-q, qmax=q - 1).astype(np.float64)
+    g = to_np(mkq.mkq_scale_gradients(to_dev(x), float(s), bits))
+    terms = c - x.astype(np.float64) / float(s)
+    assert abs(g[0] - terms.sum()) <= 1e-10 * np.abs(terms).sum()
+
+
 def test_quantize_strided_rows_and_empty(mkq):
     import torch
     rng = np.random.default_rng(3)
