@@ -2,6 +2,7 @@
 #pragma once
 
 #include "gemm_common.h"
+#include "launch_rules.h"
 
 #include <type_traits>
 
@@ -54,8 +55,7 @@ __device__ __forceinline__ void attention_pad_codes(const AttentionParams &p, in
     }
 }
 
-// Sequences of up to 512 tokens (attention.hip).
-constexpr int ATTENTION_HELD_KEYS = 512;
+// What attention_route sends to the kernel of attention.hip: up to ATTENTION_HELD_KEYS tokens, d_k <= 32 or a multiple of 8
 int run_attention_held(const AttentionParams &p, hipStream_t st);
 // once-per-device setup of its instantiations (nothing is launched)
 int setup_attention();

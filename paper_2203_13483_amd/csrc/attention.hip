@@ -63,6 +63,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     // row and masked)
     const bool full = seq > KEYS - 64;
     const int rows = full ? KEYS : (seq + 31) & ~31;
+    // (offsets within a sequence in 32 bits: attention_route keeps longer ones away)
     auto fetch = [&](int r, int d, int col) __attribute__((always_inline)) {
         Piece v{};
         const uint8_t *const base = reinterpret_cast<const uint8_t *>(p.qkv + row0 * ld + head * dk + col);

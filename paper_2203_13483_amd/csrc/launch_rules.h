@@ -1,0 +1,29 @@
+// Rules of launches in plain arithmetic, without HIP, so that they can be checked on any machine.
+#pragma once
+
+#include <cstdint>
+
+namespace mkq {
+
+// Which kernel an attention call takes.
+enum AttentionRoute {
+    ATTENTION_ONE_BLOCK,  // attention_kernel: all keys of a head at once, probabilities in registers
+    ATTENTION_HELD,       // attention_held_kernel: scores of up to ATTENTION_HELD_KEYS keys held in registers
+    ATTENTION_BLOCKS,     // attention_blocks_kernel: blocks of 128 keys, twice
+};
+constexpr int ATTENTION_HELD_KEYS = 512;
+
+// Up to 512 keys are held in registers between softmax and product with V; heads of 64 and up to 128 keys keep the one-block
+// kernel, which fits more workgroups on a CU (64 x 128 tokens, 12 heads 13.0 us, held 14.6; 64 x 32 4.7, 7.4; with few
+// workgroups held is ahead by 2 to 8 % of 6 us).  The kernel that goes over the keys twice is left with longer sequences,
+// heads of 34 to 62 that are no multiple of 8, and sequences whose rows of qkv (6 hidden bytes each) reach over 4 GiB, within
+// which the held kernel's 32-bit offsets stay.
+constexpr AttentionRoute attention_route(int64_t seq, int64_t hidden, int64_t heads, int64_t q_pitch)
+{
+    const int64_t dk = hidden / heads;
+    if (dk == 64 && seq <= 128 && q_pitch == hidden) return ATTENTION_ONE_BLOCK;
+    const bool held = seq <= ATTENTION_HELD_KEYS && (dk <= 32 || dk % 8 == 0) && seq * hidden * 6 <= 0xFFFFFFFFLL;
+    return held ? ATTENTION_HELD : ATTENTION_BLOCKS;
+}
+
+}  // namespace mkq

@@ -708,16 +708,13 @@ static int attention_run(const void *qkv, int64_t batch, int64_t seq, int64_t hi
     if (!aligned16(qkv) || (ctx && !aligned16(ctx)) || (q_out && !aligned16(q_out))) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     const uint16_t *in = (const uint16_t *)qkv;
-    // Up to 512 keys are held in registers between softmax and product with V; heads of 64 and up to 128 keys keep the kernel
-    // above, which fits more workgroups on a CU (64 x 128 tokens, 12 heads 13.0 us, held 14.6; 64 x 32 4.7, 7.4; with few
-    // workgroups held is ahead by 2 to 8 % of 6 us).  The kernel that goes over the keys twice is left with longer
-    // sequences and heads of 34 to 62 that are no multiple of 8.
-    if ((dk != 64 || seq > 128 || q_pitch != hidden) && seq <= ATTENTION_HELD_KEYS && (dk <= 32 || dk % 8 == 0)) {
+    const AttentionRoute route = attention_route(seq, hidden, heads, q_pitch);
+    if (route == ATTENTION_HELD) {
         const AttentionParams p = {in, cu, (int)batch, (int)seq, (int)hidden, (int)heads, (int)dk, (int)q_blocks,
                                    (uint16_t *)ctx, q_out, s_next, q_bits, (int)q_pitch};
         return run_attention_held(p, st);
     }
-    if (dk != 64 || seq > 128 || q_pitch != hidden) {
+    if (route == ATTENTION_BLOCKS) {
         const unsigned grid = (unsigned)(batch * heads * q_blocks);
 #define MKQ_ATT(DKP, VEC)                                                                                        \
     attention_blocks_kernel<DKP, VEC><<<grid, 256, 0, st>>>(in, (int)seq, (int)hidden, (int)heads, (int)dk,     \

@@ -146,6 +146,25 @@ def test_attention_at_the_edges_of_its_key_groups(mkq, S, dk, scores):
     assert np.all(np.abs(got - want) <= (2.0 ** -11 + 2.0 ** -14) * mass + small + 2.0 ** -11 * np.abs(want) + 2.0 ** -24)
 
 
+def test_attention_with_rows_beyond_32_bit_offsets(mkq):
+    """One sequence whose rows of qkv reach over 4 GiB: the first and the last heads against the softmax in binary64."""
+    import torch
+    S, dk, heads, few = 512, 64, 21952, 4
+    H = heads * dk
+    assert S * 6 * H > 2 ** 32
+    g = torch.Generator(device="cuda").manual_seed(5)
+    qkv = torch.empty((S, 3, heads, dk), dtype=torch.float16, device="cuda")
+    for r in range(0, S, 64):
+        qkv[r: r + 64] = torch.randn((64, 3, heads, dk), generator=g, device="cuda", dtype=torch.float16)
+    ctx, _ = mkq.mkq_attention(qkv.view(S, 3 * H), 1, S, H, heads)
+    ctx = ctx.view(S, heads, dk)
+    for sl in (slice(0, few), slice(heads - few, heads)):
+        q, k, v = (qkv[:, i, sl].double().transpose(0, 1).contiguous().cpu() for i in range(3))
+        p = torch.softmax(q @ k.transpose(1, 2).contiguous() / dk ** 0.5, dim=2)
+        want = (p @ v).transpose(0, 1).numpy()
+        assert_float_close(to_np(ctx[:, sl]).astype(np.float32), want, RTOL[1], f"heads {sl}")
+
+
 @pytest.mark.parametrize("batch,total,max_seq,heads,dk", [(5, 2300, 512, 4, 64), (5, 700, 300, 12, 26),
                                                           (4, 9, 512, 2, 64), (3, 520, 512, 2, 32)])
 def test_attention_over_long_ragged_sequences(mkq, batch, total, max_seq, heads, dk):
