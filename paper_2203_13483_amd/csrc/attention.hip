@@ -23,7 +23,7 @@ namespace mkq {
 // NG: groups of 32 keys
 template <int DKP, int NG>
 struct AttentionHeldCfg {
-    static constexpr int THREADS = 512, KEYS = 32 * NG;
+    static constexpr int THREADS = ATTENTION_HELD_THREADS, KEYS = 32 * NG;
     static constexpr int VROW = (KEYS + 127) / 128 * 256;  // bytes of a row of V^T: the swizzle moves within 16 chunks of 8 keys
     static constexpr int K_BYTES = KEYS * DKP * 2, V_BYTES = DKP * VROW;
     static constexpr int LDS_BYTES = K_BYTES + V_BYTES;
@@ -260,16 +260,9 @@ static int launch_held(const AttentionParams *p, hipStream_t st)
     int64_t resident = 0;
     const int rc = resident_workgroups(once, kernel, Cfg::THREADS, Cfg::LDS_BYTES, 1 << 20, &resident);
     if (rc != MKQ_OK || !p) return rc;
-    // Query blocks per workgroup: more share one staging of the keys (about as long as half a block), fewer fill the last
-    // round of workgroups better.
-    int per_wg = 1;
-    int64_t best = -1;
-    for (int c = 1; c <= p->q_blocks; ++c) {
-        const int64_t wgs = (int64_t)p->batch * p->heads * ceil_div(p->q_blocks, c);
-        const int64_t cost = ceil_div(wgs, resident) * (1 + 2 * c);
-        if (best < 0 || cost < best) { best = cost; per_wg = c; }
-    }
-    const unsigned grid = (unsigned)((int64_t)p->batch * p->heads * ceil_div(p->q_blocks, per_wg));
+    const int64_t sequence_heads = (int64_t)p->batch * p->heads;
+    const int per_wg = attention_held_blocks(sequence_heads, p->q_blocks, resident);
+    const unsigned grid = (unsigned)(sequence_heads * ceil_div(p->q_blocks, per_wg));
     kernel<<<grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, per_wg);
     return launch_status();
 }

@@ -5,6 +5,9 @@
 
 namespace mkq {
 
+// Work-items of a launch in one dimension: a product of grid and workgroup size that HIP takes
+constexpr int64_t MAX_WORK_ITEMS = 0xFFFFFFFFLL;
+
 // Which kernel an attention call takes.
 enum AttentionRoute {
     ATTENTION_ONE_BLOCK,  // attention_kernel: all keys of a head at once, probabilities in registers
@@ -12,18 +15,36 @@ enum AttentionRoute {
     ATTENTION_BLOCKS,     // attention_blocks_kernel: blocks of 128 keys, twice
 };
 constexpr int ATTENTION_HELD_KEYS = 512;
+constexpr int ATTENTION_HELD_THREADS = 512;  // of a workgroup
 
 // Up to 512 keys are held in registers between softmax and product with V; heads of 64 and up to 128 keys keep the one-block
 // kernel, which fits more workgroups on a CU (64 x 128 tokens, 12 heads 13.0 us, held 14.6; 64 x 32 4.7, 7.4; with few
 // workgroups held is ahead by 2 to 8 % of 6 us).  The kernel that goes over the keys twice is left with longer sequences,
-// heads of 34 to 62 that are no multiple of 8, and sequences whose rows of qkv (6 hidden bytes each) reach over 4 GiB, within
-// which the held kernel's 32-bit offsets stay.
-constexpr AttentionRoute attention_route(int64_t seq, int64_t hidden, int64_t heads, int64_t q_pitch)
+// heads of 34 to 62 that are no multiple of 8, sequences whose rows of qkv (6 hidden bytes each) reach over 4 GiB, within
+// which the held kernel's 32-bit offsets stay, and more heads than one workgroup of the held kernel each can be launched for
+// (the other's are half as large).
+constexpr AttentionRoute attention_route(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t q_pitch)
 {
     const int64_t dk = hidden / heads;
     if (dk == 64 && seq <= 128 && q_pitch == hidden) return ATTENTION_ONE_BLOCK;
-    const bool held = seq <= ATTENTION_HELD_KEYS && (dk <= 32 || dk % 8 == 0) && seq * hidden * 6 <= 0xFFFFFFFFLL;
+    const bool held = seq <= ATTENTION_HELD_KEYS && (dk <= 32 || dk % 8 == 0) && seq * hidden * 6 <= 0xFFFFFFFFLL &&
+                      batch * heads <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS;
     return held ? ATTENTION_HELD : ATTENTION_BLOCKS;
+}
+
+// Blocks of 128 queries per workgroup of the held kernel: more share one staging of the keys (about as long as half a block),
+// fewer fill the last round of workgroups better.  sequence_heads: pairs of sequence and head (attention_route bounds them, so
+// that one workgroup for each can be launched); resident: workgroups that the device runs at a time.
+constexpr int attention_held_blocks(int64_t sequence_heads, int q_blocks, int64_t resident)
+{
+    int per_wg = q_blocks;
+    int64_t best = -1;
+    for (int c = 1; c <= q_blocks; ++c) {
+        const int64_t wgs = sequence_heads * ((q_blocks + c - 1) / c);
+        const int64_t cost = (wgs + resident - 1) / resident * (1 + 2 * c);
+        if (wgs <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS && (best < 0 || cost < best)) { best = cost; per_wg = c; }
+    }
+    return per_wg;
 }
 
 }  // namespace mkq

@@ -708,7 +708,7 @@ static int attention_run(const void *qkv, int64_t batch, int64_t seq, int64_t hi
     if (!aligned16(qkv) || (ctx && !aligned16(ctx)) || (q_out && !aligned16(q_out))) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     const uint16_t *in = (const uint16_t *)qkv;
-    const AttentionRoute route = attention_route(seq, hidden, heads, q_pitch);
+    const AttentionRoute route = attention_route(batch, seq, hidden, heads, q_pitch);
     if (route == ATTENTION_HELD) {
         const AttentionParams p = {in, cu, (int)batch, (int)seq, (int)hidden, (int)heads, (int)dk, (int)q_blocks,
                                    (uint16_t *)ctx, q_out, s_next, q_bits, (int)q_pitch};

@@ -146,6 +146,17 @@ def test_attention_at_the_edges_of_its_key_groups(mkq, S, dk, scores):
     assert np.all(np.abs(got - want) <= (2.0 ** -11 + 2.0 ** -14) * mass + small + 2.0 ** -11 * np.abs(want) + 2.0 ** -24)
 
 
+@pytest.mark.parametrize("batch", [2 ** 20 - 1, 2 ** 20])
+def test_attention_of_a_million_one_token_sequences(mkq, batch):
+    """As many heads as workgroups of 512 threads can be launched for, and more: the context of one token is its v."""
+    import torch
+    heads, H = 8, 64
+    g = torch.Generator(device="cuda").manual_seed(batch)
+    qkv = torch.randn((batch, 3 * H), generator=g, device="cuda").half()
+    ctx, _ = mkq.mkq_attention(qkv, batch, 1, H, heads)
+    assert torch.equal(ctx, qkv[:, 2 * H:])
+
+
 def test_attention_with_rows_beyond_32_bit_offsets(mkq):
     """One sequence whose rows of qkv reach over 4 GiB: the first and the last heads against the softmax in binary64."""
     import torch

@@ -10,9 +10,13 @@ ONE_BLOCK, HELD, BLOCKS = range(3)
 SRC = """
 #include "launch_rules.h"
 using namespace mkq;
-extern "C" int route(int64_t seq, int64_t hidden, int64_t heads, int64_t q_pitch)
+extern "C" int route(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t q_pitch)
 {
-    return attention_route(seq, hidden, heads, q_pitch);
+    return attention_route(batch, seq, hidden, heads, q_pitch);
+}
+extern "C" int held_blocks(int64_t sequence_heads, int q_blocks, int64_t resident)
+{
+    return attention_held_blocks(sequence_heads, q_blocks, resident);
 }
 """
 
@@ -25,19 +29,20 @@ def rules(tmp_path_factory):
                     "-I", os.path.join(ROOT, "paper_2203_13483_amd", "csrc"), "-o", str(d / "rules.so"), str(d / "rules.cpp")],
                    check=True)
     lib = C.CDLL(str(d / "rules.so"))
-    lib.route.argtypes = [C.c_int64] * 4
+    lib.route.argtypes = [C.c_int64] * 5
+    lib.held_blocks.argtypes = [C.c_int64, C.c_int, C.c_int64]
     return lib
 
 
 def test_attention_of_ordinary_sizes(rules):
-    assert rules.route(128, 768, 12, 768) == ONE_BLOCK
-    assert rules.route(128, 768, 12, 896) == HELD
-    assert rules.route(129, 768, 12, 768) == HELD
-    assert rules.route(512, 1024, 16, 1024) == HELD
-    assert rules.route(513, 1024, 16, 1024) == BLOCKS
-    assert rules.route(128, 312, 12, 384) == HELD   # heads of 26
-    assert rules.route(128, 320, 8, 320) == HELD    # of 40
-    assert rules.route(128, 336, 8, 336) == BLOCKS  # of 42
+    assert rules.route(4, 128, 768, 12, 768) == ONE_BLOCK
+    assert rules.route(4, 128, 768, 12, 896) == HELD
+    assert rules.route(4, 129, 768, 12, 768) == HELD
+    assert rules.route(4, 512, 1024, 16, 1024) == HELD
+    assert rules.route(4, 513, 1024, 16, 1024) == BLOCKS
+    assert rules.route(4, 128, 312, 12, 384) == HELD   # heads of 26
+    assert rules.route(4, 128, 320, 8, 320) == HELD    # of 40
+    assert rules.route(4, 128, 336, 8, 336) == BLOCKS  # of 42
 
 
 def test_rows_beyond_32_bit_offsets_keep_the_kernel_with_64_bit_ones(rules):
@@ -46,7 +51,25 @@ def test_rows_beyond_32_bit_offsets_keep_the_kernel_with_64_bit_ones(rules):
         for seq in (129, 384, 511, 512):
             most = 2 ** 32 // (seq * 6)                  # hidden sizes up to here fit
             heads = most // dk
-            assert rules.route(seq, heads * dk, heads, heads * dk) == HELD
-            assert rules.route(seq, (heads + 1) * dk, heads + 1, (heads + 1) * dk) == BLOCKS
-    assert rules.route(512, 1400896, 21889, 1400896) == BLOCKS
-    assert rules.route(128, 64 * 10 ** 6, 10 ** 6, 64 * 10 ** 6) == ONE_BLOCK
+            assert rules.route(4, seq, heads * dk, heads, heads * dk) == HELD
+            assert rules.route(4, seq, (heads + 1) * dk, heads + 1, (heads + 1) * dk) == BLOCKS
+    assert rules.route(1, 512, 1400896, 21889, 1400896) == BLOCKS
+    assert rules.route(4, 128, 64 * 10 ** 6, 10 ** 6, 64 * 10 ** 6) == ONE_BLOCK
+
+
+def test_launches_stay_within_the_work_items_of_a_dimension(rules):
+    """Fewer than 2^32: 8388607 workgroups of 512 threads, of 256 twice as many and one."""
+    limit = (2 ** 32 - 1) // 512
+    for heads, dk in ((8, 8), (12, 26), (1, 48)):
+        H = heads * dk
+        assert rules.route(limit // heads, 1, H, heads, H) == HELD
+        assert rules.route(limit // heads + 1, 1, H, heads, H) == BLOCKS
+        assert rules.route(limit // heads, 512, H, heads, H) == HELD
+    for sequence_heads in (1, 12, 255, 256, 257, 1000, 65536, limit // 4, limit // 4 + 1, limit // 2 + 1, limit):
+        for q_blocks in (1, 2, 3, 4):
+            for resident in (256, 512, 1024):
+                c = rules.held_blocks(sequence_heads, q_blocks, resident)
+                assert 1 <= c <= q_blocks
+                assert sequence_heads * -(-q_blocks // c) <= limit
+    # as many workgroups as the device holds at a time, where blocks can be spread
+    assert [rules.held_blocks(n, 4, 256) for n in (1, 64, 65, 128, 256, 10 ** 6)] == [1, 1, 2, 2, 4, 4]
