@@ -47,4 +47,15 @@ constexpr int attention_held_blocks(int64_t sequence_heads, int q_blocks, int64_
     return per_wg;
 }
 
+// LayerNorm with one row per half wave (the kernels have 256 threads: eight rows), not per wave (four).  Up to D = 1024: where
+// half waves leave fewer lanes idle (chunks of 8 values: up to 32, or 65 to 96, of which whole waves would use half
+// and three quarters) and there are rows enough to fill the chip with them; a tie goes to whole waves, which have half the
+// work per lane.  us in a graph, half -> whole waves: 2299 x 1024 4.31 -> 3.82, with codes 5.15 -> 4.52, 16384 x 1024 12.7 -> 11.9,
+// with codes 14.8 -> 13.8, 2048 x 312 2.75 -> 2.56, 4099 x 512 3.46 -> 3.42; but 8192 x 768 5.93 -> 6.52, with codes 7.28 -> 8.09.
+// And for more rows than can be launched four to a workgroup.
+constexpr bool layernorm_half_waves(int64_t M, int64_t D)
+{
+    return D <= 1024 && M >= 2048 && (D <= 256 || (D > 512 && D <= 768) || (M + 3) / 4 > MAX_WORK_ITEMS / 256);
+}
+
 }  // namespace mkq

@@ -3,6 +3,7 @@
 // result for the next W4A4 linear, and the host-side sequencing of one post-LN
 // BERT layer in the int4 and in the binary16 baseline flavour.
 #include "attention.h"
+#include "launch_rules.h"
 
 #include <type_traits>
 
@@ -105,7 +106,7 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restri
 }
 
 // The same with one row per half wave (32 lanes, chunks lane, lane + 32, ...: D = 256 and 768 divide evenly), so a lane has up
-// to three 16-byte loads in flight; gamma and beta are fetched before the reductions, not after.
+// to four 16-byte loads in flight; gamma and beta are fetched before the reductions, not after.
 // (Two or four rows per half wave, which share gamma and beta: 4096 x 768 4.1 -> 4.6 and 6.3 us, 65536 x 768 29.8 -> 30.5 and 34.4.)
 template <int MAXC>
 __global__ __launch_bounds__(256) void layernorm_half_kernel(const uint16_t *__restrict__ x, int M, int D,
@@ -651,17 +652,15 @@ static int layernorm_run(const void *x, int64_t M, int64_t D, const float *gamma
 #define MKQ_LN(C)                                                                                       \
     layernorm_kernel<C><<<grid, 256, 0, st>>>((const uint16_t *)x, (int)M, (int)D, gamma, beta, eps, \
                                               (uint16_t *)y, s_next, (uint32_t *)q_out, q_bits, q_chunks)
-    // Half waves where they leave fewer lanes idle (chunks of 8 values: up to 32, or 65 to 96, of which whole waves would use half
-    // and three quarters) and there are rows enough to fill the chip with them; a tie goes to whole waves, which have half the
-    // work per lane.  us in a graph, half -> whole waves: 2299 x 1024 4.31 -> 3.82, with codes 5.15 -> 4.52, 16384 x 1024 12.7 -> 11.9, with
-    // codes 14.8 -> 13.8, 2048 x 312 2.75 -> 2.56, 4099 x 512 3.46 -> 3.42; but 8192 x 768 5.93 -> 6.52, with codes 7.28 -> 8.09.
-    if (M >= 2048 && (D <= 256 || (D > 512 && D <= 768))) {
+    if (layernorm_half_waves(M, D)) {
         const unsigned grid8 = (unsigned)ceil_div(M, 8);
 #define MKQ_LNH(C)                                                                                             \
     layernorm_half_kernel<C><<<grid8, 256, 0, st>>>((const uint16_t *)x, (int)M, (int)D, gamma, beta, eps, \
                                                     (uint16_t *)y, s_next, (uint32_t *)q_out, q_bits, q_chunks)
         if (D <= 256) MKQ_LNH(1);
-        else MKQ_LNH(3);
+        else if (D <= 512) MKQ_LNH(2);
+        else if (D <= 768) MKQ_LNH(3);
+        else MKQ_LNH(4);
 #undef MKQ_LNH
     } else if (D <= 512) MKQ_LN(1);
     else if (D <= 1024) MKQ_LN(2);

@@ -60,6 +60,23 @@ def test_layernorm_counts_every_lane_once(mkq, M, D):
     assert bool(((y.double() - want).abs() <= (2.0 ** -11 + 4e-6) * want.abs() + 2.0 ** -24).all())
 
 
+def test_layernorm_of_more_rows_than_fit_a_launch_four_to_a_workgroup(mkq):
+    """2^26 rows: the codes of 4096 rows over and over are those of these rows alone."""
+    import torch
+    D, rows, M = 264, 4096, 2 ** 26
+    g = torch.Generator(device="cuda").manual_seed(D)
+    base = torch.randn((rows, D), generator=g, device="cuda").half()
+    x = torch.empty((M, D), dtype=torch.float16, device="cuda")
+    x.view(M // rows, rows, D).copy_(base)
+    few, q = (mkq.mkq_layernorm(t, None, None, 1e-5, s_next=0.3, want_y=False, want_q=True)[1] for t in (base, x))
+    q = q.view(M // rows, rows, D // 2)
+    for part in q.split(1024):
+        assert bool((part == q[0]).all())
+    # means and variances over half waves and over whole waves are sums in another order: a value at a rounding boundary may
+    # fall the other way, and codes are 0.3 wide where the sums differ by 1e-6
+    assert float((q[0] != few).float().mean()) < 1e-4
+
+
 @pytest.mark.parametrize("B,S,heads", [(2, 128, 12), (3, 64, 2), (1, 32, 1), (2, 96, 4)])
 def test_attention(mkq, B, S, heads):
     H = heads * 64

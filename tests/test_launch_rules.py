@@ -18,6 +18,7 @@ extern "C" int held_blocks(int64_t sequence_heads, int q_blocks, int64_t residen
 {
     return attention_held_blocks(sequence_heads, q_blocks, resident);
 }
+extern "C" bool half_waves(int64_t M, int64_t D) { return layernorm_half_waves(M, D); }
 """
 
 
@@ -31,6 +32,7 @@ def rules(tmp_path_factory):
     lib = C.CDLL(str(d / "rules.so"))
     lib.route.argtypes = [C.c_int64] * 5
     lib.held_blocks.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
     return lib
 
 
@@ -73,3 +75,14 @@ def test_launches_stay_within_the_work_items_of_a_dimension(rules):
                 assert sequence_heads * -(-q_blocks // c) <= limit
     # as many workgroups as the device holds at a time, where blocks can be spread
     assert [rules.held_blocks(n, 4, 256) for n in (1, 64, 65, 128, 256, 10 ** 6)] == [1, 1, 2, 2, 4, 4]
+
+
+def test_layernorm_of_more_rows_than_fit_a_launch_four_to_a_workgroup(rules):
+    most = 4 * ((2 ** 32 - 1) // 256)
+    for D in (264, 312, 512, 776, 1024):
+        assert not rules.half_waves(2048, D) and not rules.half_waves(most, D)
+        assert rules.half_waves(most + 1, D) and rules.half_waves(2 * most, D)
+    for D in (8, 256, 520, 768):
+        assert not rules.half_waves(2047, D)
+        assert rules.half_waves(2048, D) and rules.half_waves(most + 1, D)
+    assert not rules.half_waves(most + 1, 1032)  # no half-wave kernel of this size
