@@ -16,7 +16,7 @@ static int launch_f16_by_epilogue(const GemmI4Params &p, hipStream_t st)
         if (p.out_dtype == MKQ_F16) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, 16>(p, st);
         if (!p.residual && !gelu) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, 16>(p, st);
     }
-    return launch_gemm_i4_dma<Cfg, EpiGeneric, 16>(p, st);
+    return launch_gemm_i4_dma_generic<Cfg, 16>(p, st);
 }
 
 // ---------------------------------------------------------------------------------
@@ -48,6 +48,7 @@ struct SplitF16 {
     static_assert(LDS_BYTES <= 160 * 1024, "LDS is 160 KiB per CU");
 };
 
+template <bool TAIL>  // epi_gelu_tail
 __global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF16Params p)
 {
     using Cfg = SplitF16;
@@ -162,11 +163,11 @@ __global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF
                     for (int e = 0; e < nvalid; ++e) y[e] += half_bits_to_float(r[e]);
                 }
             }
-            if (p.act == MKQ_ACT_GELU) {
+            if (TAIL || p.act == MKQ_ACT_GELU) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) y[e] = gelu_erf(y[e]);
+                for (int e = 0; e < 8; ++e) y[e] = TAIL ? gelu_erf_tail(y[e]) : gelu_erf(y[e]);
             }
-            if (p.out_dtype == MKQ_F32) {
+            if (TAIL || p.out_dtype == MKQ_F32) {
                 float *dst = (float *)p.out + o;
                 if (vec_ok) {
                     *reinterpret_cast<float4 *>(dst) = make_float4(y[0], y[1], y[2], y[3]);
@@ -237,18 +238,23 @@ __global__ __launch_bounds__(SplitF16::THREADS) void gemm_f16_kernel(const GemmF
     wait_vmcnt<0>();
 }
 
-static int launch_split_f16(const GemmI4Params &p, hipStream_t st)
+template <bool TAIL>
+static int launch_split_f16_as(const GemmI4Params &p, hipStream_t st)
 {
     const int64_t tiles = ceil_div(p.M, SplitF16::TILE) * ceil_div(p.N, SplitF16::TILE);
     if (tiles > 0x7FFFFFFF) return MKQ_ERR_UNSUPPORTED;
     static PerDeviceOnce once;
     int64_t resident = 0;
-    const int rc = resident_workgroups(once, gemm_f16_kernel, SplitF16::THREADS, SplitF16::LDS_BYTES, 1 << 20, &resident);
+    const int rc = resident_workgroups(once, gemm_f16_kernel<TAIL>, SplitF16::THREADS, SplitF16::LDS_BYTES, 1 << 20, &resident);
     if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
     const GemmF16Params q = {p.A, p.W, p.M, p.N, p.K, p.bias, (const uint16_t *)p.residual, p.act, p.out, p.out_dtype};
-    gemm_f16_kernel<<<grid, SplitF16::THREADS, SplitF16::LDS_BYTES, st>>>(q);
+    gemm_f16_kernel<TAIL><<<grid, SplitF16::THREADS, SplitF16::LDS_BYTES, st>>>(q);
     return launch_status();
+}
+static int launch_split_f16(const GemmI4Params &p, hipStream_t st)
+{
+    return epi_gelu_tail(p.act, p.out_dtype) ? launch_split_f16_as<true>(p, st) : launch_split_f16_as<false>(p, st);
 }
 
 // K split between two wave groups applies, and there is at most one 64x64 tile per CU

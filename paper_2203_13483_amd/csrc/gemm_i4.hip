@@ -41,7 +41,7 @@ int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int run_gemm_i8_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int gemm_i4_stream_slices(const GemmI4Params &p, const SplitKScratch *scr, int forced_ks);
 
-template <class Cfg, bool FULL_STAGES>
+template <class Cfg, bool FULL_STAGES, class Epi>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_kernel(const GemmI4Params p)
 {
     constexpr int BM = Cfg::BM, BN = Cfg::BN, RB = Cfg::RB, CH = Cfg::CH;
@@ -179,7 +179,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_kernel(const GemmI4Param
     auto epilogue = [&](int tile) {
         int tile_m, tile_n;
         tile_coords(tile, tiles_m, tiles_n, TILE_GROUP, tile_m, tile_n);
-        gemm_i4_epilogue<Cfg, EpiGeneric>(p, acc, tile_m * BM, tile_n * BN, wm, wn, fr, fh);
+        gemm_i4_epilogue<Cfg, Epi>(p, acc, tile_m * BM, tile_n * BN, wm, wn, fr, fh);
     };  // epilogue
 
     // --- main loop: LDS double buffer, registers hold the stage after next --------
@@ -230,7 +230,7 @@ struct SkinnyCfg {
 };
 
 // BITS = 8: the operands are int8 codes (the 8-bit linear): a 16-byte piece is one MFMA operand as it is.
-template <int TB, int UG, int BITS = 4>
+template <int TB, int UG, int BITS, class Epi>
 __global__ __launch_bounds__(SkinnyCfg::THREADS) void gemm_i4_skinny_kernel(const GemmI4Params p)
 {
     __shared__ __attribute__((aligned(16))) int red[2][SkinnyCfg::WAVES][4][64][4];  // 64 KiB
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(SkinnyCfg::THREADS) void gemm_i4_skinny_kernel(cons
                     sum[0][0][4 * q] += t.x; sum[0][0][4 * q + 1] += t.y;
                     sum[0][0][4 * q + 2] += t.z; sum[0][0][4 * q + 3] += t.w;
                 }
-            gemm_i4_epilogue<SkinnyCfg, EpiGeneric>(p, sum, (2 * pass + wave) * 32, n0, 0, 0, fr, fh);
+            gemm_i4_epilogue<SkinnyCfg, Epi>(p, sum, (2 * pass + wave) * 32, n0, 0, 0, fr, fh);
         }
     }
 }
@@ -360,7 +360,9 @@ template <int TB, int UG, int BITS = 4>
 static int launch_skinny(const GemmI4Params &p, hipStream_t st)
 {
     if (p.setup_only) return MKQ_OK;
-    gemm_i4_skinny_kernel<TB, UG, BITS><<<(unsigned)ceil_div(p.N, 32), SkinnyCfg::THREADS, 0, st>>>(p);
+    const unsigned grid = (unsigned)ceil_div(p.N, 32);
+    if (epi_gelu_tail(p.act, p.out_dtype)) gemm_i4_skinny_kernel<TB, UG, BITS, EpiGeluTail><<<grid, SkinnyCfg::THREADS, 0, st>>>(p);
+    else gemm_i4_skinny_kernel<TB, UG, BITS, EpiGeneric><<<grid, SkinnyCfg::THREADS, 0, st>>>(p);
     return launch_status();
 }
 
@@ -381,16 +383,16 @@ static int run_gemm_i4_skinny(const GemmI4Params &p, hipStream_t st)
     return launch_skinny<4, 1>(p, st);
 }
 
-template <class Cfg, bool FULL>
+template <class Cfg, bool FULL, class Epi>
 static int launch_one(const GemmI4Params &p, int64_t tiles, hipStream_t st)
 {
     const size_t lds = 2 * (size_t)Cfg::STAGE_BYTES;
     static PerDeviceOnce once;  // per instantiation
     int64_t resident = 0;
-    const int rc = resident_workgroups(once, gemm_i4_kernel<Cfg, FULL>, Cfg::THREADS, lds, 2, &resident);
+    const int rc = resident_workgroups(once, gemm_i4_kernel<Cfg, FULL, Epi>, Cfg::THREADS, lds, 2, &resident);
     if (rc != MKQ_OK || p.setup_only) return rc;
     const unsigned grid = (unsigned)(tiles < resident ? tiles : resident);
-    gemm_i4_kernel<Cfg, FULL><<<grid, Cfg::THREADS, lds, st>>>(p);
+    gemm_i4_kernel<Cfg, FULL, Epi><<<grid, Cfg::THREADS, lds, st>>>(p);
     return launch_status();
 }
 
@@ -400,7 +402,9 @@ static int launch_gemm_i4(const GemmI4Params &p, hipStream_t st)
     const int64_t tiles = ceil_div(p.M, Cfg::BM) * ceil_div(p.N, Cfg::BN);
     if (tiles > 0x7FFFFFFF) return MKQ_ERR_UNSUPPORTED;
     const bool full = ((p.K / 2) % Cfg::RB) == 0;
-    return full ? launch_one<Cfg, true>(p, tiles, st) : launch_one<Cfg, false>(p, tiles, st);
+    if (epi_gelu_tail(p.act, p.out_dtype))
+        return full ? launch_one<Cfg, true, EpiGeluTail>(p, tiles, st) : launch_one<Cfg, false, EpiGeluTail>(p, tiles, st);
+    return full ? launch_one<Cfg, true, EpiGeneric>(p, tiles, st) : launch_one<Cfg, false, EpiGeneric>(p, tiles, st);
 }
 
 template <class Cfg>
@@ -413,7 +417,7 @@ static int launch_dma_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st
     case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>>(p, st);
     case EPI_I4_GELU: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, true>>(p, st);
     case EPI_I4: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, false>>(p, st);
-    default: return launch_gemm_i4_dma<Cfg, EpiGeneric>(p, st);
+    default: return launch_gemm_i4_dma_generic<Cfg>(p, st);
     }
 }
 
@@ -426,7 +430,7 @@ static int launch_xsplit_by_epilogue(const GemmI4Params &p, int epi, hipStream_t
     case EPI_BF16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_BF16, false, false>, 4, KS, true>(p, st);
     case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 4, KS, true>(p, st);
     case EPI_I4_GELU: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, true>, 4, KS, true>(p, st);
-    default: return launch_gemm_i4_dma<Cfg, EpiGeneric, 4, KS, true>(p, st);
+    default: return launch_gemm_i4_dma_generic<Cfg, 4, KS, true>(p, st);
     }
 }
 
@@ -441,7 +445,7 @@ static int launch_ksplit_by_epilogue(const GemmI4Params &p, int epi, hipStream_t
     case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 4, KS>(p, st);
     case EPI_I4_GELU: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, true>, 4, KS>(p, st);
     case EPI_I4: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, false>, 4, KS>(p, st);
-    default: return launch_gemm_i4_dma<Cfg, EpiGeneric, 4, KS>(p, st);
+    default: return launch_gemm_i4_dma_generic<Cfg, 4, KS>(p, st);
     }
 }
 
@@ -632,7 +636,7 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
     case EPI_F32: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, 8>(p, st);
     case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, 8>(p, st);
     case EPI_I8_GELU: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I8, false, true>, 8>(p, st);
-    default: return launch_gemm_i4_dma<Cfg, EpiGeneric, 8>(p, st);
+    default: return launch_gemm_i4_dma_generic<Cfg, 8>(p, st);
     }
 }
 
@@ -964,8 +968,8 @@ static int launch_e3m2_by_epilogue(const GemmI4Params &p, hipStream_t st)
     case EPI_F16: return launch_gemm_e3m2<Cfg, EpiFixed<MKQ_F16, false, false>>(p, st);
     case EPI_BF16: return launch_gemm_e3m2<Cfg, EpiFixed<MKQ_BF16, false, false>>(p, st);
     case EPI_F32: return launch_gemm_e3m2<Cfg, EpiFixed<MKQ_F32, false, false>>(p, st);
-    default: return launch_gemm_e3m2<Cfg, EpiGeneric>(p, st);
     }
+    return epi_gelu_tail(p.act, p.out_dtype) ? launch_gemm_e3m2<Cfg, EpiGeluTail>(p, st) : launch_gemm_e3m2<Cfg, EpiGeneric>(p, st);
 }
 
 int run_gemm_e3m2(const GemmI4Params &p, hipStream_t st, int forced_cfg)
@@ -1147,34 +1151,35 @@ extern "C" int mkq_init(void)
     const SplitKScratch any_scratch = {reinterpret_cast<unsigned *>(16), reinterpret_cast<int32_t *>(16), (size_t)1 << 40};
     for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 60, 61, 62}) {
         // one pass per epilogue class: the parameter block is made to classify as each in turn
-        for (int e = 0; e < 7 && rc == MKQ_OK; ++e) {
+        for (int e = 0; e < 8 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
-            q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : e == 2 ? MKQ_F32 : e == 3 ? MKQ_F16 : MKQ_I4;
+            q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : e == 2 ? MKQ_F32 : e == 3 ? MKQ_F16 : e == 7 ? MKQ_F32 : MKQ_I4;
             if (e == 3) { q.residual = &q; q.residual_dtype = MKQ_F16; }
-            if (e == 4) q.act = MKQ_ACT_GELU;
+            if (e == 4 || e == 7) q.act = MKQ_ACT_GELU;
             if (e == 6) q.acc_out = reinterpret_cast<int32_t *>(&q);
             rc = run_gemm_i4(q, nullptr, cfg, cfg >= 60 ? &any_scratch : nullptr, 0);
-            if (cfg < 10) break;  // the register-staged kernel has one epilogue
+            if (cfg < 10 && e == 0) e = 6;  // the register-staged kernel has two epilogues: one for all, and the last
         }
     }
     for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47}) {  // the tile shapes of the 8-bit path
-        for (int e = 0; e < 6 && rc == MKQ_OK; ++e) {
+        for (int e = 0; e < 7 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
             q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : e == 2 ? MKQ_F32 : e == 3 ? MKQ_F16 : e == 4 ? MKQ_I8 : MKQ_F32;
             if (e == 3) { q.residual = &q; q.residual_dtype = MKQ_F16; }
-            if (e == 4) q.act = MKQ_ACT_GELU;
+            if (e == 4 || e == 6) q.act = MKQ_ACT_GELU;
             if (e == 5) q.acc_out = reinterpret_cast<int32_t *>(&q);
             rc = run_gemm_i8(q, nullptr, cfg);
         }
     }
     for (int cfg : {41, 42}) {
-        for (int e = 0; e < 4 && rc == MKQ_OK; ++e) {
+        for (int e = 0; e < 5 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q;
             q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : MKQ_F32;
             if (e == 3) q.acc_out = reinterpret_cast<int32_t *>(&q);
+            if (e == 4) q.act = MKQ_ACT_GELU;
             rc = run_gemm_e3m2(q, nullptr, cfg);
         }
     }

@@ -112,6 +112,16 @@ struct EpiGeneric {
     static constexpr int out = MKQ_F32;
     static constexpr bool res16 = false, gelu = false;
 };
+// The same for GELU with binary32 or bfloat16 outputs (epi_gelu_tail), which keep its tail.  Kernels of their own: the choice
+// inside EpiGeneric's, by value, by unit or as a second copy of the whole epilogue, cost every output 3 to 20 %.  With less to
+// choose at run time they are the faster ones besides, but for binary32 of few tiles; us in a graph, the 4-bit linear with
+// gelu_erf in EpiGeneric -> this, binary32 / bfloat16: 8192 x 1024 x 4096 62 -> 56 / 68 -> 55, 4096 x 768 x 3072
+// 21.9 -> 22.3 / 20.0 -> 19.7, 440 tokens 7.07 -> 7.23 / 6.69 -> 6.50, 16 tokens 4.27 -> 4.28 / 4.51 -> 4.27.
+struct EpiGeluTail : EpiGeneric {};
+inline bool epi_gelu_tail(int act, int out_dtype)
+{
+    return act == MKQ_ACT_GELU && (out_dtype == MKQ_F32 || out_dtype == MKQ_BF16);
+}
 
 // Epilogue of one finished tile (m0, n0 = its first token / channel; wm, wn = the
 // wave's position in the workgroup; fr = lane % 32, fh = lane / 32).
@@ -124,10 +134,11 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, AccV (&a
                                                  int m0, int n0, int wm, int wn, int fr, int fh)
 {
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
-    const int out_dtype = Epi::generic ? p.out_dtype : Epi::out;
+    constexpr bool TAIL = std::is_same<Epi, EpiGeluTail>::value;
+    const int out_dtype = TAIL ? (p.out_dtype == MKQ_F32 ? MKQ_F32 : MKQ_BF16) : Epi::generic ? p.out_dtype : Epi::out;
     const bool has_res = Epi::generic ? (p.residual != nullptr) : Epi::res16;
     const bool res_f32 = Epi::generic ? (p.residual_dtype == MKQ_F32) : false;
-    const bool gelu = Epi::generic ? (p.act == MKQ_ACT_GELU) : Epi::gelu;
+    const bool gelu = TAIL ? true : Epi::generic ? (p.act == MKQ_ACT_GELU) : Epi::gelu;
     const bool vec_ok = Epi::generic ? ((p.N % 8) == 0) : true;
     int32_t *const acc_out = Epi::generic && SCALED ? p.acc_out : nullptr;
     uint8_t *const q_extra = Epi::generic ? p.q_out : nullptr;
@@ -227,7 +238,7 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, AccV (&a
                 }
                 if (gelu) {
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) y[e] = gelu_erf(y[e]);
+                    for (int e = 0; e < 8; ++e) y[e] = TAIL ? gelu_erf_tail(y[e]) : gelu_erf(y[e]);
                 }
 
                 if (out_dtype == MKQ_F32) {
@@ -429,6 +440,7 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, Acc
                     }
                 }
                 if (Epi::gelu) {
+                    static_assert(!Epi::gelu || (Epi::out != MKQ_F32 && Epi::out != MKQ_BF16), "gelu_erf_tail");
 #pragma unroll
                     for (int e = 0; e < 8; ++e) y[e] = gelu_erf(y[e]);
                 }

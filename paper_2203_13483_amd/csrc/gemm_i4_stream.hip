@@ -80,7 +80,7 @@ __device__ __forceinline__ bool splitk_reduce(v16i (&acc)[Cfg::TB][1], const Spl
     return true;
 }
 
-template <class Cfg>
+template <class Cfg, class Epi>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_stream_kernel(const GemmI4Params p, const SplitKArgs sk)
 {
     constexpr int TB = Cfg::TB, S = Cfg::S, LPW = Cfg::LPW;
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_stream_kernel(const Gemm
     if (sk.ks > 1) {
         if (!splitk_reduce<Cfg>(acc, sk, tile, slice, wave, lane, tid, &last_ticket)) return;
     }
-    gemm_i4_epilogue<Cfg, EpiGeneric>(p, acc, 0, n0 + 32 * wave, 0, 0, fr, fh);
+    gemm_i4_epilogue<Cfg, Epi>(p, acc, 0, n0 + 32 * wave, 0, 0, fr, fh);
 }
 
 // The same linear on weights in the streaming layout (mkq_repack_weights_int4_stream): the 32 channels of a
@@ -206,7 +206,7 @@ struct WStreamCfg {
     static_assert(P >= 2 && (P - 1) * LPW <= 63, "vmcnt immediate is 6 bits");
 };
 
-template <class Cfg>
+template <class Cfg, class Epi>
 __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_wstream_kernel(const GemmI4Params p, const SplitKArgs sk)
 {
     constexpr int TB = Cfg::TB, P = Cfg::P, LPW = Cfg::LPW;
@@ -307,16 +307,16 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_wstream_kernel(const Gem
     if (sk.ks > 1) {
         if (!splitk_reduce<Cfg>(acc, sk, tile, slice, wave, lane, tid, &last_ticket)) return;
     }
-    gemm_i4_epilogue<Cfg, EpiGeneric>(p, acc, 0, n0 + 32 * wave, 0, 0, fr, fh);
+    gemm_i4_epilogue<Cfg, Epi>(p, acc, 0, n0 + 32 * wave, 0, 0, fr, fh);
 }
 
-template <class Cfg>
-static int launch_stream(const GemmI4Params &p, const SplitKArgs &sk, hipStream_t st)
+template <class Cfg, class Epi>
+static int launch_stream_as(const GemmI4Params &p, const SplitKArgs &sk, hipStream_t st)
 {
     static PerDeviceOnce once;
     const int ok = once.get([&]() -> int {
         if (Cfg::LDS_BYTES > 65536 &&
-            hipFuncSetAttribute((const void *)gemm_i4_stream_kernel<Cfg>, hipFuncAttributeMaxDynamicSharedMemorySize,
+            hipFuncSetAttribute((const void *)gemm_i4_stream_kernel<Cfg, Epi>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 Cfg::LDS_BYTES) != hipSuccess)
             return -1;
         return 1;
@@ -324,8 +324,14 @@ static int launch_stream(const GemmI4Params &p, const SplitKArgs &sk, hipStream_
     if (ok < 0) return MKQ_ERR_HIP;
     if (p.setup_only) return MKQ_OK;
     const int64_t grid = ceil_div(p.N, Cfg::BN) * sk.ks;
-    gemm_i4_stream_kernel<Cfg><<<(unsigned)grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(p, sk);
+    gemm_i4_stream_kernel<Cfg, Epi><<<(unsigned)grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(p, sk);
     return launch_status();
+}
+
+template <class Cfg>
+static int launch_stream(const GemmI4Params &p, const SplitKArgs &sk, hipStream_t st)
+{
+    return epi_gelu_tail(p.act, p.out_dtype) ? launch_stream_as<Cfg, EpiGeluTail>(p, sk, st) : launch_stream_as<Cfg, EpiGeneric>(p, sk, st);
 }
 
 bool gemm_i4_stream_ok(const GemmI4Params &p) { return p.M <= 128 && (p.K % 256) == 0; }
@@ -368,7 +374,8 @@ static int launch_wstream(const GemmI4Params &p, const SplitKArgs &sk, hipStream
     static_assert(Cfg::LDS_BYTES <= 65536, "no dynamic LDS limit to raise");
     if (p.setup_only) return MKQ_OK;
     const int64_t grid = ceil_div(p.N, Cfg::BN) * sk.ks;
-    gemm_i4_wstream_kernel<Cfg><<<(unsigned)grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(p, sk);
+    if (epi_gelu_tail(p.act, p.out_dtype)) gemm_i4_wstream_kernel<Cfg, EpiGeluTail><<<(unsigned)grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(p, sk);
+    else gemm_i4_wstream_kernel<Cfg, EpiGeneric><<<(unsigned)grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(p, sk);
     return launch_status();
 }
 
@@ -416,9 +423,15 @@ __global__ void repack_stream_kernel(const uint4 *__restrict__ src, uint4 *__res
 int setup_gemm_i4_stream(const GemmI4Params &p, hipStream_t st)
 {
     SplitKArgs sk = {1, nullptr, nullptr};
-    int rc = launch_stream<StreamCfg<1, 3>>(p, sk, st);
-    if (rc == MKQ_OK) rc = launch_stream<StreamCfg<2, 3>>(p, sk, st);
-    if (rc == MKQ_OK) rc = launch_stream<StreamCfg<4, 3>>(p, sk, st);
+    GemmI4Params q = p;
+    int rc = MKQ_OK;
+    for (int act : {MKQ_ACT_NONE, MKQ_ACT_GELU}) {  // (GELU of binary32 has kernels of its own)
+        q.act = act;
+        q.out_dtype = MKQ_F32;
+        if (rc == MKQ_OK) rc = launch_stream<StreamCfg<1, 3>>(q, sk, st);
+        if (rc == MKQ_OK) rc = launch_stream<StreamCfg<2, 3>>(q, sk, st);
+        if (rc == MKQ_OK) rc = launch_stream<StreamCfg<4, 3>>(q, sk, st);
+    }
     return rc;
 }
 

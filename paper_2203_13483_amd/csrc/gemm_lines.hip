@@ -29,7 +29,7 @@ static int launch_lines(const GemmI4Params &p, int epi, hipStream_t st)
         if constexpr (BITS == 8) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I8, false, true>, BITS, KS>(p, st);
         break;
     }
-    return launch_gemm_i4_dma<Cfg, EpiGeneric, BITS, KS>(p, st);
+    return launch_gemm_i4_dma_generic<Cfg, BITS, KS>(p, st);
 }
 
 int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st)

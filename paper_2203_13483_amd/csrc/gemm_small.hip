@@ -25,7 +25,7 @@ static inline size_t small_lds(int64_t K)
 }
 
 // AHEAD: groups of eight values that a thread fetches before it uses the first.
-template <typename T, int AHEAD>
+template <typename T, int AHEAD, class Epi>
 __global__ __launch_bounds__(SmallCfg::THREADS) void gemm_i4_small_kernel(const GemmI4Params p, const T *__restrict__ x,
                                                                            uint8_t *__restrict__ codes_out)
 {
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(SmallCfg::THREADS) void gemm_i4_small_kernel(const 
                 sum[0][0][4 * q] += t.x; sum[0][0][4 * q + 1] += t.y;
                 sum[0][0][4 * q + 2] += t.z; sum[0][0][4 * q + 3] += t.w;
             }
-        gemm_i4_epilogue<SmallCfg, EpiGeneric>(p, sum, m0, n0, 0, 0, fr, fh);
+        gemm_i4_epilogue<SmallCfg, Epi>(p, sum, m0, n0, 0, 0, fr, fh);
     }
 }
 
@@ -147,11 +147,14 @@ int run_gemm_i4_small(const GemmI4Params &p, const void *a, int a_dtype, hipStre
     const size_t lds = small_lds(p.K);
     uint8_t *const codes = const_cast<uint8_t *>(p.A);
     // K = 768 is six groups per thread, K = 1024 eight: everything in flight at once, nothing fetched twice
-#define MKQ_SMALL(T, AHEAD) gemm_i4_small_kernel<T, AHEAD><<<grid, SmallCfg::THREADS, lds, st>>>(p, (const T *)a, codes)
+#define MKQ_SMALL(T, AHEAD)                                                                                                   \
+    if (tail) gemm_i4_small_kernel<T, AHEAD, EpiGeluTail><<<grid, SmallCfg::THREADS, lds, st>>>(p, (const T *)a, codes);     \
+    else gemm_i4_small_kernel<T, AHEAD, EpiGeneric><<<grid, SmallCfg::THREADS, lds, st>>>(p, (const T *)a, codes)
+    const bool tail = epi_gelu_tail(p.act, p.out_dtype);
     if (a_dtype == MKQ_F32) {
-        if (p.K <= 768) MKQ_SMALL(float, 6); else MKQ_SMALL(float, 8);
+        if (p.K <= 768) { MKQ_SMALL(float, 6); } else { MKQ_SMALL(float, 8); }
     } else {
-        if (p.K <= 768) MKQ_SMALL(__half, 6); else MKQ_SMALL(__half, 8);
+        if (p.K <= 768) { MKQ_SMALL(__half, 6); } else { MKQ_SMALL(__half, 8); }
     }
 #undef MKQ_SMALL
     return launch_status();

@@ -622,4 +622,12 @@ static int launch_gemm_i4_dma(const GemmI4Params &p, hipStream_t st)
     return launch_status();
 }
 
+// With the epilogue that takes every option
+template <class Cfg, int BITS = 4, int KSPLIT = 1, bool XS = false>
+static int launch_gemm_i4_dma_generic(const GemmI4Params &p, hipStream_t st)
+{
+    if (epi_gelu_tail(p.act, p.out_dtype)) return launch_gemm_i4_dma<Cfg, EpiGeluTail, BITS, KSPLIT, XS>(p, st);
+    return launch_gemm_i4_dma<Cfg, EpiGeneric, BITS, KSPLIT, XS>(p, st);
+}
+
 }  // namespace mkq

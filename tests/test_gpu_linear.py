@@ -157,6 +157,39 @@ def test_gelu_over_its_range(mkq, out):
     assert np.all(np.abs(got - want) <= 8e-8 + ulp * np.abs(want) + (0 if out == 0 else 2.0 ** -25))
 
 
+@pytest.mark.parametrize("linear", ["int4", "int8", "fp16"])
+@pytest.mark.parametrize("N", [4096, 203])
+def test_gelu_keeps_its_tail_in_binary32_and_bfloat16(mkq, linear, N):
+    """Results of 1e-4 down to 1e-37, x = -4 ... -12.9 (zero operands: GELU meets the biases as they are): no further from
+    binary64, relatively, than formula 7.1.26 of Abramowitz & Stegun (0.05 % at -4, 0.5 % at -6.5, 3.7 % at -12.9), but for the
+    binary32 evaluation of the exponent (up to 125, a few 2^-24 of it) and the output's own rounding."""
+    import torch
+    x = np.linspace(-12.9, -4.0, N).astype(np.float32)
+    b, sw = torch.from_numpy(x).cuda(), torch.ones(N, device="cuda")
+    xd = torch.from_numpy(x).double()
+    want = (0.5 * xd * torch.special.erfc(-xd / 2 ** 0.5)).numpy()  # (ndtr is 0 below -8.3)
+    t = 1.0 / (1.0 + 0.3275911 * -xd / 2 ** 0.5)
+    u = 0.5 * torch.exp(-xd * xd / 2) * t * (0.254829592 + t * (-0.284496736 + t * (1.421413741 + t * (-1.453152027 + t * 1.061405429))))
+    limit = np.abs((xd * u).numpy() / want - 1.0) + 8 * 125 * 2.0 ** -24
+    for dt, half_ulp in ((mkq.MKQ_F32, 2.0 ** -24), (mkq.MKQ_BF16, 2.0 ** -8)):  # (24 and 8 significant bits)
+        for M in (3, 200):
+            if linear == "int4":
+                y = mkq.mkq_linear_int4(torch.zeros((M, 64), dtype=torch.uint8, device="cuda"), 0.1,
+                                        torch.zeros((N, 64), dtype=torch.uint8, device="cuda"), sw, b, N, 128, dt,
+                                        act=mkq.MKQ_ACT_GELU)["out"]
+            elif linear == "int8":
+                y = mkq.mkq_linear_int8(torch.zeros((M, 128), dtype=torch.int8, device="cuda"), 0.1,
+                                        torch.zeros((N, 128), dtype=torch.int8, device="cuda"), sw, b, dt,
+                                        act=mkq.MKQ_ACT_GELU)["out"]
+            elif dt == mkq.MKQ_F32:
+                y = mkq.mkq_linear_fp16(torch.zeros((M, 128), dtype=torch.float16, device="cuda"),
+                                        torch.zeros((N, 128), dtype=torch.float16, device="cuda"), b, dt, mkq.MKQ_ACT_GELU)
+            else:
+                continue
+            err = np.abs(to_np(y).astype(np.float64) - want) / np.abs(want)
+            assert np.all(err <= limit + 1.001 * half_ulp), (dt, M, (err / limit).max(), x[(err / limit).max(axis=0).argmax()])
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 3072, 768), (130, 202, 96)])
 def test_gelu_then_requant(mkq, M, N, K):
     A, Wc, s_w, s_x, bias = _codes_case(M, N, K, seed=9)
