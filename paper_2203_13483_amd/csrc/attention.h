@@ -2,7 +2,6 @@
 #pragma once
 
 #include "gemm_common.h"
-#include "launch_rules.h"
 
 #include <type_traits>
 

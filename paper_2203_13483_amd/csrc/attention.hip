@@ -33,7 +33,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 // DKP: head size rounded up to 32 or 64 (dimensions d_k .. DKP - 1 are staged as zeros and never stored).  VEC = 8: 16-byte
 // accesses (d_k % 8 == 0); VEC = 2: 4-byte ones.
 template <int DKP, int VEC, int NG>
-__global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(const AttentionParams p, int per_wg)
+__global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(const AttentionParams p, int per_wg, int first_half, const XcdRuns runs)
 {
     using Cfg = AttentionHeldCfg<DKP, NG>;
     constexpr int THREADS = Cfg::THREADS, KEYS = Cfg::KEYS, ROWB = DKP * 2, CH = DKP / 8, VROW = Cfg::VROW, DS = DKP / 32;
@@ -43,12 +43,36 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lr = lane & 15, lg = lane >> 4;
-    const int parts = (p.q_blocks + per_wg - 1) / per_wg;
-    const int block = xcd_index(blockIdx.x, gridDim.x), part = block % parts, bh = block / parts;
+    // uniform batches: an eighth of (sequence, head, part) to each XCD.  Padding-free ones: runs of heads, parts outermost (with the
+    // parts of a head side by side, all first parts of two meet on every other XCD).  us, 16 heads of 64, 16 sequences to 512, an eighth
+    // in one piece -> this with the longest shared: rising from 32 34.0 -> 25.5, random 33.5 -> 27.2, one of 512 and the others of
+    // 64 31.0 -> 18.9, all of 230 13.1 -> 13.9, all of 512 38.2 -> 38.0
+    int part, bh;
+    bool share = false;  // the longest sequences by two workgroups
+    if (p.cu_seqlens) {
+        const unsigned sequence_heads = (unsigned)p.batch * p.heads;
+        part = (int)(blockIdx.x / sequence_heads);
+        bh = xcd_run_index(blockIdx.x - part * sequence_heads, runs);
+        if (first_half) {
+            // of the first 64 sequences, at most half are longest: these are shared, and where they are at most an eighth, their
+            // second halves come before everything else (16 x 512 tokens, one sequence of 512 and the others of 64: second halves
+            // last 22.3 us, first 18.6; 16 random lengths to 512, six of them longest, 27.3 and 31.2)
+            const int n = p.batch < 64 ? p.batch : 64;
+            const int32_t *const at = p.cu_seqlens + (lane < n ? lane : 0);
+            const int many = __builtin_popcountll(__ballot(lane < n && at[1] - at[0] > (p.q_blocks - 1) * 128));
+            share = 2 * many <= n;
+            if (many && 8 * many <= n) part = 1 - part;
+        }
+    } else {
+        const int parts = (p.q_blocks + per_wg - 1) / per_wg, block = xcd_index(blockIdx.x, gridDim.x);
+        part = block % parts;
+        bh = block / parts;
+    }
     const int b = bh / p.heads, head = bh % p.heads;
     const int64_t row0 = p.cu_seqlens ? (int64_t)p.cu_seqlens[b] : (int64_t)b * p.seq;
     int seq = p.cu_seqlens ? (p.cu_seqlens[b + 1] - p.cu_seqlens[b]) : p.seq;
     seq = seq < KEYS ? seq : KEYS;  // (longer than the caller's bound on the lengths: not computed)
+    if (share && seq > (p.q_blocks - 1) * 128) per_wg = first_half;
     const int first = part * per_wg * 128;
     if (first >= seq) return;  // the whole workgroup: no barrier has been passed
     const int hidden = p.hidden, dk = p.dk, ld = 3 * hidden;
@@ -262,8 +286,9 @@ static int launch_held(const AttentionParams *p, hipStream_t st)
     if (rc != MKQ_OK || !p) return rc;
     const int64_t sequence_heads = (int64_t)p->batch * p->heads;
     const int per_wg = attention_held_blocks(sequence_heads, p->q_blocks, resident);
-    const unsigned grid = (unsigned)(sequence_heads * ceil_div(p->q_blocks, per_wg));
-    kernel<<<grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, per_wg);
+    const int first_half = p->cu_seqlens ? attention_held_first_half(sequence_heads, p->q_blocks, per_wg) : 0;
+    const unsigned grid = (unsigned)(sequence_heads * (first_half ? 2 : ceil_div(p->q_blocks, per_wg)));
+    kernel<<<grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, per_wg, first_half, attention_runs(sequence_heads, p->heads));
     return launch_status();
 }
 

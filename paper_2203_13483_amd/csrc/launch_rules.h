@@ -5,6 +5,42 @@
 
 namespace mkq {
 
+// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  A kernel that takes its share of the tokens
+// by xcd_index(blockIdx.x, gridDim.x) gives XCD x the x-th eighth of them, so it finds in its L2 what the kernel before,
+// with the same rule, wrote there.  What another XCD wrote has to come through memory first: 16 MiB just written are read
+// in 2 us by the XCDs that wrote them and in 9 by their neighbours.  (Which XCD a workgroup runs on decides only the time.)
+constexpr int XCDS = 8;
+constexpr int xcd_index(unsigned wg, unsigned total)
+{
+    const unsigned q = total / XCDS, r = total % XCDS, x = wg % XCDS;
+    return (int)(x * q + (x < r ? x : r) + wg / XCDS);
+}
+
+// Where the shares are not alike (sequences of different lengths), an eighth of them in one piece can be most of the work:
+// runs of neighbours go to one XCD after the other instead, and what is left of whole rounds one by one.
+struct XcdRuns {
+    unsigned length, whole;  // of a run; in whole rounds of eight runs
+};
+constexpr int xcd_run_index(unsigned wg, const XcdRuns &r)
+{
+    if (wg >= r.whole) return (int)wg;
+    const unsigned x = wg % XCDS, j = wg / XCDS, k = j / r.length;
+    return (int)((k * XCDS + x) * r.length + (j - k * r.length));
+}
+// Sequences times heads of a padding-free batch.  The heads of a sequence share lines of q, k, v and of the codes that are written,
+// so up to a sequence's heads make a run, as long as there are eight runs for every XCD.  us in a graph, 12 heads, an eighth in
+// one piece / one head at a time / these runs: 64 sequences, heads of 26, lengths rising from 8 to 128 9.9 / 9.7 / 8.9, all of 128
+// 10.4 / 14.9 / 10.5; 32 sequences, heads of 64, rising from 16 to 256 21.1 / 16.8 / 17.0, falling 21.3 / 15.9 / 15.7.
+// What it costs is near-equal lengths, where one piece is even and what the kernel before wrote is near: layers of the student
+// on 32 sequences of about 60 tokens 78.7 -> 79.8, of 440 tokens 39.8 -> 40.0.  (One piece where the eighths have about as many
+// tokens, decided from the offsets in the kernels, cost each launch 0.25 us and more.)
+constexpr XcdRuns attention_runs(int64_t sequence_heads, int64_t heads)
+{
+    int64_t length = sequence_heads / (8 * XCDS);
+    length = length < 1 ? 1 : length < heads ? length : heads;
+    return {(unsigned)length, (unsigned)(sequence_heads / (length * XCDS) * (length * XCDS))};
+}
+
 // Work-items of a launch in one dimension: a product of grid and workgroup size that HIP takes
 constexpr int64_t MAX_WORK_ITEMS = 0xFFFFFFFFLL;
 
@@ -45,6 +81,14 @@ constexpr int attention_held_blocks(int64_t sequence_heads, int q_blocks, int64_
         if (wgs <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS && (best < 0 || cost < best)) { best = cost; per_wg = c; }
     }
     return per_wg;
+}
+
+// Padding-free batches: where attention_held_blocks lets one workgroup take a whole sequence, the longest ones (as many blocks
+// as the bound on the lengths has) are shared by two if they are few, because the kernel would end with them.  Blocks of the first
+// of the two; 0: never shared.  Whether they are few, the kernel sees from the lengths.
+constexpr int attention_held_first_half(int64_t sequence_heads, int q_blocks, int per_wg)
+{
+    return q_blocks >= 2 && per_wg == q_blocks && 2 * sequence_heads <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS ? (q_blocks + 1) / 2 : 0;
 }
 
 // LayerNorm with one row per half wave (the kernels have 256 threads: eight rows), not per wave (four).  Up to D = 1024: where

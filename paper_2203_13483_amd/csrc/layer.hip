@@ -3,7 +3,6 @@
 // result for the next W4A4 linear, and the host-side sequencing of one post-LN
 // BERT layer in the int4 and in the binary16 baseline flavour.
 #include "attention.h"
-#include "launch_rules.h"
 
 #include <type_traits>
 
@@ -216,7 +215,12 @@ __global__ __launch_bounds__(256) void attention_kernel(const uint16_t *__restri
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 31, fh = lane >> 5;
-    const int bh = xcd_index(blockIdx.x, gridDim.x), b = bh / heads, head = bh % heads;
+    // (padding-free: one workgroup to an XCD after the other, since an eighth of the sequences can be most of the work.  64 sequences,
+    // 12 heads, us, an eighth in one piece -> this: lengths rising from 8 to 128 10.2 -> 9.7, equal lengths 8.7 -> 9.1; in the
+    // layers of near-equal lengths no difference.  Runs of heads as the other kernels have them: 9.3 and 8.9, and
+    // layers of 440 and 2298 tokens 1 % slower.)
+    const int bh = cu_seqlens ? (int)blockIdx.x : xcd_index(blockIdx.x, gridDim.x);
+    const int b = bh / heads, head = bh % heads;
     // padding-free batches: sequence b is rows cu_seqlens[b] .. cu_seqlens[b+1] - 1 (at most 32*KT of
     // them, any number); otherwise every sequence has seq_fixed rows
     const int64_t row0 = cu_seqlens ? (int64_t)cu_seqlens[b] : (int64_t)b * seq_fixed;
@@ -380,7 +384,7 @@ __global__ __launch_bounds__(256, 3) void attention_blocks_kernel(const uint16_t
                                                                int hidden, int heads, int dk, int q_blocks,
                                                                uint16_t *__restrict__ ctx, float s_next,
                                                                uint8_t *__restrict__ qout, int q_bits, int q_pitch,
-                                                               const int32_t *__restrict__ cu_seqlens)
+                                                               const int32_t *__restrict__ cu_seqlens, const XcdRuns runs)
 {
     constexpr int ROWB = DKP * 2;  // bytes of a staged q or k row
     constexpr int CH = DKP / 8;    // its 16-byte chunks
@@ -390,7 +394,19 @@ __global__ __launch_bounds__(256, 3) void attention_blocks_kernel(const uint16_t
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int fr = lane & 31, fh = lane >> 5;
-    const int block = xcd_index(blockIdx.x, gridDim.x), qb = block % q_blocks, bh = block / q_blocks;
+    // (padding-free: blocks outermost, those that only the longest have first.  8 sequences of 12 heads, 1024 tokens at most, us, one
+    // workgroup to an XCD after the other with the blocks innermost / an eighth in one piece / this: equal lengths of 460 36.6 / 33.7
+    // / 26.0, rising from 64 51.7 / 62.6 / 48.5, falling 42.4 / 63.2 / 42.8, one long 37.1 / 63.1 / 33.9)
+    int qb, bh;
+    if (cu_seqlens) {
+        const unsigned sequence_heads = gridDim.x / q_blocks, outer = blockIdx.x / sequence_heads;
+        qb = q_blocks - 1 - (int)outer;
+        bh = xcd_run_index(blockIdx.x - outer * sequence_heads, runs);
+    } else {
+        const int block = xcd_index(blockIdx.x, gridDim.x);
+        qb = block % q_blocks;
+        bh = block / q_blocks;
+    }
     const int b = bh / heads, head = bh % heads;
     const int64_t row0 = cu_seqlens ? (int64_t)cu_seqlens[b] : (int64_t)b * seq_fixed;
     const int seq = cu_seqlens ? (cu_seqlens[b + 1] - cu_seqlens[b]) : seq_fixed;
@@ -707,6 +723,7 @@ static int attention_run(const void *qkv, int64_t batch, int64_t seq, int64_t hi
     if (!aligned16(qkv) || (ctx && !aligned16(ctx)) || (q_out && !aligned16(q_out))) return MKQ_ERR_ALIGN;
     hipStream_t st = as_stream(stream);
     const uint16_t *in = (const uint16_t *)qkv;
+    const XcdRuns runs = attention_runs(batch * heads, heads);
     const AttentionRoute route = attention_route(batch, seq, hidden, heads, q_pitch);
     if (route == ATTENTION_HELD) {
         const AttentionParams p = {in, cu, (int)batch, (int)seq, (int)hidden, (int)heads, (int)dk, (int)q_blocks,
@@ -718,7 +735,7 @@ static int attention_run(const void *qkv, int64_t batch, int64_t seq, int64_t hi
 #define MKQ_ATT(DKP, VEC)                                                                                        \
     attention_blocks_kernel<DKP, VEC><<<grid, 256, 0, st>>>(in, (int)seq, (int)hidden, (int)heads, (int)dk,     \
                                                             (int)q_blocks, (uint16_t *)ctx, s_next, q_out, q_bits, \
-                                                            (int)q_pitch, cu)
+                                                            (int)q_pitch, cu, runs)
         if ((dk % 8) == 0) {
             if (dk <= 32) MKQ_ATT(32, 8);
             else MKQ_ATT(64, 8);

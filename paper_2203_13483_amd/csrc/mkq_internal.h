@@ -8,6 +8,7 @@
 
 #include <mutex>
 
+#include "launch_rules.h"
 #include "mkq.h"
 
 namespace mkq {
@@ -68,17 +69,6 @@ inline bool device_cus(int *cus)
 }
 
 // ---- device utilities ------------------------------------------------------
-
-// Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  A kernel that takes its share of the tokens
-// by xcd_index(blockIdx.x, gridDim.x) gives XCD x the x-th eighth of them, so it finds in its L2 what the kernel before,
-// with the same rule, wrote there.  What another XCD wrote has to come through memory first: 16 MiB just written are read
-// in 2 us by the XCDs that wrote them and in 9 by their neighbours.  (Which XCD a workgroup runs on decides only the time.)
-constexpr int XCDS = 8;
-__device__ __forceinline__ int xcd_index(unsigned wg, unsigned total)
-{
-    const unsigned q = total / XCDS, r = total % XCDS, x = wg % XCDS;
-    return (int)(x * q + (x < r ? x : r) + wg / XCDS);
-}
 
 // Eq. 1, integer part, for one value: binary32 divide, clamp to the signed
 // 4-bit range, round half to even.  NaN -> 0.

@@ -214,6 +214,123 @@ def test_attention_over_long_ragged_sequences(mkq, batch, total, max_seq, heads,
                     attention_code_band(qkv[rows].astype(np.float32), int(lens[b]), H, heads, s_next), "context codes")
 
 
+def _attention_bound(qkv, heads):
+    """The softmax attention of one sequence in binary64 and its bound: every probability is rounded to binary16 once (2^-11 of
+    it, or 2^-25 below the smallest normal number), the sums are binary32 and the result is binary16."""
+    import torch
+    n, dk = qkv.shape[0], qkv.shape[1] // (3 * heads)
+    q, k, v = (x.double().reshape(n, heads, dk).transpose(0, 1) for x in qkv.cpu().chunk(3, dim=1))
+    p = torch.softmax(q @ k.transpose(1, 2).contiguous() / dk ** 0.5, dim=2)
+    want = (p @ v).transpose(0, 1).reshape(n, heads * dk).numpy()
+    mass = (p @ v.abs()).transpose(0, 1).reshape(n, heads * dk).numpy()
+    return want, (2.0 ** -11 + 2.0 ** -14) * mass + n * 2.0 ** -25 * float(v.abs().max()) + 2.0 ** -11 * np.abs(want) + 2.0 ** -24
+
+
+# batch * heads well above what the device runs at a time (several blocks of 128 queries per workgroup), and as many as that
+@pytest.mark.parametrize("batch,max_seq,heads,dk", [(48, 200, 16, 64), (48, 300, 12, 26), (45, 384, 12, 32), (16, 500, 16, 64),
+                                                    (48, 512, 12, 48), (200, 500, 4, 26), (24, 256, 32, 8), (40, 700, 8, 64)])
+@pytest.mark.parametrize("longest", ["uniform", "one", "a quarter", "most"])
+def test_attention_of_many_sequences_is_that_of_each_alone(mkq, batch, max_seq, heads, dk, longest):
+    """Bit for bit, context and codes of both widths: what a query's result is does not depend on which workgroup has its block, nor
+    on how the sequences are dealt.  Some of them against binary64."""
+    import torch
+    H = heads * dk
+    g = np.random.default_rng(batch * max_seq + dk)
+    lens = g.integers(1, max_seq - 127, batch)
+    lens[:6] = [0, 1, 127, min(128, max_seq), min(129, max_seq), min(257, max_seq - 100)]
+    share = {"uniform": batch, "one": 1, "a quarter": batch // 4, "most": batch - 8}[longest]
+    lens[batch - share:] = g.integers(max_seq - max_seq % 128 + 1 if max_seq % 128 else max_seq - 127, max_seq + 1, share)
+    lens[-1] = max_seq
+    if longest == "uniform":
+        lens[:] = max_seq
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(int(cu[-1]))
+    qkv = torch.randn((int(cu[-1]), 3 * H), generator=gen, device="cuda").half()
+    s_next = 0.02
+    if longest == "uniform":
+        ctx, q4 = mkq.mkq_attention(qkv, batch, max_seq, H, heads, s_next=s_next, want_q=True)
+        _, q8 = mkq.mkq_attention_int8(qkv, batch, max_seq, H, heads, s_next=s_next / 16)
+    else:
+        ctx, q4 = mkq.mkq_attention_varlen(qkv, to_dev(cu), max_seq, H, heads, s_next=s_next, q_bits=4)
+        _, q8 = mkq.mkq_attention_varlen(qkv, to_dev(cu), max_seq, H, heads, s_next=s_next / 16, q_bits=8)
+    checked = {2, 3, 5, batch // 2, batch - 1}
+    for b, n in enumerate(int(v) for v in lens):
+        if n == 0:
+            continue
+        rows = slice(int(cu[b]), int(cu[b]) + n)
+        one = to_dev(np.array([0, n], np.int32))
+        c1, a4 = mkq.mkq_attention_varlen(qkv[rows].contiguous(), one, max_seq, H, heads, s_next=s_next, q_bits=4)
+        _, a8 = mkq.mkq_attention_varlen(qkv[rows].contiguous(), one, max_seq, H, heads, s_next=s_next / 16, q_bits=8)
+        assert torch.equal(ctx[rows], c1) and torch.equal(q4[rows], a4) and torch.equal(q8[rows], a8), (b, n)
+        if b in checked:
+            want, bound = _attention_bound(qkv[rows], heads)
+            assert np.all(np.abs(to_np(ctx[rows]).astype(np.float64) - want) <= bound), (b, n)
+
+
+@pytest.mark.parametrize("batch,seq,ragged", [(48, 128, True), (48, 300, True), (22, 512, True), (48, 300, False), (5, 520, True)])
+def test_layer_context_codes_with_a_row_pitch(mkq, batch, seq, ragged):
+    """The context codes inside a layer of hidden size 312 (rows of 384 codes): those of the attention alone on the layer's own
+    q, k, v, and zeros behind them, for more sequences than the device runs at a time."""
+    import torch
+    H, heads, F = 312, 12, 1200
+    g = torch.Generator(device="cuda").manual_seed(batch * seq)
+    rng = np.random.default_rng(batch + seq)
+    lens = rng.integers(1, seq + 1, batch) if ragged else np.full(batch, seq)
+    lens[-1] = seq
+    cu = to_dev(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    M = int(lens.sum())
+    h = torch.randn((M, H), generator=g, device="cuda").half()
+    weights = {}
+    for nm, K, N in (("qkv", H, 3 * H), ("ao", H, H), ("up", H, F), ("down", F, H)):
+        W = torch.randn((N, K), generator=g, device="cuda") * 0.05
+        weights[nm] = mkq.mkq_pack_weights_int4_padded(W) + (torch.zeros(N, device="cuda"),)
+    ln = {k: torch.full((H,), float(k.endswith("gamma")), device="cuda") for k in ("ln1_gamma", "ln1_beta", "ln2_gamma", "ln2_beta")}
+    sx = {"qkv": 0.3, "ao": 0.05, "up": 0.3, "down": 0.05}
+    layer = mkq.BertLayerInt4(batch, seq, H, heads, F, weights, sx, ln, 1e-12, cu_seqlens=cu if ragged else None,
+                              total_tokens=M if ragged else 0)
+    ws = torch.full((layer.workspace_bytes(),), 0x5A, dtype=torch.uint8, device="cuda")
+    layer(h, ws)
+    pitch = mkq.mkq_padded_k(H) // 2
+    qkv = ws[layer.layout.qkv: layer.layout.qkv + M * 3 * H * 2].view(torch.float16).reshape(M, 3 * H).contiguous()
+    codes = ws[layer.layout.c1: layer.layout.c1 + M * pitch].reshape(M, pitch)
+    _, alone = mkq.mkq_attention_varlen(qkv, cu, seq, H, heads, s_next=sx["ao"], q_bits=4)
+    assert torch.equal(codes[:, : H // 2], alone) and not codes[:, H // 2:].any()
+
+
+@pytest.mark.parametrize("S,dk", [(64, 26), (130, 64), (512, 32), (511, 64)])
+def test_attention_passes_nan_and_infinities_on(mkq, S, dk):
+    """A NaN or an infinite score makes its query's row NaN; every other row keeps its bits.  A key of -inf (scores of -inf
+    for queries with positive first dimension) has probability 0: the row is that of the sequence without the key."""
+    import torch
+    heads, H = 4, 4 * dk
+    g = torch.Generator().manual_seed(S * dk)
+    base = torch.randn((S, 3 * H), generator=g).half()
+    base[:, 0] = base[:, 0].abs() + 0.5       # q, head 0, first dimension: positive
+    clean = mkq.mkq_attention(base.cuda(), 1, S, H, heads)[0].cpu()
+    for row in (0, S // 2, S - 1):
+        for bad in (float("nan"), float("inf"), float("-inf")):
+            x = base.clone()
+            x[row, 1] = bad                   # one query, head 0
+            got = mkq.mkq_attention(x.cuda(), 1, S, H, heads)[0].cpu()
+            assert torch.isnan(got[row, :dk]).all(), (row, bad)
+            other = torch.ones(S, heads, dtype=torch.bool)
+            other[row, 0] = False
+            assert torch.equal(got.reshape(S, heads, dk)[other], clean.reshape(S, heads, dk)[other])
+        x = base.clone()
+        x[row, H] = float("-inf")             # one key, head 0: out of every row's sum
+        got = mkq.mkq_attention(x.cuda(), 1, S, H, heads)[0].cpu()
+        keep = [r for r in range(S) if r != row]
+        q, k, v = (base[:, i * H: i * H + dk].double() for i in range(3))
+        p = torch.softmax(q @ k[keep].t().contiguous() / dk ** 0.5, dim=1)
+        want, mass = (p @ v[keep]).numpy(), (p @ v[keep].abs()).numpy()
+        bound = (2.0 ** -11 + 2.0 ** -14) * mass + S * 2.0 ** -25 * float(v.abs().max()) + 2.0 ** -11 * np.abs(want) + 2.0 ** -24
+        assert np.all(np.abs(to_np(got[:, :dk]).astype(np.float64) - want) <= bound), row
+        x = base.clone()
+        x[row, 2 * H] = float("nan")          # one value: a column of head 0
+        got = mkq.mkq_attention(x.cuda(), 1, S, H, heads)[0].cpu()
+        assert torch.isnan(got[:, 0]).all() and torch.equal(got[:, 1:], clean[:, 1:])
+
+
 @pytest.mark.parametrize("M,N,K", [(128, 768, 768), (200, 328, 192), (1024, 2304, 768), (77, 64, 3072)])
 @pytest.mark.parametrize("variant", ["plain", "gelu", "residual_f32out"])
 def test_linear_fp16_baseline(mkq, M, N, K, variant):

@@ -3,6 +3,7 @@ import ctypes as C
 import os
 import subprocess
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -18,6 +19,15 @@ extern "C" int held_blocks(int64_t sequence_heads, int q_blocks, int64_t residen
 {
     return attention_held_blocks(sequence_heads, q_blocks, resident);
 }
+extern "C" int run_index(unsigned wg, int64_t sequence_heads, int64_t heads)
+{
+    return xcd_run_index(wg, attention_runs(sequence_heads, heads));
+}
+extern "C" int piece_index(unsigned wg, unsigned total) { return xcd_index(wg, total); }
+extern "C" int first_half(int64_t sequence_heads, int q_blocks, int per_wg)
+{
+    return attention_held_first_half(sequence_heads, q_blocks, per_wg);
+}
 extern "C" bool half_waves(int64_t M, int64_t D) { return layernorm_half_waves(M, D); }
 """
 
@@ -32,6 +42,9 @@ def rules(tmp_path_factory):
     lib = C.CDLL(str(d / "rules.so"))
     lib.route.argtypes = [C.c_int64] * 5
     lib.held_blocks.argtypes = [C.c_int64, C.c_int, C.c_int64]
+    lib.run_index.argtypes = [C.c_uint, C.c_int64, C.c_int64]
+    lib.piece_index.argtypes = [C.c_uint, C.c_uint]
+    lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
     return lib
 
@@ -86,3 +99,38 @@ def test_layernorm_of_more_rows_than_fit_a_launch_four_to_a_workgroup(rules):
         assert not rules.half_waves(2047, D)
         assert rules.half_waves(2048, D) and rules.half_waves(most + 1, D)
     assert not rules.half_waves(most + 1, 1032)  # no half-wave kernel of this size
+
+
+@pytest.mark.parametrize("batch,heads", [(1, 1), (3, 5), (5, 12), (8, 8), (16, 12), (21, 16), (64, 12), (67, 12), (300, 3)])
+def test_every_sequence_and_head_is_dealt_once(rules, batch, heads):
+    n = batch * heads
+    assert sorted(rules.run_index(w, n, heads) for w in range(n)) == list(range(n))
+    assert sorted(rules.piece_index(w, n) for w in range(n)) == list(range(n))
+
+
+@pytest.mark.parametrize("batch,longest", [(16, 512), (64, 128), (32, 256), (8, 512)])
+@pytest.mark.parametrize("order", ["rising", "falling", "shuffled"])
+def test_sequences_of_different_lengths_are_dealt_evenly(rules, batch, longest, order):
+    """Work of a sequence and head: its keys times its queries and the staging (half a block of queries).  The XCD with most of it
+    has at most half as much again as the mean; an eighth of the sequences in one piece has twice the mean and more."""
+    lens = np.linspace(longest // 16, longest, batch).astype(int)
+    lens = {"rising": lens, "falling": lens[::-1], "shuffled": np.random.default_rng(batch).permutation(lens)}[order]
+    heads = 12
+    n = batch * heads
+
+    def busiest(index):
+        load = np.zeros(8)
+        for w in range(n):
+            length = int(lens[index(w) // heads])
+            load[w % 8] += length * (length + 64)
+        return load.max() / load.mean()
+    assert busiest(lambda w: rules.run_index(w, n, heads)) < 1.5
+    if order != "shuffled":
+        assert busiest(lambda w: rules.piece_index(w, n)) > 2.0
+
+
+def test_only_sequences_that_one_workgroup_would_have_are_shared(rules):
+    limit = (2 ** 32 - 1) // 512
+    assert [rules.first_half(256, q, q) for q in (1, 2, 3, 4)] == [0, 1, 2, 2]
+    assert rules.first_half(256, 4, 2) == 0 and rules.first_half(256, 3, 1) == 0
+    assert rules.first_half(limit // 2, 4, 4) == 2 and rules.first_half(limit // 2 + 1, 4, 4) == 0
