@@ -185,9 +185,12 @@ def _stream(stream=None):
     if stream is not None:
         return stream.cuda_stream
     torch = _torch()
-    if not torch.cuda.is_initialized():
-        return torch.cuda.current_stream().cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if torch.cuda.is_initialized():
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:  # (names that torch does not promise to keep)
+            pass
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _dtype_code(t):

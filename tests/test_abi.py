@@ -304,3 +304,14 @@ def test_int8_tuning_argument_errors(lib):
     assert t(P, 0.1, P, P, None, 65, 64, 128, P, mkq.MKQ_F16, None, None, 30) == mkq.MKQ_ERR_UNSUPPORTED    # streaming: M <= 64
     assert t(None, 0.1, P, P, None, 16, 64, 128, P, mkq.MKQ_F16, None, None, 30) == mkq.MKQ_ERR_NULL
     assert t(P, 0.0, P, P, None, 16, 64, 128, P, mkq.MKQ_F16, None, None, 27) == mkq.MKQ_ERR_SCALE
+
+
+@pytest.mark.parametrize("initialized", [False, True])
+@pytest.mark.parametrize("private", [{}, {"_cuda_getDevice": lambda: 0}])
+def test_current_stream_without_private_names_of_torch(monkeypatch, initialized, private):
+    """The short cut to the current stream's handle is taken only where torch has it."""
+    from types import SimpleNamespace as NS
+    fake = NS(_C=NS(**private), cuda=NS(is_initialized=lambda: initialized, current_stream=lambda: NS(cuda_stream=0x1230)))
+    monkeypatch.setattr(mkq, "_torch_module", fake)
+    assert mkq._stream() == 0x1230
+    assert mkq._stream(NS(cuda_stream=0x40)) == 0x40
