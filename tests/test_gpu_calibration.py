@@ -173,6 +173,53 @@ def test_contiguous_tensors_around_the_batches(mkq, M, K):
             x.view(-1)[at] = 0.5
 
 
+@pytest.mark.parametrize("dtype", ["float16", "float32"])
+def test_absmax_reads_every_place_of_its_windows(mkq, dtype):
+    """Contiguous tensors of two windows of the grid (256 workgroups of 1024 threads, eight groups of eight values each) and a
+    remainder: the largest value in every one of the eight steps, in the first, a middle and the last workgroup, in its first and
+    last thread, of both windows, at the seams and in the remainder."""
+    import torch
+    M, K = 4100, 8208
+    step, share = 1024 * 8, 8 * 1024 * 8          # values of a step, and of a workgroup's part of a window
+    window = 256 * share
+    assert 2 * window + 8 < M * K < 3 * window
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.rand(M, K, generator=g, device="cuda").to(getattr(torch, dtype))
+    places = [w * window + wg * share + a * step + t * 8 + (3 * a + wg + w) % 8
+              for w in (0, 1) for wg in (0, 131, 255) for a in range(8) for t in (0, 1023)]
+    places += [window - 1, window, 2 * window - 1, 2 * window, 2 * window + 7, M * K - 8, M * K - 1]
+    flat, got = x.view(-1), []
+    for i in places:
+        old = flat[i].clone()
+        flat[i] = -70.0
+        got.append(mkq.mkq_absmax_scale(x))
+        flat[i] = old
+    got = to_np(torch.cat(got))
+    assert np.all(got == np.float32(70.0) / np.float32(7)), [p for p, s in zip(places, got) if s != got.max()]
+
+
+@pytest.mark.parametrize("larger", [2.0, 1.0 + 2.0 ** -10])
+def test_percentile_counts_every_value_of_its_windows_once(mkq, larger):
+    """A contiguous binary16 tensor of two windows of the grid (512 workgroups of 1024 threads, eight groups of eight values each)
+    and a remainder, of two values in random places, the rank being the number of the larger ones, or one more: one less of
+    them, or one counted twice, is another result.  The first pass tells 1 from 2, the second 1 from 1 + 2^-10."""
+    import torch
+    M, K = 8193, 8200
+    n, window = M * K, 512 * 1024 * 8 * 8
+    assert 2 * window + 8 < n < 3 * window and n % 2 == 0
+    k = n // 2
+    g = torch.Generator(device="cuda").manual_seed(11)
+    is_larger = torch.rand(n, generator=g, device="cuda") < 0.5
+    surplus = int(is_larger.sum()) - k
+    from_these = (is_larger if surplus > 0 else ~is_larger).nonzero()[:, 0]
+    is_larger[from_these[torch.randperm(len(from_these), generator=g, device="cuda")[:abs(surplus)]]] = surplus < 0
+    assert int(is_larger.sum()) == k
+    x = torch.where(is_larger, larger, 1.0).half().view(M, K)
+    assert float(mkq.mkq_percentile_scale(x, 500000)) == np.float32(larger) / np.float32(7)
+    x.view(-1)[is_larger.nonzero()[k // 3, 0]] = 1.0
+    assert float(mkq.mkq_percentile_scale(x, 500000)) == np.float32(1) / np.float32(7)
+
+
 def test_percentile_of_every_binary16_value(mkq):
     """All 65536 bit patterns, subnormals, infinities and NaN (which rank as 0) among them, at every rank."""
     import torch
