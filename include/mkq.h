@@ -80,8 +80,8 @@ int mkq_scale_gradients(const void *x, int x_dtype, int64_t M, int64_t K, int64_
 /* Percentile calibration of an activation step (section 3.1, third paragraph): the
  * clipping point T is the k-th largest |x_i|, k = max(1, floor(M*K * top_ppm / 10^6))
  * (top_ppm = 100 for the top 0.01 %), found exactly by radix selection over the bit
- * patterns of |x| (three counting passes over x); s_out[0] = T / (2^(bits-1) - 1), or 1
- * when T = 0.  NaN ranks as 0.  top_ppm = 0 gives abs-max calibration.
+ * patterns of |x| (counting passes over x: two for binary16, three for binary32);
+ * s_out[0] = T / (2^(bits-1) - 1), or 1 when T = 0.  NaN ranks as 0.  top_ppm = 0 gives abs-max calibration.
  *   workspace  at least mkq_percentile_scale_workspace_bytes() bytes, 16-byte aligned
  * M*K < 2^32.  Errors: NULL, SHAPE, ALIGN, DTYPE, WORKSPACE, UNSUPPORTED, HIP. */
 size_t mkq_percentile_scale_workspace_bytes(void);
@@ -386,8 +386,11 @@ int mkq_layernorm(const void *x, int64_t M, int64_t D, const float *gamma, const
  * Scores are scaled by 1/sqrt(d_k), d_k = hidden / heads; the softmax runs in binary32 and its normalized
  * probabilities are narrowed to binary16 before they multiply v.
  * d_k even and <= 64, hidden % 8 == 0, seq <= 4096 (anything else: UNSUPPORTED).  d_k == 64 with
- * seq <= 128 takes a kernel that holds all keys of a (sequence, head) at once; everything else one that
- * walks the keys in blocks of 128, twice (row maximum and denominator, then the weighted sum). */
+ * seq <= 128 takes a kernel that holds all keys of a (sequence, head) at once, other sequences of up to 512
+ * keys with d_k <= 32 or a multiple of 8 one that holds the scores of a query in registers; the rest (longer
+ * sequences, heads of 34 to 62 that are no multiple of 8, and batches or rows beyond what the second can address
+ * or be launched for) one that walks the keys in blocks of 128, twice (row maximum and denominator, then the
+ * weighted sum). */
 int mkq_attention(const void *qkv, int64_t batch, int64_t seq, int64_t hidden, int64_t heads,
                   void *ctx, float s_next, uint8_t *q_out, void *stream);
 

@@ -1,4 +1,5 @@
-// What the attention kernels take, and how they store a query's context.
+// What the kernel of attention.hip takes, and how it stores a query's context.  (attention_blocks_kernel of layer.hip stores the
+// same way, from arguments of its own.)
 #pragma once
 
 #include "gemm_common.h"

@@ -41,8 +41,8 @@ struct GemmI4Params {
 
 // Whether the tiles are dealt to the XCDs by rows: every XCD then reads all weights, and what it reads and writes of the
 // tokens stays in its L2 for the kernels around.  Weights come out of memory at about 5 TB/s, lines that another XCD has
-// just written at under 2, so the weights seven more times (7 W / 5) against the tokens' side once (/ 2) is 2.5 W; and
-// the weights leave most of the L2 to the tokens.  bits: of an operand.
+// just written at under 2, so the weights seven more times (7 W / 5) against the tokens' side once (/ 2) would break even
+// near 2.8 W; 2.5 is what the timings below gave.  And the weights leave most of the L2 to the tokens.  bits: of an operand.
 // 4-bit layers in a graph, us, the former order -> this: student (hidden 312) of 1024 / 2048 / 4096 tokens 40.3 -> 35.5,
 // 46.7 -> 38.6, 58.0 -> 49.2; base of 440 / 1024 / 4096 44.3 -> 42.3, 50.5 -> 46.5, 84.0 -> 83.2.  Without the first limit
 // binary16 layers of 768 tokens lost 7 %; with 2 MiB allowed K = 1024, N = 4096 of 1000 ... 3000 tokens 3 %, with 8 MiB 9 %.
