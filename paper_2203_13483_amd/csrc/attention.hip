@@ -31,9 +31,11 @@ struct AttentionHeldCfg {
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // DKP: head size rounded up to 32 or 64 (dimensions d_k .. DKP - 1 are staged as zeros and never stored).  VEC = 8: 16-byte
-// accesses (d_k % 8 == 0); VEC = 2: 4-byte ones.
+// accesses (d_k % 8 == 0); VEC = 2: 4-byte ones.  parts: workgroups per (sequence, head), from the host, 1 for up to 128 keys: the divisions
+// by it are latency in front of the first load (64 x 64 tokens, 12 heads of 26, 8.4 -> 7.5 us in a graph, 32 x 128 7.6 -> 7.45).
 template <int DKP, int VEC, int NG>
-__global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(const AttentionParams p, int per_wg, int first_half, const XcdRuns runs)
+__global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(const AttentionParams p, int per_wg, int parts, int first_half,
+                                                                                const XcdRuns runs)
 {
     using Cfg = AttentionHeldCfg<DKP, NG>;
     constexpr int THREADS = Cfg::THREADS, KEYS = Cfg::KEYS, ROWB = DKP * 2, CH = DKP / 8, VROW = Cfg::VROW, DS = DKP / 32;
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     bool share = false;  // the longest sequences by two workgroups
     if (p.cu_seqlens) {
         const unsigned sequence_heads = (unsigned)p.batch * p.heads;
-        part = (int)(blockIdx.x / sequence_heads);
+        part = parts == 1 ? 0 : (int)(blockIdx.x / sequence_heads);
         bh = xcd_run_index(blockIdx.x - part * sequence_heads, runs);
         if (first_half) {
             // of the first 64 sequences, at most half are longest: these are shared, and where they are at most an eighth, their
@@ -64,9 +66,9 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
             if (many && 8 * many <= n) part = 1 - part;
         }
     } else {
-        const int parts = (p.q_blocks + per_wg - 1) / per_wg, block = xcd_index(blockIdx.x, gridDim.x);
-        part = block % parts;
-        bh = block / parts;
+        const int block = xcd_index(blockIdx.x, gridDim.x);
+        bh = parts == 1 ? block : block / parts;
+        part = block - bh * parts;
     }
     const int b = bh / p.heads, head = bh % p.heads;
     const int64_t row0 = p.cu_seqlens ? (int64_t)p.cu_seqlens[b] : (int64_t)b * p.seq;
@@ -287,8 +289,9 @@ static int launch_held(const AttentionParams *p, hipStream_t st)
     const int64_t sequence_heads = (int64_t)p->batch * p->heads;
     const int per_wg = attention_held_blocks(sequence_heads, p->q_blocks, resident);
     const int first_half = p->cu_seqlens ? attention_held_first_half(sequence_heads, p->q_blocks, per_wg) : 0;
-    const unsigned grid = (unsigned)(sequence_heads * (first_half ? 2 : ceil_div(p->q_blocks, per_wg)));
-    kernel<<<grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, per_wg, first_half, attention_runs(sequence_heads, p->heads));
+    const int parts = first_half ? 2 : (int)ceil_div(p->q_blocks, per_wg);
+    const unsigned grid = (unsigned)(sequence_heads * parts);
+    kernel<<<grid, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, per_wg, parts, first_half, attention_runs(sequence_heads, p->heads));
     return launch_status();
 }
 
