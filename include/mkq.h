@@ -128,7 +128,10 @@ int mkq_unpack_weights_int4(const uint8_t *Wq, int64_t N, int64_t K, int8_t *cod
 
 /* Optional parts of the linear's epilogue. */
 typedef struct mkq_epilogue {
-    int act;              /* MKQ_ACT_*; applied after bias and residual (GELU: erf form, FFN of section 3.2) */
+    int act;              /* MKQ_ACT_*; applied after bias and residual (GELU: erf form, FFN of section 3.2; binary32
+                             and bfloat16 results, and codes written beside them, come from a form that also keeps
+                             values below 1e-7: within 1e-7 plus one unit in the last place of what binary16
+                             results and code outputs are decided from) */
     const void *residual; /* NULL or [M, N] added after the bias */
     int residual_dtype;   /* MKQ_F32 or MKQ_F16 */
     float s_next;         /* step of the next layer's activation quantizer; used when out_dtype == MKQ_I4
