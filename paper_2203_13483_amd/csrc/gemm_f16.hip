@@ -269,12 +269,17 @@ static bool few_tiles(const GemmI4Params &p)
 //   K = 3072, N = 768 33.5 -> 28.8; 2298 tokens 22.0 -> 14.1, 9.4 -> 8.7, 26.8 -> 20.2, 28.8 -> 23.3;
 //   16384 tokens, K = 1024, N = 4096 230 -> 153.  Over 1230 shapes (M = 1 .. 16384, 47 pairs of K and N with their
 // epilogues) six are slower than before by more than 2 %, by 11 % at most (440 tokens, K = 1280, N = 5120 with GELU 13.7 -> 15.2).
-enum { F16_SPLIT = 0, F16_64, F16_128_DEEP, F16_256x128, F16_128, F16_256, F16_CONFIGS };
+enum { F16_SPLIT = 0, F16_64, F16_128_DEEP, F16_256x128, F16_128, F16_256, F16_128x96_DEEP, F16_256x192, F16_CONFIGS };
 static int choose_f16(const GemmI4Params &p)
 {
     const int64_t t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128), t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
     // at most one 64x64 tile per CU: two wave groups share the k loop (a lone wave per SIMD waits for its own loads)
     if (few_tiles(p)) return F16_SPLIT;
+    // More than two 64x64 tiles per CU, but at most one of 128x96, whose deep ring covers the trip to memory: what a launch of this
+    // size costs is its fullest CU, and 128x128 tiles leave a quarter of the chip idle where these leave none.  us, before -> here:
+    // 4096 tokens, K = 3072, N = 768 26.5 -> 23.3, K = N = 768 with a residual 10.8 -> 9.9; 2560, K = 4096, N = 1024 32.6 -> 28.3;
+    // 1024, K = 768, N = 2304 9.7 -> 8.9, N = 3072 with GELU 10.9 -> 10.3.  In a second round it loses (4352, K = 3072, N = 768 26.9 -> 41.1).
+    if (t64 > 512 && ceil_div(p.M, 128) * ceil_div(p.N, 96) <= 256) return F16_128x96_DEEP;
     // up to two 64x64 tiles per CU, three (all that fit) where the epilogue is a large share of the tile: 3072 tokens,
     // K = N = 768 with a residual 12.1 -> 11.3, 681 tokens, K = 768, N = 3072 with GELU 11.7 -> 10.9; without either the
     // 128x128 tiles win from two per CU on (1024 tokens, K = 768, N = 2304 10.5 -> 10.0)
@@ -284,9 +289,17 @@ static int choose_f16(const GemmI4Params &p)
     if (t128 <= 256) return F16_128_DEEP;
     // one 256x128 tile of eight waves per CU in a single round
     if (ceil_div(p.M, 256) * ceil_div(p.N, 128) <= 256) return F16_256x128;
-    // at least one 256x256 tile per CU: the least traffic per product; in between two 128x128 workgroups per CU
-    // overlap one's epilogue with the other's k loop
-    return ceil_div(p.M, 256) * ceil_div(p.N, 256) >= 256 ? F16_256 : F16_128;
+    // Several rounds: the tile whose rounds add up to the least.  256x256, one per CU, has the least traffic per product; two 128x128
+    // workgroups per CU overlap one's epilogue with the other's k loop; 256x192, one per CU, is between them and fills rounds that
+    // neither does.  A round takes about 18, 11.5 and 15 (and 2 for the first) at K = 768, and in that proportion at other K.  us,
+    // without 256x192 -> with: 4096 tokens, K = 768, N = 3072 with GELU 26.0 -> 21.7, N = 2304 20.5 -> 17.8; 8192, N = 3072 46.9 -> 38.9;
+    // 12288, K = 3072, N = 768 74.6 -> 54.4; 9216, K = 4096, N = 1024 91.0 -> 66.9; where it is not taken: 5632 tokens, K = 768,
+    // N = 2304 24.4 and 31.6, 8192, K = 1024, N = 4096 56.9 and 65.4.
+    const auto rounds = [](int64_t tiles, int64_t per_round) { return (double)ceil_div(tiles, per_round); };
+    const int64_t t256 = ceil_div(p.M, 256) * ceil_div(p.N, 256);
+    const double other = t256 >= 256 ? 18.0 * rounds(t256, 256) : 11.5 * rounds(t128, 512);
+    if (15.0 * rounds(ceil_div(p.M, 256) * ceil_div(p.N, 192), 256) + 2.0 < other) return F16_256x192;
+    return t256 >= 256 ? F16_256 : F16_128;
 }
 
 static int run_config(const GemmI4Params &p, int cfg, hipStream_t st)
@@ -297,6 +310,8 @@ static int run_config(const GemmI4Params &p, int cfg, hipStream_t st)
     case F16_128_DEEP: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 128, 4>>(p, st);
     case F16_256x128: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 128, 4, 2, 128, 3>>(p, st);
     case F16_128: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 128, 2>>(p, st);
+    case F16_128x96_DEEP: return launch_f16_by_epilogue<GemmI4DmaCfg<128, 96, 4, 1, 128, 4>>(p, st);
+    case F16_256x192: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 192, 4, 2, 128, 2>>(p, st);
     default: return launch_f16_by_epilogue<GemmI4DmaCfg<256, 256, 2, 4, 128, 2>>(p, st);
     }
 }

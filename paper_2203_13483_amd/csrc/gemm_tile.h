@@ -53,7 +53,7 @@ struct GemmI4DmaCfg : GemmI4Cfg<BM_, BN_, WGM_, WGN_, RB_> {
 // tiles at a time so that the buffer fits beside the groups' rings.
 template <class Cfg>
 struct KSplitXch {
-    static constexpr int TPP = (Cfg::TM * Cfg::TN >= 2 && 2 * (Cfg::LDS_BYTES + EpiShuffle<Cfg>::EXTRA_LDS) +
+    static constexpr int TPP = (Cfg::TM * Cfg::TN % 2 == 0 && 2 * (Cfg::LDS_BYTES + EpiShuffle<Cfg>::EXTRA_LDS) +
                                                                   Cfg::WAVES * 8192 <= 160 * 1024) ? 2 : 1;
     static_assert((Cfg::TM * Cfg::TN) % TPP == 0, "whole passes");
     static constexpr int bytes(int ksplit) { return (ksplit - 1) * Cfg::WAVES * TPP * 4096; }

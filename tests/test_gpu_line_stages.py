@@ -78,7 +78,9 @@ def test_configurations_need_whole_stages(mkq):
 
 # one shape per tile choice, in its order, with one and with several stages; a ragged N takes the general epilogue
 @pytest.mark.parametrize("M,N,K", [(100, 72, 256), (1, 8, 64), (70, 136, 192), (33, 77, 128), (1500, 1544, 64), (1500, 1540, 320),
-                                   (2100, 2056, 128), (2100, 2056, 64), (4100, 2312, 192), (8200, 2312, 64), (8200, 2312, 192)])
+                                   (2100, 2056, 128), (2100, 2056, 64), (4100, 2312, 192), (8200, 2312, 64), (8200, 2312, 192)]
+                         # the last tile of 96 and of 192 channels of one and of all columns; 128x128, deep and shallow; 256x256
+                         + [(1100, 2209, 64), (1030, 2304, 256), (3850, 2497, 64), (4097, 2112, 128), (2100, 1800, 128), (6000, 2312, 64), (8192, 2048, 64)])
 def test_linear_fp16_tile_choices(mkq, M, N, K):
     import torch
     rng = np.random.default_rng(M + K)
