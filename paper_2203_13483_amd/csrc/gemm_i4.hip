@@ -478,7 +478,7 @@ static int choose_rows64(const GemmI4Params &p)
     return 28;
 }
 
-// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49, gemm_lines.hip) in the
+// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip) in the
 // ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
 // 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
 // rounds of tiles).  (us, 64-byte -> 128-byte rows)
@@ -521,8 +521,10 @@ static int choose_tiles(const GemmI4Params &p)
     // (M = 3072, K = 3072, N = 768 15.6 -> 14.4)
     if (t128 <= 256) {
         if (f32 && p.K < 1536) return rows64;  // (M = 1280, K = 768, N = 3072 10.2 -> 10.7)
-        if (p.K >= (gelu ? 2048 : 1536)) return split ? 46 : rows64;
-        return fixed ? 49 : rows64;
+        // 51, 128x96 with two wave groups, where one per CU holds all and CUs are left: three quarters of the work on the fullest CU
+        // (K = 3072, N = 768, M = 3072 14.0 -> 13.1; K = 4096, N = 1024, M = 2560 16.9 -> 15.8; layers of 24 x 128 tokens 72.2 -> 70.2,
+        // of 16 x 200 79.2 -> 77.9; with all 256 taken, 32 x 128, 78.6 -> 79.1)
+        if (p.K >= (gelu ? 2048 : 1536)) return !split ? rows64 : fixed && ceil_div(p.M, 128) * ceil_div(p.N, 96) < 256 ? 51 : 46;
     }
     if (!fixed) return rows64;
     // one and a half rounds of 43 still beat two of anything larger where the epilogue is long (M = 1536, K = 768, N = 3072 with
@@ -606,7 +608,7 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
         if (!xsplit_plan(q, scr, 128, 64, 1, forced_ks)) return MKQ_ERR_UNSUPPORTED;
         return launch_xsplit_by_epilogue<GemmI4DmaCfg<128, 64, 2, 2, 64, 3>, 1>(q, epi, st);
     }
-    if (cfg >= 43 && cfg <= 49) return run_gemm_i4_lines(p, epi, cfg, st);
+    if ((cfg >= 43 && cfg <= 49) || cfg == 51) return run_gemm_i4_lines(p, epi, cfg, st);
     switch (cfg) {
     case 2: return launch_gemm_i4<GemmI4Cfg<128, 128, 2, 2, 64>>(p, st);
     case 3: return launch_gemm_i4<GemmI4Cfg<64, 64, 2, 2, 64>>(p, st);
@@ -651,6 +653,11 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
 //       nor for binary32 until K = 1536 (M = 2560, K = 768, N = 3072 46 16.7, 44 19.6; M = 6144, K = 3072, N = 768 25.6, 23.5);
 //       and very large problems, GELU and binary32 apart (K = N = 1536, M = 16384 50.4 -> 41.0; K = 1024, N = 4096, M = 32768
 //       174 -> 161)
+//   51, 128x96, a ring of four stages, one per CU and only one round, for a long k loop (K = 3072, N = 768, M = 4096 17.5 -> 15.2,
+//       K = 4096, N = 1024, M = 2560 20.2 -> 17.8; at K = 768 43 is as fast, with GELU faster)
+//   52, a single round of 256x192 where 128x128 tiles come in two of two per CU: GELU (K = 768, N = 3072, M = 4096 20.0 -> 17.5, K = 1024,
+//       N = 4096, M = 2560 20.7 -> 18.7), residuals (K = N = 768, M = 12288 16.9 -> 15.5) and long k loops (K = 3072, N = 768, M = 12288
+//       39.7 -> 32.7); plain outputs at short k between -4 and 8 %, and not taken
 //   29, 64-byte rows, three per CU, where 46 would need a second, nearly empty round (M = 12288, K = N = 768 18.9 instead of
 //       21.1), at short k (M = 12288, K = 256, N = 768 10.5 instead of 11.8) and for GELU over several rounds
 static int choose_tiles_i8(const GemmI4Params &p)
@@ -661,6 +668,9 @@ static int choose_tiles_i8(const GemmI4Params &p)
     const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32, whole = (p.N % 8) == 0;
     if (!gelu && t256x128 >= 512 && 2.0 * p.M * p.N * p.K >= 6e10) return whole && !f32 ? 44 : 18;
     if (t64 <= 256 && (p.K % 256) == 0 && p.K >= 2048) return 47;
+    const bool fixed = classify_epilogue(p) != EPI_GENERIC && !f32;
+    if (fixed && t64 > 512 && p.K >= 1536 && ceil_div(p.M, 128) * ceil_div(p.N, 96) <= 256) return 51;
+    if (fixed && t128 > 512 && (gelu || res || p.K >= 1536) && ceil_div(p.M, 256) * ceil_div(p.N, 192) <= 256) return 52;
     const bool general = p.K < 2048 && classify_epilogue(p) == EPI_GENERIC;
     if (t64 <= 768 || (gelu && p.K < 1536 && t64 <= (general && p.K < 768 ? 1024 : 1536)) ||
         (res && !f32 && p.K <= 1024 && t64 <= 1024))
@@ -691,7 +701,7 @@ int run_gemm_i8(const GemmI4Params &p, hipStream_t st, int forced_cfg = -1)
     int epi = classify_epilogue(p);
     if (epi == EPI_I4 || epi == EPI_I4_GELU) epi = EPI_GENERIC;
     const int cfg = forced_cfg >= 0 ? forced_cfg : choose_tiles_i8(p);
-    if (cfg >= 43 && cfg <= 47) return run_gemm_i8_lines(p, epi, cfg, st);
+    if ((cfg >= 43 && cfg <= 47) || cfg == 51 || cfg == 52) return run_gemm_i8_lines(p, epi, cfg, st);
     switch (cfg) {
     case 18: return launch_i8_by_epilogue<GemmI4DmaCfg<256, 128, 2, 2, 64, 3>>(p, epi, st);
     case 29: return launch_i8_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 64, 3>>(p, epi, st);
@@ -1149,7 +1159,7 @@ extern "C" int mkq_init(void)
     int rc = setup_gemm_i4_stream(p, nullptr);
     // (the configurations that split K across workgroups only look at the scratch area's size here)
     const SplitKScratch any_scratch = {reinterpret_cast<unsigned *>(16), reinterpret_cast<int32_t *>(16), (size_t)1 << 40};
-    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 60, 61, 62}) {
+    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 60, 61, 62}) {
         // one pass per epilogue class: the parameter block is made to classify as each in turn
         for (int e = 0; e < 8 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
@@ -1162,7 +1172,7 @@ extern "C" int mkq_init(void)
             if (cfg < 10 && e == 0) e = 6;  // the register-staged kernel has two epilogues: one for all, and the last
         }
     }
-    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47}) {  // the tile shapes of the 8-bit path
+    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47, 51, 52}) {  // the tile shapes of the 8-bit path
         for (int e = 0; e < 7 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
@@ -1340,7 +1350,7 @@ extern "C" int mkq_tuning_linear_int8(const int8_t *a, float s_x, const int8_t *
                                       int out_dtype, const mkq_epilogue *epi, void *stream, int config)
 {
     if (config != -1 && config != 18 && config != 27 && config != 28 && config != 29 && config != 30 &&
-        !(config >= 43 && config <= 47 && config != 45))
+        !(config >= 43 && config <= 47 && config != 45) && config != 51 && config != 52)
         return MKQ_ERR_UNSUPPORTED;
     return linear_int8_run(a, s_x, Wq, s_w, bias, M, N, K, out, out_dtype, epi, stream, config);
 }

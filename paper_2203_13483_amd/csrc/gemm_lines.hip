@@ -42,6 +42,7 @@ int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st)
     case 47: return launch_lines<GemmI4DmaCfg<64, 64, 2, 2, 128, 3>, 4, 2>(p, epi, st);
     case 48: return launch_lines<GemmI4DmaCfg<128, 64, 2, 2, 128, 2>, 4, 2>(p, epi, st);
     case 49: return launch_lines<GemmI4DmaCfg<128, 128, 4, 2, 128, 2>, 4>(p, epi, st);
+    case 51: return launch_lines<GemmI4DmaCfg<128, 96, 4, 1, 128, 2>, 4, 2>(p, epi, st);
     default: return MKQ_ERR_UNSUPPORTED;
     }
 }
@@ -53,6 +54,8 @@ int run_gemm_i8_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st)
     case 44: return launch_lines<GemmI4DmaCfg<256, 128, 4, 2, 128, 3>, 8>(p, epi, st);
     case 46: return launch_lines<GemmI4DmaCfg<128, 128, 2, 2, 128, 2>, 8>(p, epi, st);
     case 47: return launch_lines<GemmI4DmaCfg<64, 64, 2, 2, 128, 3>, 8, 2>(p, epi, st);
+    case 51: return launch_lines<GemmI4DmaCfg<128, 96, 4, 1, 128, 4>, 8>(p, epi, st);
+    case 52: return launch_lines<GemmI4DmaCfg<256, 192, 4, 2, 128, 2>, 8>(p, epi, st);
     default: return MKQ_ERR_UNSUPPORTED;
     }
 }
