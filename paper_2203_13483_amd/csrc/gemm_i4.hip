@@ -24,7 +24,9 @@
 // in a permuted order so that a lane ends up with runs of 8 consecutive output
 // channels of one token and stores them with one or two vector stores.
 #include "gemm_tile.h"
+#include "layer_tail.h"
 #include "mkq_tuning.h"
+#include "qkv_attention.h"
 
 namespace mkq {
 
@@ -1195,6 +1197,8 @@ extern "C" int mkq_init(void)
     }
     if (rc == MKQ_OK) rc = setup_gemm_f16();
     if (rc == MKQ_OK) rc = setup_attention();
+    if (rc == MKQ_OK) rc = setup_qkv_attention();
+    if (rc == MKQ_OK) rc = setup_layer_tail();
     void *scratch_ptr = nullptr;
     if (rc == MKQ_OK) rc = static_scratch(&scratch_ptr);
     return rc;

@@ -91,6 +91,25 @@ constexpr int attention_held_first_half(int64_t sequence_heads, int q_blocks, in
     return q_blocks >= 2 && per_wg == q_blocks && 2 * sequence_heads <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS ? (q_blocks + 1) / 2 : 0;
 }
 
+// 4-bit layers of small hidden size (rows of codes, padding included, of up to 384) run in two launches and a quantizer instead of seven:
+// their kernels take 4 to 12 us each, most of it the launch and one trip to memory.  us a layer, 4-bit, hidden size 312 with heads of 26,
+// kernels of their own -> q, k, v with the attention -> what follows it in one launch as well:
+//   256 tokens 37.5 -> 34.1 -> 28.3, 1024 39.1 -> 35.2 -> 28.4, 4096 50.0 -> 45.6 -> 34.2, padding-free 440 38.3 -> 34.2 -> 27.9,
+//   2298 46.0 -> 45.0 -> 37.8; hidden 384, 4096 tokens 49.5 -> 45.3 -> 36.3, 128 33.5 -> 30.4 -> 21.9.
+constexpr int64_t SMALL_LAYER_ROW = 384;
+// q, k, v and the attention: any number of tokens (16384 of hidden size 312 109 -> 100, 65536 335 -> 292); one workgroup of 256 threads per
+// (sequence, head) has to fit a launch.
+constexpr bool small_layer_attention(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+{
+    return row <= SMALL_LAYER_ROW && row % 128 == 0 && seq <= 128 && hidden / heads <= 32 && batch * heads <= MAX_WORK_ITEMS / 256;
+}
+// The rest: one round of workgroups of 16 tokens on 256 CUs, each of which reads all weights.  In a second round the kernels of their own
+// win, which read them once per 64 or 128 tokens: hidden size 384, 8192 tokens 63.5 -> 61.6, 16384 of 312 100 -> 105, 32768 163 -> 201.
+constexpr bool small_layer_tail(int64_t tokens, int64_t row, int64_t ffn_row)
+{
+    return row <= SMALL_LAYER_ROW && row % 128 == 0 && ffn_row % 128 == 0 && ffn_row <= 65536 && tokens <= 4096;
+}
+
 // LayerNorm with one row per half wave (the kernels have 256 threads: eight rows), not per wave (four).  Up to D = 1024: where
 // half waves leave fewer lanes idle (chunks of 8 values: up to 32, or 65 to 96, of which whole waves would use half
 // and three quarters) and there are rows enough to fill the chip with them; a tie goes to whole waves, which have half the

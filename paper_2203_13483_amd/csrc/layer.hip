@@ -2,7 +2,8 @@
 // LayerNorm and the attention core, each with a fused re-quantization of its
 // result for the next W4A4 linear, and the host-side sequencing of one post-LN
 // BERT layer in the int4 and in the binary16 baseline flavour.
-#include "attention.h"
+#include "layer_tail.h"
+#include "qkv_attention.h"
 
 #include <type_traits>
 
@@ -867,6 +868,7 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
     if (p->next_bits != 0 && p->next_bits != 4 && p->next_bits != 8) return MKQ_ERR_DTYPE;
     const int next_bits = p->next_bits ? p->next_bits : bits;
     if (p->batch == 0 || layer_tokens(p) == 0) return MKQ_OK;
+    if (!(p->ln_eps >= 0.0f)) return MKQ_ERR_SCALE;  // (what LayerNorm refuses)
     if (!h_in || !h_out || (want_next && !q_out_next)) return MKQ_ERR_NULL;
     if (!p->Wq_qkv || !p->Wq_ao || !p->Wq_up || !p->Wq_down || !p->sw_qkv || !p->sw_ao || !p->sw_up ||
         !p->sw_down)
@@ -898,14 +900,29 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
         if (rc != MKQ_OK) return rc;
         c0 = ws + L.c0;
     }
-    // q | k | v
-    rc = layer_linear(bits, c0, p->sx_qkv, p->Wq_qkv, p->sw_qkv, p->b_qkv, M, 3 * H, Hp, ws + L.qkv, MKQ_F16,
-                      nullptr, stream);
-    if (rc != MKQ_OK) return rc;
-    // attention context, re-quantized for the output projection
-    rc = attention_run(ws + L.qkv, p->batch, p->seq, H, p->heads, nullptr, p->sx_ao, ws + L.c1, bits, stream,
-                       p->cu_seqlens, Hp);
-    if (rc != MKQ_OK) return rc;
+    if (bits == 4 && small_layer_attention(p->batch, p->seq, H, p->heads, Hp)) {
+        const AttentionParams att = {(const uint16_t *)(ws + L.qkv), p->cu_seqlens, (int)p->batch, (int)p->seq, (int)H, (int)p->heads,
+                                     (int)(H / p->heads), 1, nullptr, ws + L.c1, p->sx_ao, 4, (int)Hp};
+        rc = run_qkv_attention({att, c0, p->Wq_qkv, p->sw_qkv, p->b_qkv, p->sx_qkv, (int)Hp, (uint16_t *)(ws + L.qkv)}, as_stream(stream));
+        if (rc != MKQ_OK) return rc;
+    } else {
+        // q | k | v
+        rc = layer_linear(bits, c0, p->sx_qkv, p->Wq_qkv, p->sw_qkv, p->b_qkv, M, 3 * H, Hp, ws + L.qkv, MKQ_F16,
+                          nullptr, stream);
+        if (rc != MKQ_OK) return rc;
+        // attention context, re-quantized for the output projection
+        rc = attention_run(ws + L.qkv, p->batch, p->seq, H, p->heads, nullptr, p->sx_ao, ws + L.c1, bits, stream,
+                           p->cu_seqlens, Hp);
+        if (rc != MKQ_OK) return rc;
+    }
+    if (bits == 4 && h_dtype == MKQ_F16 && small_layer_tail(M, Hp, Fp)) {
+        const LayerTailParams t = {(int)M, (int)H, (int)F, (int)Hp, (int)Fp, ws + L.c1, (const uint16_t *)h_in, p->Wq_ao, p->Wq_up, p->Wq_down,
+                                   p->sw_ao, p->sw_up, p->sw_down, p->b_ao, p->b_up, p->b_down, p->sx_ao, p->sx_up, p->sx_down,
+                                   p->ln1_gamma, p->ln1_beta, p->ln2_gamma, p->ln2_beta, p->ln_eps, (uint16_t *)(ws + L.u), (uint16_t *)(ws + L.h1),
+                                   (uint16_t *)(ws + L.d), (uint16_t *)h_out, ws + L.c2, ws + L.c3, want_next ? q_out_next : nullptr,
+                                   want_next ? p->s_out_next : 1.0f, next_bits, (int)next_pitch};
+        return run_layer_tail(t, as_stream(stream));
+    }
     mkq_epilogue e = {};
     e.act = MKQ_ACT_NONE; e.residual = h_in; e.residual_dtype = h_dtype; e.s_next = 0.0f;
     e.q_out = nullptr; e.acc_out = nullptr;

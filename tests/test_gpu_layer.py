@@ -618,3 +618,54 @@ def test_attention_with_empty_and_one_token_sequences(mkq, heads, dk, max_seq):
                     attention_code_band(qkv[rows].astype(np.float32), int(n), H, heads, 0.05), "context codes")
     one = slice(cu[2], cu[3])  # one token: the context is that token's v
     assert np.array_equal(got[one], qkv[one, 2 * H:].astype(np.float32))
+
+
+# Layers of small hidden size (launch_rules.h, small_layer_*): q, k, v with the attention in one launch, and what follows it in another.
+# Smallest and largest of token tiles (1, 16, 17, 32, 33, 64, 65, 128), of heads (2 to 32, even and multiples of 8), of hidden rows (one and a
+# half 256-code units among them) and of FFN chunks (one column group, ragged, whole, several of both widths); tokens past one round.
+_SMALL = [(1, 1, 312, 12, 1200, None), (3, 17, 312, 12, 1200, None), (1, 32, 128, 4, 512, None), (3, 33, 384, 12, 1536, None), (2, 64, 256, 8, 8, None),
+          (2, 65, 376, 47, 1320, None), (2, 128, 384, 192, 2560, None), (1, 128, 104, 4, 768, None), (4, 20, 128, 2, 776, None), (2, 130, 256, 16, 1288, None),
+          (7, 128, 312, 12, 1200, (128, 0, 1, 32, 33, 64, 65)), (5, 40, 384, 48, 904, (40, 0, 16, 17, 1)), (34, 128, 312, 12, 1200, (128,) * 31 + (1, 127, 1))]
+
+
+@pytest.mark.parametrize("batch,seq,hidden,heads,ffn,lens", _SMALL)
+@pytest.mark.parametrize("bias", [True, False])
+def test_layers_of_small_hidden_size(mkq, batch, seq, hidden, heads, ffn, lens, bias):
+    import torch
+    from layer_checks import code_row_pitch
+    p, _ = _layer_case(batch + hidden, 1, 8, hidden, heads, ffn)
+    lens = [seq] * batch if lens is None else list(lens)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    M = int(cu[-1])
+    h = _f16(np.random.default_rng(hidden + M).standard_normal((M, hidden)))
+    ln = {k: to_dev(p[k]) for k in ("ln1_gamma", "ln1_beta", "ln2_gamma", "ln2_beta")}
+    base = {k: p[k] for k in ("hidden", "heads", "ffn", "ln_eps", "ln1_gamma", "ln1_beta", "ln2_gamma", "ln2_beta")}
+    packed, sx = {}, {}
+    for nm, step in (("qkv", 0.34), ("ao", 0.05), ("up", 0.34), ("down", 0.05)):
+        base["w_" + nm], base["sw_" + nm] = oracle.quantize_weights(p["W_" + nm])
+        base["b_" + nm] = p["b_" + nm] if bias else np.zeros_like(p["b_" + nm])
+        base["sx_" + nm] = sx[nm] = float(np.float32(step))
+        pack = mkq.mkq_pack_weights_int4 if p["W_" + nm].shape[1] % 32 == 0 else mkq.mkq_pack_weights_int4_padded
+        packed[nm] = pack(to_dev(p["W_" + nm])) + (to_dev(p["b_" + nm]),)
+    next_bits, s_next = (8, 0.03) if hidden % 64 == 0 else (4, 0.4)
+    uniform = len(set(lens)) == 1
+    layer = mkq.BertLayerInt4(batch, seq, hidden, heads, ffn, packed, sx, ln, p["ln_eps"], s_next, next_bits,
+                              cu_seqlens=None if uniform else to_dev(cu), total_tokens=0 if uniform else M)
+    if not bias:
+        for nm in ("qkv", "ao", "up", "down"):
+            setattr(layer.params, "b_" + nm, None)
+    ws = torch.full((layer.workspace_bytes(),), 0x5A, dtype=torch.uint8, device="cuda")  # stale contents
+    pitch = code_row_pitch(hidden)
+    q_next = torch.full((M, hidden if next_bits == 8 else pitch // 2), 0x5A, dtype=torch.uint8, device="cuda")
+    x = to_dev(h)
+    h_out = layer(x, ws, q_out_next=q_next)
+    torch.cuda.synchronize()
+    qn = to_np(q_next).view(np.int8) if next_bits == 8 else oracle.unpack_nibbles(to_np(q_next), pitch)
+    assert not qn[:, hidden:].any()
+    some = range(batch) if M < 1000 else (0, 1, 30, 31, 32, batch - 1) if batch > 30 else range(batch)
+    check_layer_stagewise(LayerBuffers(to_np(ws), layer.layout, M, hidden, ffn, 4), base, h.astype(np.float32), to_np(h_out).astype(np.float32),
+                          [(int(cu[b]), int(lens[b])) for b in some if lens[b]], q_next=qn[:, :hidden], s_out_next=s_next, next_bits=next_bits,
+                          what=f"layer {hidden}/{heads}/{ffn}")
+    # the output may take the input's place
+    again = layer(x, ws, h_out=x, q_out_next=q_next)
+    assert torch.equal(again, h_out)

@@ -29,6 +29,11 @@ extern "C" int first_half(int64_t sequence_heads, int q_blocks, int per_wg)
     return attention_held_first_half(sequence_heads, q_blocks, per_wg);
 }
 extern "C" bool half_waves(int64_t M, int64_t D) { return layernorm_half_waves(M, D); }
+extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+{
+    return small_layer_attention(batch, seq, hidden, heads, row);
+}
+extern "C" bool small_tail(int64_t tokens, int64_t row, int64_t ffn_row) { return small_layer_tail(tokens, row, ffn_row); }
 """
 
 
@@ -46,6 +51,8 @@ def rules(tmp_path_factory):
     lib.piece_index.argtypes = [C.c_uint, C.c_uint]
     lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
+    lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
+    lib.small_tail.argtypes, lib.small_tail.restype = [C.c_int64] * 3, C.c_bool
     return lib
 
 
@@ -134,3 +141,16 @@ def test_only_sequences_that_one_workgroup_would_have_are_shared(rules):
     assert [rules.first_half(256, q, q) for q in (1, 2, 3, 4)] == [0, 1, 2, 2]
     assert rules.first_half(256, 4, 2) == 0 and rules.first_half(256, 3, 1) == 0
     assert rules.first_half(limit // 2, 4, 4) == 2 and rules.first_half(limit // 2 + 1, 4, 4) == 0
+
+
+def test_small_layers(rules):
+    assert rules.small_attention(32, 128, 312, 12, 384) and rules.small_attention(1, 1, 128, 4, 128)
+    assert not rules.small_attention(32, 129, 312, 12, 384)   # longer than four tiles of 32 tokens
+    assert not rules.small_attention(32, 128, 384, 6, 384)    # heads of 64
+    assert not rules.small_attention(32, 128, 768, 24, 768) and not rules.small_attention(32, 128, 320, 10, 320)
+    # one workgroup of 256 threads per sequence and head
+    most = 0xFFFFFFFF // 256
+    assert rules.small_attention(most // 12, 128, 312, 12, 384) and not rules.small_attention(most // 12 + 1, 128, 312, 12, 384)
+    assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
+    assert not rules.small_tail(4097, 384, 1280)
+    assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
