@@ -41,6 +41,9 @@ int run_gemm_i4_small(const GemmI4Params &p, const void *a, int a_dtype, hipStre
 // tile kernels with 128-byte stage rows (gemm_lines.hip)
 int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int run_gemm_i8_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
+// tile kernels of launches that leave CUs idle (gemm_short.hip)
+int run_gemm_i4_short(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
+int run_gemm_i8_short(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int gemm_i4_stream_slices(const GemmI4Params &p, const SplitKScratch *scr, int forced_ks);
 
 template <class Cfg, bool FULL_STAGES, class Epi>
@@ -480,7 +483,7 @@ static int choose_rows64(const GemmI4Params &p)
     return 28;
 }
 
-// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip) in the
+// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip; 53 .. 55, gemm_short.hip) in the
 // ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
 // 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
 // rounds of tiles).  (us, 64-byte -> 128-byte rows)
@@ -488,6 +491,14 @@ static int choose_tiles(const GemmI4Params &p)
 {
     const int rows64 = choose_rows64(p);
     if ((p.K % 256) != 0) return rows64;
+    // At most one 32x64 tile per CU: 53 .. 55, K shared by as many wave groups as have whole stages.  A second tile on some CUs doubles
+    // the launch (M = 640, K = 3072, N = 768, 240 tiles, 7.5 -> 6.1; M = 680, 264 tiles, 7.5 -> 9.2).  At K = 1024 four groups are no
+    // faster than two (4.65 / 4.70), at K = 2048 they are (4.9 / 5.3); K = 1536 in thirds 5.4, in halves 5.5.
+    if (ceil_div(p.M, 32) * ceil_div(p.N, 64) <= 256) {
+        if ((p.K % 1024) == 0 && p.K > 1024) return 53;
+        if ((p.K % 768) == 0) return 54;
+        if ((p.K % 512) == 0) return 55;
+    }
     const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128), t256 = ceil_div(p.M, 256) * ceil_div(p.N, 256);
     const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32;
@@ -611,6 +622,7 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
         return launch_xsplit_by_epilogue<GemmI4DmaCfg<128, 64, 2, 2, 64, 3>, 1>(q, epi, st);
     }
     if ((cfg >= 43 && cfg <= 49) || cfg == 51) return run_gemm_i4_lines(p, epi, cfg, st);
+    if (cfg >= 53 && cfg <= 55) return run_gemm_i4_short(p, epi, cfg, st);
     switch (cfg) {
     case 2: return launch_gemm_i4<GemmI4Cfg<128, 128, 2, 2, 64>>(p, st);
     case 3: return launch_gemm_i4<GemmI4Cfg<64, 64, 2, 2, 64>>(p, st);
@@ -646,6 +658,8 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
 
 // Tile choice of the 8-bit linear, from sweeps of every configuration at 2200 calls (as for 4 bits, with the general epilogue's
 // forms; M to 65536; us, best 64-byte-row choice -> here):
+//   55, 32x64, at most one per CU, K in halves: M = 440, K = N = 768 with a residual 5.0 -> 4.6, K = 3072 7.6 -> 6.9; M = 100, K = 1024,
+//       N = 4096 with GELU 5.75 -> 5.2; two on some CUs are slower (M = 680, K = N = 768 5.1 -> 6.8)
 //   47, 64x64, its long k loop shared by two wave groups: M = 440, K = 3072, N = 768 12.1 -> 8.4
 //   43, 64x64, up to three per CU (M = 4096, K = 3072, N = 768 25.1 -> 20.3), and where the epilogue is long up to six (GELU,
 //       M = 1280, K = 1024, N = 4096 17.1 -> 13.9) or four (residual, short k: M = 5120, K = N = 768 10.7 -> 9.3)
@@ -665,6 +679,7 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
 static int choose_tiles_i8(const GemmI4Params &p)
 {
     if ((p.K % 128) != 0) return choose_rows64(p);
+    if ((p.K % 256) == 0 && p.K >= 512 && ceil_div(p.M, 32) * ceil_div(p.N, 64) <= 256) return 55;
     const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
     const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32, whole = (p.N % 8) == 0;
@@ -704,6 +719,7 @@ int run_gemm_i8(const GemmI4Params &p, hipStream_t st, int forced_cfg = -1)
     if (epi == EPI_I4 || epi == EPI_I4_GELU) epi = EPI_GENERIC;
     const int cfg = forced_cfg >= 0 ? forced_cfg : choose_tiles_i8(p);
     if ((cfg >= 43 && cfg <= 47) || cfg == 51 || cfg == 52) return run_gemm_i8_lines(p, epi, cfg, st);
+    if (cfg == 55) return run_gemm_i8_short(p, epi, cfg, st);
     switch (cfg) {
     case 18: return launch_i8_by_epilogue<GemmI4DmaCfg<256, 128, 2, 2, 64, 3>>(p, epi, st);
     case 29: return launch_i8_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 64, 3>>(p, epi, st);
@@ -1161,11 +1177,12 @@ extern "C" int mkq_init(void)
     int rc = setup_gemm_i4_stream(p, nullptr);
     // (the configurations that split K across workgroups only look at the scratch area's size here)
     const SplitKScratch any_scratch = {reinterpret_cast<unsigned *>(16), reinterpret_cast<int32_t *>(16), (size_t)1 << 40};
-    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 60, 61, 62}) {
+    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 53, 54, 55, 60, 61, 62}) {
         // one pass per epilogue class: the parameter block is made to classify as each in turn
         for (int e = 0; e < 8 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
+            if (cfg == 54) q.K = 768;
             q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : e == 2 ? MKQ_F32 : e == 3 ? MKQ_F16 : e == 7 ? MKQ_F32 : MKQ_I4;
             if (e == 3) { q.residual = &q; q.residual_dtype = MKQ_F16; }
             if (e == 4 || e == 7) q.act = MKQ_ACT_GELU;
@@ -1174,7 +1191,7 @@ extern "C" int mkq_init(void)
             if (cfg < 10 && e == 0) e = 6;  // the register-staged kernel has two epilogues: one for all, and the last
         }
     }
-    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47, 51, 52}) {  // the tile shapes of the 8-bit path
+    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47, 51, 52, 55}) {  // the tile shapes of the 8-bit path
         for (int e = 0; e < 7 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
@@ -1354,7 +1371,7 @@ extern "C" int mkq_tuning_linear_int8(const int8_t *a, float s_x, const int8_t *
                                       int out_dtype, const mkq_epilogue *epi, void *stream, int config)
 {
     if (config != -1 && config != 18 && config != 27 && config != 28 && config != 29 && config != 30 &&
-        !(config >= 43 && config <= 47 && config != 45) && config != 51 && config != 52)
+        !(config >= 43 && config <= 47 && config != 45) && config != 51 && config != 52 && config != 55)
         return MKQ_ERR_UNSUPPORTED;
     return linear_int8_run(a, s_x, Wq, s_w, bias, M, N, K, out, out_dtype, epi, stream, config);
 }

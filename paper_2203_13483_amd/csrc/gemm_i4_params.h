@@ -323,16 +323,22 @@ struct EpiShuffle {
                                    (Cfg::LDS_BYTES + EXTRA_LDS) * Cfg::WGS_PER_CU <= 160 * 1024;
 };
 
+
+// Waves of a single 32x32 tile have no units for the residual's latency to hide behind, but registers to spare: theirs is
+// fetched before the tile's k loop (a lane's two pieces of 16 bytes).
+template <class Cfg, class Epi>
+constexpr bool residual_early() { return EpiShuffle<Cfg>::usable && Epi::res16 && Cfg::TM * Cfg::TN == 1; }
+
 __device__ __forceinline__ int4 acc_bits(int a, int b, int c, int d) { return make_int4(a, b, c, d); }
 __device__ __forceinline__ int4 acc_bits(float a, float b, float c, float d)
 {
     return make_int4(__float_as_int(a), __float_as_int(b), __float_as_int(c), __float_as_int(d));
 }
 
-template <class Cfg, class Epi, bool SCALED = true, class AccV>
+template <class Cfg, class Epi, bool SCALED = true, bool EARLY = false, class AccV>
 __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, AccV (&acc)[Cfg::TM][Cfg::TN],
                                                       int m0, int n0, int wm, int wn, int lane, uint8_t *scr,
-                                                      float *sc_lds)
+                                                      float *sc_lds, const uint4 *early = nullptr)
 {
     using Sh = EpiShuffle<Cfg>;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, WTN = Cfg::WTN;
@@ -379,7 +385,10 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, Acc
                          : make_uint4(0, 0, 0, 0);
         }
     };
-    if constexpr (Epi::res16) {
+    if constexpr (EARLY) {
+        res_q[0][0] = early[0];
+        res_q[0][1] = early[1];
+    } else if constexpr (Epi::res16) {
         static_for<(RES_AHEAD < UNITS ? RES_AHEAD : UNITS)>([&](auto uc) { fetch_residual(uc, res_q[decltype(uc)::value]); });
     }
 
