@@ -538,6 +538,7 @@ static int choose_tiles(const GemmI4Params &p)
         // (K = 3072, N = 768, M = 3072 14.0 -> 13.1; K = 4096, N = 1024, M = 2560 16.9 -> 15.8; layers of 24 x 128 tokens 72.2 -> 70.2,
         // of 16 x 200 79.2 -> 77.9; with all 256 taken, 32 x 128, 78.6 -> 79.1)
         if (p.K >= (gelu ? 2048 : 1536)) return !split ? rows64 : fixed && ceil_div(p.M, 128) * ceil_div(p.N, 96) < 256 ? 51 : 46;
+        return fixed ? 49 : rows64;
     }
     if (!fixed) return rows64;
     // one and a half rounds of 43 still beat two of anything larger where the epilogue is long (M = 1536, K = 768, N = 3072 with
