@@ -25,9 +25,7 @@ extern "C" {
  *                          on eight waves, 46 128x128, 47 64x64 and 48 128x64 with K split between two wave
  *                          groups (K % 512 == 0), 49 128x128 on eight waves
  *             51           likewise, 128x96 with K split between two wave groups (K % 512 == 0)
- *             53, 54, 55   likewise, 32x64 with K split between four (K % 1024 == 0), three (K % 768 == 0) and two wave
- *                          groups (K % 512 == 0)
- *             30           first few-token kernel (M <= 128, K % 256 == 0; waves split K, operands through registers)
+ *             30           few-token kernel (M <= 128, K % 256 == 0; waves split K, each with operand pieces of its own)
  *             50           few-token weight-streaming kernel (M <= 128, K % 256 == 0)
  *             60, 61, 62   128 x 128, 64 x 64 (two wave groups) and 128 x 64 tiles with the k loop also split
  *                          across workgroups (needs epi->splitk_scratch; k_slices must divide K's 128-code
@@ -48,8 +46,8 @@ int mkq_tuning_linear_int4_stream(const void *a, int a_dtype, float s_x, const u
                                   int prefetch_stages, int k_slices);
 
 /* mkq_linear_int8 with config -1 (the library's choice), 18 (256x128 tiles), 29 (128x128), 28 (128x64), 27 (64x64),
- * 43 (64x64), 44 (256x128), 46 (128x128), 47 (64x64, K split between two wave groups: K % 256 == 0), 51 (128x96),
- * 52 (256x192) or 55 (32x64, K split between two wave groups) with stages of 128-byte rows (K % 128 == 0), or 30 (few-token weight-streaming kernel: M <= 64, K % 128 == 0). */
+ * 43 (64x64), 44 (256x128), 46 (128x128), 47 (64x64, K split between two wave groups: K % 256 == 0), 51 (128x96) or
+ * 52 (256x192) with stages of 128-byte rows (K % 128 == 0), or 30 (few-token kernel: M <= 64, K % 128 == 0). */
 int mkq_tuning_linear_int8(const int8_t *a, float s_x, const int8_t *Wq, const float *s_w, const float *bias,
                            int64_t M, int64_t N, int64_t K, void *out, int out_dtype, const mkq_epilogue *epi,
                            void *stream, int config);

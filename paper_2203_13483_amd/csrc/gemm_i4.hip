@@ -41,9 +41,9 @@ int run_gemm_i4_small(const GemmI4Params &p, const void *a, int a_dtype, hipStre
 // tile kernels with 128-byte stage rows (gemm_lines.hip)
 int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
 int run_gemm_i8_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
-// tile kernels of launches that leave CUs idle (gemm_short.hip)
-int run_gemm_i4_short(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
-int run_gemm_i8_short(const GemmI4Params &p, int epi, int cfg, hipStream_t st);
+// few tokens and small linears (gemm_few.hip)
+int run_gemm_few(const GemmI4Params &p, int bits, FewTile t, hipStream_t st);
+int setup_gemm_few();
 int gemm_i4_stream_slices(const GemmI4Params &p, const SplitKScratch *scr, int forced_ks);
 
 template <class Cfg, bool FULL_STAGES, class Epi>
@@ -220,174 +220,6 @@ __global__ __launch_bounds__(Cfg::THREADS) void gemm_i4_kernel(const GemmI4Param
     }
 }
 
-// ---------------------------------------------------------------------------------
-// Few tokens (M <= 128): the linear is a stream of the weight matrix, bound by HBM.
-// One workgroup of 8 waves owns 32 output channels; the waves split K between them,
-// each fetching its packed fragments straight from global memory into registers (no
-// reuse between waves, so no LDS staging) with every load of its slice in flight at
-// once, and the partial accumulators meet in LDS.  The activations ([M, K/2] bytes,
-// resident in L2) are read the same way.  Waves 0 .. TB-1 then each sum one 32-token
-// block over the 8 partials and run the generic epilogue on it.
-struct SkinnyCfg {
-    static constexpr int BM = 32, BN = 32, WGM = 1, WGN = 1, RB = 64;
-    static constexpr int THREADS = 512, WAVES = 8;
-    static constexpr int WTM = 32, WTN = 32, TM = 1, TN = 1;
-};
-
-// BITS = 8: the operands are int8 codes (the 8-bit linear): a 16-byte piece is one MFMA operand as it is.
-template <int TB, int UG, int BITS, class Epi>
-__global__ __launch_bounds__(SkinnyCfg::THREADS) void gemm_i4_skinny_kernel(const GemmI4Params p)
-{
-    __shared__ __attribute__((aligned(16))) int red[2][SkinnyCfg::WAVES][4][64][4];  // 64 KiB
-
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int fr = lane & 31, fh = lane >> 5;
-    const int n0 = blockIdx.x * 32;
-    const int row_bytes = p.K * BITS / 8;
-    // A row is cut into groups of 128 bytes (256 4-bit codes), one cache line; a lane fetches
-    // 64 contiguous bytes of its row per group (four 16-byte loads = eight k steps), so the
-    // four loads of a group touch the same 32 lines.  Which codes a lane holds does not
-    // matter to the dot product as long as weights and activations agree.
-    const int groups = row_bytes / 128;
-    const int gpw = (groups + SkinnyCfg::WAVES - 1) / SkinnyCfg::WAVES;
-    const int g_begin = wave * gpw;
-    const int g_end = (g_begin + gpw) < groups ? (g_begin + gpw) : groups;
-
-    int wrow = n0 + w_row_perm(fr);
-    wrow = wrow < p.N ? wrow : p.N - 1;  // rows past the edge are never stored
-    const uint8_t *wp = p.W + (size_t)wrow * row_bytes + fh * 64;
-    const uint8_t *ap[TB];
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        int tok = tb * 32 + fr;
-        tok = tok < p.M ? tok : p.M - 1;
-        ap[tb] = p.A + (size_t)tok * row_bytes + fh * 64;
-    }
-
-    v16i acc[TB];
-#pragma unroll
-    for (int tb = 0; tb < TB; ++tb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[tb][v] = 0;
-
-    // The epilogue's per-channel scales and biases are first touched here, by the waves that will run
-    // it, so that their round trip to memory overlaps the weight stream instead of following it.
-    float touched = 0.0f;
-    if (wave < 2) {
-        int n = n0 + fr;
-        n = n < p.N ? n : p.N - 1;
-        touched = p.s_w[n] + (p.bias ? p.bias[n] : 0.0f);
-    }
-
-    // chunks of UG groups, the next chunk's loads in flight while this one is multiplied
-    constexpr int NL = 4 * UG;  // 16-byte loads per chunk per operand row
-    uint4 fw[2][NL], fa[2][TB][NL];
-    auto fetch = [&](int buf, int g0) {
-#pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            int g = g0 + u / 4;
-            g = g < g_end ? g : g_end - 1;  // tail: fetched again, not used
-            g = g < 0 ? 0 : g;
-            const int off = g * 128 + (u % 4) * 16;
-            fw[buf][u] = *reinterpret_cast<const uint4 *>(wp + off);
-#pragma unroll
-            for (int tb = 0; tb < TB; ++tb) fa[buf][tb][u] = *reinterpret_cast<const uint4 *>(ap[tb] + off);
-        }
-    };
-    auto multiply = [&](int buf, int g0) {
-#pragma unroll
-        for (int u = 0; u < NL; ++u) {
-            if (g0 + u / 4 < g_end) {
-                if constexpr (BITS == 8) {
-                    const v4i w = {(int)fw[buf][u].x, (int)fw[buf][u].y, (int)fw[buf][u].z, (int)fw[buf][u].w};
-#pragma unroll
-                    for (int tb = 0; tb < TB; ++tb) {
-                        const v4i a = {(int)fa[buf][tb][u].x, (int)fa[buf][tb][u].y, (int)fa[buf][tb][u].z, (int)fa[buf][tb][u].w};
-                        acc[tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, a, acc[tb], 0, 0, 0);
-                    }
-                } else {
-                    const v4i w0 = widen(fw[buf][u].x, fw[buf][u].y), w1 = widen(fw[buf][u].z, fw[buf][u].w);
-#pragma unroll
-                    for (int tb = 0; tb < TB; ++tb) {
-                        acc[tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w0, widen(fa[buf][tb][u].x, fa[buf][tb][u].y), acc[tb], 0, 0, 0);
-                        acc[tb] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w1, widen(fa[buf][tb][u].z, fa[buf][tb][u].w), acc[tb], 0, 0, 0);
-                    }
-                }
-            }
-        }
-    };
-    if (g_begin < g_end) {
-        fetch(0, g_begin);
-        for (int g0 = g_begin; g0 < g_end; g0 += 2 * UG) {
-            if (g0 + UG < g_end) fetch(1, g0 + UG);
-            multiply(0, g0);
-            if (g0 + 2 * UG < g_end) fetch(0, g0 + 2 * UG);
-            if (g0 + UG < g_end) multiply(1, g0 + UG);
-        }
-    }
-
-    asm volatile("" ::"v"(touched));  // (keeps the early loads)
-    // reduce over the 8 waves, two token blocks per pass through LDS
-#pragma unroll
-    for (int pass = 0; pass < (TB + 1) / 2; ++pass) {
-        if (pass) __syncthreads();
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int tb = 2 * pass + h;
-            if (tb < TB) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    *reinterpret_cast<int4 *>(&red[h][wave][q][lane][0]) =
-                        make_int4(acc[tb][4 * q], acc[tb][4 * q + 1], acc[tb][4 * q + 2], acc[tb][4 * q + 3]);
-            }
-        }
-        __syncthreads();
-        if (wave < 2 && 2 * pass + wave < TB) {
-            v16i sum[1][1];
-#pragma unroll
-            for (int v = 0; v < 16; ++v) sum[0][0][v] = 0;
-#pragma unroll
-            for (int w = 0; w < SkinnyCfg::WAVES; ++w)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int4 t = *reinterpret_cast<const int4 *>(&red[wave][w][q][lane][0]);
-                    sum[0][0][4 * q] += t.x; sum[0][0][4 * q + 1] += t.y;
-                    sum[0][0][4 * q + 2] += t.z; sum[0][0][4 * q + 3] += t.w;
-                }
-            gemm_i4_epilogue<SkinnyCfg, Epi>(p, sum, (2 * pass + wave) * 32, n0, 0, 0, fr, fh);
-        }
-    }
-}
-
-template <int TB, int UG, int BITS = 4>
-static int launch_skinny(const GemmI4Params &p, hipStream_t st)
-{
-    if (p.setup_only) return MKQ_OK;
-    const unsigned grid = (unsigned)ceil_div(p.N, 32);
-    if (epi_gelu_tail(p.act, p.out_dtype)) gemm_i4_skinny_kernel<TB, UG, BITS, EpiGeluTail><<<grid, SkinnyCfg::THREADS, 0, st>>>(p);
-    else gemm_i4_skinny_kernel<TB, UG, BITS, EpiGeneric><<<grid, SkinnyCfg::THREADS, 0, st>>>(p);
-    return launch_status();
-}
-
-// The same kernel on int8 codes (rows of K bytes: K % 128 == 0), M <= 64.
-static int run_gemm_i8_skinny(const GemmI4Params &p, hipStream_t st)
-{
-    if (p.M <= 32) return p.K >= 4096 ? launch_skinny<1, 1, 8>(p, st) : launch_skinny<1, 2, 8>(p, st);
-    return launch_skinny<2, 2, 8>(p, st);
-}
-
-static int run_gemm_i4_skinny(const GemmI4Params &p, hipStream_t st)
-{
-    // long rows: one group per chunk keeps the wave under 128 registers, so two workgroups share a CU and
-    // one's ramp and reduction overlap the other's stream (4-6 % at K >= 8192, a loss of 3 % at K = 4096)
-    if (p.M <= 32) return p.K >= 8192 ? launch_skinny<1, 1>(p, st) : launch_skinny<1, 2>(p, st);
-    if (p.M <= 64) return launch_skinny<2, 2>(p, st);
-    if (p.M <= 96) return launch_skinny<3, 1>(p, st);
-    return launch_skinny<4, 1>(p, st);
-}
-
 template <class Cfg, bool FULL, class Epi>
 static int launch_one(const GemmI4Params &p, int64_t tiles, hipStream_t st)
 {
@@ -483,7 +315,7 @@ static int choose_rows64(const GemmI4Params &p)
     return 28;
 }
 
-// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip; 53 .. 55, gemm_short.hip) in the
+// Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip) in the
 // ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
 // 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
 // rounds of tiles).  (us, 64-byte -> 128-byte rows)
@@ -491,14 +323,6 @@ static int choose_tiles(const GemmI4Params &p)
 {
     const int rows64 = choose_rows64(p);
     if ((p.K % 256) != 0) return rows64;
-    // At most one 32x64 tile per CU: 53 .. 55, K shared by as many wave groups as have whole stages.  A second tile on some CUs doubles
-    // the launch (M = 640, K = 3072, N = 768, 240 tiles, 7.5 -> 6.1; M = 680, 264 tiles, 7.5 -> 9.2).  At K = 1024 four groups are no
-    // faster than two (4.65 / 4.70), at K = 2048 they are (4.9 / 5.3); K = 1536 in thirds 5.4, in halves 5.5.
-    if (ceil_div(p.M, 32) * ceil_div(p.N, 64) <= 256) {
-        if ((p.K % 1024) == 0 && p.K > 1024) return 53;
-        if ((p.K % 768) == 0) return 54;
-        if ((p.K % 512) == 0) return 55;
-    }
     const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128), t256 = ceil_div(p.M, 256) * ceil_div(p.N, 256);
     const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32;
@@ -585,13 +409,15 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
     const bool dma_ok = (p.K % 128) == 0;  // whole 64-byte stages
     const int epi = classify_epilogue(p);
     if (cfg == 50) return gemm_i4_stream_ok(p) ? run_gemm_i4_stream(p, scr, forced_ks, st) : MKQ_ERR_UNSUPPORTED;
-    if (cfg == 30) return (p.M <= 128 && (p.K % 256) == 0) ? run_gemm_i4_skinny(p, st) : MKQ_ERR_UNSUPPORTED;
-    // Few tokens on canonical weights: up to 64 tokens the register kernel (the faster of the two at every
-    // measured size); 65 .. 128 tokens against a large weight matrix the ring kernel with its shared
-    // activation stages (60 instead of 88 us at K = N = 16384), against a small one the tile kernels.
-    if (cfg < 0 && p.M <= 64 && (p.K % 256) == 0) return run_gemm_i4_skinny(p, st);
-    if (cfg < 0 && gemm_i4_stream_ok(p) && (int64_t)p.N * p.K >= ((int64_t)1 << 27))
+    if (cfg == 30) return (p.M <= 128 && (p.K % 256) == 0) ? run_gemm_few(p, 4, few_tile_or_largest(p.M, p.N, p.K / 2, 4), st) : MKQ_ERR_UNSUPPORTED;
+    // 65 .. 128 tokens against a large weight matrix take the ring kernel with its shared activation stages (60 instead of 88 us at
+    // K = N = 16384 with operands through registers)
+    if (cfg < 0 && p.M > 64 && gemm_i4_stream_ok(p) && (int64_t)p.N * p.K >= ((int64_t)1 << 27))
         return run_gemm_i4_stream(p, scr, forced_ks, st);
+    if (cfg < 0) {
+        const FewTile few = few_tile(p.M, p.N, p.K / 2, 4);
+        if (few != FEW_NONE) return run_gemm_few(p, 4, few, st);
+    }
     if (cfg < 0) {
         if (!dma_ok) {
             cfg = 3;
@@ -623,7 +449,6 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
         return launch_xsplit_by_epilogue<GemmI4DmaCfg<128, 64, 2, 2, 64, 3>, 1>(q, epi, st);
     }
     if ((cfg >= 43 && cfg <= 49) || cfg == 51) return run_gemm_i4_lines(p, epi, cfg, st);
-    if (cfg >= 53 && cfg <= 55) return run_gemm_i4_short(p, epi, cfg, st);
     switch (cfg) {
     case 2: return launch_gemm_i4<GemmI4Cfg<128, 128, 2, 2, 64>>(p, st);
     case 3: return launch_gemm_i4<GemmI4Cfg<64, 64, 2, 2, 64>>(p, st);
@@ -659,8 +484,6 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
 
 // Tile choice of the 8-bit linear, from sweeps of every configuration at 2200 calls (as for 4 bits, with the general epilogue's
 // forms; M to 65536; us, best 64-byte-row choice -> here):
-//   55, 32x64, at most one per CU, K in halves: M = 440, K = N = 768 with a residual 5.0 -> 4.6, K = 3072 7.6 -> 6.9; M = 100, K = 1024,
-//       N = 4096 with GELU 5.75 -> 5.2; two on some CUs are slower (M = 680, K = N = 768 5.1 -> 6.8)
 //   47, 64x64, its long k loop shared by two wave groups: M = 440, K = 3072, N = 768 12.1 -> 8.4
 //   43, 64x64, up to three per CU (M = 4096, K = 3072, N = 768 25.1 -> 20.3), and where the epilogue is long up to six (GELU,
 //       M = 1280, K = 1024, N = 4096 17.1 -> 13.9) or four (residual, short k: M = 5120, K = N = 768 10.7 -> 9.3)
@@ -680,7 +503,6 @@ static int launch_i8_by_epilogue(const GemmI4Params &p, int epi, hipStream_t st)
 static int choose_tiles_i8(const GemmI4Params &p)
 {
     if ((p.K % 128) != 0) return choose_rows64(p);
-    if ((p.K % 256) == 0 && p.K >= 512 && ceil_div(p.M, 32) * ceil_div(p.N, 64) <= 256) return 55;
     const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64), t128 = ceil_div(p.M, 128) * ceil_div(p.N, 128);
     const int64_t t256x128 = ceil_div(p.M, 256) * ceil_div(p.N, 128);
     const bool gelu = p.act == MKQ_ACT_GELU, res = p.residual != nullptr, f32 = p.out_dtype == MKQ_F32, whole = (p.N % 8) == 0;
@@ -710,17 +532,15 @@ static int choose_tiles_i8(const GemmI4Params &p)
 int run_gemm_i8(const GemmI4Params &p, hipStream_t st, int forced_cfg = -1)
 {
     if ((p.K % 64) != 0) return MKQ_ERR_UNSUPPORTED;
-    // few tokens: the linear is a stream of the weight matrix (the tile kernels take 24 us for 16 MiB of
-    // weights where this takes 8)
-    if (forced_cfg == 30) return (p.M <= 64 && (p.K % 128) == 0) ? run_gemm_i8_skinny(p, st) : MKQ_ERR_UNSUPPORTED;
-    // (33 .. 64 tokens only against at least 4 MiB of weights: below that the tile kernels are 10-20 % faster)
-    if (forced_cfg < 0 && (p.K % 128) == 0 && (p.M <= 32 || (p.M <= 64 && (int64_t)p.N * p.K >= ((int64_t)4 << 20))))
-        return run_gemm_i8_skinny(p, st);
+    if (forced_cfg == 30) return (p.M <= 64 && (p.K % 128) == 0) ? run_gemm_few(p, 8, few_tile_or_largest(p.M, p.N, p.K, 8), st) : MKQ_ERR_UNSUPPORTED;
+    if (forced_cfg < 0) {
+        const FewTile few = few_tile(p.M, p.N, p.K, 8);
+        if (few != FEW_NONE) return run_gemm_few(p, 8, few, st);
+    }
     int epi = classify_epilogue(p);
     if (epi == EPI_I4 || epi == EPI_I4_GELU) epi = EPI_GENERIC;
     const int cfg = forced_cfg >= 0 ? forced_cfg : choose_tiles_i8(p);
     if ((cfg >= 43 && cfg <= 47) || cfg == 51 || cfg == 52) return run_gemm_i8_lines(p, epi, cfg, st);
-    if (cfg == 55) return run_gemm_i8_short(p, epi, cfg, st);
     switch (cfg) {
     case 18: return launch_i8_by_epilogue<GemmI4DmaCfg<256, 128, 2, 2, 64, 3>>(p, epi, st);
     case 29: return launch_i8_by_epilogue<GemmI4DmaCfg<128, 128, 2, 2, 64, 3>>(p, epi, st);
@@ -1178,12 +998,11 @@ extern "C" int mkq_init(void)
     int rc = setup_gemm_i4_stream(p, nullptr);
     // (the configurations that split K across workgroups only look at the scratch area's size here)
     const SplitKScratch any_scratch = {reinterpret_cast<unsigned *>(16), reinterpret_cast<int32_t *>(16), (size_t)1 << 40};
-    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 53, 54, 55, 60, 61, 62}) {
+    for (int cfg : {2, 3, 11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 60, 61, 62}) {
         // one pass per epilogue class: the parameter block is made to classify as each in turn
         for (int e = 0; e < 8 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
-            if (cfg == 54) q.K = 768;
             q.out_dtype = e == 0 ? MKQ_F16 : e == 1 ? MKQ_BF16 : e == 2 ? MKQ_F32 : e == 3 ? MKQ_F16 : e == 7 ? MKQ_F32 : MKQ_I4;
             if (e == 3) { q.residual = &q; q.residual_dtype = MKQ_F16; }
             if (e == 4 || e == 7) q.act = MKQ_ACT_GELU;
@@ -1192,7 +1011,7 @@ extern "C" int mkq_init(void)
             if (cfg < 10 && e == 0) e = 6;  // the register-staged kernel has two epilogues: one for all, and the last
         }
     }
-    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47, 51, 52, 55}) {  // the tile shapes of the 8-bit path
+    for (int cfg : {18, 29, 28, 27, 43, 44, 46, 47, 51, 52}) {  // the tile shapes of the 8-bit path
         for (int e = 0; e < 7 && rc == MKQ_OK; ++e) {
             GemmI4Params q = p;
             q.out = &q; q.s_next = 1.0f;
@@ -1213,6 +1032,7 @@ extern "C" int mkq_init(void)
             rc = run_gemm_e3m2(q, nullptr, cfg);
         }
     }
+    if (rc == MKQ_OK) rc = setup_gemm_few();
     if (rc == MKQ_OK) rc = setup_gemm_f16();
     if (rc == MKQ_OK) rc = setup_attention();
     if (rc == MKQ_OK) rc = setup_qkv_attention();
@@ -1372,7 +1192,7 @@ extern "C" int mkq_tuning_linear_int8(const int8_t *a, float s_x, const int8_t *
                                       int out_dtype, const mkq_epilogue *epi, void *stream, int config)
 {
     if (config != -1 && config != 18 && config != 27 && config != 28 && config != 29 && config != 30 &&
-        !(config >= 43 && config <= 47 && config != 45) && config != 51 && config != 52 && config != 55)
+        !(config >= 43 && config <= 47 && config != 45) && config != 51 && config != 52)
         return MKQ_ERR_UNSUPPORTED;
     return linear_int8_run(a, s_x, Wq, s_w, bias, M, N, K, out, out_dtype, epi, stream, config);
 }

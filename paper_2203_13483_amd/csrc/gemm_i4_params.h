@@ -123,6 +123,12 @@ inline bool epi_gelu_tail(int act, int out_dtype)
     return act == MKQ_ACT_GELU && (out_dtype == MKQ_F32 || out_dtype == MKQ_BF16);
 }
 
+// 16-channel halves of a 32-channel tile that a kernel has (Cfg::HALVES, where it is not both)
+template <class Cfg, class = void>
+struct EpiHalves { static constexpr int value = 2; };
+template <class Cfg>
+struct EpiHalves<Cfg, std::void_t<decltype(Cfg::HALVES)>> { static constexpr int value = Cfg::HALVES; };
+
 // Epilogue of one finished tile (m0, n0 = its first token / channel; wm, wn = the
 // wave's position in the workgroup; fr = lane % 32, fh = lane / 32).
 // Register v of a lane holds channel 16*(v/8) + 8*fh + v%8 of its 32-channel tile,
@@ -145,7 +151,7 @@ __device__ __forceinline__ void gemm_i4_epilogue(const GemmI4Params &p, AccV (&a
     const bool need_y = (out_dtype >= 0) || q_extra;
     static_for<TN>([&](auto tc) {
         constexpr int t = decltype(tc)::value;
-        static_for<2>([&](auto Gc) {
+        static_for<EpiHalves<Cfg>::value>([&](auto Gc) {
             constexpr int G = decltype(Gc)::value;
             // keep the scheduler from hoisting every unit's loads to the top (register spills)
             __builtin_amdgcn_sched_barrier(0);
@@ -323,22 +329,16 @@ struct EpiShuffle {
                                    (Cfg::LDS_BYTES + EXTRA_LDS) * Cfg::WGS_PER_CU <= 160 * 1024;
 };
 
-
-// Waves of a single 32x32 tile have no units for the residual's latency to hide behind, but registers to spare: theirs is
-// fetched before the tile's k loop (a lane's two pieces of 16 bytes).
-template <class Cfg, class Epi>
-constexpr bool residual_early() { return EpiShuffle<Cfg>::usable && Epi::res16 && Cfg::TM * Cfg::TN == 1; }
-
 __device__ __forceinline__ int4 acc_bits(int a, int b, int c, int d) { return make_int4(a, b, c, d); }
 __device__ __forceinline__ int4 acc_bits(float a, float b, float c, float d)
 {
     return make_int4(__float_as_int(a), __float_as_int(b), __float_as_int(c), __float_as_int(d));
 }
 
-template <class Cfg, class Epi, bool SCALED = true, bool EARLY = false, class AccV>
+template <class Cfg, class Epi, bool SCALED = true, class AccV>
 __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, AccV (&acc)[Cfg::TM][Cfg::TN],
                                                       int m0, int n0, int wm, int wn, int lane, uint8_t *scr,
-                                                      float *sc_lds, const uint4 *early = nullptr)
+                                                      float *sc_lds)
 {
     using Sh = EpiShuffle<Cfg>;
     constexpr int TM = Cfg::TM, TN = Cfg::TN, WTN = Cfg::WTN;
@@ -385,10 +385,7 @@ __device__ __forceinline__ void gemm_i4_epilogue_rows(const GemmI4Params &p, Acc
                          : make_uint4(0, 0, 0, 0);
         }
     };
-    if constexpr (EARLY) {
-        res_q[0][0] = early[0];
-        res_q[0][1] = early[1];
-    } else if constexpr (Epi::res16) {
+    if constexpr (Epi::res16) {
         static_for<(RES_AHEAD < UNITS ? RES_AHEAD : UNITS)>([&](auto uc) { fetch_residual(uc, res_q[decltype(uc)::value]); });
     }
 

@@ -10,6 +10,28 @@
 
 namespace mkq {
 
+template <class Cfg, int BITS, int KS = 1>
+static int launch_lines(const GemmI4Params &p, int epi, hipStream_t st)
+{
+    if ((p.K % (1024 / BITS * KS)) != 0) return MKQ_ERR_UNSUPPORTED;
+    switch (epi) {
+    case EPI_F16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, BITS, KS>(p, st);
+    case EPI_BF16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_BF16, false, false>, BITS, KS>(p, st);
+    case EPI_F32: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, BITS, KS>(p, st);
+    case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, BITS, KS>(p, st);
+    case EPI_I4_GELU:
+        if constexpr (BITS == 4) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, true>, BITS, KS>(p, st);
+        break;
+    case EPI_I4:
+        if constexpr (BITS == 4) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, false>, BITS, KS>(p, st);
+        break;
+    case EPI_I8_GELU:
+        if constexpr (BITS == 8) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I8, false, true>, BITS, KS>(p, st);
+        break;
+    }
+    return launch_gemm_i4_dma_generic<Cfg, BITS, KS>(p, st);
+}
+
 int run_gemm_i4_lines(const GemmI4Params &p, int epi, int cfg, hipStream_t st)
 {
     switch (cfg) {

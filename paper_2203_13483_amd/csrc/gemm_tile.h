@@ -78,7 +78,7 @@ constexpr int PRIO_SLICE_LOG2 = 15;
 // 64-byte stage is then two k steps of 32 codes and nothing is widened.  BITS = 16: binary16 operands (the
 // baseline linear): a 64-byte stage is two k steps of 16 values, the accumulators are binary32 and the
 // epilogue adds the bias without a scale.
-// KSPLIT = 2, 3 or 4: the workgroup is that many groups of Cfg::WAVES waves, each running this
+// KSPLIT = 2 or 4: the workgroup is that many groups of Cfg::WAVES waves, each running this
 // pipeline with a ring of its own over one share of K (for launches with few tiles and a long
 // k loop, where a lone wave per SIMD is bound by its own instruction stream); the other groups'
 // partial accumulators meet the first group's in LDS at the end of a tile and the first group
@@ -99,7 +99,7 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
     static_assert(BITS != 16 || (!XS && KSPLIT == 1), "partial sums across workgroups and wave groups are integers");
     constexpr bool SCALED = BITS != 16;  // the accumulator is a sum of codes
     using Acc = typename std::conditional<SCALED, v16i, v16f>::type;
-    static_assert(KSPLIT >= 1 && KSPLIT <= 4, "one to four wave groups");
+    static_assert(KSPLIT == 1 || KSPLIT == 2 || KSPLIT == 4, "one, two or four wave groups");
     constexpr int BM = Cfg::BM, BN = Cfg::BN, RB = Cfg::RB, CH = Cfg::CH;
     constexpr int TM = Cfg::TM, TN = Cfg::TN;
     constexpr int S = Cfg::S, LPW = Cfg::LPW;
@@ -212,22 +212,6 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
         const uint32_t w = src[2 * ks + q / 2];
         return (int)(((q & 1) ? w : (w << 4)) & 0xF0F0F0F0u);
     };
-
-    // the residual of the wave's 32x32 tile of pair `pair`, as gemm_i4_epilogue_rows deals it to the lanes
-    constexpr bool RES_EARLY = residual_early<Cfg, Epi>() && !XS;  // (XS: only the workgroup that finishes a tile needs it)
-    uint4 res_early[2];
-    auto fetch_residual = [&](int pair) {
-        int tm, tn;
-        tile_coords(pair, tiles_m, tiles_n, p.group_m, tm, tn);
-        const int n = tn * BN + wn * 32 + 8 * (lane & 3);
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int m = tm * BM + wm * 32 + (lane >> 2) + 16 * i;
-            res_early[i] = (m < p.M && n < p.N) ? *reinterpret_cast<const uint4 *>((const uint16_t *)p.residual + (int64_t)m * p.N + n)
-                                                : make_uint4(0, 0, 0, 0);
-        }
-    };
-    if (RES_EARLY && grp == 0) fetch_residual(blockIdx.x);
 
     int lt = blockIdx.x, lk = 0;  // copy cursor
     set_tile(lt);
@@ -575,7 +559,6 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
                     // the slot of the stage just finished is idle (!OWN: until every wave has passed the next
                     // boundary): each wave shuffles through the share of it that it refills itself
                     const int done_slot = (buf == 0) ? S - 1 : buf - 1;
-                    if constexpr (residual_early<Cfg, Epi>() && XS) fetch_residual(ct / ks);
                     // the scale / bias copies have landed: only the stage copies issued after them (those of
                     // INFLIGHT boundaries, one less with OWN, fewer in a shorter tile) may be in flight
                     if (kt_count >= INFLIGHT) wait_vmcnt<(INFLIGHT - (OWN ? 1 : 0)) * LPW>();
@@ -587,10 +570,9 @@ void gemm_i4_dma_kernel(const GemmI4Params p)
                                                                smem + done_slot * Cfg::STAGE_BYTES +
                                                                    wave * EpiShuffle<Cfg>::REGION, sc_lds);
                     else
-                        gemm_i4_epilogue_rows<Cfg, Epi, SCALED, residual_early<Cfg, Epi>()>(p, acc, tile_m * BM, tile_n * BN, wm, wn, lane,
+                        gemm_i4_epilogue_rows<Cfg, Epi, SCALED>(p, acc, tile_m * BM, tile_n * BN, wm, wn, lane,
                                                         smem + done_slot * Cfg::STAGE_BYTES +
-                                                            wave * EpiShuffle<Cfg>::REGION, sc_lds, res_early);
-                    if (RES_EARLY && ct + (int)gridDim.x < total_tiles) fetch_residual(ct + gridDim.x);
+                                                            wave * EpiShuffle<Cfg>::REGION, sc_lds);
                 } else {
                     gemm_i4_epilogue<Cfg, Epi, SCALED>(p, acc, tile_m * BM, tile_n * BN, wm, wn, fr, fh);
                 }
@@ -646,29 +628,6 @@ static int launch_gemm_i4_dma_generic(const GemmI4Params &p, hipStream_t st)
 {
     if (epi_gelu_tail(p.act, p.out_dtype)) return launch_gemm_i4_dma<Cfg, EpiGeluTail, BITS, KSPLIT, XS>(p, st);
     return launch_gemm_i4_dma<Cfg, EpiGeneric, BITS, KSPLIT, XS>(p, st);
-}
-
-// By epilogue, for stages of whole 128-byte lines per operand row
-template <class Cfg, int BITS, int KS = 1>
-static int launch_lines(const GemmI4Params &p, int epi, hipStream_t st)
-{
-    if ((p.K % (1024 / BITS * KS)) != 0) return MKQ_ERR_UNSUPPORTED;
-    switch (epi) {
-    case EPI_F16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, false, false>, BITS, KS>(p, st);
-    case EPI_BF16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_BF16, false, false>, BITS, KS>(p, st);
-    case EPI_F32: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F32, false, false>, BITS, KS>(p, st);
-    case EPI_F16_RES16: return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_F16, true, false>, BITS, KS>(p, st);
-    case EPI_I4_GELU:
-        if constexpr (BITS == 4) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, true>, BITS, KS>(p, st);
-        break;
-    case EPI_I4:
-        if constexpr (BITS == 4) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I4, false, false>, BITS, KS>(p, st);
-        break;
-    case EPI_I8_GELU:
-        if constexpr (BITS == 8) return launch_gemm_i4_dma<Cfg, EpiFixed<MKQ_I8, false, true>, BITS, KS>(p, st);
-        break;
-    }
-    return launch_gemm_i4_dma_generic<Cfg, BITS, KS>(p, st);
 }
 
 }  // namespace mkq

@@ -121,4 +121,39 @@ constexpr bool layernorm_half_waves(int64_t M, int64_t D)
     return D <= 1024 && M >= 2048 && (D <= 256 || (D > 512 && D <= 768) || (M + 3) / 4 > MAX_WORK_ITEMS / 256);
 }
 
+// The kernels of few tokens and small linears (gemm_few.hip): tiles of channels x tokens; _LONG: waves take 128 bytes of a row at a
+// time, not 64 (rows of 2048 bytes and more: M = 128, K = N = 4096 6.4 -> 5.8; at 1536 bytes M = 440, N = 768 5.1 -> 5.4).
+enum FewTile { FEW_NONE = -1, FEW_16x16, FEW_16x32, FEW_32x32, FEW_32x64, FEW_64x64,
+               FEW_16x16_LONG, FEW_16x32_LONG, FEW_32x32_LONG, FEW_32x64_LONG, FEW_64x64_LONG };
+constexpr int64_t few_workgroups(int64_t M, int64_t N, int channels, int tokens)
+{
+    return ((N + channels - 1) / channels) * ((M + tokens - 1) / tokens);
+}
+// The smallest tile whose workgroups are resident together (LDS: 32 KiB a workgroup of 16x16 to 128 of 64x64), since a second round
+// costs as much as the first; past that the persistent kernels take over (FEW_NONE).  us, 4 bits, binary16 out:
+// K = N = 768, M = 640 (480 / 240 workgroups) 32x32 3.4, 32x64 3.6; M = 1024 (768 / 384 / 192) 4.5, 4.4, 64x64 4.6, the persistent 64x64
+// 5.1; N = 2304, M = 440 (504 of 32x64) 4.6, persistent 4.8, M = 640 (720) 6.4, 5.7; K = 3072, N = 768, M = 1024 (384 / 192) 32x64 7.7,
+// 64x64 6.7, persistent 7.7; K = N = 4096, M = 256 (256 of 64x64) 7.8, persistent 10.8, M = 440 (448) 13.8, 13.4.  8-bit operands need no
+// widening, and the persistent kernels win earlier: K = 768, N = 3072, M = 320 (480 of 32x64) 5.5, persistent 5.0; K = 3072, N = 768,
+// M = 1024 (192 of 64x64) 8.3, 7.6; in one round of 32x64 5.7 against 7.6 (M = 440).
+constexpr FewTile few_tile(int64_t M, int64_t N, int64_t row_bytes, int bits)
+{
+    if (row_bytes % 64 != 0) return FEW_NONE;
+    const bool deep = row_bytes >= 2048 && row_bytes % 128 == 0;
+    auto kind = [&](FewTile t) { return deep ? (FewTile)(t + FEW_16x16_LONG) : t; };
+    if (M <= 16) return kind(FEW_16x16);
+    if (M <= 32) return kind(few_workgroups(M, N, 16, 32) <= (deep ? 256 : 512) ? FEW_16x32 : FEW_32x32);
+    const int64_t two = row_bytes < 1024 ? 512 : 256;  // workgroups: two rounds where they are short
+    if (few_workgroups(M, N, 32, 32) <= two) return kind(FEW_32x32);
+    if (few_workgroups(M, N, 32, 64) <= (bits == 8 ? 256 : two)) return kind(FEW_32x64);
+    // (M = 64, K = 768, N = 30522 14.8, persistent 11.9; K = 4096, N = 12288 16.7 -> 8.9)
+    return (bits == 4 && few_workgroups(M, N, 64, 64) <= 256) || (M <= 64 && deep) ? kind(FEW_64x64) : FEW_NONE;
+}
+// where the kernels were asked for by number
+constexpr FewTile few_tile_or_largest(int64_t M, int64_t N, int64_t row_bytes, int bits)
+{
+    const FewTile t = few_tile(M, N, row_bytes, bits);
+    return t == FEW_NONE && row_bytes % 64 == 0 ? FEW_64x64 : t;
+}
+
 }  // namespace mkq

@@ -33,6 +33,8 @@ extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int6
 {
     return small_layer_attention(batch, seq, hidden, heads, row);
 }
+extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
+extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" bool small_tail(int64_t tokens, int64_t row, int64_t ffn_row) { return small_layer_tail(tokens, row, ffn_row); }
 """
 
@@ -154,3 +156,20 @@ def test_small_layers(rules):
     assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
     assert not rules.small_tail(4097, 384, 1280)
     assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
+
+
+def test_few_tokens(rules):
+    """The tile of the kernels of few tokens, and the shapes that their GPU test means to take each with."""
+    from test_gpu_few import SHAPES
+    few = lambda *s, bits=4: rules.few(*map(C.c_int64, s), bits)  # noqa: E731
+    assert [few(*s) for s in SHAPES] == [0] * 3 + [1] * 2 + [2] * 3 + [3] * 2 + [4] * 2 + [5, 6, 7, 8, 9, 9]
+    assert [few(*s, bits=8) for s in SHAPES] == [0] * 3 + [1] * 2 + [2] * 3 + [-1] * 4 + [5, 6, 7, 8, -1, 9]
+    assert few(16, 1 << 20, 64) == 0 and few(17, 8192, 64) == 1 and few(17, 8193, 64) == 2
+    assert few(640, 768, 384) == 2 and few(704, 768, 384) == 3 and few(641, 768, 1024) == 4 and few(512, 512, 768, bits=8) == 2
+    assert few(256, 1024, 1024, bits=8) == 2 and few(257, 1024, 1024, bits=8) == 3
+    assert few(4096, 768, 384) == -1 and few(64, 30522, 384) == -1   # persistent kernels
+    assert few(1, 8, 32) == -1 and few(1, 8, 96) == -1               # pieces of 64 bytes
+    assert few(8, 8, 2112) == 0                                      # long, but not in pieces of 128
+    # asked for by number, up to 128 tokens: some tile, whatever the size
+    assert all(rules.few_asked(C.c_int64(M), C.c_int64(N), C.c_int64(r), b) >= 0
+               for M in (1, 65, 128) for N in (8, 30522, 1 << 20) for r in (128, 1024, 4096) for b in (4, 8))

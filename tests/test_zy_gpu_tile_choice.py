@@ -6,7 +6,7 @@ import pytest
 
 pytestmark = pytest.mark.gpu
 
-CONFIGS = [11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51, 53, 54, 55]
+CONFIGS = [11, 12, 14, 18, 19, 20, 27, 28, 29, 31, 33, 35, 43, 44, 45, 46, 47, 48, 49, 51]
 # (M, K, N): BERT-base layer GEMMs at M = 1024 and 4096 and at ragged token counts, BERT-large at M = 4096 and 8192, the
 # large-M sweep at M = 16384
 SHAPES = ([(M, K, N) for M in (440, 1024, 2298, 4096) for (K, N) in ((768, 2304), (768, 768), (768, 3072), (3072, 768))]
