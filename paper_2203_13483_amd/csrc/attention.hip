@@ -13,7 +13,7 @@
 // What bounds it: the 6 KiB of q, k, v per token and 1024 hidden out of memory, all at the start of a round (10 of 38 us
 // below), then vector issue: per score one exponential (16 cycles) and about 16 cycles of other operations, against 8 of
 // matrix pipe.  us in a graph, over the keys twice -> here: 16 heads of 64, 16 x 512 tokens 56.5 -> 38.5, 4 x 512 22.3 -> 13.3,
-// 32 x 256 32.0 -> 26.1, 20 x 384 44.2 -> 37.8; 12 heads of 26, 32 x 128 9.6 -> 7.2, 64 x 128 15.3 -> 10.7, 16 x 512 33.9 -> 29.5.
+// 32 x 256 32.0 -> 24.6, 20 x 384 44.2 -> 35.7; 12 heads of 26, 32 x 128 9.6 -> 7.2, 64 x 128 15.3 -> 10.7, 16 x 512 33.9 -> 29.5.
 // Tried before it: 32 queries and half of the keys per wave, maxima and outputs exchanged by pairs of waves: 42 to 46 us at
 // 16 x 512, 46 at 20 x 384 (the pairs run in step, so exponentials and matrix products do not overlap).
 #include "attention.h"
@@ -30,6 +30,17 @@ struct AttentionHeldCfg {
 };
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+// 16-byte chunk c of key r is kept at c ^ swz_keys(r), chunk c of dimension d of V^T at c ^ swz_dims(d).  A fragment's sixteen rows
+// differ in bits 0, 1, 3 and 4 (prow below); with these functions of just those bits they meet all 64 banks, and each eight of them 32.
+// (Functions of bits 0 to 3, as for sixteen neighbouring rows, put them on half of the banks: us in a graph, 32 x 256 tokens, 16 heads
+// of 64 27.4 -> 24.6, 32 x 200, 12 heads 22.4 -> 19.3, 20 x 384, 16 heads 37.4 -> 35.7.)
+template <int CH>
+__device__ __forceinline__ int swz_keys(int r)
+{
+    return CH == 8 ? ((r >> 1) & 1) | ((r >> 2) & 2) | (((r >> 4) ^ r) & 1) << 2 : ((r >> 3) & 1) | (((r >> 4) ^ (r >> 1)) & 1) << 1;
+}
+__device__ __forceinline__ int swz_dims(int d) { return (d & 3) | ((d >> 1) & 12); }
+
 // DKP: head size rounded up to 32 or 64 (dimensions d_k .. DKP - 1 are staged as zeros and never stored).  VEC = 8: 16-byte
 // accesses (d_k % 8 == 0); VEC = 2: 4-byte ones.  parts: workgroups per (sequence, head), from the host, 1 for up to 128 keys: the divisions
 // by it are latency in front of the first load (64 x 64 tokens, 12 heads of 26, 8.4 -> 7.5 us in a graph, 32 x 128 7.6 -> 7.45).
@@ -38,6 +49,10 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
                                                                                 const XcdRuns runs)
 {
     using Cfg = AttentionHeldCfg<DKP, NG>;
+    // Groups of 32 keys by which fragments are fetched ahead of their products: with two waves on a SIMD the LDS answers too late
+    // otherwise (16 x 512 tokens, 16 heads of 64, 41.2 -> 38.2 us), with four the registers spill (32 x 256 27.8 -> 39.0).  Two groups
+    // gain nothing over one up to 384 keys and spill at 512.
+    constexpr int AHEAD = NG <= 8 ? 0 : 1;
     constexpr int THREADS = Cfg::THREADS, KEYS = Cfg::KEYS, ROWB = DKP * 2, CH = DKP / 8, VROW = Cfg::VROW, DS = DKP / 32;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint8_t *const sK = smem, *const sVt = smem + Cfg::K_BYTES;
@@ -133,7 +148,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     for (int i = 0; i < PER_T; ++i) {
         if (i * THREADS / PPR < rows && (JOBS % THREADS == 0 || tid + i * THREADS < JOBS)) {
             const int idx = tid + i * THREADS, r = idx / PPR, d = (idx % PPR) * VEC;
-            *reinterpret_cast<Piece *>(sK + r * ROWB + (((d >> 3) ^ swz<CH>(r & 15)) * 16) + (d & 7) * 2) = kv[i];
+            *reinterpret_cast<Piece *>(sK + r * ROWB + (((d >> 3) ^ swz_keys<CH>(r)) * 16) + (d & 7) * 2) = kv[i];
         }
     }
 #pragma unroll
@@ -153,7 +168,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
             for (int e = 0; e < VEC; ++e) {
                 const int d = d0 + e;
                 const uint32_t lo = (w0[e >> 1] >> (16 * (e & 1))) & 0xFFFFu, hi = (w1[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-                *reinterpret_cast<uint32_t *>(sVt + d * VROW + (((r >> 3) ^ (d & 15)) * 16) + (r & 7) * 2) = lo | (hi << 16);
+                *reinterpret_cast<uint32_t *>(sVt + d * VROW + (((r >> 3) ^ swz_dims(d)) * 16) + (r & 7) * 2) = lo | (hi << 16);
             }
         }
     }
@@ -165,6 +180,10 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     // row i = lr of a K or V^T fragment: 8 (i / 4) + i % 4 of 32, and 4 more in the second of a pair
     const int prow = 8 * (lr >> 2) + (lr & 3);
 
+    // This lane's chunks of its rows of K and V^T in the first group and part.  The swizzles leave out bit 2 of a row and the bits above 4,
+    // so parts, groups and halves of a head's dimensions are constants away (chunk 4 g + lg of V^T: 4 (g % 4) under the swizzle, 16 (g / 4)
+    // beyond).
+    const int kat = prow * ROWB + ((lg ^ swz_keys<CH>(prow)) * 16), vat = prow * VROW + ((lg ^ swz_dims(prow)) * 16);
     v4f sc[NG][2];  // scores: element e of part t of group g is key 32 g + 8 lg + 4 t + e
     auto softmax = [&](auto fullc, float &mx, float &den) __attribute__((always_inline)) {
         constexpr bool FULL = fullc.value;
@@ -176,19 +195,16 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
             qf[ds] = __builtin_bit_cast(v8h, packed);
         }
         float m2[2] = {MASKED, MASKED};
+        v8h kf[AHEAD + 1][2][DS];
+        auto fetch_k = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds)
+                    kf[g % (AHEAD + 1)][t][ds] = *reinterpret_cast<const v8h *>(sK + (kat ^ (ds * 64)) + (g * 32 + 4 * t) * ROWB);
+        };
+        auto maximum = [&](int g) __attribute__((always_inline)) {
             if (exists(g)) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    sc[g][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-                    const int krow = g * 32 + prow + 4 * t;
-#pragma unroll
-                    for (int ds = 0; ds < DS; ++ds) {
-                        const v8h kf = *reinterpret_cast<const v8h *>(sK + krow * ROWB + (((ds * 4 + lg) ^ swz<CH>(krow & 15)) * 16));
-                        sc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[ds], sc[g][t], 0, 0, 0);
-                    }
-                }
                 if ((!FULL || g >= NG - 2) && g * 32 + 32 > seq) {  // (uniform) keys that do not exist
                     int keys = seq - g * 32 - 8 * lg;
                     asm volatile("" : "+v"(keys));  // the comparisons stay here (masks carried through the loop spill)
@@ -203,8 +219,26 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
 #pragma unroll
                     for (int e = 0; e < 4; ++e) m2[t] = __builtin_amdgcn_fmed3f(m2[t], sc[g][t][e], __builtin_inff());
             }
-            if (NG == 8 || (NG < 8 ? g & 1 : (g & 3) == 3)) __builtin_amdgcn_sched_barrier(0);  // (else the fragments of all groups are fetched at once: spills)
+        };
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) fetch_k(g);
+        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            if (AHEAD ? g + AHEAD < NG : exists(g)) fetch_k(g + AHEAD);
+            if (exists(g)) {
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    sc[g][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int ds = 0; ds < DS; ++ds) sc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[g % (AHEAD + 1)][t][ds], qf[ds], sc[g][t], 0, 0, 0);
+                }
+            }
+            if (AHEAD == 0) maximum(g);
+            else if (g > 0) maximum(g - 1);
+            if (AHEAD || NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);  // (else the fragments of all groups are fetched at once: spills)
         }
+        if (AHEAD) maximum(NG - 1);
         mx = fmaxf(m2[0], m2[1]);
         mx = lane_pair<16>(mx, MaxF32());
         mx = lane_pair<32>(mx, MaxF32());
@@ -225,29 +259,37 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
         den = lane_pair<16>(den, AddF32());
         den = lane_pair<32>(den, AddF32());
     };
-    // byte of this lane's chunk lg of its rows of V^T; chunk 4 g + lg is 4 (g % 4) chunks away under the swizzle, 16 (g / 4) beyond
-    int vat[2 * DS];
-#pragma unroll
-    for (int dt = 0; dt < 2 * DS; ++dt) {
-        const int d = (dt / 2) * 32 + prow + 4 * (dt % 2);
-        vat[dt] = d * VROW + ((lg ^ (d & 15)) * 16);
-    }
     v4f ot[2 * DS];  // element e of part dt is head dimension 32 (dt / 2) + 8 lg + 4 (dt % 2) + e
     auto values = [&](auto fullc, float inv) __attribute__((always_inline)) {
         constexpr bool FULL = fullc.value;
+        v8h vf[AHEAD + 1][2 * DS], pf[2];
+        auto fetch_v = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int dt = 0; dt < 2 * DS; ++dt)
+                vf[g % (AHEAD + 1)][dt] = *reinterpret_cast<const v8h *>(sVt + (vat ^ ((g & 3) * 64)) + (g >> 2) * 256 +
+                                                                        ((dt / 2) * 32 + 4 * (dt % 2)) * VROW);
+        };
+#pragma unroll
+        for (int g = 0; g < AHEAD; ++g) fetch_v(g);
+        auto narrow = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) pf[g % 2][e] = (_Float16)(sc[g][e >> 2][e & 3] * inv);
+        };
+        auto exists = [&](int g) { return FULL || g * 32 < seq; };
+        if (AHEAD) {
+            narrow(0);
+            __builtin_amdgcn_sched_barrier(0);
+        }
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
-            if (FULL || g * 32 < seq) {
-                v8h pf;
+            if (AHEAD ? g + AHEAD < NG : exists(g)) fetch_v(g + AHEAD);
+            if (AHEAD == 0 && exists(g)) narrow(g);
+            if (exists(g)) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (_Float16)(sc[g][e >> 2][e & 3] * inv);
-#pragma unroll
-                for (int dt = 0; dt < 2 * DS; ++dt) {
-                    const v8h vf = *reinterpret_cast<const v8h *>(sVt + (vat[dt] ^ ((g & 3) * 64)) + (g >> 2) * 256);
-                    ot[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, pf, ot[dt], 0, 0, 0);
-                }
+                for (int dt = 0; dt < 2 * DS; ++dt) ot[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[g % (AHEAD + 1)][dt], pf[g % 2], ot[dt], 0, 0, 0);
             }
-            if (NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);
+            if (AHEAD && g + 1 < NG && exists(g + 1)) narrow(g + 1);
+            if (AHEAD || NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);
         }
     };
 
