@@ -121,6 +121,16 @@ constexpr bool layernorm_half_waves(int64_t M, int64_t D)
     return D <= 1024 && M >= 2048 && (D <= 256 || (D > 512 && D <= 768) || (M + 3) / 4 > MAX_WORK_ITEMS / 256);
 }
 
+// 4-bit layers of medium hidden size: attention output and LayerNorm in one launch, 16 tokens and all columns to a workgroup, where these
+// are one round on 256 CUs and LayerNorm alone would have its rows to half waves as well, so that its sums run in the same order.  us a
+// layer of hidden size 768, before -> this: 2048 tokens 56.9 -> 56.1, 2298 66.5 -> 65.7, 3072 76.1 -> 73.6, two of 4096 162.2 -> 158.8;
+// below, every workgroup's read of all weights costs more than the launch (1024 tokens 46.2 -> 46.9, 440 36.8 -> 38.3).  The FFN's second
+// linear the same way: 16 tokens for each widening of four times the weights, 4096 tokens +1.3, 2048 +5.4.
+constexpr bool output_norm(int64_t tokens, int64_t hidden, int64_t row)
+{
+    return row > 512 && row <= 768 && row % 128 == 0 && tokens <= 4096 && layernorm_half_waves(tokens, hidden);
+}
+
 // The kernels of few tokens and small linears (gemm_few.hip): tiles of channels x tokens; _LONG: waves take 128 bytes of a row at a
 // time, not 64 (rows of 2048 bytes and more: M = 128, K = N = 4096 6.4 -> 5.8; at 1536 bytes M = 440, N = 768 5.1 -> 5.4).
 enum FewTile { FEW_NONE = -1, FEW_16x16, FEW_16x32, FEW_32x32, FEW_32x64, FEW_64x64,

@@ -915,21 +915,23 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
                            p->cu_seqlens, Hp);
         if (rc != MKQ_OK) return rc;
     }
-    if (bits == 4 && h_dtype == MKQ_F16 && small_layer_tail(M, Hp, Fp)) {
+    const bool whole_tail = bits == 4 && h_dtype == MKQ_F16 && small_layer_tail(M, Hp, Fp);
+    mkq_epilogue e = {};
+    e.act = MKQ_ACT_NONE; e.residual = h_in; e.residual_dtype = h_dtype; e.s_next = 0.0f;
+    e.q_out = nullptr; e.acc_out = nullptr;
+    if (whole_tail || (bits == 4 && h_dtype == MKQ_F16 && output_norm(M, H, Hp))) {
         const LayerTailParams t = {(int)M, (int)H, (int)F, (int)Hp, (int)Fp, ws + L.c1, (const uint16_t *)h_in, p->Wq_ao, p->Wq_up, p->Wq_down,
                                    p->sw_ao, p->sw_up, p->sw_down, p->b_ao, p->b_up, p->b_down, p->sx_ao, p->sx_up, p->sx_down,
                                    p->ln1_gamma, p->ln1_beta, p->ln2_gamma, p->ln2_beta, p->ln_eps, (uint16_t *)(ws + L.u), (uint16_t *)(ws + L.h1),
                                    (uint16_t *)(ws + L.d), (uint16_t *)h_out, ws + L.c2, ws + L.c3, want_next ? q_out_next : nullptr,
                                    want_next ? p->s_out_next : 1.0f, next_bits, (int)next_pitch};
-        return run_layer_tail(t, as_stream(stream));
+        if (whole_tail) return run_layer_tail(t, as_stream(stream));
+        rc = run_output_norm(t, as_stream(stream));
+    } else {
+        rc = layer_linear(bits, ws + L.c1, p->sx_ao, p->Wq_ao, p->sw_ao, p->b_ao, M, H, Hp, ws + L.u, MKQ_F16, &e, stream);
+        if (rc != MKQ_OK) return rc;
+        rc = layernorm_run(ws + L.u, M, H, p->ln1_gamma, p->ln1_beta, p->ln_eps, ws + L.h1, p->sx_up, ws + L.c2, bits, stream, Hp);
     }
-    mkq_epilogue e = {};
-    e.act = MKQ_ACT_NONE; e.residual = h_in; e.residual_dtype = h_dtype; e.s_next = 0.0f;
-    e.q_out = nullptr; e.acc_out = nullptr;
-    rc = layer_linear(bits, ws + L.c1, p->sx_ao, p->Wq_ao, p->sw_ao, p->b_ao, M, H, Hp, ws + L.u, MKQ_F16, &e, stream);
-    if (rc != MKQ_OK) return rc;
-    rc = layernorm_run(ws + L.u, M, H, p->ln1_gamma, p->ln1_beta, p->ln_eps, ws + L.h1, p->sx_up, ws + L.c2, bits,
-                       stream, Hp);
     if (rc != MKQ_OK) return rc;
     // FFN up: GELU and re-quantization fused, only codes leave the kernel
     e.act = MKQ_ACT_GELU; e.residual = nullptr; e.s_next = p->sx_down; e.q_pitch = Fp != F ? Fp : 0;

@@ -24,6 +24,8 @@ struct LayerTailParams {
 
 // Launches it.
 int run_layer_tail(const LayerTailParams &p, hipStream_t st);
+// Launches the attention output with the LayerNorm behind it alone (u, h1, c2): rows of up to 768 codes.
+int run_output_norm(const LayerTailParams &p, hipStream_t st);
 // once-per-device setup of its instantiations (nothing is launched)
 int setup_layer_tail();
 

@@ -62,7 +62,8 @@ __device__ __forceinline__ int token_operand_at(int t, int k)
     return s * 1024 + (qq * 16 + (t ^ qq ^ (sj * 4))) * 16 + (k & 8);
 }
 
-template <class Cfg>
+// FFN: all of it; otherwise the attention output and the LayerNorm behind it
+template <class Cfg, bool FFN>
 __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const LayerTailParams p)
 {
     constexpr int GH = Cfg::GH, GF = Cfg::GF, RH = Cfg::RH, RF = Cfg::RF, BM = Cfg::BM, MAXC = Cfg::MAXC, CF = Cfg::CF;
@@ -249,7 +250,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
                     for (int e = 0; e < 4; ++e) o[4 * h + e] = v[i][4 * h + e] * rstd * gg[e] + bb[e];
                 }
                 const v4u y = {pack2_f16(o[0], o[1]), pack2_f16(o[2], o[3]), pack2_f16(o[4], o[5]), pack2_f16(o[6], o[7])};
-                if (MID) *reinterpret_cast<v4u *>(tile + r * Cfg::PITCH + c * 16) = y;
+                if (MID && FFN) *reinterpret_cast<v4u *>(tile + r * Cfg::PITCH + c * 16) = y;
                 if (in) {
                     *reinterpret_cast<v4u *>(x_out + row * p.H + c * 8) = raw[i];
                     *reinterpret_cast<v4u *>(y_out + row * p.H + c * 8) = y;
@@ -259,12 +260,12 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
             }
             if (MID) {
                 if (in && c * 8 < p.Hp) reinterpret_cast<uint32_t *>(q_out)[row * (p.Hp / 8) + c] = packed;
-                if (c * 8 < Cfg::KH) *reinterpret_cast<uint2 *>(oph + token_operand_at(r, c * 8)) = token_operand(packed, csum);
+                if (FFN && c * 8 < Cfg::KH) *reinterpret_cast<uint2 *>(oph + token_operand_at(r, c * 8)) = token_operand(packed, csum);
             } else if (q_out && in && p.next_bits == 4 && c * 8 < p.next_pitch) {
                 reinterpret_cast<uint32_t *>(q_out)[row * (p.next_pitch / 8) + c] = packed;
             }
         }
-        if (MID) {
+        if (MID && FFN) {
             const float total = lane_reduce<32>((float)csum, AddF32());
             if (hl == 0) corr[BM + r] = (int)total;
         }
@@ -329,7 +330,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
             corr[2 * BM + r] = 0;
         }
     }
-    rows_of(IntC<GF>{}, n_f, p.F, pitch_h, voff_f);
+    if constexpr (FFN) rows_of(IntC<GF>{}, n_f, p.F, pitch_h, voff_f);
     wait_vmcnt<0>();
     lds_barrier();
     take(IntC<0>{}, 0);
@@ -338,12 +339,13 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
         v4i acc[GH];
 #pragma unroll
         for (int T = 0; T < GH; ++T) acc[T] = v4i{0, 0, 0, 0};
-        units(IntC<GH>{}, IntC<RH>{}, IntC<RF>{}, acc, oph, units_h,
+        units(IntC<GH>{}, IntC<RH>{}, IntC<FFN ? RF : 0>{}, acc, oph, units_h,
               [&](auto Tc, int k) { copy(IntC<decltype(Tc)::value % RH>{}, p.W_ao, k, pitch_h, voff_h[decltype(Tc)::value]); },
-              [&] { copy_scales(IntC<Cfg::NSF>{}, SCALES_F, n_f, p.F, p.sw_up, p.b_up); }, next_up);
+              [&] { if constexpr (FFN) copy_scales(IntC<Cfg::NSF>{}, SCALES_F, n_f, p.F, p.sw_up, p.b_up); }, next_up);
         add_to_tile(acc, 8 * corr[t], p.sx_ao, p.b_ao != nullptr);
     }
     layernorm(IntC<1>{}, p.u, p.h1, p.c2, p.sx_up);
+    if constexpr (!FFN) return;
     lds_barrier();
     copy_affine(p.g2, p.be2);
     copy_scales(IntC<Cfg::NSH>{}, SCALES_H, n_h, p.H, p.sw_down, p.b_down);
@@ -405,30 +407,34 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
 }
 
 // p null: setup only
-template <class Cfg>
+template <class Cfg, bool FFN>
 static int launch_tail(const LayerTailParams *p, hipStream_t st)
 {
     static PerDeviceOnce once;
     int64_t resident = 0;
-    const int rc = resident_workgroups(once, layer_tail_kernel<Cfg>, Cfg::THREADS, Cfg::LDS_BYTES, 1, &resident);
+    const int rc = resident_workgroups(once, layer_tail_kernel<Cfg, FFN>, Cfg::THREADS, Cfg::LDS_BYTES, 1, &resident);
     if (rc != MKQ_OK || !p) return rc;
-    layer_tail_kernel<Cfg><<<(unsigned)ceil_div(p->M, Cfg::BM), Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p);
+    layer_tail_kernel<Cfg, FFN><<<(unsigned)ceil_div(p->M, Cfg::BM), Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p);
     return launch_status();
 }
 using TailWide = LayerTailCfg<3, 3, 10, 5>;    // chunks of 1280 FFN columns
 using TailNarrow = LayerTailCfg<3, 3, 6, 3>;   // of 768
+using OutputNorm = LayerTailCfg<6, 6, 2, 1>;   // up to 768 hidden columns, without the FFN
 
 int run_layer_tail(const LayerTailParams &p, hipStream_t st)
 {
     // the chunks whose columns add up to less (a chunk is multiplied whole), and the fewer of them
     const int64_t wide = ceil_div(p.F, TailWide::CF) * TailWide::CF, narrow = ceil_div(p.F, TailNarrow::CF) * TailNarrow::CF;
-    return wide <= narrow ? launch_tail<TailWide>(&p, st) : launch_tail<TailNarrow>(&p, st);
+    return wide <= narrow ? launch_tail<TailWide, true>(&p, st) : launch_tail<TailNarrow, true>(&p, st);
 }
+
+int run_output_norm(const LayerTailParams &p, hipStream_t st) { return launch_tail<OutputNorm, false>(&p, st); }
 
 int setup_layer_tail()
 {
-    const int rc = launch_tail<TailWide>(nullptr, nullptr);
-    return rc != MKQ_OK ? rc : launch_tail<TailNarrow>(nullptr, nullptr);
+    int rc = launch_tail<TailWide, true>(nullptr, nullptr);
+    if (rc == MKQ_OK) rc = launch_tail<TailNarrow, true>(nullptr, nullptr);
+    return rc != MKQ_OK ? rc : launch_tail<OutputNorm, false>(nullptr, nullptr);
 }
 
 }  // namespace mkq

@@ -669,3 +669,39 @@ def test_layers_of_small_hidden_size(mkq, batch, seq, hidden, heads, ffn, lens, 
     # the output may take the input's place
     again = layer(x, ws, h_out=x, q_out_next=q_next)
     assert torch.equal(again, h_out)
+
+
+# Attention output and LayerNorm in one launch (launch_rules.h, output_norm): the fewest and the most tokens, last workgroups of 1 and 15 rows,
+# rows of whole 256-code units and with a half one, with padding codes, the smallest FFN and the base one
+@pytest.mark.parametrize("hidden,heads,ffn,tokens", [(768, 12, 64, 2048), (768, 12, 3072, 2049), (640, 10, 128, 4095), (640, 10, 96, 4096), (744, 12, 200, 2063),
+                                                     (760, 19, 64, 3000)])
+@pytest.mark.parametrize("bias", [True, False])
+def test_attention_output_with_its_layernorm(mkq, hidden, heads, ffn, tokens, bias):
+    """Bit for bit what the same sequences give among more of them, which take the linear and the LayerNorm one after the other."""
+    import torch
+    p, _ = _layer_case(hidden + ffn, 1, 8, hidden, heads, ffn)
+    ln = {k: to_dev(p[k]) for k in ("ln1_gamma", "ln1_beta", "ln2_gamma", "ln2_beta")}
+    packed = {}
+    for nm in ("qkv", "ao", "up", "down"):
+        pack = mkq.mkq_pack_weights_int4 if p["W_" + nm].shape[1] % 32 == 0 else mkq.mkq_pack_weights_int4_padded
+        packed[nm] = pack(to_dev(p["W_" + nm])) + (to_dev(p["b_" + nm]),)
+    sx = {"qkv": 0.34, "ao": 0.05, "up": 0.34, "down": 0.05}
+    lens = [128] * (tokens // 128) + ([tokens % 128] if tokens % 128 else [])
+    more = lens + [128] * 17 + [77] * (len(lens) % 2)
+    while sum(more) <= 4096:
+        more.append(128)
+    x = torch.randn((sum(more), hidden), generator=torch.Generator(device="cuda").manual_seed(hidden), device="cuda").half()
+    from layer_checks import code_row_pitch
+    results = []
+    for part in (lens, more):
+        M = sum(part)
+        cu = to_dev(np.concatenate([[0], np.cumsum(part)]).astype(np.int32))
+        layer = mkq.BertLayerInt4(len(part), 128, hidden, heads, ffn, packed, sx, ln, p["ln_eps"], 0.4, 4, cu_seqlens=cu, total_tokens=M)
+        if not bias:
+            for nm in ("qkv", "ao", "up", "down"):
+                setattr(layer.params, "b_" + nm, None)
+        ws = torch.full((layer.workspace_bytes(),), 0x5A, dtype=torch.uint8, device="cuda")  # stale contents
+        q_next = torch.full((M, code_row_pitch(hidden) // 2), 0x5A, dtype=torch.uint8, device="cuda")
+        h_out = layer(x[:M].contiguous(), ws, q_out_next=q_next)
+        results.append((h_out[:tokens], q_next[:tokens]))
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])

@@ -36,6 +36,7 @@ extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int6
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" bool small_tail(int64_t tokens, int64_t row, int64_t ffn_row) { return small_layer_tail(tokens, row, ffn_row); }
+extern "C" bool output_with_norm(int64_t tokens, int64_t hidden, int64_t row) { return output_norm(tokens, hidden, row); }
 """
 
 
@@ -54,6 +55,7 @@ def rules(tmp_path_factory):
     lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
+    lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
     lib.small_tail.argtypes, lib.small_tail.restype = [C.c_int64] * 3, C.c_bool
     return lib
 
@@ -156,6 +158,13 @@ def test_small_layers(rules):
     assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
     assert not rules.small_tail(4097, 384, 1280)
     assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
+
+
+def test_output_norm(rules):
+    assert all(rules.output_with_norm(m, *hr) for m in (2048, 4096) for hr in ((768, 768), (640, 640), (744, 768)))
+    assert not rules.output_with_norm(2047, 768, 768) and not rules.output_with_norm(4097, 768, 768)
+    assert not rules.output_with_norm(4096, 1024, 1024) and not rules.output_with_norm(4096, 512, 512)
+    assert not rules.output_with_norm(4096, 672, 672)  # no whole half units of 128 codes
 
 
 def test_few_tokens(rules):
