@@ -151,6 +151,7 @@ constexpr FewTile few_tile(int64_t M, int64_t N, int64_t row_bytes, int bits)
     if (row_bytes % 64 != 0) return FEW_NONE;
     const bool deep = row_bytes >= 2048 && row_bytes % 128 == 0;
     auto kind = [&](FewTile t) { return deep ? (FewTile)(t + FEW_16x16_LONG) : t; };
+    if (few_workgroups(M, N, 16, 16) > MAX_WORK_ITEMS / 512) return FEW_NONE;  // (of 512 threads)
     if (M <= 16) return kind(FEW_16x16);
     if (M <= 32) return kind(few_workgroups(M, N, 16, 32) <= (deep ? 256 : 512) ? FEW_16x32 : FEW_32x32);
     const int64_t two = row_bytes < 1024 ? 512 : 256;  // workgroups: two rounds where they are short

@@ -179,6 +179,7 @@ def test_few_tokens(rules):
     assert few(4096, 768, 384) == -1 and few(64, 30522, 384) == -1   # persistent kernels
     assert few(1, 8, 32) == -1 and few(1, 8, 96) == -1               # pieces of 64 bytes
     assert few(8, 8, 2112) == 0                                      # long, but not in pieces of 128
+    assert few(16, 0xFFFFFFFF // 512 * 16, 64) == 0 and few(16, 0xFFFFFFFF // 512 * 16 + 1, 64) == -1  # what a launch takes
     # asked for by number, up to 128 tokens: some tile, whatever the size
     assert all(rules.few_asked(C.c_int64(M), C.c_int64(N), C.c_int64(r), b) >= 0
                for M in (1, 65, 128) for N in (8, 30522, 1 << 20) for r in (128, 1024, 4096) for b in (4, 8))
