@@ -18,6 +18,11 @@ struct AttentionParams {
     int q_bits, q_pitch;
 };
 
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// Chunk of 16 bytes c of head dimension d of V^T is kept at c ^ swz_dims(d): the sixteen rows of a fragment differ in bits 0, 1, 3 and 4
+__device__ __forceinline__ int swz_dims(int d) { return (d & 3) | ((d >> 1) & 12); }
+
 // Head dimensions d0 .. d0 + 7 of one query (those below d_k; d0 is a multiple of 8).  VEC = 8: d_k % 8 == 0; 2: even.
 template <int VEC>
 __device__ __forceinline__ void attention_store(const AttentionParams &p, int64_t row, int head, int d0, const float (&o)[8])

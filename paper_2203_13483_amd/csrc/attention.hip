@@ -28,9 +28,8 @@ struct AttentionHeldCfg {
     static constexpr int K_BYTES = KEYS * DKP * 2, V_BYTES = DKP * VROW;
     static constexpr int LDS_BYTES = K_BYTES + V_BYTES;
 };
-typedef float v4f __attribute__((ext_vector_type(4)));
 
-// 16-byte chunk c of key r is kept at c ^ swz_keys(r), chunk c of dimension d of V^T at c ^ swz_dims(d).  A fragment's sixteen rows
+// 16-byte chunk c of key r is kept at c ^ swz_keys(r) (of V^T: swz_dims).  A fragment's sixteen rows
 // differ in bits 0, 1, 3 and 4 (prow below); with these functions of just those bits they meet all 64 banks, and each eight of them 32.
 // (Functions of bits 0 to 3, as for sixteen neighbouring rows, put them on half of the banks: us in a graph, 32 x 256 tokens, 16 heads
 // of 64 27.4 -> 24.6, 32 x 200, 12 heads 22.4 -> 19.3, 20 x 384, 16 heads 37.4 -> 35.7.)
@@ -39,7 +38,6 @@ __device__ __forceinline__ int swz_keys(int r)
 {
     return CH == 8 ? ((r >> 1) & 1) | ((r >> 2) & 2) | (((r >> 4) ^ r) & 1) << 2 : ((r >> 3) & 1) | (((r >> 4) ^ (r >> 1)) & 1) << 1;
 }
-__device__ __forceinline__ int swz_dims(int d) { return (d & 3) | ((d >> 1) & 12); }
 
 // DKP: head size rounded up to 32 or 64 (dimensions d_k .. DKP - 1 are staged as zeros and never stored).  VEC = 8: 16-byte
 // accesses (d_k % 8 == 0); VEC = 2: 4-byte ones.  parts: workgroups per (sequence, head), from the host, 1 for up to 128 keys: the divisions

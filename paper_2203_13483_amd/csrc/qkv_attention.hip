@@ -28,6 +28,10 @@ struct QkvAttentionCfg {
     static_assert(SCALE_AT + 2 * 3 * DKP * 4 <= LDS_BYTES, "");
 };
 
+// 16-byte chunk c of row r of q, K and V is kept at c ^ swz_rows(r): a product's fragment takes rows that differ in bits 0, 1, 3 and 4 of
+// K, and in bits 0 to 3 of q, and each sixteen meet all 64 banks; so do eight neighbouring rows that are written.
+__device__ __forceinline__ int swz_rows(int r) { return ((r >> 3) & 1) | (((r >> 2) ^ (r >> 4)) & 1) << 1; }
+
 // VEC = 8: d_k % 8 == 0; 2: even
 template <int VEC, int KT>
 __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentionParams p)
@@ -52,6 +56,7 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
     seq = seq < 32 * KT ? seq : 32 * KT;  // (longer than the caller's bound on the lengths: not computed)
     if (seq <= 0) return;                 // the whole workgroup
     const int hidden = a.hidden, dk = a.dk, pitch = p.K / 2;
+    constexpr float MASKED = -1.0e30f;  // the score of a key past the end of the sequence
 
     const QuantStep step = quant_step<4>(a.s_next);
     uint8_t *const codes = a.qout + ((row0 * a.q_pitch + head * dk) >> 1);
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
         }
 
         // ---- q, k, v: dequantized and narrowed, to LDS ----
-        constexpr int ROWB = DKP * 2, CH = DKP / 8, SMAX = 32 * NM;
+        constexpr int ROWB = DKP * 2, SMAX = 32 * NM;
         constexpr int VCHP = NM == 1 ? 4 : NM == 2 ? 8 : 16, VROW = VCHP * 16;
         uint8_t *const sQ = lds, *const sK = lds + SMAX * ROWB, *const sVt = lds + 3 * SMAX * ROWB;  // (V row by row between the last two)
         float *const scale = reinterpret_cast<float *>(lds + Cfg::SCALE_AT);
@@ -163,7 +168,7 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
                     asm volatile("" : "+v"(y0), "+v"(y1));
                     h[e] = d0 + 2 * e < dk ? pack2_f16(y0, y1) : 0;  // (d_k is even)
                 }
-                *reinterpret_cast<uint4 *>(sQ + (part * SMAX + m) * ROWB + (((d0 >> 3) ^ swz<CH>(m & 15)) * 16)) = make_uint4(h[0], h[1], h[2], h[3]);
+                *reinterpret_cast<uint4 *>(sQ + (part * SMAX + m) * ROWB + (((d0 >> 3) ^ swz_rows(m)) * 16)) = make_uint4(h[0], h[1], h[2], h[3]);
                 if (part == 2) {
                     // two neighbouring lanes have the same head dimensions of two neighbouring keys: each takes four of them for both
                     const bool odd = lane & 1;
@@ -177,7 +182,7 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
                         for (int e = 0; e < 2; ++e) {
                             const int d = d0 + (odd ? 4 : 0) + 2 * i + e;
                             const uint32_t v = e ? (even_key >> 16) | (odd_key & 0xFFFF0000u) : (even_key & 0xFFFFu) | (odd_key << 16);
-                            *reinterpret_cast<uint32_t *>(sVt + d * VROW + (((m >> 3) ^ (d & (VCHP - 1))) * 16) + (m & 6) * 2) = v;
+                            *reinterpret_cast<uint32_t *>(sVt + d * VROW + (((m >> 3) ^ (swz_dims(d) & (VCHP - 1))) * 16) + (m & 6) * 2) = v;
                         }
                     }
                 }
@@ -194,7 +199,7 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
                 const int idx = tid + i * 256, r = idx / PPR, c = idx % PPR;
                 if (TOTAL % 256 != 0 && idx >= TOTAL) break;
                 const int part = r / SMAX, mm = r % SMAX;
-                const v4i_4 v = *reinterpret_cast<const v4i *>(sQ + r * ROWB + ((c ^ swz<CH>(mm & 15)) * 16));
+                const v4i_4 v = *reinterpret_cast<const v4i *>(sQ + r * ROWB + ((c ^ swz_rows(mm)) * 16));
                 uint32_t *const to = reinterpret_cast<uint32_t *>(to0 + (uint32_t)mm * (uint32_t)(3 * hidden) + part * hidden + c * 8);
                 if (mm < seq) {
                     if (c * 8 + 8 <= dk) {
@@ -208,72 +213,96 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
             }
         }
 
-        // ---- attention: 32 queries to a wave, all keys at once, as attention_kernel does it ----
+        // ---- attention: two blocks of 16 queries to a wave, all keys at once, with the products, the sums and their order of
+        // attention_held_kernel, so that a layer's bits are those of its two launches ----
         if (wave * 32 >= seq) return;  // (no barrier follows)
-        v16f sc[NM];
+        const int lr = lane & 15, lg = lane >> 4;
+        const int prow = 8 * (lr >> 2) + (lr & 3);  // row i = lr of a fragment of K or V^T, and 4 more in the second of a pair
+        v4f sc[2][NM][2];  // scores: element e of part t of group g is key 32 g + 8 lg + 4 t + e
+        v8h qf[2];
 #pragma unroll
-        for (int kt = 0; kt < NM; ++kt)
+        for (int j = 0; j < 2; ++j) {
+            const int r = wave * 32 + 16 * j + lr;
+            qf[j] = *reinterpret_cast<const v8h *>(sQ + r * ROWB + ((lg ^ swz_rows(r)) * 16));
+        }
+        float m2[2][2] = {{MASKED, MASKED}, {MASKED, MASKED}};
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sc[kt][v] = 0.0f;
-        const int qrow = wave * 32 + fr;
+        for (int g = 0; g < NM; ++g) {
 #pragma unroll
-        for (int ds = 0; ds < DKP / 16; ++ds) {
-            const int c = ds * 2 + fh;
-            const v8h qf = *reinterpret_cast<const v8h *>(sQ + qrow * ROWB + ((c ^ swz<CH>(qrow & 15)) * 16));
+            for (int t = 0; t < 2; ++t) {
+                const int r = g * 32 + prow + 4 * t;
+                const v8h kf = *reinterpret_cast<const v8h *>(sK + r * ROWB + ((lg ^ swz_rows(r)) * 16));
 #pragma unroll
-            for (int kt = 0; kt < NM; ++kt) {
-                const int krow = kt * 32 + w_row_perm(fr);
-                const v8h kf = *reinterpret_cast<const v8h *>(sK + krow * ROWB + ((c ^ swz<CH>(krow & 15)) * 16));
-                sc[kt] = __builtin_amdgcn_mfma_f32_32x32x16_f16(kf, qf, sc[kt], 0, 0, 0);
+                for (int j = 0; j < 2; ++j) sc[j][g][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf, qf[j], v4f{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
             }
+            if (g * 32 + 32 > seq) {  // (uniform) keys that do not exist
+                const int keys = seq - g * 32 - 8 * lg;
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int t = 0; t < 2; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) sc[j][g][t][e] = (4 * t + e < keys) ? sc[j][g][t][e] : MASKED;
+            }
+            // (median with infinity: a maximum that does not quiet its operand with a second instruction first)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) m2[j][t] = __builtin_amdgcn_fmed3f(m2[j][t], sc[j][g][t][e], __builtin_inff());
         }
         const float c_exp = (1.0f / sqrtf((float)dk)) * 1.4426950408889634f;
-        float mx = -1.0e30f;
+        float inv[2];
 #pragma unroll
-        for (int kt = 0; kt < NM; ++kt)
-            if (kt * 32 + 32 > seq) {  // (uniform) keys that do not exist
+        for (int j = 0; j < 2; ++j) {
+            float mx = fmaxf(m2[j][0], m2[j][1]);
+            mx = lane_pair<16>(mx, MaxF32());
+            mx = lane_pair<32>(mx, MaxF32());
+            const float shift = -mx * c_exp;
+            float d2[2] = {0.0f, 0.0f};
 #pragma unroll
-                for (int v = 0; v < 16; ++v) sc[kt][v] = (kt * 32 + 16 * (v / 8) + 8 * fh + (v % 8) < seq) ? sc[kt][v] : -1.0e30f;
-            }
+            for (int g = 0; g < NM; ++g)
 #pragma unroll
-        for (int kt = 0; kt < NM; ++kt)
+                for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) mx = __builtin_amdgcn_fmed3f(mx, sc[kt][v], __builtin_inff());  // (a maximum without quieting first)
-        mx = lane_pair<32>(mx, MaxF32());
-        const float shift = -mx * c_exp;
-        float den = 0.0f;
-#pragma unroll
-        for (int kt = 0; kt < NM; ++kt)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                sc[kt][v] = __builtin_amdgcn_exp2f(__fmaf_rn(sc[kt][v], c_exp, shift));
-                den += sc[kt][v];
-            }
-        den = lane_pair<32>(den, AddF32());
-        const float inv = 1.0f / den;
+                    for (int e = 0; e < 4; ++e) {
+                        sc[j][g][t][e] = __builtin_amdgcn_exp2f(__fmaf_rn(sc[j][g][t][e], c_exp, shift));
+                        d2[t] += sc[j][g][t][e];
+                    }
+            float den = d2[0] + d2[1];
+            den = lane_pair<16>(den, AddF32());
+            den = lane_pair<32>(den, AddF32());
+            inv[j] = 1.0f / den;
+        }
 
-        v16f ot;
+        v4f ot[2][2];  // element e of part dt is head dimension 8 lg + 4 dt + e
 #pragma unroll
-        for (int v = 0; v < 16; ++v) ot[v] = 0.0f;
+        for (int j = 0; j < 2; ++j)
 #pragma unroll
-        for (int kt = 0; kt < NM; ++kt)
+            for (int dt = 0; dt < 2; ++dt) ot[j][dt] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                v8h pf;
+        for (int g = 0; g < NM; ++g) {
+            v8h pf[2];
 #pragma unroll
-                for (int e = 0; e < 8; ++e) pf[e] = (_Float16)(sc[kt][8 * half + e] * inv);
-                const int kc = (2 * kt + half) * 2 + fh;  // chunk of 8 keys
-                const int d = w_row_perm(fr);
-                const v8h vf = *reinterpret_cast<const v8h *>(sVt + d * VROW + ((kc ^ (d & (VCHP - 1))) * 16));
-                ot = __builtin_amdgcn_mfma_f32_32x32x16_f16(vf, pf, ot, 0, 0, 0);
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) pf[j][e] = (_Float16)(sc[j][g][e >> 2][e & 3] * inv[j]);
+#pragma unroll
+            for (int dt = 0; dt < 2; ++dt) {
+                const int d = prow + 4 * dt;
+                const v8h vf = *reinterpret_cast<const v8h *>(sVt + d * VROW + (((4 * g + lg) ^ (swz_dims(d) & (VCHP - 1))) * 16));
+#pragma unroll
+                for (int j = 0; j < 2; ++j) ot[j][dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf, pf[j], ot[j][dt], 0, 0, 0);
             }
-        if (qrow >= seq) return;
+        }
 #pragma unroll
-        for (int G = 0; G < 2; ++G) {
-            const int d0 = 16 * G + 8 * fh;
+        for (int j = 0; j < 2; ++j) {
+            const int qrow = wave * 32 + 16 * j + lr, d0 = 8 * lg;
+            if (qrow >= seq) continue;
             float o[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = ot[8 * G + e];
+            for (int e = 0; e < 8; ++e) o[e] = ot[j][e >> 2][e & 3];
             const uint32_t packed = quantize8<4>(o, step).x;
             uint8_t *const to = codes + (uint32_t)qrow * (uint32_t)(a.q_pitch / 2) + d0 / 2;
             if (d0 + 8 <= dk) *reinterpret_cast<word_1 *>(to) = packed;  // (aligned to 4 bytes where VEC = 8)
@@ -282,8 +311,8 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
                 if (d0 + 2 < dk) to[1] = (uint8_t)(packed >> 8);
                 if (d0 + 4 < dk) to[2] = (uint8_t)(packed >> 16);
             }
+            if (lg == 0 && head == a.heads - 1) attention_pad_codes(a, row0 + qrow);
         }
-        if (fh == 0 && head == a.heads - 1) attention_pad_codes(a, row0 + qrow);
     };
     if (KT == 1 || seq <= 32) run(IntC<1>{});
     else if (KT == 2 || seq <= 64) run(IntC<KT < 2 ? 1 : 2>{});

@@ -671,6 +671,45 @@ def test_layers_of_small_hidden_size(mkq, batch, seq, hidden, heads, ffn, lens, 
     assert torch.equal(again, h_out)
 
 
+def _small_layer(mkq, hidden, heads, ffn, seq, lens):
+    """A 4-bit layer of small hidden size over a padding-free batch; its workspace after a run, tensors and output."""
+    import torch
+    from layer_checks import code_row_pitch
+    p, _ = _layer_case(hidden + heads, 1, 8, hidden, heads, ffn)
+    ln = {k: to_dev(p[k]) for k in ("ln1_gamma", "ln1_beta", "ln2_gamma", "ln2_beta")}
+    packed = {}
+    for nm in ("qkv", "ao", "up", "down"):
+        pack = mkq.mkq_pack_weights_int4 if p["W_" + nm].shape[1] % 32 == 0 else mkq.mkq_pack_weights_int4_padded
+        packed[nm] = pack(to_dev(p["W_" + nm])) + (to_dev(p["b_" + nm]),)
+    M = sum(lens)
+    cu = to_dev(np.concatenate([[0], np.cumsum(lens)]).astype(np.int32))
+    layer = mkq.BertLayerInt4(len(lens), seq, hidden, heads, ffn, packed, {"qkv": 0.34, "ao": 0.05, "up": 0.34, "down": 0.05}, ln, p["ln_eps"], 0.4, 4,
+                              cu_seqlens=cu, total_tokens=M)
+    ws = torch.full((layer.workspace_bytes(),), 0x5A, dtype=torch.uint8, device="cuda")  # stale contents
+    q_next = torch.full((M, code_row_pitch(hidden) // 2), 0x5A, dtype=torch.uint8, device="cuda")
+    x = torch.randn((M, hidden), generator=torch.Generator(device="cuda").manual_seed(hidden), device="cuda").half()
+    h_out = layer(x, ws, q_out_next=q_next)
+    return dict(ws=ws, L=layer.layout, cu=cu, M=M, ln=ln, eps=p["ln_eps"], h_out=h_out, q_next=q_next, pitch=code_row_pitch(hidden))
+
+
+def _f16_rows(r, at, cols):
+    import torch
+    return r["ws"][at: at + r["M"] * cols * 2].view(torch.float16).view(r["M"], cols)
+
+
+# heads of 26 (words), 32, 16, 8, 4 (16-byte pieces and words), sequences of one, two and four tiles of tokens, whole and ragged
+@pytest.mark.parametrize("hidden,heads,seq,lens", [(312, 12, 128, (128, 1, 16, 17, 32, 33, 64, 65, 127, 96)), (384, 12, 128, (128, 100, 64, 3) * 8),
+                                                   (256, 16, 64, (64, 33, 32, 31) * 12), (128, 16, 32, (32, 1, 17) * 40), (104, 26, 128, (128, 77) * 20)])
+def test_attention_of_small_layers_is_that_of_its_own_launch(mkq, hidden, heads, seq, lens):
+    """Context codes of a layer that runs q, k, v and the attention in one launch: bit for bit those of the attention on the same q, k, v."""
+    r = _small_layer(mkq, hidden, heads, 256, seq, lens)
+    qkv = _f16_rows(r, r["L"].qkv, 3 * hidden).contiguous()
+    _, want = mkq.mkq_attention_varlen(qkv, r["cu"], seq, hidden, heads, s_next=0.05, want_ctx=False, q_bits=4)
+    got = r["ws"][r["L"].c1: r["L"].c1 + r["M"] * r["pitch"] // 2].view(r["M"], -1)
+    assert np.array_equal(to_np(got[:, :hidden // 2]), to_np(want))
+    assert not got[:, hidden // 2:].any()
+
+
 # Attention output and LayerNorm in one launch (launch_rules.h, output_norm): the fewest and the most tokens, last workgroups of 1 and 15 rows,
 # rows of whole 256-code units and with a half one, with padding codes, the smallest FFN and the base one
 @pytest.mark.parametrize("hidden,heads,ffn,tokens", [(768, 12, 64, 2048), (768, 12, 3072, 2049), (640, 10, 128, 4095), (640, 10, 96, 4096), (744, 12, 200, 2063),
