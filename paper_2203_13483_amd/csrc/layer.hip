@@ -72,11 +72,10 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const uint16_t *__restri
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
         if (lane + i * 64 < chunks) {
+            float d[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = v[i][e] - mean;
-                sq += d * d;
-            }
+            for (int e = 0; e < 8; ++e) d[e] = v[i][e] - mean;
+            sq = i == 0 ? add_squares<true>(sq, d) : add_squares<false>(sq, d);
         }
     }
     const float rstd = 1.0f / sqrtf(wave_sum(sq) / (float)D + eps);
@@ -159,11 +158,10 @@ __global__ __launch_bounds__(256) void layernorm_half_kernel(const uint16_t *__r
 #pragma unroll
     for (int i = 0; i < MAXC; ++i) {
         if (lane + i * 32 < chunks) {
+            float d[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float d = v[i][e] - mean;
-                sq += d * d;
-            }
+            for (int e = 0; e < 8; ++e) d[e] = v[i][e] - mean;
+            sq = i == 0 ? add_squares<true>(sq, d) : add_squares<false>(sq, d);
         }
     }
     sq = lane_reduce<32>(sq, AddF32());

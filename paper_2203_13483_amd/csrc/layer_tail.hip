@@ -196,7 +196,11 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
         copy_floats(nc, (bias ? bias : s_w) + from, n - from, lds0 + Cfg::SCALE_AT + wave * SCALES + at + NS * 256);
     };
 
-    // LayerNorm of the tile's rows, one to a half wave; out: what the rows become (binary16, to the tile too), codes to the operand
+    // LayerNorm of the tile's rows, one to a half wave; out: what the rows become (binary16, to the tile too), codes to the operand.
+    // Sums run in the order of the kernel that has these rows at other token counts (layernorm_half_waves): up to 512 values the whole
+    // wave's, in which lane l of 64 has chunk l, and l and l + 32 meet first; beyond, the half wave's, one chunk after the other.
+    constexpr bool MEET = FFN;
+    static_assert(MEET ? Cfg::HCAP <= 512 && MAXC <= 2 : Cfg::HCAP <= 768, "");
     const int hl = lane & 31, hw = wave * 2 + (lane >> 5);
     const int chunks = p.H / 8;
     auto layernorm = [&](auto midc, uint16_t *x_out, uint16_t *y_out, uint8_t *q_out, float s_q) __attribute__((always_inline)) {
@@ -206,7 +210,7 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
         const int r = hw;
         const int64_t row = row0 + r;
         const bool in = r < rows;
-        float v[MAXC][8], sum = 0.0f;
+        float v[MAXC][8], sums[2] = {0.0f, 0.0f};
         v4u raw[MAXC];
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
@@ -221,21 +225,20 @@ __global__ __launch_bounds__(Cfg::THREADS, 2) void layer_tail_kernel(const Layer
                 v[i][2 * e + 1] = half_bits_to_float((uint16_t)(raw[i][e] >> 16));
             }
 #pragma unroll
-            for (int e = 0; e < 8; ++e) sum += v[i][e];
+            for (int e = 0; e < 8; ++e) sums[MEET ? i : 0] += v[i][e];
         }
-        const float mean = lane_reduce<32>(sum, AddF32()) / (float)p.H;
-        float sq = 0.0f;
+        const float mean = lane_reduce<32>(sums[0] + sums[1], AddF32()) / (float)p.H;
+        float sqs[2] = {0.0f, 0.0f};
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {
             if (hl + i * 32 < chunks) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    v[i][e] -= mean;
-                    sq += v[i][e] * v[i][e];
-                }
+                for (int e = 0; e < 8; ++e) v[i][e] -= mean;
+                float &sq = sqs[MEET ? i : 0];
+                sq = MEET || i == 0 ? add_squares<true>(sq, v[i]) : add_squares<false>(sq, v[i]);
             }
         }
-        const float rstd = 1.0f / sqrtf(lane_reduce<32>(sq, AddF32()) / (float)p.H + p.eps);
+        const float rstd = 1.0f / sqrtf(lane_reduce<32>(sqs[0] + sqs[1], AddF32()) / (float)p.H + p.eps);
         int csum = 0;
 #pragma unroll
         for (int i = 0; i < MAXC; ++i) {

@@ -221,6 +221,17 @@ struct MaxF32 {
 __device__ __forceinline__ float wave_max(float v) { return lane_reduce<64>(v, MaxF32()); }
 __device__ __forceinline__ float wave_sum(float v) { return lane_reduce<64>(v, AddF32()); }
 
+// A LayerNorm's sum of squares: sq and those of eight more values of the lane, FIRST: of its first eight.  Written out, because several
+// kernels have the same rows at different token counts and the compiler, left to contract a * a + b * b, keeps either product exact.
+template <bool FIRST>
+__device__ __forceinline__ float add_squares(float sq, const float (&d)[8])
+{
+    sq = FIRST ? __fmaf_rn(d[0], d[0], d[1] * d[1]) : __fmaf_rn(d[1], d[1], __fmaf_rn(d[0], d[0], sq));
+#pragma unroll
+    for (int e = 2; e < 8; ++e) sq = __fmaf_rn(d[e], d[e], sq);
+    return sq;
+}
+
 __device__ __forceinline__ float half_bits_to_float(uint16_t h)
 {
     return __half2float(__ushort_as_half(h));

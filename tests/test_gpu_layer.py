@@ -687,7 +687,7 @@ def _small_layer(mkq, hidden, heads, ffn, seq, lens):
                               cu_seqlens=cu, total_tokens=M)
     ws = torch.full((layer.workspace_bytes(),), 0x5A, dtype=torch.uint8, device="cuda")  # stale contents
     q_next = torch.full((M, code_row_pitch(hidden) // 2), 0x5A, dtype=torch.uint8, device="cuda")
-    x = torch.randn((M, hidden), generator=torch.Generator(device="cuda").manual_seed(hidden), device="cuda").half()
+    x = torch.randn((5000, hidden), generator=torch.Generator(device="cuda").manual_seed(hidden), device="cuda").half()[:M].contiguous()
     h_out = layer(x, ws, q_out_next=q_next)
     return dict(ws=ws, L=layer.layout, cu=cu, M=M, ln=ln, eps=p["ln_eps"], h_out=h_out, q_next=q_next, pitch=code_row_pitch(hidden))
 
@@ -708,6 +708,28 @@ def test_attention_of_small_layers_is_that_of_its_own_launch(mkq, hidden, heads,
     got = r["ws"][r["L"].c1: r["L"].c1 + r["M"] * r["pitch"] // 2].view(r["M"], -1)
     assert np.array_equal(to_np(got[:, :hidden // 2]), to_np(want))
     assert not got[:, hidden // 2:].any()
+
+
+# rows that a whole wave sums (a half-full second chunk of the half wave, one value of it, all of it) and rows that fit one chunk
+@pytest.mark.parametrize("hidden,heads", [(312, 12), (264, 12), (384, 12), (344, 43), (256, 8)])
+def test_layernorms_of_small_layers_are_those_of_their_own_launch(mkq, hidden, heads):
+    """Both LayerNorms of a layer that runs them with the linears: bit for bit mkq_layernorm's, whose order of a row's sum the same
+    sentence meets in a larger batch; the codes of the last one likewise."""
+    r = _small_layer(mkq, hidden, heads, 256, 128, (128,) * 12 + (77,))
+    L, ln = r["L"], r["ln"]
+    for at, got, gamma, beta in ((L.u, _f16_rows(r, L.h1, hidden), "ln1_gamma", "ln1_beta"), (L.d, r["h_out"], "ln2_gamma", "ln2_beta")):
+        y, q = mkq.mkq_layernorm(_f16_rows(r, at, hidden).contiguous(), ln[gamma], ln[beta], r["eps"], s_next=0.4, want_q=True)
+        assert np.array_equal(to_np(got).view(np.uint16), to_np(y).view(np.uint16))
+    assert np.array_equal(to_np(r["q_next"][:, :hidden // 2]), to_np(q))
+
+
+@pytest.mark.parametrize("hidden,heads", [(312, 12), (384, 12)])
+def test_a_sentence_has_the_same_bits_in_a_larger_batch(mkq, hidden, heads):
+    """The same sequences within 4096 tokens (launch_rules.h, small_layer_tail) and among more."""
+    few, more = (_small_layer(mkq, hidden, heads, 1200, 128, lens) for lens in ([128] * 20 + [50], [128] * 20 + [50] + [128] * 12))
+    assert few["M"] <= 4096 < more["M"]
+    assert np.array_equal(to_np(few["h_out"]).view(np.uint16), to_np(more["h_out"][:few["M"]]).view(np.uint16))
+    assert np.array_equal(to_np(few["q_next"]), to_np(more["q_next"][:few["M"]]))
 
 
 # Attention output and LayerNorm in one launch (launch_rules.h, output_norm): the fewest and the most tokens, last workgroups of 1 and 15 rows,
