@@ -103,11 +103,30 @@ constexpr bool small_layer_attention(int64_t batch, int64_t seq, int64_t hidden,
 {
     return row <= SMALL_LAYER_ROW && row % 128 == 0 && seq <= 128 && hidden / heads <= 32 && batch * heads <= MAX_WORK_ITEMS / 256;
 }
-// The rest: one round of workgroups of 16 tokens on 256 CUs, each of which reads all weights.  In a second round the kernels of their own
-// win, which read them once per 64 or 128 tokens: hidden size 384, 8192 tokens 63.5 -> 61.6, 16384 of 312 100 -> 105, 32768 163 -> 201.
+// The rest: one round of workgroups of 16 tokens on 256 CUs, each of which reads all weights and goes through the FFN's columns one chunk
+// after the other (columns of a chunk, and what whole chunks of the better of the two sizes add up to).  In a second round the kernels of
+// their own win, which read the weights once per 64 or 128 tokens: hidden size 384, 8192 tokens 63.5 -> 61.6, 16384 of 312 100 -> 105, 32768
+// 163 -> 201.
+constexpr int64_t LAYER_TAIL_WIDE = 1280, LAYER_TAIL_NARROW = 768;
+constexpr int64_t layer_tail_columns(int64_t ffn, int64_t chunk) { return (ffn + chunk - 1) / chunk * chunk; }
+// Its time is that of its columns at any token count, the others' grows with the tokens and, up to 1024 of them, hardly with the columns, so
+// the line rises: 768 columns always, with 4/3 more for every token, and 3840 at most.  us a layer, kernels of their own / this, hidden
+// size 312, heads of 26:
+//   tokens        16          128         440         1024        1536        2048        4096
+//    768 columns  21.6 21.6   25.9 25.2   27.0 25.8   29.6 26.1   32.4 26.4   36.2 26.7   39.1 30.2
+//   1280          21.9 25.6   26.4 29.1   27.6 29.6   31.4 29.6   33.8 30.3   39.8 30.7   43.0 34.5
+//   1536          21.7 27.1   26.6 30.5   28.6 31.0   32.1 31.1   35.4 31.7   40.6 31.9   44.1 35.8
+//   2304          22.1 32.0   27.3 35.7   29.4 36.1   34.9 36.5   40.7 37.1   45.1 37.0   51.1 42.7
+//   3072          22.3 37.2   28.0 40.8   31.4 41.2   36.8 41.3   43.5 42.2   47.1 42.3   52.5 49.4
+//   3840          22.4 41.6   28.3 45.3   31.6 45.7   39.8 45.8   44.2 46.6   47.9 46.7   57.1 54.8
+//   8448          23.5 72.1   31.0 76.1   35.7 78.4   45.5 79.3   51.8 82.2   58.1 83.4   80.4 92.4
+// (384 alike; 128 and 256 up to 5 % in this one's favour.)
 constexpr bool small_layer_tail(int64_t tokens, int64_t row, int64_t ffn_row)
 {
-    return row <= SMALL_LAYER_ROW && row % 128 == 0 && ffn_row % 128 == 0 && ffn_row <= 65536 && tokens <= 4096;
+    if (row > SMALL_LAYER_ROW || row % 128 != 0 || ffn_row % 128 != 0 || ffn_row > 3840 || tokens > 4096) return false;
+    const int64_t wide = layer_tail_columns(ffn_row, LAYER_TAIL_WIDE), narrow = layer_tail_columns(ffn_row, LAYER_TAIL_NARROW);
+    const int64_t columns = wide < narrow ? wide : narrow;
+    return columns <= LAYER_TAIL_NARROW || columns <= 320 + tokens * 4 / 3;
 }
 
 // LayerNorm with one row per half wave (the kernels have 256 threads: eight rows), not per wave (four).  Up to D = 1024: where

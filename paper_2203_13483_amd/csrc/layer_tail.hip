@@ -427,7 +427,8 @@ using OutputNorm = LayerTailCfg<6, 6, 2, 1>;   // up to 768 hidden columns, with
 int run_layer_tail(const LayerTailParams &p, hipStream_t st)
 {
     // the chunks whose columns add up to less (a chunk is multiplied whole), and the fewer of them
-    const int64_t wide = ceil_div(p.F, TailWide::CF) * TailWide::CF, narrow = ceil_div(p.F, TailNarrow::CF) * TailNarrow::CF;
+    static_assert(TailWide::CF == LAYER_TAIL_WIDE && TailNarrow::CF == LAYER_TAIL_NARROW, "");
+    const int64_t wide = layer_tail_columns(p.F, TailWide::CF), narrow = layer_tail_columns(p.F, TailNarrow::CF);
     return wide <= narrow ? launch_tail<TailWide, true>(&p, st) : launch_tail<TailNarrow, true>(&p, st);
 }
 

@@ -622,7 +622,8 @@ def test_attention_with_empty_and_one_token_sequences(mkq, heads, dk, max_seq):
 
 # Layers of small hidden size (launch_rules.h, small_layer_*): q, k, v with the attention in one launch, and what follows it in another.
 # Smallest and largest of token tiles (1, 16, 17, 32, 33, 64, 65, 128), of heads (2 to 32, even and multiples of 8), of hidden rows (one and a
-# half 256-code units among them) and of FFN chunks (one column group, ragged, whole, several of both widths); tokens past one round.
+# half 256-code units among them) and of FFN columns (one group, ragged and whole chunks); tokens past one round.  (With so few tokens only
+# FFNs of up to 768 columns are in one launch: the larger ones' is test_a_sentence_has_the_same_bits_in_a_larger_batch.)
 _SMALL = [(1, 1, 312, 12, 1200, None), (3, 17, 312, 12, 1200, None), (1, 32, 128, 4, 512, None), (3, 33, 384, 12, 1536, None), (2, 64, 256, 8, 8, None),
           (2, 65, 376, 47, 1320, None), (2, 128, 384, 192, 2560, None), (1, 128, 104, 4, 768, None), (4, 20, 128, 2, 776, None), (2, 130, 256, 16, 1288, None),
           (7, 128, 312, 12, 1200, (128, 0, 1, 32, 33, 64, 65)), (5, 40, 384, 48, 904, (40, 0, 16, 17, 1)), (34, 128, 312, 12, 1200, (128,) * 31 + (1, 127, 1))]
@@ -689,7 +690,8 @@ def _small_layer(mkq, hidden, heads, ffn, seq, lens):
     q_next = torch.full((M, code_row_pitch(hidden) // 2), 0x5A, dtype=torch.uint8, device="cuda")
     x = torch.randn((5000, hidden), generator=torch.Generator(device="cuda").manual_seed(hidden), device="cuda").half()[:M].contiguous()
     h_out = layer(x, ws, q_out_next=q_next)
-    return dict(ws=ws, L=layer.layout, cu=cu, M=M, ln=ln, eps=p["ln_eps"], h_out=h_out, q_next=q_next, pitch=code_row_pitch(hidden))
+    return dict(ws=ws, L=layer.layout, cu=cu, M=M, ln=ln, eps=p["ln_eps"], h_out=h_out, q_next=q_next, pitch=code_row_pitch(hidden),
+                ffn_pitch=code_row_pitch(ffn))
 
 
 def _f16_rows(r, at, cols):
@@ -723,13 +725,21 @@ def test_layernorms_of_small_layers_are_those_of_their_own_launch(mkq, hidden, h
     assert np.array_equal(to_np(r["q_next"][:, :hidden // 2]), to_np(q))
 
 
-@pytest.mark.parametrize("hidden,heads", [(312, 12), (384, 12)])
-def test_a_sentence_has_the_same_bits_in_a_larger_batch(mkq, hidden, heads):
-    """The same sequences within 4096 tokens (launch_rules.h, small_layer_tail) and among more."""
-    few, more = (_small_layer(mkq, hidden, heads, 1200, 128, lens) for lens in ([128] * 20 + [50], [128] * 20 + [50] + [128] * 12))
-    assert few["M"] <= 4096 < more["M"]
-    assert np.array_equal(to_np(few["h_out"]).view(np.uint16), to_np(more["h_out"][:few["M"]]).view(np.uint16))
-    assert np.array_equal(to_np(few["q_next"]), to_np(more["q_next"][:few["M"]]))
+# one chunk of FFN columns, ragged and whole, two and three of either size; last workgroups of 1, 2 and 15 rows
+@pytest.mark.parametrize("hidden,heads,ffn,tokens", [(312, 12, 1200, 2610), (384, 12, 1280, 720), (312, 12, 8, 1), (264, 12, 768, 130), (376, 47, 1320, 999),
+                                                     (104, 4, 1536, 1025), (384, 12, 2304, 1536), (256, 8, 2560, 2047), (128, 2, 3840, 2640),
+                                                     (312, 12, 3080, 4095)])
+def test_a_sentence_has_the_same_bits_in_a_larger_batch(mkq, hidden, heads, ffn, tokens):
+    """The same sequences where one launch runs what follows the attention (launch_rules.h, small_layer_tail) and among so many that
+    kernels of their own do."""
+    lens = [128] * (tokens // 128) + ([tokens % 128] if tokens % 128 else [])
+    few, more = (_small_layer(mkq, hidden, heads, ffn, 128, part) for part in (lens, lens + [128] * ((4096 - tokens) // 128 + 1)))
+    assert few["M"] == tokens and more["M"] > 4096
+    assert np.array_equal(to_np(few["h_out"]).view(np.uint16), to_np(more["h_out"][:tokens]).view(np.uint16))
+    assert np.array_equal(to_np(few["q_next"]), to_np(more["q_next"][:tokens]))
+    for at, bytes_ in (("u", 2 * hidden), ("h1", 2 * hidden), ("c2", few["pitch"] // 2), ("c3", few["ffn_pitch"] // 2), ("d", 2 * hidden)):
+        a, b = (r["ws"][getattr(r["L"], at):][:tokens * bytes_] for r in (few, more))
+        assert np.array_equal(to_np(a), to_np(b)), at
 
 
 # Attention output and LayerNorm in one launch (launch_rules.h, output_norm): the fewest and the most tokens, last workgroups of 1 and 15 rows,

@@ -157,6 +157,12 @@ def test_small_layers(rules):
     assert rules.small_attention(most // 12, 128, 312, 12, 384) and not rules.small_attention(most // 12 + 1, 128, 312, 12, 384)
     assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
     assert not rules.small_tail(4097, 384, 1280)
+    # FFN columns in whole chunks: 768 always, with 4/3 more for every token, 3840 at most
+    assert rules.small_tail(16, 384, 768) and not rules.small_tail(16, 384, 896) and not rules.small_tail(16, 384, 8192)
+    assert rules.small_tail(720, 384, 1280) and not rules.small_tail(719, 384, 1280) and not rules.small_tail(440, 384, 1280)
+    assert rules.small_tail(912, 384, 1408) and not rules.small_tail(911, 384, 1408)  # two narrow chunks
+    assert rules.small_tail(4096, 384, 3840) and rules.small_tail(2640, 384, 3840) and not rules.small_tail(2639, 384, 3840)
+    assert not rules.small_tail(4096, 384, 3968) and not rules.small_tail(4096, 384, 16384)
     assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
 
 
