@@ -34,7 +34,7 @@ __device__ __forceinline__ int swz_rows(int r) { return ((r >> 3) & 1) | (((r >>
 
 // VEC = 8: d_k % 8 == 0; 2: even
 template <int VEC, int KT>
-__global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentionParams p)
+__global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentionParams p, const XcdRuns runs)
 {
     using Cfg = QkvAttentionCfg<KT>;
     constexpr int DKP = Cfg::DKP;
@@ -44,7 +44,10 @@ __global__ __launch_bounds__(256, 2) void qkv_attention_kernel(const QkvAttentio
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int fr = lane & 31, fh = lane >> 5;
-    const int bh = a.cu_seqlens ? (int)blockIdx.x : xcd_index(blockIdx.x, gridDim.x);
+    // Uniform batches: an eighth of (sequence, head) to each XCD.  Padding-free ones: runs of heads (attention_runs), which read the same
+    // codes and write the same lines.  us a layer of hidden size 312, heads one by one -> runs: 32 x 128 tokens 37.3 -> 34.5, 64 rising
+    // from 8 to 128 54.4 -> 52.4, 64 of 2298 37.5 -> 36.9, 16 of 440 27.1 -> 27.1, 256 x 40 80.3 -> 80.8.
+    const int bh = a.cu_seqlens ? xcd_run_index(blockIdx.x, runs) : xcd_index(blockIdx.x, gridDim.x);
     const int b = bh / a.heads, head = bh - b * a.heads;
     int64_t row0 = (int64_t)b * a.seq;
     int seq = a.seq;
@@ -329,7 +332,8 @@ static int launch_qkv_attention(const QkvAttentionParams *p, hipStream_t st)
     int64_t resident = 0;
     const int rc = resident_workgroups(once, kernel, Cfg::THREADS, Cfg::LDS_BYTES, 8, &resident);
     if (rc != MKQ_OK || !p) return rc;
-    kernel<<<(unsigned)((int64_t)p->att.batch * p->att.heads), Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p);
+    const int64_t sequence_heads = (int64_t)p->att.batch * p->att.heads;
+    kernel<<<(unsigned)sequence_heads, Cfg::THREADS, Cfg::LDS_BYTES, st>>>(*p, attention_runs(sequence_heads, p->att.heads));
     return launch_status();
 }
 
