@@ -152,8 +152,11 @@ def test_small_layers(rules):
     assert not rules.small_attention(32, 129, 312, 12, 384)   # longer than four tiles of 32 tokens
     assert not rules.small_attention(32, 128, 384, 6, 384)    # heads of 64
     assert not rules.small_attention(32, 128, 768, 24, 768) and not rules.small_attention(32, 128, 320, 10, 320)
-    # one workgroup of 256 threads per sequence and head
-    most = 0xFFFFFFFF // 256
+    # only where the launch of its own is the held kernel, whose bits it has: beyond, that launch is another kernel
+    most = 0xFFFFFFFF // 512
+    for hidden, heads, row in ((312, 12, 384), (128, 4, 128), (384, 192, 384)):
+        for batch in (most // heads, most // heads + 1):
+            assert rules.small_attention(batch, 128, hidden, heads, row) == (rules.route(batch, 128, hidden, heads, row) == HELD)
     assert rules.small_attention(most // 12, 128, 312, 12, 384) and not rules.small_attention(most // 12 + 1, 128, 312, 12, 384)
     assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
     assert not rules.small_tail(4097, 384, 1280)
