@@ -866,7 +866,6 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
     if (p->next_bits != 0 && p->next_bits != 4 && p->next_bits != 8) return MKQ_ERR_DTYPE;
     const int next_bits = p->next_bits ? p->next_bits : bits;
     if (p->batch == 0 || layer_tokens(p) == 0) return MKQ_OK;
-    if (!(p->ln_eps >= 0.0f)) return MKQ_ERR_SCALE;  // (what LayerNorm refuses)
     if (!h_in || !h_out || (want_next && !q_out_next)) return MKQ_ERR_NULL;
     if (!p->Wq_qkv || !p->Wq_ao || !p->Wq_up || !p->Wq_down || !p->sw_qkv || !p->sw_ao || !p->sw_up ||
         !p->sw_down)
@@ -886,6 +885,7 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
     const int64_t Hp = code_row(bits, H), Fp = code_row(bits, F);
     const int64_t next_pitch = want_next ? code_row(next_bits, H) : H;
     if (next_bits == 8 && (H % 64) != 0) return MKQ_ERR_SHAPE;  // the 8-bit layer that would read them
+    if (!(p->ln_eps >= 0.0f)) return MKQ_ERR_SCALE;  // (what LayerNorm refuses, and where it did: behind all other faults)
     const int code_dtype = bits == 8 ? MKQ_I8 : MKQ_I4;
     uint8_t *ws = (uint8_t *)workspace;
     // (every writer of codes -- quantizer, attention, LayerNorm, the FFN-up epilogue -- fills the padding

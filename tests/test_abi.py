@@ -216,6 +216,34 @@ def test_padding_free_argument_errors(lib):
         mkq.MKQ_ERR_SCALE, mkq.MKQ_ERR_DTYPE)
 
 
+def test_layer_names_other_faults_before_a_bad_epsilon(lib):
+    """A call with several faults answers what it answered when LayerNorm was the first to look at epsilon."""
+    for entry, hidden, heads in ((lib.mkq_bert_layer_int4, 312, 12), (lib.mkq_bert_layer_int4, 768, 12), (lib.mkq_bert_layer_int8, 768, 12)):
+        for eps in (-1.0, float("nan")):
+            lay = mkq.BertLayerParams()
+            lay.batch, lay.seq, lay.hidden, lay.heads, lay.ffn, lay.ln_eps = 2, 16, hidden, heads, 1216, eps
+            for f in ("sx_qkv", "sx_ao", "sx_up", "sx_down"):
+                setattr(lay, f, 0.1)
+            pointers = [f for f, _ in lay._fields_ if f[:2] in ("Wq", "sw") or f[:3] in ("ln1", "ln2")]
+            for f in pointers:
+                setattr(lay, f, 0x1000)
+
+            def call(h_in=P, ws=P, size=1 << 30):
+                return entry(C.byref(lay), h_in, mkq.MKQ_F16, None, P, P, ws, size, None)
+
+            assert call(h_in=None) == mkq.MKQ_ERR_NULL
+            assert call(h_in=ODD) == mkq.MKQ_ERR_ALIGN
+            assert call(ws=None) == mkq.MKQ_ERR_WORKSPACE and call(size=16) == mkq.MKQ_ERR_WORKSPACE
+            for f in pointers:
+                setattr(lay, f, None)
+                assert call() == mkq.MKQ_ERR_NULL
+                setattr(lay, f, 0x1000)
+            assert call() == mkq.MKQ_ERR_SCALE
+            if hidden % 64:
+                lay.s_out_next, lay.next_bits = 0.1, 8  # an 8-bit layer could not read these rows
+                assert call() == mkq.MKQ_ERR_SHAPE
+
+
 def test_padded_k_argument_errors(lib):
     assert lib.mkq_padded_k(312) == 384 and lib.mkq_padded_k(1200) == 1280
     assert lib.mkq_padded_k(768) == 768 and lib.mkq_padded_k(8) == 128 and lib.mkq_padded_k(0) == 0
