@@ -29,7 +29,7 @@ struct FewLds {
 };
 
 template <int NT, int MT, int PB, int BITS, class Epi>
-__global__ __launch_bounds__(512) void gemm_few_kernel(const GemmI4Params p)
+__global__ __launch_bounds__(512) void gemm_few_kernel(const GemmI4Params p, const FewOrder order)
 {
     using L = FewLds<NT, MT, PB>;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem_all[];
@@ -37,7 +37,9 @@ __global__ __launch_bounds__(512) void gemm_few_kernel(const GemmI4Params p)
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     uint8_t *const smem = smem_all + wave * L::WAVE;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
-    const int n0 = blockIdx.x * (16 * NT), m0 = blockIdx.y * (16 * MT);
+    FewPlace at = {(int)blockIdx.x, (int)blockIdx.y};
+    if (order.inner) at = few_place(blockIdx.x, gridDim.x, order);
+    const int n0 = at.channels * (16 * NT), m0 = at.tokens * (16 * MT);
     const uint32_t row_bytes = (uint32_t)p.K / 8 * BITS;
     const int pieces = (int)(row_bytes / PB);
     const int g0 = pieces * wave / 8, n = pieces * (wave + 1) / 8 - g0;  // this wave's share
@@ -171,9 +173,11 @@ static int launch_few(const GemmI4Params &p, hipStream_t st)
         if (ok <= 0) return MKQ_ERR_HIP;
     }
     if (p.setup_only) return MKQ_OK;
-    const dim3 grid((unsigned)ceil_div(p.N, 16 * NT), (unsigned)ceil_div(p.M, 16 * MT));
-    if (tail) gemm_few_kernel<NT, MT, PB, BITS, EpiGeluTail><<<grid, 512, lds, st>>>(p);
-    else gemm_few_kernel<NT, MT, PB, BITS, EpiGeneric><<<grid, 512, lds, st>>>(p);
+    const int64_t channel_tiles = ceil_div(p.N, 16 * NT), token_tiles = ceil_div(p.M, 16 * MT);
+    const FewOrder order = few_order(p.M, p.N, (int64_t)p.K / 8 * BITS, 16 * NT, 16 * MT);
+    const dim3 grid = order.inner ? dim3((unsigned)(channel_tiles * token_tiles)) : dim3((unsigned)channel_tiles, (unsigned)token_tiles);
+    if (tail) gemm_few_kernel<NT, MT, PB, BITS, EpiGeluTail><<<grid, 512, lds, st>>>(p, order);
+    else gemm_few_kernel<NT, MT, PB, BITS, EpiGeneric><<<grid, 512, lds, st>>>(p, order);
     return launch_status();
 }
 

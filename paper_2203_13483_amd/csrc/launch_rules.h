@@ -180,6 +180,32 @@ constexpr FewTile few_tile(int64_t M, int64_t N, int64_t row_bytes, int bits)
     // (M = 64, K = 768, N = 30522 14.8, persistent 11.9; K = 4096, N = 12288 16.7 -> 8.9)
     return (bits == 4 && few_workgroups(M, N, 64, 64) <= 256) || (M <= 64 && deep) ? kind(FEW_64x64) : FEW_NONE;
 }
+// Which tiles an XCD has: by tokens, an eighth of them with all channels, where what kernels around the linear left of its activations
+// in an L2 is worth more than weights that each XCD reads (M > N, or half of that if they are small beside it: 8-bit K = 5120, N = 768,
+// M = 444 would take 9.3 instead of 7.3); or by channels, an eighth with all tokens.  Workgroups dealt one by one do the latter by
+// themselves if the channel tiles are a multiple of 8; if not, every XCD reads everything, which costs as soon as that is more than its
+// L2.  us, dealt one by one -> this: layers of hidden size 512 and 1024 tokens 36.5 -> 31.8, of 1536 44.0 -> 39.0, 8-bit ones of 256 and
+// 2048 tokens 36.5 -> 29.7; 8-bit K = 4096, N = 64, M = 7379 12.9 -> 10.1, 4-bit K = 8192, N = 576, M = 1679 15.9 -> 13.2.  Finding the
+// tile is 0.05 us of a launch (1 to 2 % of the smallest), so it is left out where it gives nothing.
+struct FewOrder {
+    unsigned inner, magic;  // tiles along the dimension that is gone through first, 0: the grid has both; i / inner = i * magic >> 20
+    bool by_tokens;
+};
+constexpr FewOrder few_order(int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
+{
+    const int64_t ct = (N + channels - 1) / channels, tt = (M + tokens - 1) / tokens;
+    const bool by_tokens = M > N || (2 * M > N && N * row_bytes <= (3 << 19));
+    const bool worth_it = by_tokens ? M * row_bytes >= (1 << 16) : tt > 2 && ct % XCDS != 0 && (M + N) * row_bytes > (4 << 20);
+    if (tt == 1 || !worth_it) return {0, 0, false};
+    const int64_t inner = by_tokens ? ct : tt;
+    return {(unsigned)inner, ct * tt <= 512 ? (unsigned)(((1 << 20) + inner - 1) / inner) : 0, by_tokens};
+}
+struct FewPlace { int channels, tokens; };
+constexpr FewPlace few_place(unsigned wg, unsigned total, const FewOrder &o)
+{
+    const unsigned i = (unsigned)xcd_index(wg, total), outer = o.magic ? i * o.magic >> 20 : i / o.inner, in = i - outer * o.inner;
+    return o.by_tokens ? FewPlace{(int)in, (int)outer} : FewPlace{(int)outer, (int)in};
+}
 // where the kernels were asked for by number
 constexpr FewTile few_tile_or_largest(int64_t M, int64_t N, int64_t row_bytes, int bits)
 {

@@ -35,6 +35,14 @@ extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int6
 }
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
+extern "C" int few_at(unsigned wg, int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
+{
+    const FewOrder o = few_order(M, N, row_bytes, channels, tokens);
+    const int64_t ct = (N + channels - 1) / channels, tt = (M + tokens - 1) / tokens;
+    if (!o.inner) return (int)wg;
+    const FewPlace at = few_place(wg, (unsigned)(ct * tt), o);
+    return (int)(at.tokens * ct + at.channels);
+}
 extern "C" bool small_tail(int64_t tokens, int64_t row, int64_t ffn_row) { return small_layer_tail(tokens, row, ffn_row); }
 extern "C" bool output_with_norm(int64_t tokens, int64_t hidden, int64_t row) { return output_norm(tokens, hidden, row); }
 """
@@ -56,6 +64,7 @@ def rules(tmp_path_factory):
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
     lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
+    lib.few_at.argtypes = [C.c_uint, C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_int]
     lib.small_tail.argtypes, lib.small_tail.restype = [C.c_int64] * 3, C.c_bool
     return lib
 
@@ -174,6 +183,25 @@ def test_output_norm(rules):
     assert not rules.output_with_norm(2047, 768, 768) and not rules.output_with_norm(4097, 768, 768)
     assert not rules.output_with_norm(4096, 1024, 1024) and not rules.output_with_norm(4096, 512, 512)
     assert not rules.output_with_norm(4096, 672, 672)  # no whole half units of 128 codes
+
+
+@pytest.mark.parametrize("M,N,row_bytes,channels,tokens", [(1024, 512, 256, 32, 64), (2048, 256, 1024, 32, 64), (16384, 64, 64, 64, 64), (33, 8, 64, 32, 32),
+                                                           (440, 768, 384, 32, 32), (444, 768, 5120, 32, 64), (700, 940, 4096, 64, 64), (500, 936, 64, 32, 32), (900, 2000, 4096, 64, 64), (128, 1 << 17, 1024, 64, 64),
+                                                           (128, 30000, 4096, 64, 64), (7379, 64, 4096, 32, 64)])
+def test_tiles_of_few_tokens_by_xcd(rules, M, N, row_bytes, channels, tokens):
+    """Every tile has its workgroup, and each XCD an eighth of the tokens with all channels, or of the channels with all tokens, unless both
+    fit its L2 anyway."""
+    ct, tt = -(-N // channels), -(-M // tokens)
+    at = np.array([rules.few_at(w, M, N, row_bytes, channels, tokens) for w in range(ct * tt)])
+    assert np.array_equal(np.sort(at), np.arange(ct * tt))
+    if M > N or (2 * M > N and N * row_bytes <= 3 << 19):
+        if M * row_bytes < 1 << 16:
+            return  # little to read
+        for x in range(8):
+            assert len(set(at[x::8] // ct)) <= -(-tt // 8) + 1
+    elif (M + N) * row_bytes > 1 << 22 and tt > 2:
+        for x in range(8):
+            assert len(set(at[x::8] % ct)) <= -(-ct // 8) + 1
 
 
 def test_few_tokens(rules):
