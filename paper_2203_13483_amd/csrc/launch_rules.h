@@ -97,12 +97,17 @@ constexpr int attention_held_first_half(int64_t sequence_heads, int q_blocks, in
 //   256 tokens 37.5 -> 34.1 -> 28.3, 1024 39.1 -> 35.2 -> 28.4, 4096 50.0 -> 45.6 -> 34.2, padding-free 440 38.3 -> 34.2 -> 27.9,
 //   2298 46.0 -> 45.0 -> 37.8; hidden 384, 4096 tokens 49.5 -> 45.3 -> 36.3, 128 33.5 -> 30.4 -> 21.9.
 constexpr int64_t SMALL_LAYER_ROW = 384;
-// q, k, v and the attention: any number of tokens (16384 of hidden size 312 109 -> 100, 65536 335 -> 292), where the attention would
-// take the held kernel, whose sums it has in the same order (more heads than that one can be launched for sum otherwise).
+// q, k, v and the attention: any number of tokens (16384 of hidden size 312 109 -> 100, 65536 335 -> 292); one workgroup of 256 threads per
+// (sequence, head) has to fit a launch.
 constexpr bool small_layer_attention(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
 {
-    return row <= SMALL_LAYER_ROW && row % 128 == 0 && seq <= 128 && hidden / heads <= 32 &&
-           attention_route(batch, seq, hidden, heads, row) == ATTENTION_HELD;
+    return row <= SMALL_LAYER_ROW && row % 128 == 0 && seq <= 128 && hidden / heads <= 32 && batch * heads <= MAX_WORK_ITEMS / 256;
+}
+// What a layer takes: that, where the attention would take the held kernel, whose sums it has in the same order (more heads than that
+// one can be launched for sum otherwise).
+constexpr bool small_layer_attention_choice(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+{
+    return small_layer_attention(batch, seq, hidden, heads, row) && attention_route(batch, seq, hidden, heads, row) == ATTENTION_HELD;
 }
 // The rest: one round of workgroups of 16 tokens on 256 CUs, each of which reads all weights and goes through the FFN's columns one chunk
 // after the other (columns of a chunk, and what whole chunks of the better of the two sizes add up to).  In a second round the kernels of

@@ -15,7 +15,7 @@ struct QkvAttentionParams {
     uint16_t *qkv;            // [tokens, 3 hidden]
 };
 
-// Launches it (small_layer says for which layers).
+// Launches it (small_layer_attention_choice says for which layers).
 int run_qkv_attention(const QkvAttentionParams &p, hipStream_t st);
 // once-per-device setup of its instantiations (nothing is launched)
 int setup_qkv_attention();

@@ -622,8 +622,7 @@ def test_attention_with_empty_and_one_token_sequences(mkq, heads, dk, max_seq):
 
 # Layers of small hidden size (launch_rules.h, small_layer_*): q, k, v with the attention in one launch, and what follows it in another.
 # Smallest and largest of token tiles (1, 16, 17, 32, 33, 64, 65, 128), of heads (2 to 32, even and multiples of 8), of hidden rows (one and a
-# half 256-code units among them) and of FFN columns (one group, ragged and whole chunks); tokens past one round.  (With so few tokens only
-# FFNs of up to 768 columns are in one launch: the larger ones' is test_a_sentence_has_the_same_bits_in_a_larger_batch.)
+# half 256-code units among them) and of FFN chunks (one column group, ragged, whole, several of both widths); tokens past one round.
 _SMALL = [(1, 1, 312, 12, 1200, None), (3, 17, 312, 12, 1200, None), (1, 32, 128, 4, 512, None), (3, 33, 384, 12, 1536, None), (2, 64, 256, 8, 8, None),
           (2, 65, 376, 47, 1320, None), (2, 128, 384, 192, 2560, None), (1, 128, 104, 4, 768, None), (4, 20, 128, 2, 776, None), (2, 130, 256, 16, 1288, None),
           (7, 128, 312, 12, 1200, (128, 0, 1, 32, 33, 64, 65)), (5, 40, 384, 48, 904, (40, 0, 16, 17, 1)), (34, 128, 312, 12, 1200, (128,) * 31 + (1, 127, 1))]

@@ -33,6 +33,10 @@ extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int6
 {
     return small_layer_attention(batch, seq, hidden, heads, row);
 }
+extern "C" bool small_attention_taken(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+{
+    return small_layer_attention_choice(batch, seq, hidden, heads, row);
+}
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" int few_at(unsigned wg, int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
@@ -62,6 +66,7 @@ def rules(tmp_path_factory):
     lib.piece_index.argtypes = [C.c_uint, C.c_uint]
     lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
+    lib.small_attention_taken.argtypes, lib.small_attention_taken.restype = [C.c_int64] * 5, C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
     lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
     lib.few_at.argtypes = [C.c_uint, C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_int]
@@ -161,21 +166,29 @@ def test_small_layers(rules):
     assert not rules.small_attention(32, 129, 312, 12, 384)   # longer than four tiles of 32 tokens
     assert not rules.small_attention(32, 128, 384, 6, 384)    # heads of 64
     assert not rules.small_attention(32, 128, 768, 24, 768) and not rules.small_attention(32, 128, 320, 10, 320)
-    # only where the launch of its own is the held kernel, whose bits it has: beyond, that launch is another kernel
-    most = 0xFFFFFFFF // 512
-    for hidden, heads, row in ((312, 12, 384), (128, 4, 128), (384, 192, 384)):
-        for batch in (most // heads, most // heads + 1):
-            assert rules.small_attention(batch, 128, hidden, heads, row) == (rules.route(batch, 128, hidden, heads, row) == HELD)
+    # one workgroup of 256 threads per sequence and head
+    most = 0xFFFFFFFF // 256
     assert rules.small_attention(most // 12, 128, 312, 12, 384) and not rules.small_attention(most // 12 + 1, 128, 312, 12, 384)
     assert rules.small_tail(4096, 384, 1280) and rules.small_tail(1, 128, 128)
     assert not rules.small_tail(4097, 384, 1280)
-    # FFN columns in whole chunks: 768 always, with 4/3 more for every token, 3840 at most
+    assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
+
+
+def test_small_layers_keep_the_kernel_that_their_attention_would_take(rules):
+    """In one launch with q, k, v only where the launch of its own is the held kernel, whose bits it has: beyond, that is another kernel."""
+    most = 0xFFFFFFFF // 512
+    for hidden, heads, row in ((312, 12, 384), (128, 4, 128), (384, 12, 384)):
+        for batch in (1, most // heads, most // heads + 1):
+            assert rules.small_attention_taken(batch, 128, hidden, heads, row) == (rules.route(batch, 128, hidden, heads, row) == HELD)
+
+
+def test_small_layers_in_one_launch(rules):
+    """FFN columns in whole chunks: 768 always, with 4/3 more for every token, 3840 at most."""
     assert rules.small_tail(16, 384, 768) and not rules.small_tail(16, 384, 896) and not rules.small_tail(16, 384, 8192)
     assert rules.small_tail(720, 384, 1280) and not rules.small_tail(719, 384, 1280) and not rules.small_tail(440, 384, 1280)
     assert rules.small_tail(912, 384, 1408) and not rules.small_tail(911, 384, 1408)  # two narrow chunks
     assert rules.small_tail(4096, 384, 3840) and rules.small_tail(2640, 384, 3840) and not rules.small_tail(2639, 384, 3840)
     assert not rules.small_tail(4096, 384, 3968) and not rules.small_tail(4096, 384, 16384)
-    assert not rules.small_tail(4096, 512, 2048) and not rules.small_tail(4096, 352, 1280) and not rules.small_tail(4096, 384, 1312)
 
 
 def test_output_norm(rules):
