@@ -318,7 +318,8 @@ static int choose_rows64(const GemmI4Params &p)
 // Tile choice: where whole 256-code stages fit K, the kernels with 128-byte stage rows (43 .. 49 and 51, gemm_lines.hip) in the
 // ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
 // 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
-// rounds of tiles).  (us, 64-byte -> 128-byte rows)
+// rounds of tiles).  (us, 64-byte -> 128-byte rows)  Of the calls with up to 256 tiles of 64x64 most are few_tile's: what comes here
+// has K = 128 or 256, or K from 2048 to 4095 and pieces that eight waves do not share evenly.
 static int choose_tiles(const GemmI4Params &p)
 {
     const int rows64 = choose_rows64(p);
@@ -345,11 +346,10 @@ static int choose_tiles(const GemmI4Params &p)
     }
     if (t64 <= 512 && ceil_div(p.M, 128) * ceil_div(p.N, 64) <= 256 && p.K >= 1024) {
         // few tiles and a long k loop, shared by the wave groups of a workgroup (a lone wave per SIMD is bound by its own
-        // instruction stream): 47, 64x64: M = 440, K = 3072, N = 768 8.3 -> 7.8; 48, 128x64: M = 2298 12.5 -> 10.7
+        // instruction stream): 47, 64x64: K = 2560, N = 1024, M = 963 8.7 -> 8.0; 48, 128x64: M = 2298, K = 3072, N = 768 12.5 -> 10.7
         if (split) return t64 <= 256 ? 47 : p.K >= 1536 ? 48 : 43;
-        // an odd number of 256-code stages: the 64-byte rows can be shared (K = 1280, N = 312 with a residual 43 would take
-        // 6.4 instead of 5.9; K = 2304, N = 768, M = 440 8.6 instead of 7.3)
-        return p.K >= 2048 || (res && t64 <= 256) ? rows64 : 43;
+        // an odd number of 256-code stages: a long loop can be shared in 64-byte rows
+        return p.K >= 2048 ? rows64 : 43;
     }
     // 43, 64x64, up to three per CU: M = 4096, K = N = 768 with a residual 8.7 -> 8.1; M = 1024, N = 3072 with GELU 9.2 -> 8.6
     if (t64 <= 768 && (p.K < 1536 || (p.K < 2048 && (gelu || !split)))) return 43;
@@ -415,7 +415,7 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
     if (cfg < 0 && p.M > 64 && gemm_i4_stream_ok(p) && (int64_t)p.N * p.K >= ((int64_t)1 << 27))
         return run_gemm_i4_stream(p, scr, forced_ks, st);
     if (cfg < 0) {
-        const FewTile few = few_tile(p.M, p.N, p.K / 2, 4);
+        const FewTile few = few_choice(p.M, p.N, p.K / 2, 4);
         if (few != FEW_NONE) return run_gemm_few(p, 4, few, st);
     }
     if (cfg < 0) {
@@ -427,12 +427,11 @@ int run_gemm_i4(const GemmI4Params &p, hipStream_t st, int forced_cfg, const Spl
     }
     if (cfg >= 10 && !dma_ok) return MKQ_ERR_UNSUPPORTED;
     // few 64x64 tiles (at most two workgroups per CU) and a k loop long enough to halve, in 64-byte rows (an odd
-    // number of 256-code stages): two wave groups per workgroup, with the deeper ring when the k loop is very long or
-    // for a weight matrix of 4 MiB and more, which comes from memory rather than from the caches on most calls
-    if (forced_cfg < 0 && cfg == 27 && (p.K % 256) == 0 && p.K >= 512) {
+    // number of 256-code stages): two wave groups per workgroup, with the deeper ring for a weight matrix of 4 MiB and more,
+    // which comes from memory rather than from the caches on most calls
+    if (forced_cfg < 0 && cfg == 27 && (p.K % 256) == 0 && p.K >= 2048) {
         const int64_t t64 = ceil_div(p.M, 64) * ceil_div(p.N, 64);
-        if (t64 <= 256 || (t64 <= 512 && p.K >= 2048))
-            cfg = (t64 <= 256 && (p.K >= 6144 || (int64_t)p.N * p.K >= ((int64_t)8 << 20))) ? 31 : 33;
+        if (t64 <= 512) cfg = t64 <= 256 && (int64_t)p.N * p.K >= ((int64_t)8 << 20) ? 31 : 33;
     }
     if ((cfg == 31 || cfg == 33 || cfg == 35) && (p.K % 256) != 0) return MKQ_ERR_UNSUPPORTED;
     if (cfg >= 60 && cfg <= 62) {  // tile kernels with the k loop also split across workgroups
@@ -534,7 +533,7 @@ int run_gemm_i8(const GemmI4Params &p, hipStream_t st, int forced_cfg = -1)
     if ((p.K % 64) != 0) return MKQ_ERR_UNSUPPORTED;
     if (forced_cfg == 30) return (p.M <= 64 && (p.K % 128) == 0) ? run_gemm_few(p, 8, few_tile_or_largest(p.M, p.N, p.K, 8), st) : MKQ_ERR_UNSUPPORTED;
     if (forced_cfg < 0) {
-        const FewTile few = few_tile(p.M, p.N, p.K, 8);
+        const FewTile few = few_choice(p.M, p.N, p.K, 8);
         if (few != FEW_NONE) return run_gemm_few(p, 8, few, st);
     }
     int epi = classify_epilogue(p);

@@ -164,8 +164,11 @@ constexpr int64_t few_workgroups(int64_t M, int64_t N, int channels, int tokens)
 {
     return ((N + channels - 1) / channels) * ((M + tokens - 1) / tokens);
 }
-// The smallest tile whose workgroups are resident together (LDS: 32 KiB a workgroup of 16x16 to 128 of 64x64), since a second round
-// costs as much as the first; past that the persistent kernels take over (FEW_NONE).  us, 4 bits, binary16 out:
+// LDS of a workgroup: 16, 24, 32, 64 and 128 KiB for the five tiles, 32, 48, 64, 96 and 128 with the long pieces.
+// Up to 16 tokens the smallest tile, up to 32 it or 32x32, however many workgroups there are: more tokens to a tile would only be
+// padding.  Beyond, the smallest tile whose workgroups are about one round, because a second costs as much as the first: one per CU, or
+// two (32x32 and 32x64 of rows below 1024 bytes; more than two of 32x32 fit and gain nothing).  Past that the persistent kernels take
+// over (FEW_NONE), but for up to 64 tokens with rows of 2048 bytes and more, whose 64x64 tiles have any number.  us, 4 bits, binary16 out:
 // K = N = 768, M = 640 (480 / 240 workgroups) 32x32 3.4, 32x64 3.6; M = 1024 (768 / 384 / 192) 4.5, 4.4, 64x64 4.6, the persistent 64x64
 // 5.1; N = 2304, M = 440 (504 of 32x64) 4.6, persistent 4.8, M = 640 (720) 6.4, 5.7; K = 3072, N = 768, M = 1024 (384 / 192) 32x64 7.7,
 // 64x64 6.7, persistent 7.7; K = N = 4096, M = 256 (256 of 64x64) 7.8, persistent 10.8, M = 440 (448) 13.8, 13.4.  8-bit operands need no
@@ -179,11 +182,24 @@ constexpr FewTile few_tile(int64_t M, int64_t N, int64_t row_bytes, int bits)
     if (few_workgroups(M, N, 16, 16) > MAX_WORK_ITEMS / 512) return FEW_NONE;  // (of 512 threads)
     if (M <= 16) return kind(FEW_16x16);
     if (M <= 32) return kind(few_workgroups(M, N, 16, 32) <= (deep ? 256 : 512) ? FEW_16x32 : FEW_32x32);
-    const int64_t two = row_bytes < 1024 ? 512 : 256;  // workgroups: two rounds where they are short
+    const int64_t two = row_bytes < 1024 ? 512 : 256;  // workgroups: two per CU where they are short
     if (few_workgroups(M, N, 32, 32) <= two) return kind(FEW_32x32);
     if (few_workgroups(M, N, 32, 64) <= (bits == 8 ? 256 : two)) return kind(FEW_32x64);
     // (M = 64, K = 768, N = 30522 14.8, persistent 11.9; K = 4096, N = 12288 16.7 -> 8.9)
     return (bits == 4 && few_workgroups(M, N, 64, 64) <= 256) || (M <= 64 && deep) ? kind(FEW_64x64) : FEW_NONE;
+}
+// What a call takes: that, but for shapes where it leaves waves idle and the persistent kernels are ahead.
+constexpr FewTile few_choice(int64_t M, int64_t N, int64_t row_bytes, int bits)
+{
+    const FewTile t = few_tile(M, N, row_bytes, bits);
+    // One or two pieces leave most waves without one, and a second 32x64 workgroup per CU is no gain any more (4 bits, K = 128, N = 936,
+    // M = 1048, 510 workgroups 4.9, persistent 4.2; K = 256, N = 768, M = 1019 4.45, 4.2; but 59 tokens, N = 12288 4.4, 7.1)
+    if (t == FEW_32x64 && (row_bytes == 64 || (row_bytes == 128 && M > 64)) && few_workgroups(M, N, 32, 64) > 256) return FEW_NONE;
+    // Pieces of 64 bytes that are not the same number for all waves cost a round of them: K = 2304 (18 pieces), N = 936, M = 1032 (255
+    // workgroups) 8.2, persistent 7.9, up to 208 of them 0.94 to 1.0 of its time; where that one's wave groups share K evenly it is ahead
+    // sooner (K = 2560, N = 4096, M = 228, 256 workgroups 7.9, 7.45; up to 144 0.96 to 1.0).
+    if (t == FEW_64x64 && row_bytes % 512 != 0 && few_workgroups(M, N, 64, 64) > (row_bytes % 256 == 0 ? 144 : 208)) return FEW_NONE;
+    return t;
 }
 // Which tiles an XCD has: by tokens, an eighth of them with all channels, where what kernels around the linear left of its activations
 // in an L2 is worth more than weights that each XCD reads (M > N, or half of that if they are small beside it: 8-bit K = 5120, N = 768,

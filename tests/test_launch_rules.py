@@ -38,6 +38,7 @@ extern "C" bool small_attention_taken(int64_t batch, int64_t seq, int64_t hidden
     return small_layer_attention_choice(batch, seq, hidden, heads, row);
 }
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
+extern "C" int few_taken(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_choice(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" int few_at(unsigned wg, int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
 {
@@ -196,6 +197,18 @@ def test_output_norm(rules):
     assert not rules.output_with_norm(2047, 768, 768) and not rules.output_with_norm(4097, 768, 768)
     assert not rules.output_with_norm(4096, 1024, 1024) and not rules.output_with_norm(4096, 512, 512)
     assert not rules.output_with_norm(4096, 672, 672)  # no whole half units of 128 codes
+
+
+def test_few_tokens_leaves_short_and_uneven_rows_to_the_persistent_kernels(rules):
+    few = lambda *s, bits=4: rules.few_taken(*map(C.c_int64, s), bits)  # noqa: E731
+    assert few(1024, 512, 64) == 2 and few(1024, 513, 64) == -1 and few(41, 12288, 64) == -1  # one piece: a second 32x64 per CU
+    assert few(1024, 512, 128) == 2 and few(1024, 544, 128) == -1 and few(59, 12288, 128) == 3 and few(65, 8192, 128) == -1
+    assert few(1024, 544, 192) == 3
+    # 18 and 20 pieces of 64 bytes among eight waves, 24 and 16, 20 of 128 bytes
+    assert few(1040, 768, 1152) == 4 and few(1041, 768, 1152) == 4 and few(1664, 512, 1152) == 4 and few(1665, 512, 1152) == -1
+    assert few(1152, 512, 1280) == 4 and few(1153, 512, 1280) == -1
+    assert few(2048, 512, 1536) == 4 and few(2048, 512, 1024) == 4 and few(2048, 512, 2560) == 9
+    assert few(2049, 512, 1536) == -1
 
 
 @pytest.mark.parametrize("M,N,row_bytes,channels,tokens", [(1024, 512, 256, 32, 64), (2048, 256, 1024, 32, 64), (16384, 64, 64, 64, 64), (33, 8, 64, 32, 32),
