@@ -508,8 +508,8 @@ static int choose_tiles_i8(const GemmI4Params &p)
     if (!gelu && t256x128 >= 512 && 2.0 * p.M * p.N * p.K >= 6e10) return whole && !f32 ? 44 : 18;
     if (t64 <= 256 && (p.K % 256) == 0 && p.K >= 2048) return 47;
     const bool fixed = classify_epilogue(p) != EPI_GENERIC && !f32;
-    if (fixed && t64 > 512 && p.K >= 1536 && ceil_div(p.M, 128) * ceil_div(p.N, 96) <= 256) return 51;
-    if (fixed && t128 > 512 && (gelu || res || p.K >= 1536) && ceil_div(p.M, 256) * ceil_div(p.N, 192) <= 256) return 52;
+    if (fixed && i8_128x96(p.M, p.N, p.K, gelu)) return 51;
+    if (fixed && i8_256x192(p.M, p.N, p.K, gelu, res)) return 52;
     const bool general = p.K < 2048 && classify_epilogue(p) == EPI_GENERIC;
     if (t64 <= 768 || (gelu && p.K < 1536 && t64 <= (general && p.K < 768 ? 1024 : 1536)) ||
         (res && !f32 && p.K <= 1024 && t64 <= 1024))

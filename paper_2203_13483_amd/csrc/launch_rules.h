@@ -201,6 +201,25 @@ constexpr FewTile few_choice(int64_t M, int64_t N, int64_t row_bytes, int bits)
     if (t == FEW_64x64 && row_bytes % 512 != 0 && few_workgroups(M, N, 64, 64) > (row_bytes % 256 == 0 ? 144 : 208)) return FEW_NONE;
     return t;
 }
+// Tiles of three parts, one per CU in one round: when an 8-bit linear takes 128x96 and 256x192.
+constexpr int64_t tiles_of(int64_t M, int64_t N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+// 128x96: more than two 64x64 tiles per CU and a long k loop, with GELU, which nothing covers, a longer one (us, 43 -> 51: K = 1536, N = 256,
+// M = 8653 with GELU 11.2 -> 11.75, N = 1024, M = 2372 11.9 -> 11.8, without 11.0 -> 9.8; K = 2048, N = 768, M = 3815 with GELU 14.6 -> 14.1).
+constexpr bool i8_128x96(int64_t M, int64_t N, int64_t K, bool gelu)
+{
+    return K >= (gelu ? 2048 : 1536) && tiles_of(M, N, 64, 64) > 512 && tiles_of(M, N, 128, 96) <= 256;
+}
+// 256x192: where 128x128 tiles come in two rounds of two per CU, for GELU, residuals and long k loops.  At short k the epilogue is the tile and
+// three 128x128 ones per CU share it out (us, 29 -> 52: K = 128, N = 768, M = 10942 with a residual 10.3 -> 11.35, with GELU 13.2 -> 14.5;
+// K = 256, N = 6144, M = 1759 14.1 -> 15.3; K = 384, N = 1920, M = 6365 with GELU 18.0 -> 16.9, with a residual 16.8 -> 16.9; K = 512, N = 2304,
+// M = 3615 15.1 -> 14.65), longer where a residual's rows end inside a line (K = 512, N = 936, M = 11546 17.4 -> 20.25; K = 1024, M = 8557
+// 20.9 -> 20.5).
+constexpr bool i8_256x192(int64_t M, int64_t N, int64_t K, bool gelu, bool residual)
+{
+    const bool takes = K >= 1536 || (gelu && K >= 384) || (residual && K >= (N % 64 != 0 ? 1024 : 512));
+    return takes && tiles_of(M, N, 128, 128) > 512 && tiles_of(M, N, 256, 192) <= 256;
+}
+
 // Which tiles an XCD has: by tokens, an eighth of them with all channels, where what kernels around the linear left of its activations
 // in an L2 is worth more than weights that each XCD reads (M > N, or half of that if they are small beside it: 8-bit K = 5120, N = 768,
 // M = 444 would take 9.3 instead of 7.3); or by channels, an eighth with all tokens.  Workgroups dealt one by one do the latter by

@@ -38,6 +38,10 @@ extern "C" bool small_attention_taken(int64_t batch, int64_t seq, int64_t hidden
     return small_layer_attention_choice(batch, seq, hidden, heads, row);
 }
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
+extern "C" int i8_tiles_of_three(int64_t M, int64_t N, int64_t K, bool gelu, bool residual)
+{
+    return i8_128x96(M, N, K, gelu) + 2 * i8_256x192(M, N, K, gelu, residual);
+}
 extern "C" int few_taken(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_choice(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" int few_at(unsigned wg, int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
@@ -70,6 +74,7 @@ def rules(tmp_path_factory):
     lib.small_attention_taken.argtypes, lib.small_attention_taken.restype = [C.c_int64] * 5, C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
     lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
+    lib.i8_tiles_of_three.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
     lib.few_at.argtypes = [C.c_uint, C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_int]
     lib.small_tail.argtypes, lib.small_tail.restype = [C.c_int64] * 3, C.c_bool
     return lib
@@ -197,6 +202,17 @@ def test_output_norm(rules):
     assert not rules.output_with_norm(2047, 768, 768) and not rules.output_with_norm(4097, 768, 768)
     assert not rules.output_with_norm(4096, 1024, 1024) and not rules.output_with_norm(4096, 512, 512)
     assert not rules.output_with_norm(4096, 672, 672)  # no whole half units of 128 codes
+
+
+def test_tiles_of_three_parts_leave_short_k_loops_to_smaller_ones(rules):
+    """(M, N, K): neither, 1 128x96, 2 256x192; plain, with a residual, with GELU."""
+    def kinds(*shape):
+        return [rules.i8_tiles_of_three(*shape, gelu, res) for gelu, res in ((False, False), (False, True), (True, False))]
+    assert kinds(8653, 256, 1536) == [1, 1, 0] and kinds(3815, 768, 2048) == [1, 1, 1] and kinds(3815, 768, 1472) == [0, 0, 0]
+    assert kinds(10942, 768, 128) == [0, 0, 0] and kinds(10942, 768, 320) == [0, 0, 0] and kinds(10942, 768, 384) == [0, 0, 2]
+    assert kinds(10942, 768, 512) == [0, 2, 2] and kinds(10942, 768, 1536) == [2, 2, 2]
+    assert kinds(11546, 936, 512) == [0, 0, 2] and kinds(11546, 936, 960) == [0, 0, 2] and kinds(11546, 936, 1024) == [0, 2, 2]
+    assert kinds(16384, 768, 1024) == [0, 2, 2] and kinds(16385, 768, 1024) == [0, 0, 0]  # one round
 
 
 def test_few_tokens_leaves_short_and_uneven_rows_to_the_persistent_kernels(rules):
