@@ -279,7 +279,7 @@ static int choose_f16(const GemmI4Params &p)
     // size costs is its fullest CU, and 128x128 tiles leave a quarter of the chip idle where these leave none.  us, before -> here:
     // 4096 tokens, K = 3072, N = 768 26.5 -> 23.3, K = N = 768 with a residual 10.8 -> 9.9; 2560, K = 4096, N = 1024 32.6 -> 28.3;
     // 1024, K = 768, N = 2304 9.7 -> 8.9, N = 3072 with GELU 10.9 -> 10.3.  In a second round it loses (4352, K = 3072, N = 768 26.9 -> 41.1).
-    if (t64 > 512 && ceil_div(p.M, 128) * ceil_div(p.N, 96) <= 256) return F16_128x96_DEEP;
+    if (f16_128x96(p.M, p.N, p.K, p.act == MKQ_ACT_GELU, p.residual != nullptr)) return F16_128x96_DEEP;
     // up to two 64x64 tiles per CU, three (all that fit) where the epilogue is a large share of the tile: 3072 tokens,
     // K = N = 768 with a residual 12.1 -> 11.3, 681 tokens, K = 768, N = 3072 with GELU 11.7 -> 10.9; without either the
     // 128x128 tiles win from two per CU on (1024 tokens, K = 768, N = 2304 10.5 -> 10.0)
@@ -298,7 +298,7 @@ static int choose_f16(const GemmI4Params &p)
     const auto rounds = [](int64_t tiles, int64_t per_round) { return (double)ceil_div(tiles, per_round); };
     const int64_t t256 = ceil_div(p.M, 256) * ceil_div(p.N, 256);
     const double other = t256 >= 256 ? 18.0 * rounds(t256, 256) : 11.5 * rounds(t128, 512);
-    if (15.0 * rounds(ceil_div(p.M, 256) * ceil_div(p.N, 192), 256) + 2.0 < other) return F16_256x192;
+    if (15.0 * rounds(ceil_div(p.M, 256) * ceil_div(p.N, 192), 256) + 2.0 < other && f16_256x192_suits(p.N, p.K, p.residual != nullptr)) return F16_256x192;
     return t256 >= 256 ? F16_256 : F16_128;
 }
 

@@ -219,6 +219,16 @@ constexpr bool i8_256x192(int64_t M, int64_t N, int64_t K, bool gelu, bool resid
     const bool takes = K >= 1536 || (gelu && K >= 384) || (residual && K >= (N % 64 != 0 ? 1024 : 512));
     return takes && tiles_of(M, N, 128, 128) > 512 && tiles_of(M, N, 256, 192) <= 256;
 }
+// The same of a binary16 linear.  128x96: as above, at any k but with a longer epilogue (us, before -> 128x96: K = 128, N = 512, M = 5204 with
+// GELU 6.85 -> 7.25, K = 512, N = 936, M = 2223 with GELU 9.0 -> 9.3; K = 256, N = 936, M = 2593 with a residual 7.4 -> 7.65; K = 768 with GELU
+// 4 % in its favour).
+constexpr bool f16_128x96(int64_t M, int64_t N, int64_t K, bool gelu, bool residual)
+{
+    return K >= (gelu ? 640 : residual ? 384 : 0) && tiles_of(M, N, 64, 64) > 512 && tiles_of(M, N, 128, 96) <= 256;
+}
+// 256x192: not for a short k loop and a residual whose rows end inside a line (K = 384, N = 936, M = 11647 21.6 -> 23.4, K = 512, M = 11461
+// 24.3 -> 25.4; K = 768, M = 11428 31.0 -> 29.6).  Otherwise the tile whose rounds add up to the least (choose_f16).
+constexpr bool f16_256x192_suits(int64_t N, int64_t K, bool residual) { return !(residual && N % 64 != 0 && K < 768); }
 
 // Which tiles an XCD has: by tokens, an eighth of them with all channels, where what kernels around the linear left of its activations
 // in an L2 is worth more than weights that each XCD reads (M > N, or half of that if they are small beside it: 8-bit K = 5120, N = 768,

@@ -42,6 +42,10 @@ extern "C" int i8_tiles_of_three(int64_t M, int64_t N, int64_t K, bool gelu, boo
 {
     return i8_128x96(M, N, K, gelu) + 2 * i8_256x192(M, N, K, gelu, residual);
 }
+extern "C" int f16_tiles_of_three(int64_t M, int64_t N, int64_t K, bool gelu, bool residual)
+{
+    return f16_128x96(M, N, K, gelu, residual) + 2 * f16_256x192_suits(N, K, residual);
+}
 extern "C" int few_taken(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_choice(M, N, row_bytes, bits); }
 extern "C" int few_asked(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile_or_largest(M, N, row_bytes, bits); }
 extern "C" int few_at(unsigned wg, int64_t M, int64_t N, int64_t row_bytes, int channels, int tokens)
@@ -75,6 +79,7 @@ def rules(tmp_path_factory):
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
     lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
     lib.i8_tiles_of_three.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
+    lib.f16_tiles_of_three.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
     lib.few_at.argtypes = [C.c_uint, C.c_int64, C.c_int64, C.c_int64, C.c_int, C.c_int]
     lib.small_tail.argtypes, lib.small_tail.restype = [C.c_int64] * 3, C.c_bool
     return lib
@@ -213,6 +218,14 @@ def test_tiles_of_three_parts_leave_short_k_loops_to_smaller_ones(rules):
     assert kinds(10942, 768, 512) == [0, 2, 2] and kinds(10942, 768, 1536) == [2, 2, 2]
     assert kinds(11546, 936, 512) == [0, 0, 2] and kinds(11546, 936, 960) == [0, 0, 2] and kinds(11546, 936, 1024) == [0, 2, 2]
     assert kinds(16384, 768, 1024) == [0, 2, 2] and kinds(16385, 768, 1024) == [0, 0, 0]  # one round
+
+
+def test_binary16_tiles_of_three_parts_leave_short_k_loops_to_smaller_ones(rules):
+    """(M, N, K): 1 128x96 is taken, 2 256x192 may be; plain, with a residual, with GELU."""
+    def kinds(*shape):
+        return [rules.f16_tiles_of_three(*shape, gelu, res) for gelu, res in ((False, False), (False, True), (True, False))]
+    assert kinds(5204, 512, 128) == [3, 2, 2] and kinds(5204, 512, 384) == [3, 3, 2] and kinds(5204, 512, 640) == [3, 3, 3]
+    assert kinds(11647, 936, 384) == [2, 0, 2] and kinds(11428, 936, 768) == [2, 2, 2] and kinds(11647, 960, 384) == [2, 2, 2]
 
 
 def test_few_tokens_leaves_short_and_uneven_rows_to_the_persistent_kernels(rules):
