@@ -47,10 +47,6 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
                                                                                 const XcdRuns runs)
 {
     using Cfg = AttentionHeldCfg<DKP, NG>;
-    // Groups of 32 keys by which fragments are fetched ahead of their products: with two waves on a SIMD the LDS answers too late
-    // otherwise (16 x 512 tokens, 16 heads of 64, 41.2 -> 38.2 us), with four the registers spill (32 x 256 27.8 -> 39.0).  Two groups
-    // gain nothing over one up to 384 keys and spill at 512.
-    constexpr int AHEAD = NG <= 8 ? 0 : 1;
     constexpr int THREADS = Cfg::THREADS, KEYS = Cfg::KEYS, ROWB = DKP * 2, CH = DKP / 8, VROW = Cfg::VROW, DS = DKP / 32;
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     uint8_t *const sK = smem, *const sVt = smem + Cfg::K_BYTES;
@@ -185,6 +181,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     v4f sc[NG][2];  // scores: element e of part t of group g is key 32 g + 8 lg + 4 t + e
     auto softmax = [&](auto fullc, float &mx, float &den) __attribute__((always_inline)) {
         constexpr bool FULL = fullc.value;
+        constexpr int AHEAD = held_fetch_ahead(FULL, NG);
         auto exists = [&](int g) { return FULL || g * 32 < seq; };  // (uniform)
         v8h qf[DS];
 #pragma unroll
@@ -201,42 +198,52 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
                 for (int ds = 0; ds < DS; ++ds)
                     kf[g % (AHEAD + 1)][t][ds] = *reinterpret_cast<const v8h *>(sK + (kat ^ (ds * 64)) + (g * 32 + 4 * t) * ROWB);
         };
+        auto scores = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                sc[g][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                for (int ds = 0; ds < DS; ++ds) sc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[g % (AHEAD + 1)][t][ds], qf[ds], sc[g][t], 0, 0, 0);
+            }
+        };
         auto maximum = [&](int g) __attribute__((always_inline)) {
-            if (exists(g)) {
-                if ((!FULL || g >= NG - 2) && g * 32 + 32 > seq) {  // (uniform) keys that do not exist
-                    int keys = seq - g * 32 - 8 * lg;
-                    asm volatile("" : "+v"(keys));  // the comparisons stay here (masks carried through the loop spill)
-#pragma unroll
-                    for (int t = 0; t < 2; ++t)
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) sc[g][t][e] = (4 * t + e < keys) ? sc[g][t][e] : MASKED;
-                }
-                // (median with infinity: a maximum that does not quiet its operand with a second instruction first)
+            if ((!FULL || g >= NG - 2) && g * 32 + 32 > seq) {  // (uniform) keys that do not exist
+                int keys = seq - g * 32 - 8 * lg;
+                asm volatile("" : "+v"(keys));  // the comparisons stay here (masks carried through the loop spill)
 #pragma unroll
                 for (int t = 0; t < 2; ++t)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) m2[t] = __builtin_amdgcn_fmed3f(m2[t], sc[g][t][e], __builtin_inff());
+                    for (int e = 0; e < 4; ++e) sc[g][t][e] = (4 * t + e < keys) ? sc[g][t][e] : MASKED;
             }
+            // (median with infinity: a maximum that does not quiet its operand with a second instruction first)
+#pragma unroll
+            for (int t = 0; t < 2; ++t)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m2[t] = __builtin_amdgcn_fmed3f(m2[t], sc[g][t][e], __builtin_inff());
         };
+        if constexpr (AHEAD == 0) {
 #pragma unroll
-        for (int g = 0; g < AHEAD; ++g) fetch_k(g);
-        if (AHEAD) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            if (AHEAD ? g + AHEAD < NG : exists(g)) fetch_k(g + AHEAD);
-            if (exists(g)) {
-#pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    sc[g][t] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-                    for (int ds = 0; ds < DS; ++ds) sc[g][t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(kf[g % (AHEAD + 1)][t][ds], qf[ds], sc[g][t], 0, 0, 0);
+            for (int g = 0; g < NG; ++g) {
+                if (exists(g)) {
+                    fetch_k(g);
+                    scores(g);
+                    maximum(g);
                 }
+                // (else the fragments of all groups are fetched at once: spills)
+                if (NG == 8 || (NG < 8 ? g & 1 : (g & 3) == 3)) __builtin_amdgcn_sched_barrier(0);
             }
-            if (AHEAD == 0) maximum(g);
-            else if (g > 0) maximum(g - 1);
-            if (AHEAD || NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);  // (else the fragments of all groups are fetched at once: spills)
+        } else {
+            fetch_k(0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (g + 1 < NG) fetch_k(g + 1);
+                scores(g);
+                if (g > 0) maximum(g - 1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            maximum(NG - 1);
         }
-        if (AHEAD) maximum(NG - 1);
         mx = fmaxf(m2[0], m2[1]);
         mx = lane_pair<16>(mx, MaxF32());
         mx = lane_pair<32>(mx, MaxF32());
@@ -260,6 +267,7 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
     v4f ot[2 * DS];  // element e of part dt is head dimension 32 (dt / 2) + 8 lg + 4 (dt % 2) + e
     auto values = [&](auto fullc, float inv) __attribute__((always_inline)) {
         constexpr bool FULL = fullc.value;
+        constexpr int AHEAD = held_fetch_ahead(FULL, NG);
         v8h vf[AHEAD + 1][2 * DS], pf[2];
         auto fetch_v = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
@@ -267,27 +275,35 @@ __global__ __launch_bounds__(512, NG <= 8 ? 4 : 2) void attention_held_kernel(co
                 vf[g % (AHEAD + 1)][dt] = *reinterpret_cast<const v8h *>(sVt + (vat ^ ((g & 3) * 64)) + (g >> 2) * 256 +
                                                                         ((dt / 2) * 32 + 4 * (dt % 2)) * VROW);
         };
-#pragma unroll
-        for (int g = 0; g < AHEAD; ++g) fetch_v(g);
         auto narrow = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) pf[g % 2][e] = (_Float16)(sc[g][e >> 2][e & 3] * inv);
         };
-        auto exists = [&](int g) { return FULL || g * 32 < seq; };
-        if (AHEAD) {
+        auto products = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+            for (int dt = 0; dt < 2 * DS; ++dt) ot[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[g % (AHEAD + 1)][dt], pf[g % 2], ot[dt], 0, 0, 0);
+        };
+        if constexpr (AHEAD == 0) {
+#pragma unroll
+            for (int g = 0; g < NG; ++g) {
+                if (FULL || g * 32 < seq) {
+                    fetch_v(g);
+                    narrow(g);
+                    products(g);
+                }
+                if (NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            fetch_v(0);
             narrow(0);
             __builtin_amdgcn_sched_barrier(0);
-        }
 #pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            if (AHEAD ? g + AHEAD < NG : exists(g)) fetch_v(g + AHEAD);
-            if (AHEAD == 0 && exists(g)) narrow(g);
-            if (exists(g)) {
-#pragma unroll
-                for (int dt = 0; dt < 2 * DS; ++dt) ot[dt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vf[g % (AHEAD + 1)][dt], pf[g % 2], ot[dt], 0, 0, 0);
+            for (int g = 0; g < NG; ++g) {
+                if (g + 1 < NG) fetch_v(g + 1);
+                products(g);
+                if (g + 1 < NG) narrow(g + 1);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (AHEAD && g + 1 < NG && exists(g + 1)) narrow(g + 1);
-            if (AHEAD || NG == 8 || (g & 1)) __builtin_amdgcn_sched_barrier(0);
         }
     };
 

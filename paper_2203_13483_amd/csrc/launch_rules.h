@@ -91,6 +91,13 @@ constexpr int attention_held_first_half(int64_t sequence_heads, int q_blocks, in
     return q_blocks >= 2 && per_wg == q_blocks && 2 * sequence_heads <= MAX_WORK_ITEMS / ATTENTION_HELD_THREADS ? (q_blocks + 1) / 2 : 0;
 }
 
+// Groups of 32 keys by which the held kernel fetches fragments ahead of their products: with two waves on a SIMD the LDS answers too late
+// otherwise (16 x 512 tokens, 16 heads of 64, 41.2 -> 38.2 us), with four the registers spill (32 x 256 27.8 -> 39.0).  Two groups
+// gain nothing over one up to 384 keys and spill at 512.  Sequences with groups that do not exist take theirs one at a time, fetch,
+// products and maximum under one condition: ahead, they would fetch the missing ones as well (20 sequences of 1500 tokens in all, at most 384,
+// 16 heads of 16 8.7 -> 7.55, 12 x 288 of 2000 tokens, 12 heads of 26 10.8 -> 8.7).
+constexpr int held_fetch_ahead(bool full, int groups) { return full && groups > 8 ? 1 : 0; }
+
 // 4-bit layers of small hidden size (rows of codes, padding included, of up to 384) run in two launches and a quantizer instead of seven:
 // their kernels take 4 to 12 us each, most of it the launch and one trip to memory.  us a layer, 4-bit, hidden size 312 with heads of 26,
 // kernels of their own -> q, k, v with the attention -> what follows it in one launch as well:

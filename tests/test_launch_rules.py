@@ -28,6 +28,7 @@ extern "C" int first_half(int64_t sequence_heads, int q_blocks, int per_wg)
 {
     return attention_held_first_half(sequence_heads, q_blocks, per_wg);
 }
+extern "C" int fetch_ahead(bool full, int groups) { return held_fetch_ahead(full, groups); }
 extern "C" bool half_waves(int64_t M, int64_t D) { return layernorm_half_waves(M, D); }
 extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
 {
@@ -74,6 +75,7 @@ def rules(tmp_path_factory):
     lib.run_index.argtypes = [C.c_uint, C.c_int64, C.c_int64]
     lib.piece_index.argtypes = [C.c_uint, C.c_uint]
     lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
+    lib.fetch_ahead.argtypes = [C.c_bool, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
     lib.small_attention_taken.argtypes, lib.small_attention_taken.restype = [C.c_int64] * 5, C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
@@ -170,6 +172,10 @@ def test_only_sequences_that_one_workgroup_would_have_are_shared(rules):
     assert [rules.first_half(256, q, q) for q in (1, 2, 3, 4)] == [0, 1, 2, 2]
     assert rules.first_half(256, 4, 2) == 0 and rules.first_half(256, 3, 1) == 0
     assert rules.first_half(limit // 2, 4, 4) == 2 and rules.first_half(limit // 2 + 1, 4, 4) == 0
+
+
+def test_only_groups_of_keys_that_exist_are_fetched_ahead(rules):
+    assert [rules.fetch_ahead(full, g) for full in (False, True) for g in (2, 4, 6, 8, 10, 12, 14, 16)] == [0] * 12 + [1] * 4
 
 
 def test_small_layers(rules):
