@@ -111,10 +111,19 @@ constexpr bool small_layer_attention(int64_t batch, int64_t seq, int64_t hidden,
     return row <= SMALL_LAYER_ROW && row % 128 == 0 && seq <= 128 && hidden / heads <= 32 && batch * heads <= MAX_WORK_ITEMS / 256;
 }
 // What a layer takes: that, where the attention would take the held kernel, whose sums it has in the same order (more heads than that
-// one can be launched for sum otherwise).
-constexpr bool small_layer_attention_choice(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+// one can be launched for sum otherwise), and where it is the faster one.  A head takes the room of 32 in its products and a sequence that
+// of 32, 64 or 128 tokens, so what one launch saves is used up by that many workgroups' waste: sooner for small heads, and in padding-free
+// batches, whose short sequences share one bound.  us a layer, kernels of their own / this:
+//   hidden size 256, heads of 8: 16 x 128 tokens (512 workgroups) 25.6 / 24.1, 32 x 128 (1024) 31.8 / 32.7, 64 x 64 (2048) 31.7 / 33.8;
+//     of 4, 200 sequences of at most 128, 12000 tokens in all (12800) 151.6 / 191.4
+//   384, heads of 16: 32 x 128 (768) 43.7 / 42.6, 64 x 128 (1536) 74.4 / 75.0, 128 sequences of 4097 (3072) 67.6 / 74.1
+//   312, heads of 26: 128 x 128 (1536) 104.8 / 100.0, 200 sequences of 12000 (2400) 97.1 / 99.9
+constexpr bool small_layer_attention_choice(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row, bool padding_free)
 {
-    return small_layer_attention(batch, seq, hidden, heads, row) && attention_route(batch, seq, hidden, heads, row) == ATTENTION_HELD;
+    if (!small_layer_attention(batch, seq, hidden, heads, row) || attention_route(batch, seq, hidden, heads, row) != ATTENTION_HELD) return false;
+    const int64_t tiles = seq <= 32 ? 1 : seq <= 64 ? 2 : 4, work = batch * heads * tiles, dk = hidden / heads;
+    if (dk < 16) return work <= 2048;
+    return work <= 4096 || (!padding_free && dk >= (tiles == 1 ? 24 : 26));
 }
 // The rest: one round of workgroups of 16 tokens on 256 CUs, each of which reads all weights and goes through the FFN's columns one chunk
 // after the other (columns of a chunk, and what whole chunks of the better of the two sizes add up to).  In a second round the kernels of

@@ -898,7 +898,7 @@ static int bert_layer_run(int bits, const mkq_bert_layer_params *p, const void *
         if (rc != MKQ_OK) return rc;
         c0 = ws + L.c0;
     }
-    if (bits == 4 && small_layer_attention_choice(p->batch, p->seq, H, p->heads, Hp)) {
+    if (bits == 4 && small_layer_attention_choice(p->batch, p->seq, H, p->heads, Hp, p->cu_seqlens != nullptr)) {
         const AttentionParams att = {(const uint16_t *)(ws + L.qkv), p->cu_seqlens, (int)p->batch, (int)p->seq, (int)H, (int)p->heads,
                                      (int)(H / p->heads), 1, nullptr, ws + L.c1, p->sx_ao, 4, (int)Hp};
         rc = run_qkv_attention({att, c0, p->Wq_qkv, p->sw_qkv, p->b_qkv, p->sx_qkv, (int)Hp, (uint16_t *)(ws + L.qkv)}, as_stream(stream));

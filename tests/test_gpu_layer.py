@@ -700,7 +700,7 @@ def _f16_rows(r, at, cols):
 
 # heads of 26 (words), 32, 16, 8, 4 (16-byte pieces and words), sequences of one, two and four tiles of tokens, whole and ragged
 @pytest.mark.parametrize("hidden,heads,seq,lens", [(312, 12, 128, (128, 1, 16, 17, 32, 33, 64, 65, 127, 96)), (384, 12, 128, (128, 100, 64, 3) * 8),
-                                                   (256, 16, 64, (64, 33, 32, 31) * 12), (128, 16, 32, (32, 1, 17) * 40), (104, 26, 128, (128, 77) * 20)])
+                                                   (256, 16, 64, (64, 33, 32, 31) * 12), (128, 16, 32, (32, 1, 17) * 40), (104, 26, 128, (128, 77) * 9)])
 def test_attention_of_small_layers_is_that_of_its_own_launch(mkq, hidden, heads, seq, lens):
     """Context codes of a layer that runs q, k, v and the attention in one launch: bit for bit those of the attention on the same q, k, v."""
     r = _small_layer(mkq, hidden, heads, 256, seq, lens)

@@ -34,9 +34,9 @@ extern "C" bool small_attention(int64_t batch, int64_t seq, int64_t hidden, int6
 {
     return small_layer_attention(batch, seq, hidden, heads, row);
 }
-extern "C" bool small_attention_taken(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row)
+extern "C" bool small_attention_taken(int64_t batch, int64_t seq, int64_t hidden, int64_t heads, int64_t row, bool padding_free)
 {
-    return small_layer_attention_choice(batch, seq, hidden, heads, row);
+    return small_layer_attention_choice(batch, seq, hidden, heads, row, padding_free);
 }
 extern "C" int few(int64_t M, int64_t N, int64_t row_bytes, int bits) { return few_tile(M, N, row_bytes, bits); }
 extern "C" int i8_tiles_of_three(int64_t M, int64_t N, int64_t K, bool gelu, bool residual)
@@ -77,7 +77,7 @@ def rules(tmp_path_factory):
     lib.first_half.argtypes = [C.c_int64, C.c_int, C.c_int]
     lib.fetch_ahead.argtypes = [C.c_bool, C.c_int]
     lib.half_waves.argtypes, lib.half_waves.restype = [C.c_int64] * 2, C.c_bool
-    lib.small_attention_taken.argtypes, lib.small_attention_taken.restype = [C.c_int64] * 5, C.c_bool
+    lib.small_attention_taken.argtypes, lib.small_attention_taken.restype = [C.c_int64] * 5 + [C.c_bool], C.c_bool
     lib.small_attention.argtypes, lib.small_attention.restype = [C.c_int64] * 5, C.c_bool
     lib.output_with_norm.argtypes, lib.output_with_norm.restype = [C.c_int64] * 3, C.c_bool
     lib.i8_tiles_of_three.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
@@ -196,7 +196,20 @@ def test_small_layers_keep_the_kernel_that_their_attention_would_take(rules):
     most = 0xFFFFFFFF // 512
     for hidden, heads, row in ((312, 12, 384), (128, 4, 128), (384, 12, 384)):
         for batch in (1, most // heads, most // heads + 1):
-            assert rules.small_attention_taken(batch, 128, hidden, heads, row) == (rules.route(batch, 128, hidden, heads, row) == HELD)
+            assert rules.small_attention_taken(batch, 128, hidden, heads, row, False) == (rules.route(batch, 128, hidden, heads, row) == HELD)
+
+
+def test_small_layers_of_many_small_heads_keep_kernels_of_their_own(rules):
+    def taken(batch, seq, hidden, heads, padding_free=False):
+        return rules.small_attention_taken(batch, seq, hidden, heads, -(-hidden // 128) * 128, padding_free)
+    for ragged in (False, True):
+        assert taken(16, 128, 256, 32, ragged) and not taken(17, 128, 256, 32, ragged)     # heads of 8
+        assert taken(32, 64, 256, 32, ragged) and not taken(33, 64, 256, 32, ragged)
+        assert taken(64, 32, 256, 32, ragged) and not taken(65, 32, 256, 32, ragged)
+        assert taken(42, 128, 384, 24, ragged) and not taken(43, 128, 384, 24, ragged)     # of 16
+        assert taken(78, 128, 312, 13, ragged) and not taken(79, 128, 312, 13, ragged)     # of 24
+        assert taken(85, 128, 312, 12, ragged) and taken(86, 128, 312, 12, ragged) == (not ragged)  # of 26
+        assert taken(315, 32, 312, 13, ragged) and taken(316, 32, 312, 13, ragged) == (not ragged)
 
 
 def test_small_layers_in_one_launch(rules):
