@@ -194,9 +194,10 @@ int mkq_linear_int4(const void *a, int a_dtype, float s_x, const uint8_t *Wq, co
                     const mkq_epilogue *epi, void *workspace, size_t workspace_bytes, void *stream);
 
 /* Few tokens (M <= 128): the linear is one pass over the weights and is bound by how fast they stream from
- * HBM.  Canonical rows, K/2 bytes apart, are a poor stream (32 rows fetched side by side, a power-of-two
- * pitch apart, land on the same few memory channels), so weights that serve few tokens can be kept in a
- * second layout in which the bytes that the chip reads at one moment lie next to each other: the 32 channels
+ * HBM.  Canonical rows, K/2 bytes apart, are a poorer stream (rows fetched side by side, a power-of-two
+ * pitch apart, land on the same few memory channels), so large weights that serve few tokens can be kept in a
+ * second layout (16 tokens, us, mkq_linear_int4 and this: K = N = 4096 4.9 and 9.2, 8192 9.5 and 12.8, 16384 28.4 and
+ * 27.6, 32768 107 and 92; K = 8192, N = 28672 26 and 22.5, the other way round 25 and 27), in which the bytes that the chip reads at one moment lie next to each other: the 32 channels
  * of panel q (q = 0 .. P-1, P = ceil(N / 32)) and the 64 codes of k position g (g = 0 .. K/64 - 1) form a
  * block of 1 KiB = 64 pieces of 16 bytes; the block is number g P' + q, where P' = P if P is odd, else P + 1
  * (all panels of one k position, one unused block when P is even, then the next k position: an odd pitch keeps
