@@ -33,7 +33,7 @@ struct GemmI4Params {
     int ks = 1;
     unsigned *sk_counters = nullptr;
     int32_t *sk_partials = nullptr;
-    int group_m = TILE_GROUP;  // tile order: see tile_coords; the launch sets it
+    int group_m = TILE_GROUP;  // tile order: see tile_coords; the launch sets it (gemm_few.hip: this, ks and by_rows are a FewOrder)
     bool by_rows = false;
     // host side only: do the once-per-device setup of the kernel that would run, launch nothing
     bool setup_only = false;
