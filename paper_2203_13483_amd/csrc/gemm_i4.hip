@@ -319,7 +319,7 @@ static int choose_rows64(const GemmI4Params &p)
 // ranges where they are the faster ones.  From sweeps of every configuration at 1600 calls (K = 256 .. 8192, N = 40 ..
 // 30522, M = 65 .. 65536; binary16, binary32, GELU, code and residual epilogues; M dense enough to meet full and ragged
 // rounds of tiles).  (us, 64-byte -> 128-byte rows)  Of the calls with up to 256 tiles of 64x64 most are few_tile's: what comes here
-// has K = 128 or 256, or K from 2048 to 4095 and pieces that eight waves do not share evenly.
+// has K = 128 or 256, or K from 2048 on and pieces that eight waves do not share evenly.
 static int choose_tiles(const GemmI4Params &p)
 {
     const int rows64 = choose_rows64(p);
