@@ -101,8 +101,10 @@ constexpr int held_fetch_ahead(bool full, int groups) { return full && groups > 
 // 4-bit layers of small hidden size (rows of codes, padding included, of up to 384) run in two launches and a quantizer instead of seven:
 // their kernels take 4 to 12 us each, most of it the launch and one trip to memory.  us a layer, 4-bit, hidden size 312 with heads of 26,
 // kernels of their own -> q, k, v with the attention -> what follows it in one launch as well:
-//   256 tokens 37.5 -> 34.1 -> 28.3, 1024 39.1 -> 35.2 -> 28.4, 4096 50.0 -> 45.6 -> 34.2, padding-free 440 38.3 -> 34.2 -> 27.9,
-//   2298 46.0 -> 45.0 -> 37.8; hidden 384, 4096 tokens 49.5 -> 45.3 -> 36.3, 128 33.5 -> 30.4 -> 21.9.
+//   1024 tokens 39.1 -> 35.2 -> 28.4, 4096 50.0 -> 45.6 -> 34.5, padding-free 2298 46.0 -> 45.0 -> 37.8; hidden 384, 4096 tokens
+//   49.5 -> 45.3 -> 36.6; with fewer tokens only the first step is taken (small_layer_tail): 256 37.5 -> 34.1, padding-free 440 38.3 -> 34.2.
+//   In a graph, where launches cost less, and with the few-token kernels for what is left to them: 256 32.7 -> 25.9, 440 31.6 -> 25.8,
+//   1024 31.8 -> 29.5, 2298 44.3 -> 37.2, 4096 46.3 -> 34.9.
 constexpr int64_t SMALL_LAYER_ROW = 384;
 // q, k, v and the attention: any number of tokens (16384 of hidden size 312 109 -> 100, 65536 335 -> 292); one workgroup of 256 threads per
 // (sequence, head) has to fit a launch.
@@ -132,23 +134,22 @@ constexpr bool small_layer_attention_choice(int64_t batch, int64_t seq, int64_t 
 constexpr int64_t LAYER_TAIL_WIDE = 1280, LAYER_TAIL_NARROW = 768;
 constexpr int64_t layer_tail_columns(int64_t ffn, int64_t chunk) { return (ffn + chunk - 1) / chunk * chunk; }
 // Its time is that of its columns at any token count, the others' grows with the tokens and, up to 1024 of them, hardly with the columns, so
-// the line rises: 768 columns always, with 4/3 more for every token, and 3840 at most.  us a layer, kernels of their own / this, hidden
-// size 312, heads of 26:
+// the line rises: 768 columns always, beyond 600 more than there are tokens, and 3840 at most.  us a layer from call to call, where seven
+// launches cost the host about 25, kernels of their own / this, hidden size 312, heads of 26 (440: padding-free; 4096: in a graph):
 //   tokens        16          128         440         1024        1536        2048        4096
-//    768 columns  21.6 21.6   25.9 25.2   27.0 25.8   29.6 26.1   32.4 26.4   36.2 26.7   39.1 30.2
-//   1280          21.9 25.6   26.4 29.1   27.6 29.6   31.4 29.6   33.8 30.3   39.8 30.7   43.0 34.5
-//   1536          21.7 27.1   26.6 30.5   28.6 31.0   32.1 31.1   35.4 31.7   40.6 31.9   44.1 35.8
-//   2304          22.1 32.0   27.3 35.7   29.4 36.1   34.9 36.5   40.7 37.1   45.1 37.0   51.1 42.7
-//   3072          22.3 37.2   28.0 40.8   31.4 41.2   36.8 41.3   43.5 42.2   47.1 42.3   52.5 49.4
-//   3840          22.4 41.6   28.3 45.3   31.6 45.7   39.8 45.8   44.2 46.6   47.9 46.7   57.1 54.8
-//   8448          23.5 72.1   31.0 76.1   35.7 78.4   45.5 79.3   51.8 82.2   58.1 83.4   80.4 92.4
-// (384 alike; 128 and 256 up to 5 % in this one's favour.)
+//    768 columns  26.3 21.3   27.0 24.7   27.3 25.0   27.9 25.5   31.4 26.5   33.5 26.4   39.9 31.2
+//   1280          25.0 25.0   27.2 28.5   28.2 28.7   30.6 29.0   32.2 30.0   35.3 30.1   44.6 35.1
+//   1536          24.3 26.5   27.3 29.9   28.7 30.3   31.0 30.7   33.7 31.8   35.3 32.1   45.2 36.3
+//   2304          23.7 31.5   28.2 35.4   29.2 36.0   33.7 36.8   35.2 37.7   40.3 38.2   50.1 41.2
+//   3072          24.6 38.2   28.8 41.9   30.8 42.9   33.5 43.3   37.7 43.9   40.6 44.1   52.7 48.3
+// (384 alike.  In a graph their own kernels cost less: 1280 columns 25.8 28.2 at 128 tokens, 28.8 29.5 at 1024, 30.1 30.4 at 1536;
+// 3840 columns 49.2 51.3 at 3072, 57.2 53.1 at 3584.)
 constexpr bool small_layer_tail(int64_t tokens, int64_t row, int64_t ffn_row)
 {
     if (row > SMALL_LAYER_ROW || row % 128 != 0 || ffn_row % 128 != 0 || ffn_row > 3840 || tokens > 4096) return false;
     const int64_t wide = layer_tail_columns(ffn_row, LAYER_TAIL_WIDE), narrow = layer_tail_columns(ffn_row, LAYER_TAIL_NARROW);
     const int64_t columns = wide < narrow ? wide : narrow;
-    return columns <= LAYER_TAIL_NARROW || columns <= 320 + tokens * 4 / 3;
+    return columns <= LAYER_TAIL_NARROW || columns <= tokens + 600;
 }
 
 // LayerNorm with one row per half wave (the kernels have 256 threads: eight rows), not per wave (four).  Up to D = 1024: where

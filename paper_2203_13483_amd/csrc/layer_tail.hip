@@ -11,7 +11,7 @@
 // and code decisions of 16 x 1280 columns take 6000 of the workgroup's 37000 cycles, LayerNorm 4800 and 3200, widening 7000.
 // Widening is two operations per eight codes, not three: 16 * high nibble meets the token's code, low nibble + 8 meets 16 times the code, and
 // 128 times the sum of a token's even codes comes off its accumulators (token_operand).
-// Layers of hidden size 312 and 4096 tokens 45.6 -> 34.2 us, of 256 tokens 34.1 -> 28.3 (small_layer_tail).  Of hidden size 768 (2.65 MB of
+// Layers of hidden size 312 and 4096 tokens 44.6 -> 35.1 us in a graph, of 1024 30.6 -> 29.0 from call to call (small_layer_tail).  Of hidden size 768 (2.65 MB of
 // weights, 50000 cycles at that rate and as much again of vector issue) it takes 56 us at 4096 tokens and 41 at 440, the five kernels 52 and 26.
 #include "layer_tail.h"
 

@@ -4,10 +4,10 @@
 // 32 each (dimensions past d_k repeat the last one's weights and are cleared behind the product).
 // What bounds it is one workgroup's chain, with 384 of them for 32 sequences of 12 heads: of 16500 cycles (128 tokens, hidden size 312) set-up
 // 2000, first stage out of memory 2100, product 2900, dequantization into LDS 2000, rows to memory 2500, softmax 2100, product with V
-// 900, codes 1000.  (Rows leave through LDS, neighbouring lanes with neighbouring pieces: straight from the result registers, a row to a
-// lane, they took twice as long.)  Of a layer of hidden size 312 it takes 4.5 us of 50 at 4096 tokens, 3.9 of 39 at 1024
-// (small_layer_attention).  With heads of 64 and hidden size 768 the chain is longer than what it saves: layers of 32 x 128 tokens 79.8 -> 79.3,
-// padding-free of 440 40.1 -> 43.7.
+// 900, codes 1000 (these three with 32x32x16 products; the ones that give the held kernel's bits add 0.4 us to 11.1).  (Rows leave
+// through LDS, neighbouring lanes with neighbouring pieces: straight from the result registers, a row to a lane, they took twice as long.)
+// Of a layer of hidden size 312 it takes 4.5 us of 50 at 4096 tokens, 3.9 of 39 at 1024 (small_layer_attention_choice).  With heads of 64
+// and hidden size 768 the chain is longer than what it saves: layers of 32 x 128 tokens 79.8 -> 79.3, padding-free of 440 40.1 -> 43.7.
 #include "qkv_attention.h"
 
 #include "gemm_i4_params.h"

@@ -213,11 +213,11 @@ def test_small_layers_of_many_small_heads_keep_kernels_of_their_own(rules):
 
 
 def test_small_layers_in_one_launch(rules):
-    """FFN columns in whole chunks: 768 always, with 4/3 more for every token, 3840 at most."""
+    """FFN columns in whole chunks: 768 always, beyond 600 more than there are tokens, 3840 at most."""
     assert rules.small_tail(16, 384, 768) and not rules.small_tail(16, 384, 896) and not rules.small_tail(16, 384, 8192)
-    assert rules.small_tail(720, 384, 1280) and not rules.small_tail(719, 384, 1280) and not rules.small_tail(440, 384, 1280)
-    assert rules.small_tail(912, 384, 1408) and not rules.small_tail(911, 384, 1408)  # two narrow chunks
-    assert rules.small_tail(4096, 384, 3840) and rules.small_tail(2640, 384, 3840) and not rules.small_tail(2639, 384, 3840)
+    assert rules.small_tail(680, 384, 1280) and not rules.small_tail(679, 384, 1280) and not rules.small_tail(440, 384, 1280)
+    assert rules.small_tail(936, 384, 1408) and not rules.small_tail(935, 384, 1408)  # two narrow chunks
+    assert rules.small_tail(4096, 384, 3840) and rules.small_tail(3240, 384, 3840) and not rules.small_tail(3239, 384, 3840)
     assert not rules.small_tail(4096, 384, 3968) and not rules.small_tail(4096, 384, 16384)
 
 
